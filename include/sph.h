@@ -103,9 +103,9 @@ typedef struct {
                              one cell per wavefront, XCD-contiguous blocks;
                              1 = persistent wavefronts popping per-XCD queues */
     int32_t queue_batch;  /* cells per queue pop when schedule = 1 (4) */
-    int32_t tile_cap;     /* candidates of a cell the density kernel keeps in LDS
-                             for all its passes: 128, 256 or 512 (128); a larger
-                             tile means fewer reloads but fewer wavefronts per CU */
+    int32_t tile_cap;     /* accepted (128, 256 or 512; 128) and without effect: the
+                             density kernel stages every item's candidates
+                             through one tile size */
     int32_t cell_order;   /* order cells reach wavefronts: 0 = by decreasing cost,
                              dealt out to the 8 XCDs (balance; default);
                              1 = Morton order, a contiguous range per XCD
@@ -181,9 +181,9 @@ typedef struct {
     int64_t n_pairs;            /* (cell, neighbour cell) entries, self included */
     int64_t sweep_interactions_density; /* pairs inside the trial h, summed over
                                            every Newton evaluation */
-    int64_t rescanned_density;  /* particles whose solve re-tested every candidate
-                                   at each evaluation (unequal masses or a
-                                   neighbour list too long for its slots) */
+    int64_t rescanned_density;  /* particles whose candidates the solve walked more
+                                   than once (unequal masses, or a neighbour
+                                   list far too long for its slots) */
     int64_t tests_density;      /* FP32 loops: (i, j) candidate pairs tested against
                                    i's search radius outside the Newton lists (the
                                    list-building scans, and the rare re-walks of a

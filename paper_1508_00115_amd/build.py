@@ -31,7 +31,10 @@ def hipcc() -> str:
 def command(out: str) -> list:
     return [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-            "-munsafe-fp-atomics", "-I", INCLUDE, "-I", CSRC,
+            "-munsafe-fp-atomics",
+            # matrix instructions with their results in vector registers: the
+            # vector code reads every one of them at once
+            "-mllvm", "-amdgpu-mfma-vgpr-form", "-I", INCLUDE, "-I", CSRC,
             *[os.path.join(CSRC, s) for s in SOURCES], "-o", out]
 
 

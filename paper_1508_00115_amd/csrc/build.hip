@@ -50,6 +50,8 @@ __device__ __forceinline__ uint32_t compact3(uint64_t x)
 struct KeyLayout {
     int bits_top;  // bits of the top-cell index
     int levels;    // octree levels below the top grid (3 key bits each)
+    int low;       // key bits below the top-cell index: 3 levels of Morton bits, or
+                   // (the first sort) the fine cell in z
 };
 
 // Raise base[key] to v over a workgroup of WBS threads (valid lanes only).
@@ -142,16 +144,18 @@ __global__ void k_box_hmax(int64_t n, const int64_t* __restrict__ box_first, int
     block_atomic_max_u32(box_hmax, b, __float_as_uint(margin * h), ok);
 }
 
+// Sort keys: box, top cell, and below it the Morton code of the particle's
+// place (fzb < 0) or its fine cell, one of 2^fzb slices of the top cell in z.
 __global__ void k_keys(int64_t n, const double* __restrict__ pos_w, const int64_t* __restrict__ box_first,
                        int n_boxes, const double* __restrict__ box_len, const int* __restrict__ box_G,
-                       KeyLayout kl, uint64_t* __restrict__ keys, uint32_t* __restrict__ vals)
+                       KeyLayout kl, int fzb, uint64_t* __restrict__ keys, uint32_t* __restrict__ vals)
 {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
     const int b = box_of(box_first, n_boxes, p);
     const int G = box_G[b];
     const double wtop = box_len[b] / G;
-    const uint32_t nsub = 1u << kl.levels;
+    const uint32_t nsub = fzb >= 0 ? 1u << fzb : 1u << kl.levels;
     uint32_t tc[3], sc[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -166,9 +170,161 @@ __global__ void k_keys(int64_t n, const double* __restrict__ pos_w, const int64_
         sc[a] = (uint32_t)si;
     }
     const uint64_t top = ((uint64_t)tc[0] * G + tc[1]) * G + tc[2];
-    const uint64_t mort = (spread3(sc[0]) << 2) | (spread3(sc[1]) << 1) | spread3(sc[2]);
-    keys[p] = ((uint64_t)b << (kl.bits_top + 3 * kl.levels)) | (top << (3 * kl.levels)) | mort;
+    const uint64_t below = fzb >= 0 ? (uint64_t)sc[2] : (spread3(sc[0]) << 2) | (spread3(sc[1]) << 1) | spread3(sc[2]);
+    keys[p] = ((uint64_t)b << (kl.bits_top + kl.low)) | (top << kl.low) | below;
     vals[p] = (uint32_t)p;
+}
+
+// ---- the grid layout (no top cell split) -----------------------------------------------
+// Particles sorted by box, column of top cells (x, y), z in fine cells. Work
+// items take them 16 at a time along each column, whatever cells they are in:
+// cells of a grid one search radius wide hold 8 to 27 particles, and items of
+// single cells left a third of the lanes without a particle.
+
+// First particle of every fine cell (starts[n_fine] = n): the thread of a
+// particle that begins a cell also fills the empty cells before it.
+__global__ void k_fine_starts(int64_t n, const uint64_t* __restrict__ keys, KeyLayout kl,
+                              const int64_t* __restrict__ box_top_base, int64_t n_fine, int* __restrict__ starts)
+{
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= n) return;
+    auto fine = [&](uint64_t k) {
+        const int b = (int)(k >> (kl.bits_top + kl.low));
+        return (box_top_base[b] << kl.low) + (int64_t)(k & ((1ull << (kl.bits_top + kl.low)) - 1));
+    };
+    const uint64_t k = keys[p];
+    if (p == 0 || k != keys[p - 1]) {
+        const int64_t f = fine(k);
+        for (int64_t c = p == 0 ? 0 : fine(keys[p - 1]) + 1; c <= f; ++c) starts[c] = (int)p;
+    }
+    if (p == n - 1)
+        for (int64_t c = fine(k) + 1; c <= n_fine; ++c) starts[c] = (int)n;
+}
+
+// Columns of box b: [col_base[b], col_base[b + 1]).
+__device__ __forceinline__ int box_of_col(const int* col_base, int n_boxes, int r)
+{
+    int lo = 0, hi = n_boxes - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (col_base[mid] <= r) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
+
+__global__ void k_col_count(int n_cols, int n_boxes, const int* __restrict__ col_base, const int* __restrict__ box_G,
+                            const int64_t* __restrict__ box_top_base, int fzb, const int* __restrict__ starts,
+                            uint32_t* __restrict__ it_cnt)
+{
+    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= n_cols) return;
+    const int b = box_of_col(col_base, n_boxes, r);
+    const int gz = box_G[b] << fzb;
+    const int64_t f = (box_top_base[b] << fzb) + (int64_t)(r - col_base[b]) * gz;
+    it_cnt[r] = (uint32_t)((starts[f + gz] - starts[f] + 15) / 16);
+}
+
+// The items of each column (one wavefront per column) and the first item of
+// each box. An item that spans so many cells that some cell would be its
+// candidate twice (a sparse column of a small grid) sets grid[1]: the build then
+// uses the tree layout. grid[0]: the number of items.
+__global__ void __launch_bounds__(256) k_col_items(int n_cols, int n_boxes, const int* __restrict__ col_base,
+                                                   const int* __restrict__ box_G, const double* __restrict__ box_len,
+                                                   const int64_t* __restrict__ box_top_base, KeyLayout kl,
+                                                   const int* __restrict__ starts, const uint64_t* __restrict__ keys,
+                                                   const uint32_t* __restrict__ it_start, int4* __restrict__ cells,
+                                                   int* __restrict__ box_item, uint32_t* __restrict__ grid)
+{
+    const int r = (int)(((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
+    const int lane = threadIdx.x & 63;
+    if (r >= n_cols) return;  // whole wavefronts
+    const int fzb = kl.low;
+    const int b = box_of_col(col_base, n_boxes, r);
+    const int G = box_G[b], gz = G << fzb, xy = r - col_base[b];
+    const int x = xy / G, y = xy % G;
+    const int64_t base = box_top_base[b] << fzb;
+    const int64_t f = base + (int64_t)xy * gz;
+    const int p0 = starts[f], p1 = starts[f + gz];
+    const double unit = box_len[b] / 4294967296.0;
+    const float sh = (float)unit, sl = (float)(unit - (double)sh);
+    const uint64_t mask = (1ull << (kl.bits_top + kl.low)) - 1;
+    if (lane == 0) {
+        if (xy == 0) box_item[b] = (int)it_start[r];
+        if (r == n_cols - 1) {
+            box_item[n_boxes] = (int)it_start[n_cols];
+            grid[0] = it_start[n_cols];
+        }
+    }
+    for (int t = lane; t < (p1 - p0 + 15) / 16; t += 64) {
+        const int i0 = p0 + 16 * t, ni = min(16, p1 - i0);
+        const int z0 = (int)((keys[i0] & mask) - (uint64_t)(f - base));
+        const int z1 = (int)((keys[i0 + ni - 1] & mask) - (uint64_t)(f - base));
+        if ((z1 >> fzb) - (z0 >> fzb) + 3 > G) atomicOr(&grid[1], 1u);
+        const int64_t it = it_start[r] + t;
+        cells[2 * it] = make_int4(i0, ni | (G << 8), x | (y << 16), z0 | (z1 << 16));
+        cells[2 * it + 1] = make_int4((int)base, __float_as_int(sh), __float_as_int(sl), 0);
+    }
+}
+
+// Positions as 32-bit fractions of the box, sorted: differences are exact and
+// wrap around the box by themselves.
+__global__ void k_fix_fill(int64_t n, const uint32_t* __restrict__ perm, const double* __restrict__ pos_w,
+                           const int64_t* __restrict__ box_first, int n_boxes, const double* __restrict__ box_len,
+                           int4* __restrict__ xfix)
+{
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= n) return;
+    const int64_t o = perm[p];
+    const double s = 4294967296.0 / box_len[box_of(box_first, n_boxes, o)];
+    int v[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) v[a] = (int)(unsigned)(unsigned long long)llrint(pos_w[3 * o + a] * s);
+    xfix[p] = make_int4(v[0], v[1], v[2], 0);
+}
+
+// As k_cell_pbox for a grid layout: the box's centre in 32-bit fractions.
+__global__ void __launch_bounds__(256) k_fix_pbox(int64_t n_items, const int4* __restrict__ cells,
+                                                  const int4* __restrict__ xfix, const float* __restrict__ Hs,
+                                                  float4* __restrict__ pbox)
+{
+    const int64_t it = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
+    const int sub = threadIdx.x & 15;
+    const bool live = it < n_items;
+    const int4 c0 = live ? cells[2 * it] : make_int4(0, 0, 0, 0);
+    const int ni = c0.y & 0xff;
+    const int4 x0 = live ? xfix[c0.x] : make_int4(0, 0, 0, 0);
+    int lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
+    float H = 0.0f;
+    if (sub < ni) {
+        const int4 x = xfix[c0.x + sub];
+        lo[0] = hi[0] = (int)((unsigned)x.x - (unsigned)x0.x);
+        lo[1] = hi[1] = (int)((unsigned)x.y - (unsigned)x0.y);
+        lo[2] = hi[2] = (int)((unsigned)x.z - (unsigned)x0.z);
+        H = Hs[c0.x + sub];
+    }
+    for (int o = 8; o >= 1; o >>= 1) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = min(lo[a], __shfl_xor(lo[a], o, 64));
+            hi[a] = max(hi[a], __shfl_xor(hi[a], o, 64));
+        }
+        H = fmaxf(H, __shfl_xor(H, o, 64));
+    }
+    if (live && sub == 0) {
+        const int4 c1 = cells[2 * it + 1];
+        const double u = (double)__int_as_float(c1.y) + (double)__int_as_float(c1.z);
+        unsigned o[3];
+        float h[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const long long mid = ((long long)lo[a] + (long long)hi[a]) >> 1;
+            const unsigned base = (unsigned)(a == 0 ? x0.x : a == 1 ? x0.y : x0.z);
+            o[a] = base + (unsigned)mid;
+            h[a] = (float)((double)((long long)hi[a] - mid) * u) * 1.00001f;
+        }
+        pbox[2 * it] = make_float4(__int_as_float((int)o[0]), __int_as_float((int)o[1]), __int_as_float((int)o[2]), H);
+        pbox[2 * it + 1] = make_float4(h[0], h[1], h[2], 0.0f);
+    }
 }
 
 __global__ void k_sorted_H(int64_t n, const uint32_t* __restrict__ perm, const float* __restrict__ hg,
@@ -218,7 +374,7 @@ __global__ void k_lvl_nodes(int64_t n, const uint64_t* __restrict__ keys, const 
         id = (int)(node_base + (int64_t)excl[p] + head[p] - 1);
         nid[p] = id;
         const uint64_t k = keys[p];
-        const int b = (int)(k >> (kl.bits_top + 3 * kl.levels));
+        const int b = (int)(k >> (kl.bits_top + kl.low));
         const double w = box_len[b] / box_G[b] / (double)(1u << level);
         const float H = Hs[p];
         hb = __float_as_uint(H);
@@ -250,10 +406,10 @@ __global__ void k_lvl_nodes(int64_t n, const uint64_t* __restrict__ keys, const 
     }
     if (valid && head[p]) {
         const uint64_t k = keys[p];
-        const int b = (int)(k >> (kl.bits_top + 3 * kl.levels));
-        const uint64_t top = (k >> (3 * kl.levels)) & ((1ull << kl.bits_top) - 1);
+        const int b = (int)(k >> (kl.bits_top + kl.low));
+        const uint64_t top = (k >> kl.low) & ((1ull << kl.bits_top) - 1);
         const int G = box_G[b];
-        const uint64_t pre = (k & ((1ull << (3 * kl.levels)) - 1)) >> (3 * (kl.levels - level));
+        const uint64_t pre = level > 0 ? (k & ((1ull << kl.low) - 1)) >> (3 * (kl.levels - level)) : 0;
         const uint32_t mx = compact3(pre >> 2), my = compact3(pre >> 1), mz = compact3(pre);
         const uint32_t tz = (uint32_t)(top % G), ty = (uint32_t)((top / G) % G), tx = (uint32_t)(top / ((uint64_t)G * G));
         nd_start[id] = (int)p;
@@ -380,15 +536,16 @@ __global__ void k_leaf_fill(int64_t n, const uint32_t* __restrict__ head, const 
     }
 }
 
-// First leaf of each box: leaves follow the sorted particles, whose boxes are
-// contiguous blocks, so box b owns leaves [box_leaf[b], box_leaf[b + 1]).
-__global__ void k_box_leaf(int n_boxes, int64_t n, int64_t nl, const int64_t* __restrict__ box_first,
-                           const int* __restrict__ leaf_of, int* __restrict__ box_leaf)
+// First item of each box (tree): leaves follow the sorted particles, whose
+// boxes are contiguous blocks, and items the leaves.
+__global__ void k_box_item(int n_boxes, int64_t n, int64_t nl, const int64_t* __restrict__ box_first,
+                           const int* __restrict__ leaf_of, const uint32_t* __restrict__ it_start,
+                           int* __restrict__ box_item)
 {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b > n_boxes) return;
     const int64_t p = box_first[b];
-    box_leaf[b] = p < n ? leaf_of[p] : (int)nl;
+    box_item[b] = (int)it_start[p < n ? leaf_of[p] : nl];
 }
 
 // Particles of each leaf of 2 to 64 particles in decreasing order of search
@@ -493,7 +650,7 @@ struct RecordOut {
 // for the leaves of partner lists of leaf a (centre cA, width wA, largest
 // search radius HA): every leaf whose box lies within max(HA, its own largest
 // radius) of a's box. nd counts those within HA, nf the others. FILL writes
-// them from od and of on, and nj adds up their particles. The walk needs no
+// them from od and of on; nj adds up their particles. The walk needs no
 // stack: a split node's children have consecutive ids, so after a node the
 // walk goes to its next sibling, or climbs to the first ancestor below T that
 // has one. Children come in increasing id order. A tree that would take more
@@ -528,15 +685,15 @@ __device__ __forceinline__ void walk_top(int T, const double S[3], int code, con
                 continue;
             }
             const bool dens = d2 < (double)HA * (double)HA;
+            const int cnt = ro.lf_count[lf];
+            nj += cnt;
             if (FILL) {
                 const uint32_t o = dens ? od + nd : of + nf;
-                const int cnt = ro.lf_count[lf];
                 ro.p_leaf[o] = lf;
                 ro.p_rec[o] = make_int2(ro.lf_start[lf], cnt);
                 ro.p_shift[o] = make_float4((float)(cX[0] + S[0] - cA[0]), (float)(cX[1] + S[1] - cA[1]),
-                                            (float)(cX[2] + S[2] - cA[2]), 0.0f);
+                                            (float)(cX[2] + S[2] - cA[2]), (float)(0.5 * wX));
                 ro.p_code[o] = code;
-                nj += cnt;
             }
             nd += dens ? 1u : 0u;
             nf += dens ? 0u : 1u;
@@ -573,7 +730,7 @@ constexpr int PBS = 256;
 // into its spread slot (one per wavefront would be 10^5 atomics on a few
 // cache lines for the largest sets). Every thread of the group must call it.
 template <int NV>
-__device__ __forceinline__ void block_counters(const int64_t (&v)[NV], int64_t (&red)[4][PBS / 64],
+__device__ __forceinline__ void block_counters(const int64_t (&v)[NV], int64_t (&red)[NV][PBS / 64],
                                                int64_t* __restrict__ ctr, int k0, int n_sum)
 {
     const int w = threadIdx.x >> 6;
@@ -600,6 +757,25 @@ __device__ __forceinline__ void block_counters(const int64_t (&v)[NV], int64_t (
     }
 }
 
+// Work items of the hot kernels: the particles of a leaf in runs of at most
+// ITEM_N, one wavefront each. A wavefront takes ITEM_N particles at a time
+// (four lanes per particle), so a leaf of more would be a serial loop: as
+// separate items its runs go to several wavefronts (a box of 16^3 particles
+// has 125 leaves of 27 to 64 particles for 1024 SIMDs). The nt items of a leaf of ni particles hold
+// ni / nt each, the first ni % nt one more: (offset, count) of item t.
+constexpr int ITEM_N = 16;
+__device__ __forceinline__ int2 item_range(int ni, int nt, int t)
+{
+    const int q = ni / nt, r = ni % nt;
+    return make_int2(t * q + min(t, r), q + (t < r ? 1 : 0));
+}
+
+__global__ void k_item_count(int64_t nl, const int* __restrict__ lf_count, uint32_t* __restrict__ it_cnt)
+{
+    const int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (a < nl) it_cnt[a] = (uint32_t)((lf_count[a] + ITEM_N - 1) / ITEM_N);
+}
+
 // The cell-pair tasks (section 3.1: the neighbouring cells of each leaf, found
 // with a tree), one half-wavefront per leaf and one lane per surrounding top
 // cell. fill == 0 counts each leaf's records (all into p_cnt, the density's
@@ -610,11 +786,12 @@ __device__ __forceinline__ void block_counters(const int64_t (&v)[NV], int64_t (
 // inside max(h_i, h_j)) takes both. Within each part the records follow the
 // NB27 order of their top cells, depth-first below each, so each lane writes
 // from the sum of the counts of the lanes before it (it walks its subtree
-// twice: to count, then to write). The fill also writes the leaf's schedule
-// key (sk != null), its cost particles x candidates as 12 bits of its float
-// (exponent and four bits of mantissa) in decreasing order, prefixed with
-// the XCD whose Morton range holds the leaf when xcd_local; and the build's
-// shape counters (CT_B_*).
+// twice: to count, then to write). The count also adds up the build's shape
+// counters (CT_B_*). The fill also writes (it_start != null) the leaf of each of
+// its work items and the item's schedule key (sk != null), its cost particles
+// x candidates as 12 bits of its float (exponent and four bits of mantissa)
+// in decreasing order, prefixed with the XCD whose Morton range holds the
+// item when xcd_local.
 __global__ void __launch_bounds__(PBS) k_partners(int64_t nl, int fill, const int* __restrict__ lf_node,
                                                   TreeView tv, const int* __restrict__ nd_box,
                                                   const int* __restrict__ top,
@@ -622,8 +799,9 @@ __global__ void __launch_bounds__(PBS) k_partners(int64_t nl, int fill, const in
                                                   const int* __restrict__ box_G, const double* __restrict__ box_len,
                                                   uint32_t* __restrict__ p_cnt, uint32_t* __restrict__ p_cntd,
                                                   const uint32_t* __restrict__ p_start, RecordOut ro,
-                                                  uint64_t* __restrict__ sk, uint32_t* __restrict__ sv,
-                                                  int xcd_local, int64_t* __restrict__ ctr)
+                                                  const uint32_t* __restrict__ it_start, int64_t n_items,
+                                                  int* __restrict__ it_leaf, uint64_t* __restrict__ sk,
+                                                  uint32_t* __restrict__ sv, int xcd_local, int64_t* __restrict__ ctr)
 {
     const int q = threadIdx.x & 31;
     const int64_t a = ((int64_t)blockIdx.x * PBS + threadIdx.x) >> 5;
@@ -655,98 +833,95 @@ __global__ void __launch_bounds__(PBS) k_partners(int64_t nl, int fill, const in
     }
     int nj = 0;
     if (T >= 0) walk_top<false>(T, S, code, cA, wA, wtop, HA, tv, ro, 0u, 0u, nd, nf, nj, ctr);
-    __shared__ int64_t red[4][PBS / 64];
+    __shared__ int64_t red[5][PBS / 64];
     if (!fill) {
         const uint32_t td = half_sum(nd), tf = half_sum(nf);
-        if (leaf_ok && q == 0) {
+        const int tj = (int)half_sum((uint32_t)nj);
+        const bool lead = leaf_ok && q == 0;
+        if (lead) {
             p_cnt[a] = td + tf;
             p_cntd[a] = td;
         }
-        // the records of all leaves in 64 bits: the list offsets are a 32-bit scan
-        const int64_t v = (leaf_ok && q == 0) ? (int64_t)(td + tf) : 0;
-        const int64_t r[1] = {v};
-        block_counters<1>(r, red, ctr, CT_B_PAIRS64, 1);
+        // the build's shape: the candidate pairs and the records of all leaves
+        // (in 64 bits: the list offsets are a 32-bit scan), then the maxima
+        const int ni = leaf_ok ? ro.lf_count[a] : 0;
+        const int64_t r[5] = {lead ? (int64_t)ni * tj : 0, lead ? (int64_t)(td + tf) : 0, lead ? ni : 0,
+                              lead ? (int64_t)(td + tf) : 0, lead ? tj : 0};
+        block_counters<5>(r, red, ctr, CT_B_CAND_PAIRS, 2);
         return;
     }
     const uint32_t sd = half_excl_scan(nd), sf = half_excl_scan(nf);
     if (T >= 0) {
         const uint32_t base = p_start[a];
         uint32_t cd = 0, cf = 0;
-        walk_top<true>(T, S, code, cA, wA, wtop, HA, tv, ro, base + sd, base + p_cntd[a] + sf, cd, cf, nj, ctr);
+        int again = 0;
+        walk_top<true>(T, S, code, cA, wA, wtop, HA, tv, ro, base + sd, base + p_cntd[a] + sf, cd, cf, again, ctr);
     }
+    if (!it_start) return;
     nj = (int)half_sum((uint32_t)nj);
-    int ni = 0, np = 0;
     if (leaf_ok) {
-        ni = ro.lf_count[a];
-        np = (int)(p_start[a + 1] - p_start[a]);
-        if (sk && q == 0) {
-            const float cost = (float)ni * (float)nj;
+        // the leaf's work items, one lane each
+        const int ni = ro.lf_count[a];
+        const int t0 = (int)it_start[a], nt = (int)it_start[a + 1] - t0;
+        for (int t = q; t < nt; t += 32) {
+            const int it = t0 + t;
+            it_leaf[it] = (int)a;
+            if (!sk) continue;
+            const float cost = (float)item_range(ni, nt, t).y * (float)nj;
             uint64_t x = 0;
             if (xcd_local)
-                while (x < 7 && a >= sph::xcd_start(nl, (int)x + 1)) ++x;
-            sk[a] = (x << 12) | (uint64_t)(0xfffu - (__float_as_uint(cost) >> 19));
-            sv[a] = (uint32_t)a;
+                while (x < 7 && it >= sph::xcd_start(n_items, (int)x + 1)) ++x;
+            sk[it] = (x << 12) | (uint64_t)(0xfffu - (__float_as_uint(cost) >> 19));
+            sv[it] = (uint32_t)it;
         }
     }
-    const bool lead = leaf_ok && q == 0;
-    // CT_B_CAND_PAIRS, then the maxima CT_B_MAX_NI, _NP, _NJ
-    const int64_t r[4] = {lead ? (int64_t)ni * nj : 0, lead ? ni : 0, lead ? np : 0, lead ? nj : 0};
-    block_counters<4>(r, red, ctr, CT_B_CAND_PAIRS, 1);
 }
 
-// Schedule slots. by_cost != null and deal: the leaf of cost rank r goes to
-// slot xcd_start(nl, r % 8) + r / 8. by_cost != null, no deal: slot r holds
-// the leaf of rank r (the ranks already group each XCD's range). by_cost ==
-// null: slot r holds leaf r (Morton order, so each XCD takes a contiguous
-// range of neighbouring cells).
-// cell_geom: half the leaf's width and its largest search radius, for the
-// hot kernels' cell-box test on staged candidates.
-__global__ void k_sched_fill(int64_t nl, const uint32_t* __restrict__ by_cost, int deal, const int* __restrict__ lf_start,
-                             const int* __restrict__ lf_count, const uint32_t* __restrict__ p_start,
-                             const int* __restrict__ lf_node, const int* __restrict__ nd_box,
-                             const int* __restrict__ nd_level, const int* __restrict__ box_G,
-                             const double* __restrict__ box_len, const float* __restrict__ lf_hmax,
-                             const uint32_t* __restrict__ p_cntd, int4* __restrict__ cells,
-                             int2* __restrict__ cell_aux, float2* __restrict__ cell_geom, int4* __restrict__ cells_d)
+// Schedule slots, one per work item. by_cost != null and deal: the item of
+// cost rank r goes to slot xcd_start(n, r % 8) + r / 8. by_cost != null, no
+// deal: slot r holds the item of rank r (the ranks already group each XCD's
+// range). by_cost == null: slot r holds item r (Morton order, so each XCD
+// takes a contiguous range of neighbouring cells).
+__global__ void k_sched_fill(int64_t n_items, const uint32_t* __restrict__ by_cost, int deal,
+                             const int* __restrict__ it_leaf, const uint32_t* __restrict__ it_start,
+                             const int* __restrict__ lf_start, const int* __restrict__ lf_count,
+                             const uint32_t* __restrict__ p_start, const uint32_t* __restrict__ p_cntd,
+                             int4* __restrict__ cells, int* __restrict__ cell_item, int4* __restrict__ cells_d)
 {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nl) return;
-    const int a = by_cost ? (int)by_cost[r] : (int)r;
-    const int64_t slot = by_cost && deal ? sph::xcd_start(nl, (int)(r & 7)) + (r >> 3) : r;
-    const int node = lf_node[a];
-    const int b = nd_box[node];
-    cells[slot] = make_int4(lf_start[a], lf_count[a], (int)p_start[a], (int)(p_start[a + 1] - p_start[a]));
-    cell_aux[slot] = make_int2(a, b);
-    cells_d[slot] = make_int4(lf_start[a], lf_count[a], (int)p_start[a], (int)p_cntd[a]);
-    const double w = box_len[b] / box_G[b] / (double)(1u << nd_level[node]);
-    cell_geom[slot] = make_float2((float)(0.5 * w), lf_hmax[a]);
+    if (r >= n_items) return;
+    const int it = by_cost ? (int)by_cost[r] : (int)r;
+    const int64_t slot = by_cost && deal ? sph::xcd_start(n_items, (int)(r & 7)) + (r >> 3) : r;
+    const int a = it_leaf[it];
+    const int t0 = (int)it_start[a], nt = (int)it_start[a + 1] - t0;
+    const int2 rg = item_range(lf_count[a], nt, it - t0);
+    cells[slot] = make_int4(lf_start[a] + rg.x, rg.y, (int)p_start[a], (int)(p_start[a + 1] - p_start[a]));
+    cells_d[slot] = make_int4(lf_start[a] + rg.x, rg.y, (int)p_start[a], (int)p_cntd[a]);
+    cell_item[slot] = it;
 }
 
-// Bounding box of each leaf's particles at their current offsets (sixteen
-// lanes per schedule slot), for the density loop's culling of staged
-// candidates: centre and the leaf's largest search radius, then the half
-// widths, rounded up by a relative 1e-6 of the coordinates so that the FP32
-// centre and widths still contain every particle.
-__global__ void __launch_bounds__(256) k_cell_pbox(int64_t nl, const int4* __restrict__ cells,
-                                                   const float4* __restrict__ xrel,
-                                                   const float2* __restrict__ cell_geom, float4* __restrict__ pbox)
+// Bounding box of each item's particles at their current offsets (sixteen
+// lanes per schedule slot), for the culling of staged candidates: centre and
+// the item's largest search radius, then the half widths, rounded up by a
+// relative 1e-6 of the coordinates so that the FP32 centre and widths still
+// contain every particle.
+__global__ void __launch_bounds__(256) k_cell_pbox(int64_t n_items, const int4* __restrict__ cells,
+                                                   const float4* __restrict__ xrel, const float* __restrict__ Hs,
+                                                   float4* __restrict__ pbox)
 {
-    // sixteen lanes per leaf (a leaf holds about that many particles); every
-    // lane takes part in the shuffles, a group past the last leaf with no data
+    // every lane takes part in the shuffles, a group past the last item with no data
     const int64_t slot = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
     const int sub = threadIdx.x & 15;
-    const bool live = slot < nl;
+    const bool live = slot < n_items;
     const int4 ci = live ? cells[slot] : make_int4(0, 0, 0, 0);
     const float BIG = 3.0e38f;
-    float lx = BIG, ly = BIG, lz = BIG, hx = -BIG, hy = -BIG, hz = -BIG;
-    for (int k = sub; k < ci.y; k += 16) {
-        const float4 x = xrel[ci.x + k];
-        lx = fminf(lx, x.x);
-        ly = fminf(ly, x.y);
-        lz = fminf(lz, x.z);
-        hx = fmaxf(hx, x.x);
-        hy = fmaxf(hy, x.y);
-        hz = fmaxf(hz, x.z);
+    float lx = BIG, ly = BIG, lz = BIG, hx = -BIG, hy = -BIG, hz = -BIG, H = 0.0f;
+    if (sub < ci.y) {
+        const float4 x = xrel[ci.x + sub];
+        H = Hs[ci.x + sub];
+        lx = hx = x.x;
+        ly = hy = x.y;
+        lz = hz = x.z;
     }
     for (int o = 8; o >= 1; o >>= 1) {  // within the group of 16
         lx = fminf(lx, __shfl_xor(lx, o, 64));
@@ -755,9 +930,10 @@ __global__ void __launch_bounds__(256) k_cell_pbox(int64_t nl, const int4* __res
         hx = fmaxf(hx, __shfl_xor(hx, o, 64));
         hy = fmaxf(hy, __shfl_xor(hy, o, 64));
         hz = fmaxf(hz, __shfl_xor(hz, o, 64));
+        H = fmaxf(H, __shfl_xor(H, o, 64));
     }
     if (live && sub == 0) {
-        pbox[2 * slot] = make_float4(0.5f * (lx + hx), 0.5f * (ly + hy), 0.5f * (lz + hz), cell_geom[slot].y);
+        pbox[2 * slot] = make_float4(0.5f * (lx + hx), 0.5f * (ly + hy), 0.5f * (lz + hz), H);
         pbox[2 * slot + 1] = make_float4(0.5f * (hx - lx) * 1.000001f + 1.0e-6f * fmaxf(fabsf(lx), fabsf(hx)),
                                          0.5f * (hy - ly) * 1.000001f + 1.0e-6f * fmaxf(fabsf(ly), fabsf(hy)),
                                          0.5f * (hz - lz) * 1.000001f + 1.0e-6f * fmaxf(fabsf(lz), fabsf(hz)), 0.0f);
@@ -816,15 +992,15 @@ __global__ void k_build_out(const int64_t* __restrict__ ctr, const unsigned* __r
                             int64_t* __restrict__ out)
 {
     const int k = threadIdx.x;  // CT_B_CAND_PAIRS + k
-    if (k < 4) {
+    if (k < 5) {
         int64_t v = ctr[CT_B_CAND_PAIRS + k];
         for (int sl = 0; sl < CT_SPREAD_SLOTS; ++sl) {
             const int64_t x = ctr[CT_SPREAD + sl * CT_SUMS + CT_B_CAND_PAIRS + k];
-            v = k == 0 ? v + x : max(v, x);
+            v = k < 2 ? v + x : max(v, x);
         }
         out[k] = v;
-    } else if (k == 4) {
-        out[4] = (int64_t)*hmin;
+    } else if (k == 5) {
+        out[5] = (int64_t)*hmin;
     }
 }
 
@@ -838,6 +1014,81 @@ int ceil_log2(uint64_t v)
 }  // namespace
 
 namespace sph {
+
+static TreeView tree_view(sph_ctx* c)
+{
+    return TreeView{static_cast<int*>(c->nd_coord.p),  static_cast<int*>(c->nd_level.p),
+                    static_cast<unsigned*>(c->nd_hmax.p), static_cast<int*>(c->nd_leaf.p),
+                    static_cast<int*>(c->nd_child0.p), static_cast<int*>(c->nd_child1.p),
+                    static_cast<int*>(c->nd_parent.p), (int)c->n_nodes};
+}
+
+// Offsets of the leaves' partner lists from their counts (p_cnt); sets n_pairs
+// (from the counters of the build under way; later builds' read-back has set
+// it: known). Synchronises the stream.
+static void list_offsets(sph_ctx* c, bool known, hipStream_t s)
+{
+    const int64_t nl = c->n_leaves;
+    uint32_t* p_start = ensure<uint32_t>(c, c->p_start, nl + 1);
+    scan_exclusive(c, static_cast<uint32_t*>(c->p_cnt.p), p_start, nl, p_start + nl, s);
+    uint32_t np = 0;
+    SPH_HIP(hipMemcpyAsync(&np, p_start + nl, 4, hipMemcpyDeviceToHost, s));
+    int64_t np64 = c->n_pairs;
+    if (known) {
+        SPH_HIP(hipStreamSynchronize(s));
+    } else {
+        const int64_t* hc = read_counters(c, s);  // synchronises: np is in
+        np64 = hc[CT_B_PAIRS64];
+        SPH_REQUIRE(hc[CT_BAD_INPUT] == 0, SPH_E_HIP,
+                    "inconsistent cell tree: a walk took more steps than the tree has nodes");
+    }
+    SPH_REQUIRE(np64 <= (int64_t)UINT32_MAX && (int64_t)np == np64, SPH_E_ARG,
+                std::to_string(np64) + " (cell, neighbour cell) records: more than 2^32 - 1 cannot be indexed");
+    c->n_pairs = np;
+}
+
+// The partner lists at those offsets (and the items' leaves and schedule keys).
+static void fill_lists(sph_ctx* c, const uint32_t* it_start, int64_t n_items, int* it_leaf, uint64_t* sk, uint32_t* sv,
+                       int xcd_local, hipStream_t s)
+{
+    const int64_t nl = c->n_leaves, np = c->n_pairs;
+    int* p_leaf = ensure<int>(c, c->p_leaf, np);
+    float4* p_shift = ensure<float4>(c, c->p_shift, np);
+    int* p_code = ensure<int>(c, c->p_code, np);
+    int2* p_rec = ensure<int2>(c, c->p_rec, np);
+    k_partners<<<(unsigned)blocks_for(nl * 32, PBS), PBS, 0, s>>>(
+        nl, 1, static_cast<int*>(c->lf_node.p), tree_view(c), static_cast<int*>(c->nd_box.p),
+        static_cast<int*>(c->top.p), static_cast<int64_t*>(c->box_top_base.p), static_cast<int*>(c->box_G.p),
+        static_cast<double*>(c->box_len.p), static_cast<uint32_t*>(c->p_cnt.p), static_cast<uint32_t*>(c->p_cntd.p),
+        static_cast<uint32_t*>(c->p_start.p),
+        RecordOut{p_leaf, p_shift, p_code, p_rec, static_cast<int*>(c->lf_start.p), static_cast<int*>(c->lf_count.p)},
+        it_start, n_items, it_leaf, sk, sv, xcd_local, static_cast<int64_t*>(c->counters.p));
+    SPH_HIP(hipGetLastError());
+    c->lists_built = true;
+}
+
+static void sorted_fill(sph_ctx* c, hipStream_t s)
+{
+    const int64_t n = c->n;
+    double* pos_s = ensure<double>(c, c->pos_s, 3 * n);
+    float4* xrel = ensure<float4>(c, c->xrel, n);
+    k_sorted_fill<<<blocks_for(n, BS), BS, 0, s>>>(
+        n, static_cast<uint32_t*>(c->perm.p), static_cast<double*>(c->pos_w.p), static_cast<int*>(c->leaf_of.p),
+        static_cast<int*>(c->lf_node.p), static_cast<int*>(c->nd_coord.p), static_cast<int*>(c->nd_level.p),
+        static_cast<int*>(c->nd_box.p), static_cast<int*>(c->box_G.p), static_cast<double*>(c->box_len.p), pos_s, xrel);
+    SPH_HIP(hipGetLastError());
+}
+
+void partner_lists(sph_ctx* c, hipStream_t s)
+{
+    if (!c->uni) return;  // the build made them, and every drift the positions
+    finish_build_read(c);
+    if (!c->lists_built) {
+        list_offsets(c, true, s);
+        fill_lists(c, nullptr, 0, nullptr, nullptr, nullptr, 0, s);
+    }
+    sorted_fill(c, s);
+}
 
 // Everything after the positions are wrapped: keys, sort, tree, leaves, lists.
 static void build_from_wrapped(sph_ctx* c, hipStream_t s)
@@ -878,6 +1129,15 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
         maxG3 = std::max<uint64_t>(maxG3, (uint64_t)G * G * G);
     }
     c->n_top = c->h_box_top_base[nb];
+    // columns of top cells of each box, for a grid layout, which needs at least
+    // four cells per side (the frame of an item reaches a cell and a half from
+    // its centre) and a table of fine cells in proportion to the particles
+    std::vector<int> col_base_h(nb + 1, 0);
+    bool grid_ok = true;
+    for (int b = 0; b < nb; ++b) {
+        col_base_h[b + 1] = col_base_h[b] + c->h_box_G[b] * c->h_box_G[b];
+        if (c->h_box_first[b + 1] > c->h_box_first[b] && c->h_box_G[b] < 4) grid_ok = false;
+    }
     c->bits_box = nb > 1 ? ceil_log2((uint64_t)nb) : 0;
     c->bits_top = std::max(1, ceil_log2(maxG3));
     c->levels = std::min(10, (63 - c->bits_box - c->bits_top) / 3);
@@ -889,7 +1149,18 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
                            hipMemcpyHostToDevice, s));
 
     // ---- keys and sort -------------------------------------------------------------------
-    KeyLayout kl{c->bits_top, c->levels};
+    // Sorted by box, top cell and fine cell in z first (as many fine cells, up to
+    // eight, as the last 8-bit pass of the sort has bits for, or four): all a
+    // grid layout needs. Where a top cell splits, the particles are sorted again
+    // by the whole Morton key after level 0, below.
+    {
+        const int base = c->bits_box + c->bits_top;
+        c->fzb = base % 8 == 0 ? 2 : std::min(3, 8 - base % 8);
+    }
+    const int64_t n_fine = c->n_top << c->fzb;
+    grid_ok = grid_ok && n_fine <= 16 * n + 4096 && n_fine < (int64_t)1 << 30;
+    const int n_cols = col_base_h[nb];
+    KeyLayout kl{c->bits_top, c->levels, c->fzb};
     uint64_t* keys = ensure<uint64_t>(c, c->keys, n);
     uint64_t* keys_alt = ensure<uint64_t>(c, c->keys_alt, n);
     uint32_t* perm = ensure<uint32_t>(c, c->perm, n);
@@ -897,14 +1168,30 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     const int64_t* box_first = static_cast<int64_t*>(c->box_first.p);
     const double* box_len = static_cast<double*>(c->box_len.p);
     k_keys<<<blocks_for(n, BS), BS, 0, s>>>(n, static_cast<double*>(c->pos_w.p), box_first, nb, box_len,
-                                            box_G, kl, keys, perm);
+                                            box_G, kl, c->fzb, keys, perm);
     SPH_HIP(hipGetLastError());
-    // Sorted by box and top cell first; the Morton bits below the top grid
-    // matter only where a top cell splits, and uniform sets have none (the
-    // particles of a top-cell leaf keep their input order). Where one does,
-    // the whole key is sorted after level 0, below.
-    const int key_bits = c->bits_box + c->bits_top + 3 * c->levels;
-    radix_sort(c, keys, perm, keys_alt, perm_alt, n, key_bits, s, 3 * c->levels);
+    radix_sort(c, keys, perm, keys_alt, perm_alt, n, c->bits_box + c->bits_top + c->fzb, s);
+
+    // ---- the items of a grid layout (used if no top cell splits) --------------------------------
+    uint32_t* d_grid = reinterpret_cast<uint32_t*>(&ctr[CT_GRID]);
+    if (grid_ok) {
+        int* col_base = ensure<int>(c, c->col_base, nb + 1);
+        SPH_HIP(hipMemcpyAsync(col_base, col_base_h.data(), (size_t)(nb + 1) * 4, hipMemcpyHostToDevice, s));
+        int* starts = ensure<int>(c, c->starts, (size_t)n_fine + 1);
+        uint32_t* it_start = ensure<uint32_t>(c, c->it_start, (size_t)n_cols + 1);
+        int* box_item = ensure<int>(c, c->box_item, nb + 1);
+        int4* cells = ensure<int4>(c, c->cells, 2 * (size_t)(n / 16 + n_cols));
+        k_fine_starts<<<blocks_for(n, BS), BS, 0, s>>>(n, keys, kl, box_top_base, n_fine, starts);
+        SPH_HIP(hipGetLastError());
+        k_col_count<<<blocks_for(n_cols, BS), BS, 0, s>>>(n_cols, nb, col_base, box_G, box_top_base, c->fzb, starts,
+                                                         it_start);
+        SPH_HIP(hipGetLastError());
+        scan_exclusive(c, it_start, it_start, n_cols, it_start + n_cols, s);
+        k_col_items<<<blocks_for((int64_t)n_cols * 64, 256), 256, 0, s>>>(n_cols, nb, col_base, box_G, box_len,
+                                                                          box_top_base, kl, starts, keys, it_start,
+                                                                          cells, box_item, d_grid);
+        SPH_HIP(hipGetLastError());
+    }
 
     float* Hs = ensure<float>(c, c->Hs, n);
     int* leaf_tmp = ensure<int>(c, c->lf_tmp, n);
@@ -932,7 +1219,7 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     // are renumbered in Morton order
     int* lo2node = ensure<int>(c, c->lf_start, n + 1);
     for (int level = 0; level <= c->levels && bound > 0; ++level) {
-        const int shift = 3 * (c->levels - level);
+        const int shift = level == 0 ? kl.low : 3 * (c->levels - level);
         k_lvl_head<<<blocks_for(n, BS), BS, 0, s>>>(n, keys, leaf_tmp, shift, head);
         SPH_HIP(hipGetLastError());
         scan_exclusive(c, head, excl, n, d_M, s);
@@ -992,20 +1279,28 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
         SPH_HIP(hipGetLastError());
         k_lvl_assign<<<blocks_for(n, BS), BS, 0, s>>>(n, nid, nd_leaf, leaf_tmp);
         SPH_HIP(hipGetLastError());
-        uint32_t mk[2] = {0u, 0u};
+        uint32_t mk[6] = {0u, 0u, 0u, 0u, 0u, 0u};  // d_M, d_K, -, -, d_grid
+        static_assert(CT_GRID == CT_TOTAL + 2, "the level's counts and the grid's travel in one copy");
         SPH_HIP(hipMemcpyAsync(mk, d_M, sizeof(mk), hipMemcpyDeviceToHost, s));
         SPH_HIP(hipStreamSynchronize(s));
         const int64_t M = mk[0], K = mk[1];
-        if (level == 0) c->cells_refined = K < M;
+        if (level == 0) {
+            c->uni = grid_ok && K == M && mk[5] == 0u;
+            if (c->uni) c->n_items = mk[4];
+        }
         // every particle not yet in a leaf heads or joins a node of this level,
         // so the bound (its parents' children) holds them; a larger count is a bug
         SPH_REQUIRE(M <= bound && K <= M, SPH_E_HIP, "cell tree level outside its bound");
         if (level == 0 && K < M) {
-            // A top cell splits: order the particles by the whole key. The
-            // sort is stable and keeps every top cell's range, so the level-0
-            // nodes, their sums and each particle's node and leaf stay as
-            // they are; only the sorted search radii follow the new order.
-            radix_sort(c, keys, perm, keys_alt, perm_alt, n, key_bits, s);
+            // A top cell splits: order the particles by the whole key. Every top
+            // cell keeps its range, so the level-0 nodes, their sums and each
+            // particle's node and leaf stay as they are; only the keys and the
+            // sorted search radii follow the new order.
+            kl.low = 3 * c->levels;
+            k_keys<<<blocks_for(n, BS), BS, 0, s>>>(n, static_cast<double*>(c->pos_w.p), box_first, nb, box_len,
+                                                    box_G, kl, -1, keys, perm);
+            SPH_HIP(hipGetLastError());
+            radix_sort(c, keys, perm, keys_alt, perm_alt, n, c->bits_box + c->bits_top + 3 * c->levels, s);
             k_sorted_H<<<blocks_for(n, BS), BS, 0, s>>>(n, perm, static_cast<float*>(c->hguess.p), margin, Hs,
                                                         nullptr);
             SPH_HIP(hipGetLastError());
@@ -1038,80 +1333,58 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
                                                  static_cast<unsigned*>(c->nd_hmax.p),
                                                  static_cast<int*>(c->nd_leaf.p), lf_count, lf_hmax);
     SPH_HIP(hipGetLastError());
-    k_leaf_sort_h<<<(unsigned)blocks_for(nl * 64, 256), 256, 0, s>>>(nl, lf_start, lf_count, perm, Hs);
-    SPH_HIP(hipGetLastError());
-    {
-        int* box_leaf = ensure<int>(c, c->box_leaf, c->n_boxes + 1);
-        k_box_leaf<<<blocks_for(c->n_boxes + 1, BS), BS, 0, s>>>(c->n_boxes, n, nl,
-                                                                  static_cast<int64_t*>(c->box_first.p), leaf_of,
-                                                                  box_leaf);
+    if (!c->uni) {  // (a grid's items follow z)
+        k_leaf_sort_h<<<(unsigned)blocks_for(nl * 64, 256), 256, 0, s>>>(nl, lf_start, lf_count, perm, Hs);
         SPH_HIP(hipGetLastError());
     }
 
-    // ---- neighbour lists ------------------------------------------------------------------------
+    // ---- partner lists: their number, and in a tree layout the lists and the items ------------
     uint32_t* p_cnt = ensure<uint32_t>(c, c->p_cnt, nl + 1);
     uint32_t* p_cntd = ensure<uint32_t>(c, c->p_cntd, nl + 1);
-    uint32_t* p_start = ensure<uint32_t>(c, c->p_start, nl + 1);
-    const int* nd_coord = static_cast<int*>(c->nd_coord.p);
-    const int* nd_level = static_cast<int*>(c->nd_level.p);
-    const int* nd_box = static_cast<int*>(c->nd_box.p);
-    const unsigned* nd_hmax = static_cast<unsigned*>(c->nd_hmax.p);
-    const int* nd_leaf = static_cast<int*>(c->nd_leaf.p);
-    const int* nd_child0 = static_cast<int*>(c->nd_child0.p);
-    const int* nd_child1 = static_cast<int*>(c->nd_child1.p);
-    const TreeView tv{nd_coord, nd_level, nd_hmax, nd_leaf, nd_child0, nd_child1,
-                      static_cast<int*>(c->nd_parent.p), (int)c->n_nodes};
-    const unsigned p_blocks = (unsigned)blocks_for(nl * 32, PBS);
-    k_partners<<<p_blocks, PBS, 0, s>>>(nl, 0, lf_node, tv, nd_box, top, box_top_base, box_G, box_len, p_cnt,
-                                        p_cntd, nullptr, RecordOut{}, nullptr, nullptr, 0, ctr);
+    const TreeView tv = tree_view(c);
+    k_partners<<<(unsigned)blocks_for(nl * 32, PBS), PBS, 0, s>>>(
+        nl, 0, lf_node, tv, static_cast<int*>(c->nd_box.p), top, box_top_base, box_G, box_len, p_cnt, p_cntd, nullptr,
+        RecordOut{nullptr, nullptr, nullptr, nullptr, lf_start, lf_count}, nullptr, 0, nullptr, nullptr, nullptr, 0,
+        ctr);
     SPH_HIP(hipGetLastError());
-    scan_exclusive(c, p_cnt, p_start, nl, p_start + nl, s);
-    uint32_t np = 0;
-    SPH_HIP(hipMemcpyAsync(&np, p_start + nl, 4, hipMemcpyDeviceToHost, s));
-    const int64_t* hc0 = read_counters(c, s);  // synchronises: np is in
-    const int64_t bad2 = hc0[CT_BAD_INPUT], np64 = hc0[CT_B_PAIRS64];
-    SPH_REQUIRE(bad2 == 0, SPH_E_HIP, "inconsistent cell tree: a walk took more steps than the tree has nodes");
-    SPH_REQUIRE(np64 <= (int64_t)UINT32_MAX && (int64_t)np == np64, SPH_E_ARG,
-                std::to_string(np64) + " (cell, neighbour cell) records: more than 2^32 - 1 cannot be indexed");
-    c->n_pairs = np;
-    int* p_leaf = ensure<int>(c, c->p_leaf, np);
-    float4* p_shift = ensure<float4>(c, c->p_shift, np);
-    int* p_code = ensure<int>(c, c->p_code, np);
-    int2* p_rec = ensure<int2>(c, c->p_rec, np);
-    const int order = c->prm.cell_order;
-    const bool by_cost = order != 1;
-    uint64_t* sk = ensure<uint64_t>(c, c->sched_key, nl);
-    uint32_t* sv = ensure<uint32_t>(c, c->sched_val, nl);
-    k_partners<<<p_blocks, PBS, 0, s>>>(nl, 1, lf_node, tv, nd_box, top, box_top_base, box_G, box_len, p_cnt,
-                                        p_cntd, p_start, RecordOut{p_leaf, p_shift, p_code, p_rec, lf_start, lf_count},
-                                        by_cost ? sk : nullptr, sv, order == 2 ? 1 : 0, ctr);
-    SPH_HIP(hipGetLastError());
-
-    // ---- work schedule: leaves by decreasing cost dealt out to the XCDs, Morton ranges, or Morton
-    //      ranges each ordered by decreasing cost --------------------------------------------------
-    {
-        uint64_t* ska = ensure<uint64_t>(c, c->sched_key_alt, nl);
-        uint32_t* sva = ensure<uint32_t>(c, c->sched_val_alt, nl);
-        if (by_cost) radix_sort(c, sk, sv, ska, sva, nl, order == 2 ? 15 : 12, s);
-        int4* cells = ensure<int4>(c, c->cells, nl);
-        int2* cell_aux = ensure<int2>(c, c->cell_aux, nl);
-        float2* cell_geom = ensure<float2>(c, c->cell_geom, nl);
-        int4* cells_d = ensure<int4>(c, c->cells_d, nl);
-        k_sched_fill<<<blocks_for(nl, BS), BS, 0, s>>>(nl, by_cost ? sv : nullptr, order == 0 ? 1 : 0, lf_start,
-                                                       lf_count, p_start, lf_node, nd_box, nd_level,
-                                                       static_cast<int*>(c->box_G.p),
-                                                       static_cast<double*>(c->box_len.p), lf_hmax, p_cntd, cells,
-                                                       cell_aux, cell_geom, cells_d);
+    c->lists_built = false;
+    if (!c->uni) {
+        uint32_t* it_start = ensure<uint32_t>(c, c->it_start, nl + 1);
+        k_item_count<<<blocks_for(nl, BS), BS, 0, s>>>(nl, lf_count, it_start);
+        SPH_HIP(hipGetLastError());
+        scan_exclusive(c, it_start, it_start, nl, it_start + nl, s);
+        uint32_t nit = 0;
+        SPH_HIP(hipMemcpyAsync(&nit, it_start + nl, 4, hipMemcpyDeviceToHost, s));
+        list_offsets(c, false, s);  // synchronises: nit is in
+        const int64_t ni = nit;
+        c->n_items = ni;
+        int* box_item = ensure<int>(c, c->box_item, nb + 1);
+        k_box_item<<<blocks_for(nb + 1, BS), BS, 0, s>>>(nb, n, nl, box_first, leaf_of, it_start, box_item);
+        SPH_HIP(hipGetLastError());
+        // the schedule: items by decreasing cost dealt out to the XCDs, Morton ranges, or Morton
+        // ranges each ordered by decreasing cost
+        const int order = c->prm.cell_order;
+        const bool by_cost = order != 1;
+        int* it_leaf = ensure<int>(c, c->it_leaf, ni);
+        uint64_t* sk = by_cost ? ensure<uint64_t>(c, c->sched_key, ni) : nullptr;
+        uint32_t* sv = by_cost ? ensure<uint32_t>(c, c->sched_val, ni) : nullptr;
+        fill_lists(c, it_start, ni, it_leaf, sk, sv, order == 2 ? 1 : 0, s);
+        if (by_cost) {
+            uint64_t* ska = ensure<uint64_t>(c, c->sched_key_alt, ni);
+            uint32_t* sva = ensure<uint32_t>(c, c->sched_val_alt, ni);
+            radix_sort(c, sk, sv, ska, sva, ni, order == 2 ? 15 : 12, s);
+        }
+        int4* cells = ensure<int4>(c, c->cells, ni);
+        int* cell_item = ensure<int>(c, c->cell_item, ni);
+        int4* cells_d = ensure<int4>(c, c->cells_d, ni);
+        k_sched_fill<<<blocks_for(ni, BS), BS, 0, s>>>(ni, sv, order == 0 ? 1 : 0, it_leaf, it_start, lf_start,
+                                                       lf_count, static_cast<uint32_t*>(c->p_start.p), p_cntd, cells,
+                                                       cell_item, cells_d);
         SPH_HIP(hipGetLastError());
     }
 
     // ---- sorted particle streams ------------------------------------------------------------------
-    double* pos_s = ensure<double>(c, c->pos_s, 3 * n);
-    float4* xrel = ensure<float4>(c, c->xrel, n);
-    k_sorted_fill<<<blocks_for(n, BS), BS, 0, s>>>(n, perm, static_cast<double*>(c->pos_w.p), leaf_of, lf_node,
-                                                   nd_coord, nd_level, nd_box, box_G, box_len, pos_s, xrel);
-    SPH_HIP(hipGetLastError());
-    cell_boxes(c, s);
+    refresh_offsets(c, s);
     // no drift since this build; the smallest search radius bounds how far
     // the particles may drift before the cells are rebuilt
     unsigned* drift = ensure<unsigned>(c, c->drift, 4);
@@ -1129,7 +1402,6 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     SPH_HIP(hipEventRecord(c->ev_build, s));
     c->build_read_pending = true;
     c->binfo.n_cells = nl;
-    c->binfo.n_pairs = c->n_pairs;
     c->built = true;
     ++c->tm.builds;
     c->drift_pending = false;
@@ -1148,10 +1420,11 @@ void finish_build_read(sph_ctx* c)
     c->build_read_pending = false;
     const int64_t* hb = c->h_build;
     c->binfo.candidate_pairs = hb[0];
-    c->binfo.max_cell_particles = hb[1];
-    c->binfo.max_neighbour_cells = hb[2];
-    c->binfo.max_candidates = hb[3];
-    const uint32_t bits = (uint32_t)hb[4];
+    c->binfo.n_pairs = c->n_pairs = hb[1];
+    c->binfo.max_cell_particles = hb[2];
+    c->binfo.max_neighbour_cells = hb[3];
+    c->binfo.max_candidates = hb[4];
+    const uint32_t bits = (uint32_t)hb[5];
     std::memcpy(&c->h_min, &bits, 4);
 }
 
@@ -1183,29 +1456,38 @@ void build_cells(sph_ctx* c, int32_t n_boxes, const int64_t* box_first, const do
     build_from_wrapped(c, s);
 }
 
-// Offsets of every particle from its leaf centre (and the sorted FP64
-// positions) from the current positions, keeping the cells: after a drift.
+// The sorted positions (32-bit fractions, or offsets from the leaf centres and
+// FP64 positions) and the items' boxes from the current positions, keeping the
+// cells: at a build and after a drift.
 void refresh_offsets(sph_ctx* c, hipStream_t s)
 {
-    const int64_t n = c->n;
-    k_sorted_fill<<<blocks_for(n, BS), BS, 0, s>>>(
-        n, static_cast<uint32_t*>(c->perm.p), static_cast<double*>(c->pos_w.p), static_cast<int*>(c->leaf_of.p),
-        static_cast<int*>(c->lf_node.p), static_cast<int*>(c->nd_coord.p), static_cast<int*>(c->nd_level.p),
-        static_cast<int*>(c->nd_box.p), static_cast<int*>(c->box_G.p), static_cast<double*>(c->box_len.p),
-        static_cast<double*>(c->pos_s.p), static_cast<float4*>(c->xrel.p));
-    SPH_HIP(hipGetLastError());
+    if (c->uni) {
+        int4* xfix = ensure<int4>(c, c->xfix, c->n);
+        k_fix_fill<<<blocks_for(c->n, BS), BS, 0, s>>>(c->n, static_cast<uint32_t*>(c->perm.p),
+                                                      static_cast<double*>(c->pos_w.p),
+                                                      static_cast<int64_t*>(c->box_first.p), c->n_boxes,
+                                                      static_cast<double*>(c->box_len.p), xfix);
+        SPH_HIP(hipGetLastError());
+    } else {
+        sorted_fill(c, s);
+    }
     cell_boxes(c, s);
 }
 
-// The particle boxes of every leaf (k_cell_pbox) from the current offsets.
+// The particle boxes of every work item from the current offsets.
 void cell_boxes(sph_ctx* c, hipStream_t s)
 {
-    const int64_t nl = c->n_leaves;
-    float4* pbox = ensure<float4>(c, c->cell_pbox, 2 * nl);
-    if (nl == 0) return;
-    k_cell_pbox<<<blocks_for(16 * nl, 256), 256, 0, s>>>(nl, static_cast<int4*>(c->cells.p),
-                                                        static_cast<float4*>(c->xrel.p),
-                                                        static_cast<float2*>(c->cell_geom.p), pbox);
+    const int64_t ni = c->n_items;
+    float4* pbox = ensure<float4>(c, c->cell_pbox, 2 * ni);
+    if (ni == 0) return;
+    if (c->uni)
+        k_fix_pbox<<<blocks_for(16 * ni, 256), 256, 0, s>>>(ni, static_cast<int4*>(c->cells.p),
+                                                           static_cast<int4*>(c->xfix.p),
+                                                           static_cast<float*>(c->Hs.p), pbox);
+    else
+        k_cell_pbox<<<blocks_for(16 * ni, 256), 256, 0, s>>>(ni, static_cast<int4*>(c->cells.p),
+                                                            static_cast<float4*>(c->xrel.p),
+                                                            static_cast<float*>(c->Hs.p), pbox);
     SPH_HIP(hipGetLastError());
 }
 

@@ -65,10 +65,10 @@ enum {
     CT_DENS_SWEEP_INTER = 8,  // pairs inside the trial h, summed over every evaluation
     CT_NEED_SCAN = 9,    // particles left to the re-scanning density kernel
     CT_B_CAND_PAIRS = 10,  // build: sum over leaves of particles x candidates
-    CT_B_MAX_NI = 11,      // build: largest leaf (max)
-    CT_B_MAX_NP = 12,      // build: longest neighbour-cell list (max)
-    CT_B_MAX_NJ = 13,      // build: most candidates of a leaf (max)
-    CT_B_PAIRS64 = 14,     // build: (cell, neighbour cell) records, counted in 64 bits
+    CT_B_PAIRS64 = 11,     // build: (cell, neighbour cell) records, counted in 64 bits
+    CT_B_MAX_NI = 12,      // build: largest leaf (max)
+    CT_B_MAX_NP = 13,      // build: longest neighbour-cell list (max)
+    CT_B_MAX_NJ = 14,      // build: most candidates of a leaf (max)
     CT_DENS_TESTS = 15,  // density: candidate pairs tested against the search radius (phase A)
     CT_DENS_LISTED = 16, // density: candidates listed (inside the search radius) by phase A
     CT_SUMS = 17,        // entries [0, CT_SUMS) have spread slots
@@ -77,6 +77,7 @@ enum {
     CT_SCAN_POP = 18,    // next queued cell to take
     CT_TOTAL = 19,       // scratch for device-computed totals read by the host (two uint32)
     CT_DT_MIN = 20,      // sph_timestep: smallest h / v_sig (float bits in the low word)
+    CT_GRID = 21,        // build: work items of a grid layout, and nonzero if it cannot be used (two uint32)
     CT_QUEUE = 32,       // 8 work-queue heads (one per XCD), one 64-byte line each: CT_QUEUE + 8 q
     CT_SPREAD = 96,      // CT_SPREAD_SLOTS copies of the sums, CT_SUMS entries each
     CT_SPREAD_SLOTS = 64,
@@ -144,7 +145,7 @@ struct sph_ctx {
     std::vector<int64_t> h_box_top_base;   // offset of each box in the top-cell table
     int bits_box = 0, bits_top = 0, levels = 0;
     int64_t n_top = 0;                     // entries of the top-cell table
-    int64_t n_nodes = 0, n_leaves = 0, n_pairs = 0;
+    int64_t n_nodes = 0, n_leaves = 0, n_items = 0, n_pairs = 0;
     int32_t rebuilds = 0;
 
     sph::Buf box_first, box_len, box_G, box_top_base, box_hmax;  // per box
@@ -161,7 +162,12 @@ struct sph_ctx {
     // smallest Hs. Cleared by every build.
     sph::Buf drift;
     float h_min = 0.0f;           // smallest Hs of the last build (host copy; see finish_build_read)
-    bool cells_refined = false;   // a top cell was split in the last build (leaves of several sizes)
+    // The layout of the last build (Item in tiles.h). Grid: no top cell was
+    // split and no item meets a cell twice; tree otherwise. A grid build leaves
+    // the leaves' partner lists to the calls that walk them (partner_lists).
+    bool uni = false;
+    int fzb = 0;                  // grid: fine cells in z per top cell, logarithm
+    bool lists_built = false;     // p_start, p_leaf, p_code ... hold the current cells' lists
     bool drift_pending = false;   // a drift since the last check of delta
     sph::Buf leaf_of;        // int, sorted particle -> leaf
     sph::Buf unassigned;     // int flags per particle during the level loop
@@ -186,11 +192,18 @@ struct sph_ctx {
     sph::Buf p_rec;          // int2 per record: first particle and count of the neighbour leaf
     sph::Buf p_shift;        // float4 (dx, dy, dz, 0): leaf-centre frame offset
     sph::Buf p_code;         // int: periodic image code (3 x 2 bits)
-    // work schedule of the hot kernels (one slot per leaf, see xcd_start)
-    sph::Buf cells;          // int4 per slot: first particle, count, first neighbour entry, neighbour entries
-    sph::Buf cell_aux;       // int2 per slot: leaf index, box
-    sph::Buf cell_geom;      // float2 per slot: half width of the leaf, largest search radius in it
-    sph::Buf cell_pbox;      // float4 x 2 per slot: box of the leaf's particles at their current offsets
+    // work items of the hot kernels: runs of at most 16 particles of one leaf
+    // (tree), or of one column of top cells (grid)
+    sph::Buf it_start;       // uint32: first item of each leaf or column, and their number
+    sph::Buf it_leaf;        // int per item: its leaf (tree)
+    sph::Buf box_item;       // int, n_boxes + 1: first item of each box
+    sph::Buf starts;         // grid: int, first particle of each fine cell
+    sph::Buf col_base;       // grid: int, n_boxes + 1: first column of each box
+    sph::Buf xfix;           // grid: int4 (x, y, z, 0), positions as 32-bit fractions of the box, sorted
+    // their schedule (one slot per item, see xcd_start)
+    sph::Buf cells;          // int4 per slot (grid: two) as CellArgs (tiles.h) describes
+    sph::Buf cell_item;      // int per slot: item
+    sph::Buf cell_pbox;      // float4 x 2 per slot: box of the item's particles at their current offsets
                              // (centre, largest search radius; half widths, 0)
     sph::Buf cells_d;        // int4 per slot as `cells`, with the density's record count (a prefix)
     sph::Buf sched_key, sched_key_alt, sched_val, sched_val_alt;  // cost sort
@@ -203,7 +216,7 @@ struct sph_ctx {
     sph::Buf hs, rhos, fs;   // float, sorted
     sph::Buf status;         // uint8, caller order
     sph::Buf st_s;           // uint8, sorted copy of status
-    sph::Buf scan_cells;     // int: leaves holding particles left to the re-scan
+    sph::Buf scan_cells;     // int: schedule slots holding particles left to the re-scan
     sph::Buf jf;             // 3 float4 per particle for the force loop
     sph::Buf vsig_s;         // float, sorted: signal velocity of the last force pass
     bool vsig_valid = false; // vsig_s matches the current cells and h
@@ -213,8 +226,7 @@ struct sph_ctx {
     bool bal_valid = false;  // bal_s matches the current cells and h
     sph::Buf counters;       // int64[CT_COUNT]
     sph::Buf cons_d;         // double, 4 per box (FP32 force loop)
-    sph::Buf cons_part;      // double, 4 per leaf: each cell's share of cons_d
-    sph::Buf box_leaf;       // int, n_boxes + 1: first leaf of each box (leaves follow the boxes)
+    sph::Buf cons_part;      // double, 4 per item: its share of cons_d
     sph::Buf cons64_d;       // double, CONS_SLOTS x 4 per box (plain FP64 form)
     int64_t* h_counters = nullptr;  // pinned host mirror of counters
     // the build's shape counters and smallest search radius come back without
@@ -413,10 +425,10 @@ void scan_exclusive(sph_ctx* c, const uint32_t* in, uint32_t* out, int64_t n, ui
 void radix_sort(sph_ctx* c, uint64_t* keys, uint32_t* vals, uint64_t* keys_alt,
                 uint32_t* vals_alt, int64_t n, int bits, hipStream_t s, int lo_bit = 0);
 
-// Waits for the build's deferred read-back (if any) and sets h_min and the
-// build info from it.
+// Waits for the build's deferred read-back (if any) and sets h_min, n_pairs
+// and the build info from it.
 void finish_build_read(sph_ctx* c);
-constexpr int BUILD_OUT_WORDS = 5;  // candidate pairs, largest leaf, list, candidates; smallest H (bits)
+constexpr int BUILD_OUT_WORDS = 6;  // candidate pairs, records, largest leaf, list, candidates; smallest H (bits)
 
 void build_cells(sph_ctx* c, int32_t n_boxes, const int64_t* box_first, const double* box_len,
                  int64_t n, const double* pos, const float* h_guess, hipStream_t s);
@@ -469,7 +481,10 @@ double timestep_noalloc(sph_ctx* c, double courant, hipStream_t s);
 void scratch_setup(int device);
 // Offsets from the leaf centres from the current positions (build.hip).
 void refresh_offsets(sph_ctx* c, hipStream_t s);
-// Bounding boxes of the leaves' particles at their current offsets (cell_pbox).
+// The leaves' partner lists and sorted FP64 positions of the current cells,
+// where the build left them out (a grid layout; the plain FP64 form walks them).
+void partner_lists(sph_ctx* c, hipStream_t s);
+// Bounding boxes of the items' particles at their current offsets (cell_pbox).
 void cell_boxes(sph_ctx* c, hipStream_t s);
 // Before a density pass after a drift: reject non-finite positions, and
 // rebuild the cells (around h_caller, or the last guesses when null) once the

@@ -1,34 +1,35 @@
 // FP32 density loop with the smoothing-length solve (section 2, Eq. 1 of the
 // Swift paper, and the choice of h for a fixed weighted neighbour number).
 //
-// Work unit: one leaf cell, handled by one wavefront. The cell's candidates
-// are the particles of every cell within reach (its self task and its pair
-// tasks, section 3.1); they are staged through the wavefront's LDS tile in
-// chunks of 128, shifted into the cell's FP32 frame, and the next chunk is in
-// flight while the current one is used.
+// Work unit: an item of at most 16 particles (tiles.h), handled by one
+// wavefront. Its candidates, the particles of the cells within reach (the self
+// task and the pair tasks of section 3.1), are staged through the wavefront's
+// LDS tile in the item's FP32 frame, the next 64 in flight meanwhile.
 //
-// Two phases per particle of the cell (k_density):
-//   A. every candidate is tested once against the particle's search radius H
-//      (the radius the cells were built for) and the squared distances of the
-//      hits are appended, branch-free, to a per-lane list in LDS;
-//   B. Newton's method on h runs against that list only: each evaluation
-//      reads one float per entry instead of re-testing every candidate. The
-//      density sums of a particle depend only on its own h and the fixed
-//      positions, so the whole iteration stays inside the wavefront: no
-//      global sweep and no ghost pass between iterations.
-// Lists hold distances only, so they serve cells whose candidates all share
-// one mass (checked on the staged chunks); they are sized for the common case
-// so many wavefronts fit on a CU. A particle whose list does not fit, or every
-// particle of a cell with mixed masses, is left to k_density_scan: k_density
-// queues such cells, and the re-scanning kernel (launched after it on the
-// same stream, idle when the queue is empty) solves them over longer lists of
-// distances and masses, 16 lanes per particle. A particle whose root lies
-// beyond its search radius is flagged; the host rebuilds the cells around a
-// larger guess and solves it again.
-//
-// Lanes: a cell's particles are spread over the 64 lanes, 2 to 16 lanes per
-// particle; the lanes of a particle split the candidates and meet through lane
-// shuffles.
+// Two phases (k_density):
+//   A. the matrix cores propose the candidates inside each particle's search
+//      radius (the filter of tiles.h); the distances of those, from FP32
+//      differences, go to the particle's list in LDS;
+//   B. the four lanes of a particle hold its list in registers and run
+//      Newton's method on h against it: the density sums of a particle depend
+//      only on its own h and the fixed positions, so the whole iteration stays
+//      inside the wavefront: no global sweep and no ghost pass between
+//      iterations.
+// With a margin above LIST_WIDE the lists at first reach LIST_GROW times the
+// starting h rather than the H the cells were built for: a third fewer entries
+// at the default margin of 1.26, and a particle whose root lies beyond gets a
+// second list out to H. (With a narrow margin H is the better guide: cells
+// rebuilt around converged radii are often met with poorer starting values.)
+// Particles whose lists did not fit are taken again, four at a time with four
+// times the room. Lists hold distances only, so items whose candidates do not
+// all share one mass (checked on the staged candidates) take one more sweep
+// over them for the mass-weighted sums at the final h. A particle with more
+// neighbours than even that room holds is left to k_density_scan: k_density
+// queues its item, and the re-scanning kernel (launched after it on the same
+// stream, idle when the queue is empty) solves it over longer lists of distances
+// and masses, or by re-testing every candidate, 16 lanes per particle. A
+// particle whose root lies beyond its search radius H is flagged; the host
+// rebuilds the cells around a larger guess and solves it again.
 #include "common.h"
 #include "tiles.h"
 
@@ -40,21 +41,14 @@ namespace {
 
 constexpr int BS = 64;         // one wavefront per block (finest LDS allocation)
 constexpr int WAVES = BS / 64;
-constexpr int DCH = 128;       // candidates per staged chunk (list kernel)
-constexpr int DSLOTS = 30;     // list entries per lane, plus one spare slot that
-                               // takes the stores of misses once a list is full
-                               // (with a 128-candidate tile: < 10 KB of LDS per
-                               // wavefront, 16 wavefronts per CU)
-constexpr int DCH_U = 192;     // candidates per chunk of the persistent list kernel without
-                               // culling, which streams every chunk: fewer, longer chunks per
-                               // cell (batched list kernel -1.1%). At three wavefronts per SIMD
-                               // the LDS allows it; the hardware-dispatch instance, at four,
-                               // would lose wavefronts (Sedov +5%), and keeps DCH
-constexpr int SCAP = 512;      // candidates per LDS chunk (re-scanning kernel)
-static_assert(DCH % (4 * 16) == 0 && DCH_U % (8 * 4) == 0 && DCH_U % 64 == 0, "every phase-A stride divides a chunk");
+constexpr int DCAP = 128;      // candidates per LDS tile (list kernel)
+constexpr int SCAP = 512;      // candidates per LDS tile (re-scanning kernel)
+constexpr float LIST_GROW = 1.12f;  // first list radius over the starting h, where the margin is wide
+constexpr double LIST_WIDE = 1.2;   // h_margin from which lists start at LIST_GROW
+constexpr int LIST_MOST = 240;      // candidates inside it from which a particle counts as re-scanned
 
 struct DensArgs {
-    const float4* jd;        // sorted (x, y, z) in the leaf frame, m
+    const float4* jd;        // sorted (x, y, z) as the layout stores them, m
     const float* Hs;         // sorted search radii
     float* hs;               // sorted h: in, start value; out, result
     float* rhos;
@@ -67,13 +61,8 @@ struct DensArgs {
     float* f_out;
     float* nw_out;           // weighted neighbour count (null: not wanted)
     uint8_t* status;         // caller order
-    const int4* cells;       // per schedule slot: first particle, count, first neighbour entry, and
-                             // the entries within the leaf's largest search radius (a prefix of its
-                             // list: the density needs no others)
-    const float4* cell_pbox; // per schedule slot, 2: bounding box of the leaf's particles (centre, largest
-                             // search radius; half widths, 0), at their current offsets
-    const int2* p_rec;       // per (cell, neighbour cell) record: first particle and count of the neighbour
-    const float4* p_shift;
+    CellArgs cell;           // the items, their frames and candidates (tree: the records within the leaf's
+                             // largest search radius, a prefix of its list: the density needs no others)
     int64_t* ctr;
     int* scan_cells;         // schedule slots queued for k_density_scan (ctr[CT_SCAN_CELLS] of them)
     WorkSched W;             // which wavefront takes which cell
@@ -81,8 +70,6 @@ struct DensArgs {
     float inv_target;        // 1 / target
     float tol;               // on |S0 / target - 1|
     int max_iter;
-    int lpi_min;             // fewest lanes per particle (a power of two): spreads a list over enough slots
-    float nl_est;            // expected list length of a particle: n_ngb * h_margin^3
     // ghost step fused into the outputs (null jf: not fused): the force
     // loop's three float4 per particle from the final h, rho, f and the
     // caller-order velocity and u
@@ -91,21 +78,22 @@ struct DensArgs {
     float4* jf;
     float gamma;
     const float* drift;      // [0]: bound on the drift since the build (search Hs - 2 drift)
+    float grow;              // first list radius over the starting h
     int detail;              // count the list-building tests and the listed candidates
                              // (sph_params.timing = 2; the list kernel's DETAIL instance)
 };
 
-// Sorted copies of position (cell frame), mass, h and state. fresh: every
+// Sorted copies of position (bits as the layout stores it), mass, h and state. fresh: every
 // particle starts active; otherwise the caller-order state of the previous
 // pass is kept (an overflowed particle starts again). The pass's fused ghost
 // step reads velocity and u itself, by caller index, where it writes the
 // particle's force streams: copying them here would gather them once more.
 __global__ void __launch_bounds__(256) k_dens_prologue(int64_t n, const uint32_t* __restrict__ perm,
-                                                       const float4* __restrict__ xrel,
+                                                       const int4* __restrict__ xs,
                                                        const float* __restrict__ mass,
                                                        const float* __restrict__ h_in,
                                                        const uint8_t* __restrict__ status, int fresh,
-                                                       float4* __restrict__ jd, float* __restrict__ hs,
+                                                       int4* __restrict__ jd, float* __restrict__ hs,
                                                        uint8_t* __restrict__ st_s, int64_t* __restrict__ ctr)
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -114,8 +102,8 @@ __global__ void __launch_bounds__(256) k_dens_prologue(int64_t n, const uint32_t
         const uint32_t o = perm[p];
         const float m = mass[o];
         const float h = h_in[o];
-        const float4 x = xrel[p];
-        jd[p] = make_float4(x.x, x.y, x.z, m);
+        const int4 x = xs[p];
+        jd[p] = make_int4(x.x, x.y, x.z, __float_as_int(m));
         hs[p] = h;
         const uint8_t st = fresh ? (uint8_t)ST_ACTIVE : status[o];
         st_s[p] = st == ST_OVERFLOW ? (uint8_t)ST_ACTIVE : st;
@@ -211,465 +199,473 @@ __device__ __forceinline__ void hsolve_step(HSolve& s, float S0, float S1, float
 // false leaves the sorted state as it is: the re-scanning kernel's wavefronts
 // that share a cell number its flagged particles from it, and nothing reads it
 // after that kernel (the caller-order state carries over to the next pass).
-template <bool SORTED_STATE = true, class I>
-__device__ __forceinline__ void write_result(const DensArgs& A, int i, uint32_t o, const HSolve& s, float S0,
-                                             float M0, float M1, int cnt, I& inter_acc, I& n_over,
-                                             I& n_unconv, int& max_ev)
+template <bool SORTED_STATE = true>
+__device__ __forceinline__ void write_result(KernArgs<DensArgs> A, int i, uint32_t o, const HSolve& s, float S0,
+                                             float M0, float M1)
 {
     float h_report = s.h;
     if (s.state == ST_OVERFLOW) {
         // propose the radius at which a uniform density would hold the target
         // (the rebuild starts this particle from there)
-        h_report = s.h * fmaxf(cbrtf(A.target / S0), 1.0f) * 1.05f;
+        h_report = s.h * fmaxf(cbrtf(A->target / S0), 1.0f) * 1.05f;
     }
-    // (selects, not branches: a branch here makes the compiler keep the two
-    // counters in a scratch array behind a pointer select)
-    n_over += s.state == ST_OVERFLOW ? 1 : 0;
-    n_unconv += s.state == ST_UNCONVERGED ? 1 : 0;
+    // (rare: counted at once rather than in registers that live through the kernel)
+    if (s.state == ST_OVERFLOW) atomicAdd((unsigned long long*)&ctr_slot(A->ctr)[CT_OVERFLOW], 1ull);
+    if (s.state == ST_UNCONVERGED) atomicAdd((unsigned long long*)&ctr_slot(A->ctr)[CT_UNCONV], 1ull);
     const float hinv = __builtin_amdgcn_rcpf(s.h);
     const float rho = (8.0f / SPH_PI_F) * M0 * hinv * hinv * hinv;
     const float f = M1 < 0.0f ? -3.0f * M0 * __builtin_amdgcn_rcpf(M1) : 1.0f;
-    A.hs[i] = s.h;
-    A.rhos[i] = rho;
-    A.fs[i] = f;
-    if (SORTED_STATE) A.st_s[i] = s.state;
-    A.h_out[o] = h_report;
-    A.rho_out[o] = rho;
-    A.f_out[o] = f;
-    if (A.nw_out) A.nw_out[o] = (32.0f / 3.0f) * S0;
-    A.status[o] = s.state;
-    if (s.state == ST_DONE) inter_acc += cnt - 1;
-    max_ev = max(max_ev, s.nev);
-    if (A.jf) {
+    A->hs[i] = s.h;
+    A->rhos[i] = rho;
+    A->fs[i] = f;
+    if (SORTED_STATE) A->st_s[i] = s.state;
+    A->h_out[o] = h_report;
+    A->rho_out[o] = rho;
+    A->f_out[o] = f;
+    if (A->nw_out) A->nw_out[o] = (32.0f / 3.0f) * S0;
+    A->status[o] = s.state;
+    if (A->jf) {
         // the ghost step of this particle (the same arithmetic as the force
         // loop's ghost kernel, so both give the same bits), with the checks
         // of its velocity and u: every particle of the pass passes here once
-        const float4 x = A.jd[i];
+        const float4 x = A->jd[i];
         const float h = s.h;
-        const float uu = A.u_in[o];
-        const float vx = A.vel_in[3 * (int64_t)o], vy = A.vel_in[3 * (int64_t)o + 1],
-                    vz = A.vel_in[3 * (int64_t)o + 2];
+        const float uu = A->u_in[o];
+        const float vx = A->vel_in[3 * (int64_t)o], vy = A->vel_in[3 * (int64_t)o + 1],
+                    vz = A->vel_in[3 * (int64_t)o + 2];
         if (!(uu >= 0.0f) || !isfinite(uu) || !isfinite(vx) || !isfinite(vy) || !isfinite(vz))
-            atomicAdd((unsigned long long*)&ctr_slot(A.ctr)[CT_BAD_INPUT], 1ull);
-        const float gamma = A.gamma;
+            atomicAdd((unsigned long long*)&ctr_slot(A->ctr)[CT_BAD_INPUT], 1ull);
+        const float gamma = A->gamma;
         const float P = (gamma - 1.0f) * rho * uu;
         const float c = sqrtf(gamma * (gamma - 1.0f) * uu);
         const float phi = f * P / (rho * rho);
-        A.jf[3 * (int64_t)i + 0] = make_float4(x.x, x.y, x.z, h * h);
-        A.jf[3 * (int64_t)i + 1] = make_float4(vx, vy, vz, x.w);
-        A.jf[3 * (int64_t)i + 2] = make_float4(rho, phi, c, 1.0f / h);
+        A->jf[3 * (int64_t)i + 0] = make_float4(x.x, x.y, x.z, h * h);
+        A->jf[3 * (int64_t)i + 1] = make_float4(vx, vy, vz, x.w);
+        A->jf[3 * (int64_t)i + 2] = make_float4(rho, phi, c, 1.0f / h);
     }
 }
 
-__device__ __forceinline__ void flush_counters(const DensArgs& A, int64_t cand_acc, int64_t list_acc,
-                                               int64_t inter_acc, int64_t sweep_acc, int64_t n_over,
-                                               int64_t n_unconv, int max_ev, int64_t n_scan,
+// The wavefront's totals (every argument wave-uniform).
+__device__ __forceinline__ void flush_counters(KernArgs<DensArgs> A, int64_t cand_acc, int64_t list_acc,
+                                               int64_t inter_acc, int64_t sweep_acc, int max_ev, int64_t n_scan,
                                                int64_t listed_acc)
 {
-    // cand_acc and listed_acc are wavefront totals already
-    ctr_add_uniform(A.ctr, CT_DENS_CAND, cand_acc);
-    if (A.detail) {
-        ctr_add_uniform(A.ctr, CT_DENS_TESTS, cand_acc);
-        ctr_add_uniform(A.ctr, CT_DENS_LISTED, listed_acc);
+    ctr_add_uniform(A->ctr, CT_DENS_CAND, cand_acc + list_acc);
+    if (A->detail) {
+        ctr_add_uniform(A->ctr, CT_DENS_TESTS, cand_acc);
+        ctr_add_uniform(A->ctr, CT_DENS_LISTED, listed_acc);
     }
-    ctr_wave_add(A.ctr, CT_DENS_CAND, list_acc);
-    ctr_wave_add(A.ctr, CT_DENS_INTER, inter_acc);
-    ctr_wave_add(A.ctr, CT_DENS_SWEEP_INTER, sweep_acc);
-    ctr_wave_add(A.ctr, CT_OVERFLOW, n_over);
-    ctr_wave_add(A.ctr, CT_UNCONV, n_unconv);
-    ctr_wave_add(A.ctr, CT_NEED_SCAN, n_scan);
-    ctr_wave_max_sweeps(A.ctr, max_ev);
-}
-
-// Flag the still-active particles [first, ni) of the cell starting at i0 for
-// the re-scanning kernel; returns how many of them this lane flagged.
-__device__ __forceinline__ int flag_for_scan(const DensArgs& A, int i0, int first, int ni)
-{
-    int n = 0;
-    for (int gi = first + (int)(threadIdx.x & 63); gi < ni; gi += 64) {
-        if (A.st_s[i0 + gi] == ST_ACTIVE) {
-            A.st_s[i0 + gi] = ST_SCAN;
-            ++n;
-        }
-    }
-    return n;
+    ctr_add_uniform(A->ctr, CT_DENS_INTER, inter_acc);
+    ctr_add_uniform(A->ctr, CT_DENS_SWEEP_INTER, sweep_acc);
+    ctr_add_uniform(A->ctr, CT_NEED_SCAN, n_scan);
+    if ((threadIdx.x & 63) == 0) atomicMax((unsigned long long*)&ctr_slot(A->ctr)[CT_SWEEPS], (unsigned long long)max_ev);
 }
 
 // Queue schedule slot `slot` for the re-scanning kernel when any lane flagged
 // a particle of its cell.
-__device__ __forceinline__ void enqueue_scan(const DensArgs& A, int slot, int n_flag)
+__device__ __forceinline__ void enqueue_scan(KernArgs<DensArgs> A, int slot, int n_flag)
 {
     if (__any(n_flag > 0) && (threadIdx.x & 63) == 0) {
-        const int64_t k = (int64_t)atomicAdd((unsigned long long*)&A.ctr[CT_SCAN_CELLS], 1ull);
-        A.scan_cells[k] = slot;
+        const int64_t k = (int64_t)atomicAdd((unsigned long long*)&A->ctr[CT_SCAN_CELLS], 1ull);
+        A->scan_cells[k] = slot;
     }
 }
 
 // ---- the list kernel ----------------------------------------------------------------
 
-// Phase A over one staged chunk for the lanes of one particle: the lane with
-// index sub in its group tests candidates sub, sub + LPI, ... (tc points at
-// candidate sub) and appends the squared distance of every hit inside H to
-// its list. The chunk is padded with far positions to its full size
-// (commit_chunk_padded), so there is no bounds test; U tile reads (x, y, z
-// only) are in flight at once (eight where the lanes per particle are fixed
-// at four: 0.7% faster; four where they vary, since eight wide groups pad
-// more) and the appends are branch-free
-// (the store always happens, the slot only advances on a hit). The slot is
-// kept as a byte offset into the lists (o, advancing by one row of 64
-// floats per hit) and clamped to the lane's spare slot (o_cap).
-template <int LPI, int U = 4>
-__device__ __forceinline__ void scan_chunk(const float4* tc, int len, float xx, float xy, float xz, float H2,
-                                           float* lists, unsigned& o, unsigned o_cap)
+// One wavefront per item. LCAP: list entries of a particle, LCAP / 4 per lane in
+// registers. UNI: a grid layout (no culling of the candidates there: a cell one
+// search radius wide loses only the block's corners, which costs about what it
+// saves; a tree layout keeps the candidates within reach of the box around the
+// item's particles). DETAIL: also count the candidates inside H
+// (sph_params.timing = 2).
+//
+// Rounds: the first takes all of the item's particles, four lanes each; those
+// whose list did not fit, or whose root lies beyond it, are taken up to four at
+// a time after that, 16 lanes and four times the room each.
+template <int LCAP, bool UNI, bool DETAIL>
+__global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_density(DensArgs A)
 {
-    const int len_pad = (len + U * LPI - 1) & ~(U * LPI - 1);
-    char* base = reinterpret_cast<char*>(lists);
-    for (int k0 = 0; k0 < len_pad; k0 += U * LPI, tc += U * LPI) {
-        float3 pj[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) pj[u] = *reinterpret_cast<const float3*>(tc + u * LPI);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float dx = xx - pj[u].x, dy = xy - pj[u].y, dz = xz - pj[u].z;
-            const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-            *reinterpret_cast<float*>(base + min(o, o_cap)) = r2;
-            o += r2 < H2 ? 256u : 0u;
-        }
-    }
-}
-
-// The first 64 neighbour records of a cell (lane q: record q), loaded with
-// independent loads. A wavefront with a next cell loads them for that cell
-// while it computes the current one; the particles of a cell are loaded
-// together with its first chunk of candidates. So the chain cell -> records
-// -> candidates costs about one memory latency per cell, not three.
-struct CellRecs {
-    int4 ci;      // first particle, count, first record, records
-    int2 rec;     // p_rec of record `lane`
-    float4 sh;    // p_shift of record `lane`
-};
-
-__device__ __forceinline__ void cell_recs(const DensArgs& A, CellRecs& P)
-{
+    static_assert(LCAP % 16 == 0, "a lane reads its list four entries at a time");
+    constexpr int SEG = LCAP + 4;    // (skewed against bank conflicts)
+    constexpr int NR = LCAP / 16;
+    constexpr int NW = (DCAP + 127) / 128;
+    constexpr int U = 2;             // candidates per lane and step
+    constexpr float FAR2 = 1.0e30f;  // r^2 of an empty entry
+    __shared__ float4 t0[DCAP];      // x, y, z, m
+    __shared__ uint2 fa[DCAP];       // filter input: x, y; z, |x|^2 (half precision)
+    __shared__ float4 list4[16 * SEG / 4];
+    __shared__ float4 scratch4[WALK_LDS<UNI> / 16];
+    float* list = reinterpret_cast<float*>(list4);
+    char* scratch = reinterpret_cast<char*>(scratch4);
     const int lane = threadIdx.x & 63;
-    const int pb0 = P.ci.z, np = P.ci.w;
-    P.rec = make_int2(0, 0);
-    P.sh = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (lane < np) {
-        P.rec = A.p_rec[pb0 + lane];
-        P.sh = A.p_shift[pb0 + lane];
-    }
-}
-
-// One evaluation of the sums over a lane's list at 1/h = hinv. w(q) = 2 t^3 -
-// 8 u^3 and q w'(q) = q (24 u^2 - 6 t^2) with t = max(1 - q, 0), u =
-// max(1/2 - q, 0): the cubic spline as truncated powers, no branch and no
-// select (both clamps are the FMA's clamp to [0, 1]). FIRST: the list still
-// holds r^2; each entry is replaced by r as it is read.
-template <bool FIRST>
-__device__ __forceinline__ void eval_list(float* lst, int len, float hinv, float& S0, float& S1, int& cnt)
-{
-    float At = 0.f, Au = 0.f, Bt = 0.f, Bu = 0.f;
-    int c = 0;
-#pragma unroll 2
-    for (int e = 0; e < len; ++e) {
-        float r = lst[e * 64];
-        if (FIRST) {
-            r = __builtin_amdgcn_sqrtf(r);
-            lst[e * 64] = r;
-        }
-        const float q = r * hinv;
-        const float t = __builtin_amdgcn_fmed3f(fmaf(-r, hinv, 1.0f), 0.0f, 1.0f);
-        const float u = __builtin_amdgcn_fmed3f(fmaf(-r, hinv, 0.5f), 0.0f, 1.0f);
-        const float t2 = t * t, u2 = u * u;
-        At = fmaf(t2, t, At);
-        Au = fmaf(u2, u, Au);
-        Bt = fmaf(q, t2, Bt);
-        Bu = fmaf(q, u2, Bu);
-        c += t > 0.0f ? 1 : 0;  // r < h
-    }
-    S0 = fmaf(2.0f, At, -8.0f * Au);
-    S1 = fmaf(24.0f, Bu, -6.0f * Bt);
-    cnt = c;
-}
-
-// One wavefront per cell. TCAP: candidates the LDS tile holds; a cell with at
-// most TCAP candidates stages them once and keeps them for all its passes,
-// a larger one streams them through the first DCH slots in every pass.
-// PERSIST (the per-XCD queues): a wavefront takes cell after cell and loads
-// the next cell's records while it computes the current one; the registers
-// that takes leave three wavefronts per SIMD, which then cover the memory
-// latency the prefetch does not. Hardware dispatch (one cell per wavefront)
-// has no next cell: at most 128 VGPRs, four wavefronts per SIMD.
-// DETAIL: also count the candidates listed (sph_params.timing = 2); a
-// separate instance, since the counter costs the hot loop registers.
-// CULL: the culling of staged candidates and the per-cell choice of lanes
-// per particle (layouts that split a top cell, or whose lists need more
-// than four lanes); without it, four lanes per particle and no culling,
-// which lets the compiler specialise every loop on the lane count.
-template <int TCAP, bool PERSIST, bool DETAIL, bool CULL>
-__global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(PERSIST ? 3 : 4))) k_density(DensArgs A)
-{
-    constexpr int CH = (CULL || !PERSIST) ? DCH : DCH_U;  // candidates per streamed chunk
-    __shared__ float4 tile[CULL ? TCAP : CH];  // (no resident tiles without CULL)
-    __shared__ float lists[(DSLOTS + 1) * 64];
-    __shared__ uint8_t marks[CH];  // record starts of the chunk being fetched
-    __shared__ float4 box_lds[2];   // the cell's particle box (cull_pbox), culling cells only
-    const int lane = threadIdx.x & 63;
-    float4* sj = tile;
-    float* lst = lists + lane;
-    const unsigned o_lane = 4u * (unsigned)lane, o_cap = o_lane + 256u * DSLOTS;
+    const int pc = lane & 15, gc = lane >> 4;  // column (particle) and lane group of the filter
+    const int fin = 4 * (lane & 3) + gc;       // the candidate (of 16) this lane feeds to the filter
     const float two_delta = 2.0f * A.drift[0];  // the cells are searched to Hs - 2 drift
     int wstate = 0, a_cur = 0, a_end = 0;
-    int64_t cand_acc = 0;  // wave-uniform
-    // per-lane counts (far below 2^31 for any particle count that fits a GPU)
-    int inter_acc = 0, sweep_acc = 0, n_over = 0, n_unconv = 0, n_scan = 0, list_acc = 0;
-    int max_ev = 0;
-    int64_t listed_acc = 0;  // wave-uniform
+    int64_t cand_acc = 0, inter_acc = 0, sweep_acc = 0, listed_acc = 0, list_acc = 0;  // wave-uniform
+    int n_scan = 0, max_ev = 0;                                                        // wave-uniform
 
-    // the next schedule slot of this wavefront (wave-uniform), if any
-    auto next_slot = [&](int& sl) -> bool {
-        if (a_cur >= a_end && !next_items(A.W, A.ctr, WAVES, wstate, a_cur, a_end)) return false;
-        sl = __builtin_amdgcn_readfirstlane(a_cur++);
-        return true;
-    };
+    for (;;) {
+        if (a_cur >= a_end && !next_items(A.W, A.ctr, WAVES, wstate, a_cur, a_end)) break;
+        const int slot = __builtin_amdgcn_readfirstlane(a_cur);
+        ++a_cur;
+        Item<UNI> it;
+        CandWalk<UNI> w;
+        item_load(it, w, A.cell, slot, 0.5f * two_delta, 0.0f);
+        const int i0 = it.i0, ni = it.ni;
+        // this lane's column
+        const int ic = i0 + min(pc, ni - 1);
+        const float4 jc = A.jd[ic];
+        const float Hc = A.Hs[ic] - two_delta, hc = A.hs[ic];
+        const float m0 = uniform_f(jc.w);  // the mass of the item's first particle
+        const float xc = item_coord<UNI>(jc.x, it.ox, it.sh, it.sl, 0.0f),
+                    yc = item_coord<UNI>(jc.y, it.oy, it.sh, it.sl, 0.0f),
+                    zc = item_coord<UNI>(jc.z, it.oz, it.sh, it.sl, 0.0f);
+        // masks over the item's particles: unsolved; those to be listed out to H; left to the re-scan
+        unsigned todo = (unsigned)__ballot(lane < ni && A.st_s[ic] == ST_ACTIVE);
+        unsigned wide = 0u, scan = 0u;
+        int n_flag = 0;
 
-    int slot = 0;
-    bool have = next_slot(slot);
-    CellRecs cur;
-    if (have) {
-        cur.ci = A.cells[slot];
-        cell_recs(A, cur);
-    }
-    while (have) {
-        int nslot = 0;
-        const bool have_next = PERSIST && next_slot(nslot);
-        CellRecs nxt;
-        if (have_next) nxt.ci = A.cells[nslot];  // in flight while this cell is staged
-        // (a leaf of a layout of top cells only has at most the 27 records of
-        // its block, within one block of 64: telling the compiler drops the
-        // multi-block paths)
-        const int i0 = cur.ci.x, ni = cur.ci.y, pb0 = cur.ci.z, np_all = CULL ? cur.ci.w : min(cur.ci.w, 64);
-        // the cell's first 64 particles, one per lane (in flight with the first chunk)
-        float4 px = make_float4(0.f, 0.f, 0.f, 0.f);
-        float ph = 0.f, pH = 0.f;
-        int pst = ST_DONE;
-        uint32_t pperm = 0;
-        if (lane < ni) {
-            px = A.jd[i0 + lane];
-            ph = A.hs[i0 + lane];
-            pH = A.Hs[i0 + lane] - two_delta;
-            pst = A.st_s[i0 + lane];
-            pperm = A.perm[i0 + lane];
-        }
-        int n_flag = 0;  // this lane's particles of the cell left to the re-scan
-        NbrCursor cu;
-        cursor_init_from(cu, nbr_from(cur.rec, cur.sh, min(np_all, 64)), pb0, np_all);
-        const int nj = np_all <= 64 ? cu.nb.nj : count_candidates(A.p_rec, pb0, np_all);
-        // resident: one block of neighbour records and at most TCAP candidates,
-        // staged once at fixed tile slots of DCH
-        // (the instance without culling always streams: with four lanes a
-        // cell of up to 16 particles takes one pass, where a resident tile
-        // saves nothing, and dropping that path frees registers)
-        const bool resident = CULL && np_all <= 64 && nj <= TCAP;
-        // a layout of top cells only runs with four lanes per particle (its
-        // cells hold similar numbers of particles, for which the choice is
-        // four, and the fixed count lets the compiler specialise every loop)
-        const int lpi = CULL ? choose_lpi(ni, nj, A.lpi_min, 5.0f * A.nl_est, resident, CH) : 4;
-        const int lg = __builtin_ctz(lpi);
-        const int per_pass = 64 >> lg;
-        const int g = lane >> lg;
-        const int sub = lane & (lpi - 1);
-        bool loaded = false;  // (resident) every candidate is in the tile
-        bool mixed = false;   // a candidate with another mass was staged
-        bool pre_issued = false;
-        float m0 = 0.0f;      // the mass of the cell's first particle
-        unsigned kept_pack = 0;  // (resident) candidates kept of each staged chunk, 8 bits each
-        // neighbour cells of other sizes than the cell's own (only where a
-        // top cell was split: CULL)
-        const bool cull = CULL && np_all > 27;
-        // the bounding box of the cell's particles at their current offsets
-        // and the cell's largest search radius; the box waits in LDS for the
-        // commits (held in registers across the passes it would cost the hot
-        // loops)
-        float geom_y = 0.0f;
-        if (cull) {
-            const float4 b = A.cell_pbox[2 * slot + (lane & 1)];
-            if (lane < 2) box_lds[lane] = b;
-            geom_y = uniform_f(__shfl(b.w, 0, 64));
-        }
-
-        for (int ib = 0; ib < ni; ib += per_pass) {
-            const int gi = ib + g;
-            const bool valid = gi < ni;
-            const int i = i0 + (valid ? gi : 0);
-            float4 xi;
-            float h_start, H_i;
-            int st_i;
-            uint32_t o_i;
-            if (ib + per_pass <= 64) {
-                // the particles of this pass were loaded with the cell
-                const int src = valid ? gi : 0;
-                xi.x = __shfl(px.x, src, 64);
-                xi.y = __shfl(px.y, src, 64);
-                xi.z = __shfl(px.z, src, 64);
-                h_start = __shfl(ph, src, 64);
-                H_i = __shfl(pH, src, 64);
-                st_i = __shfl(pst, src, 64);
-                o_i = (uint32_t)__shfl((int)pperm, src, 64);
-            } else {
-                xi = A.jd[i];
-                h_start = A.hs[i];
-                H_i = A.Hs[i] - two_delta;
-                st_i = A.st_s[i];
-                o_i = A.perm[i];
+        for (int round = 0; todo; ++round) {
+            // ---- this round's particles, and which one this lane works for -------------------
+            const int lpp = round == 0 ? 4 : 16, lg = round == 0 ? 2 : 4;
+            const int sub = lane & (lpp - 1);
+            unsigned batch = todo;
+            int pq = lane >> lg;
+            if (round > 0) {
+                unsigned rest = todo;
+                int pk = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    pk = pq == k && rest ? __builtin_ctz(rest) : pk;
+                    rest &= rest - 1;
+                }
+                batch = todo & ~rest;
+                const bool any = pq < __popc(batch);
+                pq = any ? pk : 31;
             }
-            const uint8_t st0 = (uint8_t)st_i;
-            HSolve s = hsolve_init(h_start, H_i, !valid || st0 != ST_ACTIVE, st0);
-            const int active_groups = wave_count(!s.done && sub == 0);
-            if (active_groups == 0) continue;
-
-            // ---- phase A: squared distances inside the search radius -----------
-            unsigned o = o_lane;  // byte offset of this lane's next list slot
+            const bool mine = (batch >> pq) & 1u;
+            const int iq = i0 + (mine ? pq : 0);
+            // column pc: its list segment, and the first lane of its particle
+            const bool inb = (batch >> pc) & 1u;
+            const int rank = round == 0 ? pc : __popc(batch & ((1u << pc) - 1u));
+            const int lane_c = (rank << lg) & 63;
+            const int seg = round == 0 ? SEG * pc : 4 * SEG * rank;
+            const int room = round == 0 ? LCAP : 4 * LCAP;
+            const float h_start = A.hs[iq], H = A.Hs[iq] - two_delta;
+            HSolve s = hsolve_init(h_start, H, !mine, ST_ACTIVE);
             {
-                const float H2 = s.done ? -1.0f : s.Hi * s.Hi;
-                const bool stream = !(resident && loaded);
-                // staging keeps only the candidates within reach of the box of
-                // the cell's particles (cell_pbox, at their current offsets):
-                // the largest search radius of this pass, or of the whole cell
-                // when the tile stays for later passes. A cell of a uniform
-                // grid (27 neighbour cells, all as wide as the reach) loses
-                // only the block's corners, which costs about what it saves,
-                // so it keeps every candidate.
-                const float reach2 = !cull ? 0.0f : cull_reach2(resident ? geom_y : wave_max(s.done ? 0.0f : s.Hi));
-                int kept_tot = 0;
-                ChunkRegs<1, CH> R;
-                if (stream) {
-                    cursor_seek(cu, A.p_rec, A.p_shift, 0);
-                    fetch_chunk(R, A.jd, cu.nb, 0, cursor_chunk(cu, 0, CH), marks);
+                const float R = (wide >> pq) & 1u ? H : fminf(H, A.grow * s.h);
+                s.h = fminf(s.h, R);
+                s.Hi = s.hi = R;
+            }
+            const bool cut = s.Hi < H;  // the list may miss the root
+            bool solved = false, many = false;
+            bool mixed = false;         // wave-uniform: masses differ
+            float fS0 = 0.f, fS1 = 0.f, M0 = 0.f, M1 = 0.f;
+            for (int acc = 0;; acc = 1) {
+                // ---- sweep the candidates: lists inside R, or (acc) the sums inside h ---------------
+                float Rc;
+                if (acc) {
+                    Rc = __shfl(solved ? s.h : 0.0f, lane_c, 64);
+                } else {
+                    const float h0 = !(hc > 0.0f) || hc > Hc ? Hc : hc;
+                    Rc = (wide >> pc) & 1u ? Hc : fminf(Hc, A.grow * h0);
                 }
-                if (have_next && !pre_issued) {
-                    // the next cell's records, in flight from here on
-                    cell_recs(A, nxt);
-                    pre_issued = true;
+                if (!inb) Rc = 0.0f;
+                const float R2 = Rc * Rc;
+                const float hic = __builtin_amdgcn_rcpf(Rc > 0.0f ? Rc : 1.0f);
+                const float reach = uniform_f(group_max(Rc, 16));
+                const float reach2 = cull_reach2(reach);
+                const float fs = FILTER_SCALE / (fmaxf(fmaxf(it.hx, it.hy), it.hz) + reach);
+                f16x4 fcol;
+                f32x4 C;
+                {
+                    const float ux = (xc - it.bx) * fs, uy = (yc - it.by) * fs, uz = (zc - it.bz) * fs;
+                    const float n2 = fmaf(ux, ux, fmaf(uy, uy, uz * uz)) * (1.0f - FILTER_EPS) - FILTER_ABS;
+                    fcol = filter_column(ux, uy, uz);
+                    const float c = Rc > 0.0f ? fmaf(R2 * (fs * fs), -(1.0f + FILTER_EPS), n2) : 1.0e9f;
+                    C = {c, c, c, c};
                 }
-                // the cell's own particles are among its candidates: when
-                // every candidate has this mass, so has every particle of it
-                m0 = __shfl(px.w, 0, 64);
-                int len;
-                for (int c0 = 0; c0 < nj; c0 += len) {
-                    len = stream ? R.len : min(CH, nj - c0);
-                    const float4* tc = resident ? sj + c0 : sj;
-                    int slen;  // candidates of this chunk within reach
-                    if (stream) {
-                        mixed |= chunk_mass_differs(R, m0);
-                        // store this chunk's candidates within reach (padded to
-                        // DCH), put the next chunk in flight
-                        if (cull) {
-                            const float4 b0 = box_lds[0], b1 = box_lds[1];
-                            CullBox cbox;
-                            cbox.cx = b0.x;
-                            cbox.cy = b0.y;
-                            cbox.cz = b0.z;
-                            cbox.hx = b1.x;
-                            cbox.hy = b1.y;
-                            cbox.hz = b1.z;
-                            slen = commit_chunk_culled_padded(sj + (resident ? c0 : 0), R, cbox, reach2);
-                        } else {
-                            commit_chunk_padded(sj + (resident ? c0 : 0), R);
-                            slen = len;
+                int T = 0, kept = 0, nk = 0;  // entries of this column's particle; candidates kept; in the tile
+                int inside = 0;               // (DETAIL) lane p: candidates of particle p inside its H
+                bool differs = false;
+                float cM0t = 0.f, cM0u = 0.f, cM1t = 0.f, cM1u = 0.f;
+                Slots<U> S;
+                float4 p0[U];
+                auto fetch = [&]() -> bool {
+                    if (!walk_next<U>(w, A.cell, scratch, S)) return false;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) p0[u] = A.jd[S.src[u]];
+                    return true;
+                };
+                walk_start(w, A.cell, scratch);
+                bool more = fetch();
+                for (;;) {
+                    // ---- stage, while the tile has room ------------------------------------------------
+                    bool full = !more;
+                    if (more) {
+                        float x[U], y[U], z[U];
+                        uint64_t m[U];
+                        int n = 0;
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            x[u] = item_coord<UNI>(p0[u].x, it.ox, it.sh, it.sl, S.sh[u].x);
+                            y[u] = item_coord<UNI>(p0[u].y, it.oy, it.sh, it.sl, S.sh[u].y);
+                            z[u] = item_coord<UNI>(p0[u].z, it.oz, it.sh, it.sl, S.sh[u].z);
+                            bool keep = S.ok[u];
+                            if constexpr (!UNI) {
+                                const float gx = fmaxf(fabsf(x[u] - it.bx) - it.hx, 0.0f),
+                                            gy = fmaxf(fabsf(y[u] - it.by) - it.hy, 0.0f),
+                                            gz = fmaxf(fabsf(z[u] - it.bz) - it.hz, 0.0f);
+                                keep = keep && fmaf(gx, gx, fmaf(gy, gy, gz * gz)) < reach2;
+                            }
+                            m[u] = __ballot(keep);
+                            n += __popcll(m[u]);
                         }
-                        // (a resident tile is scanned again by later passes)
-                        if (resident) kept_pack |= (unsigned)slen << (8 * (c0 / CH));
-                        const int nx = c0 + len;
-                        if (nx < nj) {
-                            cursor_seek(cu, A.p_rec, A.p_shift, nx);
-                            fetch_chunk(R, A.jd, cu.nb, nx - cu.off0, cursor_chunk(cu, nx, CH), marks);
+                        full = nk + n > DCAP;
+                        if (!full) {
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                differs |= S.ok[u] && p0[u].w != m0;
+                                if constexpr (DETAIL) {
+                                    for (int p = 0; p < (round == 0 && !acc ? ni : 0); ++p) {
+                                        const float Hp = __shfl(inb ? Hc : 0.0f, p, 64);
+                                        const float dx = x[u] - __shfl(xc, p, 64), dy = y[u] - __shfl(yc, p, 64),
+                                                    dz = z[u] - __shfl(zc, p, 64);
+                                        const int k =
+                                            wave_count(S.ok[u] && fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < Hp * Hp);
+                                        inside += lane == p ? k : 0;
+                                    }
+                                }
+                                if ((m[u] >> lane) & 1u) {
+                                    const int d = nk + lanes_below(m[u]);
+                                    const float fx = (x[u] - it.bx) * fs, fy = (y[u] - it.by) * fs,
+                                                fz = (z[u] - it.bz) * fs;
+                                    const float n2 = fmaf(fx, fx, fmaf(fy, fy, fz * fz)) * (1.0f - FILTER_EPS);
+                                    fa[d] = make_uint2(pack_f16(fx, fy), pack_f16(fz, n2));
+                                    t0[d] = make_float4(x[u], y[u], z[u], p0[u].w);
+                                }
+                                nk += __popcll(m[u]);
+                            }
+                            more = fetch();
+                        }
+                    }
+                    if (!full) continue;
+                    kept += nk;
+                    if (nk + lane < ((nk + 63) & ~63)) fa[nk + lane] = make_uint2(0u, pack_f16(0.0f, FILTER_FAR));
+                    wave_sync_lds();
+
+                    // ---- filter --------------------------------------------------------------------------
+                    unsigned hit[NW];
+#pragma unroll
+                    for (int k = 0; k < NW; ++k) hit[k] = 0u;
+#pragma unroll
+                    for (int q = 0; q < DCAP / 64; ++q) {
+                        if (64 * q < nk) {
+                            unsigned m = hit[q >> 1];
+#pragma unroll
+                            for (int b = 4 * q; b < 4 * q + 4; ++b) {
+                                const uint2 a = fa[16 * b + fin];
+                                const f32x4 D =
+                                    __builtin_amdgcn_mfma_f32_4x4x4f16(f16x4_of(a.x, a.y), fcol, C, 0, 0, 0);
+#pragma unroll
+                                for (int r = 0; r < 4; ++r) m = __builtin_amdgcn_alignbit(m, __float_as_uint(D[r]), 31);
+                            }
+                            hit[q >> 1] = m;
+                        }
+                    }
+                    if (acc) {
+                        // the mass-weighted sums at the final h (zero from r = h on)
+#pragma unroll
+                        for (int k = 0; k < NW; ++k) {
+                            unsigned m = hit[k];
+                            const int top = 128 * k + 4 * (word_tests(nk, k) - 1) + gc;
+                            while (m) {
+                                const int bit = __builtin_ctz(m);
+                                m &= m - 1;
+                                const float4 q = t0[top - 4 * bit];
+                                const float dx = xc - q.x, dy = yc - q.y, dz = zc - q.z;
+                                const float r = __builtin_amdgcn_sqrtf(fmaf(dx, dx, fmaf(dy, dy, dz * dz)));
+                                const float t = __builtin_amdgcn_fmed3f(fmaf(-r, hic, 1.0f), 0.0f, 1.0f);
+                                const float u = __builtin_amdgcn_fmed3f(fmaf(-r, hic, 0.5f), 0.0f, 1.0f);
+                                const float mt = q.w * t * t, mu = q.w * u * u;
+                                cM0t = fmaf(mt, t, cM0t);
+                                cM0u = fmaf(mu, u, cM0u);
+                                cM1t = fmaf(r * hic, mt, cM1t);
+                                cM1u = fmaf(r * hic, mu, cM1u);
+                            }
                         }
                     } else {
-                        slen = (int)((kept_pack >> (8 * (c0 / CH))) & 0xffu);
+                        int n = 0, tot = 0;
+#pragma unroll
+                        for (int k = 0; k < NW; ++k) n += __popc(hit[k]);
+                        const int pre = column_excl_scan(n, tot);
+                        float* lp = list + seg + T + pre;
+                        T += tot;
+                        const bool fits = T <= room;
+#pragma unroll
+                        for (int k = 0; k < NW; ++k) {
+                            unsigned m = fits ? hit[k] : 0u;
+                            const int top = 128 * k + 4 * (word_tests(nk, k) - 1) + gc;
+                            while (m) {
+                                const int bit = __builtin_ctz(m);
+                                m &= m - 1;
+                                const float4 q = t0[top - 4 * bit];
+                                const float dx = xc - q.x, dy = yc - q.y, dz = zc - q.z;
+                                const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                                // (the filter's margin lets a few through: kept as empty entries)
+                                *lp++ = r2 < R2 ? r2 : FAR2;
+                            }
+                        }
                     }
-                    kept_tot += slen;
-                    if (lpi == 2)
-                        scan_chunk<2>(tc + sub, slen, xi.x, xi.y, xi.z, H2, lists, o, o_cap);
-                    else if (lpi == 4)
-                        scan_chunk<4, CULL ? 4 : 8>(tc + sub, slen, xi.x, xi.y, xi.z, H2, lists, o, o_cap);
-                    else if (lpi == 8)
-                        scan_chunk<8>(tc + sub, slen, xi.x, xi.y, xi.z, H2, lists, o, o_cap);
-                    else
-                        scan_chunk<16>(tc + sub, slen, xi.x, xi.y, xi.z, H2, lists, o, o_cap);
-                    if (!resident) wave_sync_lds();
+                    wave_sync_lds();
+                    nk = 0;
+                    if (!more) break;
                 }
-                loaded = true;
-                cand_acc += (int64_t)active_groups * kept_tot;
-            }
-            int nl = (int)((o - o_lane) >> 8);
-            if (mixed) {
-                // lists hold no masses: the cell's remaining particles re-scan
-                // (every candidate is staged in the first pass that streams,
-                // and earlier passes had no active particle)
-                n_flag += flag_for_scan(A, i0, ib, ni);
-                break;
-            }
-            // a group whose list does not fit goes to the re-scanning kernel
-            const bool fits = group_sum_i(nl > DSLOTS ? 1 : 0, lpi) == 0;
-            if (!s.done && !fits) {
-                s.done = true;
-                if (sub == 0) {
-                    A.st_s[i] = ST_SCAN;
-                    ++n_flag;
+                mixed |= __any(differs);
+                cand_acc += (int64_t)__popc((unsigned)__ballot(Rc > 0.0f) & 0xffffu) * kept;
+                if (acc) {
+                    // the column's lanes, then over to the particle's
+                    float t = cM0t, u = cM0u, v = cM1t, x = cM1u;
+#pragma unroll
+                    for (int o = 16; o <= 32; o <<= 1) {
+                        t += __shfl_xor(t, o, 64);
+                        u += __shfl_xor(u, o, 64);
+                        v += __shfl_xor(v, o, 64);
+                        x += __shfl_xor(x, o, 64);
+                    }
+                    M0 = __shfl(fmaf(2.0f, t, -8.0f * u), pq & 15, 64);
+                    M1 = __shfl(fmaf(24.0f, x, -6.0f * v), pq & 15, 64);
+                    break;
                 }
-            }
-            if (s.done) nl = 0;
-            wave_sync_lds();
-            nl = balance_lists(lists, nl, lpi);  // phase B's trip count follows the mean, not the longest list
 
-            // ---- phase B: Newton iteration on h over the list --------------------
-            // (fS0, fS1, fcnt: the sums of this particle's last evaluation; a
-            // finished particle skips its list while others still iterate; the
-            // first evaluation also turns r^2 into r)
-            float fS0 = 0.f, fS1 = 0.f;
-            int fcnt = 0;
-            bool first = true;
-            while (__any(!s.done)) {
-                const float hinv = __builtin_amdgcn_rcpf(s.h);
-                const int len_l = s.done ? 0 : nl;
-                float S0, S1;
-                int cnt;
-                if (first)
-                    eval_list<true>(lst, len_l, hinv, S0, S1, cnt);
-                else
-                    eval_list<false>(lst, len_l, hinv, S0, S1, cnt);
-                first = false;
-                list_acc += len_l;
-                S0 = group_sum(S0, lpi);
-                S1 = group_sum(S1, lpi);
-                cnt = group_sum_i(cnt, lpi);
-                if (s.done) continue;
-                if (sub == 0) sweep_acc += cnt;
-                fS0 = S0;
-                fS1 = S1;
-                fcnt = cnt;
-                hsolve_step(s, S0, S1, A.inv_target, A.tol, A.max_iter);
+                // ---- the lists that fit, in registers: entries 4 (j lpp + sub) ... + 3 -----------------
+                const unsigned over = (unsigned)__ballot(inb && T > room) & 0xffffu;
+                if (round > 0) scan |= over;  // (no room here either)
+                if (round == 0) n_scan += wave_count(lane < 16 && inb && T > LIST_MOST);  // walked again
+                if constexpr (DETAIL) {
+                    if (round == 0) {
+                        int v = lane < 16 && inb ? inside : 0;
+                        for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+                        listed_acc += __builtin_amdgcn_readfirstlane(v);
+                    }
+                }
+                const int Tq = __shfl(T, pq & 15, 64);
+                solved = mine && Tq <= room;
+                many = Tq > LIST_MOST;
+                const int len = solved ? Tq : 0;
+                const int nj4 = (__builtin_amdgcn_readfirstlane((int)wave_max((float)len)) + 4 * lpp - 1) >> (lg + 2);
+                float* lq = list + (round == 0 ? SEG : 4 * SEG) * (lane >> lg);
+                for (int e = len + sub; e < 4 * lpp * nj4; e += lpp) lq[e] = FAR2;
+                wave_sync_lds();
+                float4 r4[NR];
+#pragma unroll
+                for (int j = 0; j < NR; ++j) {
+                    r4[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (j < nj4) {
+                        const float4 v = *reinterpret_cast<const float4*>(lq + 4 * (j * lpp + sub));
+                        r4[j] = make_float4(__builtin_amdgcn_sqrtf(v.x), __builtin_amdgcn_sqrtf(v.y),
+                                            __builtin_amdgcn_sqrtf(v.z), __builtin_amdgcn_sqrtf(v.w));
+                    }
+                }
+
+                // ---- phase B: Newton's method on h. w(q) = 2 t^3 - 8 u^3 and q w'(q) = q (24 u^2 - 6
+                //      t^2) with t = max(1 - q, 0), u = max(1/2 - q, 0): the cubic spline as truncated
+                //      powers, no branch and no select ------------------------------------------------
+                bool run = solved;
+                while (__any(run)) {
+                    const float hinv = __builtin_amdgcn_rcpf(s.h);
+                    const uint64_t live = __ballot(run);
+                    float At = 0.f, Au = 0.f, Bt = 0.f, Bu = 0.f;
+                    int cnt = 0;  // wave-uniform
+                    auto entry = [&](float r) {
+                        const float q = r * hinv;
+                        const float t = __builtin_amdgcn_fmed3f(fmaf(-r, hinv, 1.0f), 0.0f, 1.0f);
+                        const float u = __builtin_amdgcn_fmed3f(fmaf(-r, hinv, 0.5f), 0.0f, 1.0f);
+                        const float t2 = t * t, u2 = u * u;
+                        At = fmaf(t2, t, At);
+                        Au = fmaf(u2, u, Au);
+                        Bt = fmaf(q, t2, Bt);
+                        Bu = fmaf(q, u2, Bu);
+                        cnt += __popcll(__ballot(t > 0.0f) & live);  // r < h
+                    };
+#pragma unroll
+                    for (int j = 0; j < NR; ++j) {
+                        if (j < nj4) {
+                            entry(r4[j].x);
+                            entry(r4[j].y);
+                            entry(r4[j].z);
+                            entry(r4[j].w);
+                        }
+                    }
+                    sweep_acc += cnt;
+                    const float S0 = group_sum(fmaf(2.0f, At, -8.0f * Au), lpp);
+                    const float S1 = group_sum(fmaf(24.0f, Bu, -6.0f * Bt), lpp);
+                    if (run) {
+                        fS0 = S0;
+                        fS1 = S1;
+                        hsolve_step(s, S0, S1, A.inv_target, A.tol, A.max_iter);
+                        run = !s.done;
+                    }
+                }
+                {
+                    // evaluations: their most, and the entries they read
+                    while (__any(solved && s.nev > max_ev)) ++max_ev;
+                    int v = solved && sub == 0 ? s.nev * len : 0;
+#pragma unroll
+                    for (int o = 32; o >= 4; o >>= 1) v += __shfl_xor(v, o, 64);
+                    list_acc += __builtin_amdgcn_readfirstlane(v);
+                }
+                // a root beyond a list that stopped short of H: once more, out to H
+                const bool beyond = solved && s.state == ST_OVERFLOW && cut;
+                if (beyond) solved = false;
+                const bool beyond_c = __shfl(beyond ? 1 : 0, lane_c, 64) != 0;
+                const unsigned bm = (unsigned)__ballot(inb && beyond_c) & 0xffffu;
+                wide |= bm;
+                todo &= ~(batch & ~bm & (round == 0 ? ~over : ~0u));
+                {
+                    // interactions at the final h (less the particle itself)
+                    const uint64_t live = __ballot(solved && s.state == ST_DONE);
+                    if (live) {
+                        const float hinv = __builtin_amdgcn_rcpf(s.h);
+                        int cnt = 0;
+                        auto entry = [&](float r) {
+                            const float t = __builtin_amdgcn_fmed3f(fmaf(-r, hinv, 1.0f), 0.0f, 1.0f);
+                            cnt += __popcll(__ballot(t > 0.0f) & live);
+                        };
+#pragma unroll
+                        for (int j = 0; j < NR; ++j) {
+                            if (j < nj4) {
+                                entry(r4[j].x);
+                                entry(r4[j].y);
+                                entry(r4[j].z);
+                                entry(r4[j].w);
+                            }
+                        }
+                        inter_acc += cnt - (__popcll(live) >> lg);
+                    }
+                }
+                if (!mixed || !__any(solved)) break;
             }
-            if constexpr (DETAIL) {
-                // the candidates listed in this pass (balancing moved entries
-                // between a particle's lanes but kept their number): one wave sum
-                int v = nl;
-                for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-                listed_acc += __builtin_amdgcn_readfirstlane(v);
+            if (mixed) n_scan += wave_count(solved && sub == 0 && !many);  // walked again
+            if (solved && sub == 0) {
+                if (!mixed) {
+                    M0 = m0 * fS0;
+                    M1 = m0 * fS1;
+                }
+                const KernArgs<DensArgs> K = late_args<DensArgs>();
+                write_result(K, iq, K->perm[iq], s, fS0, M0, M1);
             }
-            if (valid && sub == 0 && st0 == ST_ACTIVE && fits)
-                write_result(A, i, o_i, s, fS0, m0 * fS0, m0 * fS1, fcnt, inter_acc, n_over, n_unconv, max_ev);
         }
-        if (have_next && !pre_issued) cell_recs(A, nxt);  // (no pass had an active particle)
-        enqueue_scan(A, slot, n_flag);
-        n_scan += n_flag;
-        cur = nxt;
-        slot = nslot;
-        have = have_next;
+        if ((scan >> lane) & 1u && lane < 16) {
+            late_args<DensArgs>()->st_s[i0 + lane] = ST_SCAN;
+            n_flag = 1;
+        }
+        enqueue_scan(late_args<DensArgs>(), slot, n_flag);
     }
-    flush_counters(A, cand_acc, list_acc, inter_acc, sweep_acc, n_over, n_unconv, max_ev, n_scan, listed_acc);
+    flush_counters(late_args<DensArgs>(), cand_acc, list_acc, inter_acc, sweep_acc, max_ev, n_scan, listed_acc);
 }
 
 // ---- the re-scanning kernel: particles flagged ST_SCAN -------------------------------
@@ -681,8 +677,7 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(PERSIST
 // appends the distance and the mass of every hit inside the search radius to
 // the lane's lists (room for RLPI * RSLOTS hits per particle, four times what
 // the list kernel gives its widest groups); phase B runs Newton's method over
-// the lists with mass-weighted sums, so mixed masses need no other path. A
-// particle with still more hits re-tests every candidate at each evaluation
+// the lists with mass-weighted sums. A particle with still more hits re-tests every candidate at each evaluation
 // (rewalk_solve).
 constexpr int RLPI = 16;
 constexpr int RSLOTS = 32;
@@ -727,40 +722,44 @@ __device__ __forceinline__ ListSums list_sums(const float* lr, const float* lm, 
     return L;
 }
 
-// Stage the chunk of candidates starting at c0 into the tile (unless a
-// single-tile cell already holds them all); returns its length.
-// Candidates [c0, c0 + len) into the tile; returns len. A cell whose
-// candidates fit one tile stages them once for all its groups of particles
-// (kept = every candidate). Otherwise only those within reach2 of the
-// group's box are kept, packed from slot 0 (kept of them): a particle of the
-// group pairs with no other.
-__device__ __forceinline__ int rescan_stage(const DensArgs& A, NbrCursor& cu, float4* tile, int c0, int nj,
-                                            bool single_tile, bool& loaded, const CullBox& box, float reach2,
-                                            int& kept)
+// The candidates of an item within reach2 of a group's box, SCAP at a time (x,
+// y, z in the item's frame, m): a particle of the group pairs with no other.
+// Returns how many were staged; more: there are others.
+template <bool UNI>
+struct RescanItem {
+    Item<UNI> it;
+    CandWalk<UNI> w;
+};
+
+template <bool UNI>
+__device__ __forceinline__ int rescan_stage(const DensArgs& A, RescanItem<UNI>& I, float4* tile, char* scratch,
+                                            bool first, bool& more, const CullBox& box, float reach2)
 {
-    if (single_tile && loaded) {
-        kept = nj;
-        return nj;
-    }
-    cursor_seek(cu, A.p_rec, A.p_shift, c0);
-    const int len = cursor_chunk(cu, c0, SCAP);
-    if (single_tile) {
-        stage_fast<1, SCAP>(tile, A.jd, cu.nb, c0 - cu.off0, len);
-        kept = len;
-    } else {
-        kept = stage_fast_culled<1, SCAP>(tile, A.jd, cu.nb, c0 - cu.off0, len, box, reach2);
-    }
-    loaded = true;
-    return len;
+    int nk = 0;
+    if (first) walk_start(I.w, A.cell, scratch);
+    do {
+        Slots<1> S;
+        more = walk_next<1>(I.w, A.cell, scratch, S);
+        if (!more) break;
+        float4 a = A.jd[S.src[0]];
+        a.x = item_coord<UNI>(a.x, I.it.ox, I.it.sh, I.it.sl, S.sh[0].x);
+        a.y = item_coord<UNI>(a.y, I.it.oy, I.it.sh, I.it.sl, S.sh[0].y);
+        a.z = item_coord<UNI>(a.z, I.it.oz, I.it.sh, I.it.sl, S.sh[0].z);
+        const bool keep = S.ok[0] && box_dist2(a.x, a.y, a.z, box) < reach2;
+        const uint64_t m = __ballot(keep);
+        if (keep) tile[nk + lanes_below(m)] = a;
+        nk += __popcll(m);
+    } while (nk + 64 <= SCAP);
+    wave_sync_lds();
+    return nk;
 }
 
 // Newton's method re-testing every candidate at each evaluation, for the
 // lanes whose particle (active) has more hits than its lists hold.
-template <class I>
-__device__ __forceinline__ void rewalk_solve(const DensArgs& A, NbrCursor& cu, float4* tile, int nj, bool single_tile,
-                                             bool& loaded, bool active, int i, float4 xi, int sub,
-                                             const CullBox& box, float reach2, int64_t& cand_acc, I& inter_acc,
-                                             I& sweep_acc, I& n_over, I& n_unconv, int& max_ev)
+template <bool UNI, class N>
+__device__ __forceinline__ void rewalk_solve(const DensArgs& A, RescanItem<UNI>& I, float4* tile, char* scratch,
+                                             bool active, int i, float4 xi, int sub, const CullBox& box, float reach2,
+                                             int64_t& cand_acc, N& inter_acc, N& sweep_acc, int& max_ev)
 {
     HSolve s = hsolve_init(A.hs[i], A.Hs[i] - 2.0f * A.drift[0], !active, ST_ACTIVE);
     float S0 = 0.f, S1 = 0.f, M0 = 0.f, M1 = 0.f;
@@ -771,10 +770,10 @@ __device__ __forceinline__ void rewalk_solve(const DensArgs& A, NbrCursor& cu, f
         S0 = S1 = M0 = M1 = 0.f;
         cnt = 0;
         const int groups_now = wave_count(!s.done && sub == 0);
-        int len, kept_tot = 0;
-        for (int c0 = 0; c0 < nj; c0 += len) {
-            int kept;
-            len = rescan_stage(A, cu, tile, c0, nj, single_tile, loaded, box, reach2, kept);
+        int kept_tot = 0;
+        bool more = true;
+        for (bool head = true; more; head = false) {
+            const int kept = rescan_stage(A, I, tile, scratch, head, more, box, reach2);
             kept_tot += kept;
             for (int k = sub; k < kept; k += RLPI) {
                 const float4 pj = tile[k];
@@ -791,7 +790,7 @@ __device__ __forceinline__ void rewalk_solve(const DensArgs& A, NbrCursor& cu, f
                 M1 = fmaf(pj.w, qdw, M1);
                 cnt += in ? 1 : 0;
             }
-            if (!single_tile) wave_sync_lds();
+            wave_sync_lds();
         }
         cand_acc += (int64_t)groups_now * kept_tot;
         S0 = group_sum(S0, RLPI);
@@ -803,16 +802,22 @@ __device__ __forceinline__ void rewalk_solve(const DensArgs& A, NbrCursor& cu, f
         if (sub == 0) sweep_acc += cnt;
         hsolve_step(s, S0, S1, A.inv_target, A.tol, A.max_iter);
     }
-    if (active && sub == 0)
-        write_result<false>(A, i, A.perm[i], s, S0, M0, M1, cnt, inter_acc, n_over, n_unconv, max_ev);
+    if (active && sub == 0) {
+        if (s.state == ST_DONE) inter_acc += cnt - 1;
+        max_ev = max(max_ev, s.nev);
+        write_result<false>(late_args<DensArgs>(), i, A.perm[i], s, S0, M0, M1);
+    }
 }
 
+template <bool UNI>
 __global__ void __launch_bounds__(BS) k_density_scan(DensArgs A)
 {
     __shared__ float4 tile[SCAP];
     __shared__ float lr_all[(RSLOTS + 1) * 64];
     __shared__ float lm_all[(RSLOTS + 1) * 64];
     __shared__ int pidx[64];
+    __shared__ float4 scratch4[WALK_LDS<UNI> / 16];
+    char* scratch = reinterpret_cast<char*>(scratch4);
     const int lane = threadIdx.x & 63;
     const int g = lane / RLPI, sub = lane & (RLPI - 1);
     float* lr = lr_all + lane;
@@ -822,7 +827,7 @@ __global__ void __launch_bounds__(BS) k_density_scan(DensArgs A)
     const unsigned o_lane = 4u * (unsigned)lane, o_cap = o_lane + 256u * RSLOTS;
     const float two_delta = 2.0f * A.drift[0];
     int64_t cand_acc = 0;  // wave-uniform
-    int list_acc = 0, inter_acc = 0, sweep_acc = 0, n_over = 0, n_unconv = 0;
+    int list_acc = 0, inter_acc = 0, sweep_acc = 0;
     int64_t listed_acc = 0;  // wave-uniform
     int max_ev = 0;
     const int n_queued = (int)A.ctr[CT_SCAN_CELLS];  // final: written by the list kernel
@@ -845,13 +850,9 @@ __global__ void __launch_bounds__(BS) k_density_scan(DensArgs A)
         if (k >= n_items) break;
         const int kc = k / split, part = k - kc * split;
         const int slot = A.scan_cells[kc];
-        const int4 ci = A.cells[slot];
-        const int i0 = ci.x, ni = ci.y, pb0 = ci.z, np_all = ci.w;
-        NbrCursor cu;  // neighbour records 64 at a time
-        cursor_init(cu, A.p_rec, A.p_shift, pb0, np_all);
-        const int nj = np_all <= 64 ? cu.nb.nj : count_candidates(A.p_rec, pb0, np_all);
-        const bool single_tile = np_all <= 64 && nj <= SCAP;
-        bool loaded = false;
+        RescanItem<UNI> I;
+        item_load(I.it, I.w, A.cell, slot, 0.5f * two_delta, 0.0f);
+        const int i0 = I.it.i0, ni = I.it.ni;
         int gbase = 0;  // groups in the cell's earlier blocks
         for (int b0 = 0; b0 < ni; b0 += 64) {
             // the flagged particles of these 64, compacted into pidx
@@ -868,7 +869,10 @@ __global__ void __launch_bounds__(BS) k_density_scan(DensArgs A)
                 const int p0 = q * GP;
                 const bool valid = p0 + g < nflag;
                 const int i = i0 + pidx[valid ? p0 + g : p0];
-                const float4 xi = A.jd[i];
+                float4 xi = A.jd[i];
+                xi.x = item_coord<UNI>(xi.x, I.it.ox, I.it.sh, I.it.sl, 0.0f);
+                xi.y = item_coord<UNI>(xi.y, I.it.oy, I.it.sh, I.it.sl, 0.0f);
+                xi.z = item_coord<UNI>(xi.z, I.it.oz, I.it.sh, I.it.sl, 0.0f);
                 HSolve s = hsolve_init(A.hs[i], A.Hs[i] - two_delta, !valid, ST_ACTIVE);
 
                 // ---- phase A: every candidate once, hits inside H listed ----------
@@ -878,10 +882,10 @@ __global__ void __launch_bounds__(BS) k_density_scan(DensArgs A)
                 const CullBox gbox = pass_box(xi.x, xi.y, xi.z, valid);
                 const float greach2 = uniform_f(cull_reach2(wave_max(valid ? s.Hi : 0.0f)));
                 unsigned o = o_lane;
-                int len, kept_tot = 0;
-                for (int c0 = 0; c0 < nj; c0 += len) {
-                    int kept;
-                    len = rescan_stage(A, cu, tile, c0, nj, single_tile, loaded, gbox, greach2, kept);
+                int kept_tot = 0;
+                bool more = true;
+                for (bool head = true; more; head = false) {
+                    const int kept = rescan_stage(A, I, tile, scratch, head, more, gbox, greach2);
                     kept_tot += kept;
                     for (int kk = sub; kk < kept; kk += RLPI) {
                         const float4 pj = tile[kk];
@@ -892,7 +896,7 @@ __global__ void __launch_bounds__(BS) k_density_scan(DensArgs A)
                         *reinterpret_cast<float*>(bm + oo) = pj.w;
                         o += r2 < H2 ? 256u : 0u;
                     }
-                    if (!single_tile) wave_sync_lds();
+                    wave_sync_lds();
                 }
                 cand_acc += (int64_t)wave_count(valid && sub == 0) * kept_tot;
                 const int nl = (int)((o - o_lane) >> 8);
@@ -928,20 +932,29 @@ __global__ void __launch_bounds__(BS) k_density_scan(DensArgs A)
                     fcnt = cnt;
                     hsolve_step(s, S0, S1, A.inv_target, A.tol, A.max_iter);
                 }
-                if (listed && sub == 0)
-                    write_result<false>(A, i, A.perm[i], s, fS0, fM0, fM1, fcnt, inter_acc, n_over, n_unconv,
-                                        max_ev);
+                if (listed && sub == 0) {
+                    if (s.state == ST_DONE) inter_acc += fcnt - 1;
+                    max_ev = max(max_ev, s.nev);
+                    write_result<false>(late_args<DensArgs>(), i, A.perm[i], s, fS0, fM0, fM1);
+                }
 
                 // ---- lists too short: re-test every candidate per evaluation -------
                 const bool rewalk = valid && !fits;
                 if (__any(rewalk))
-                    rewalk_solve(A, cu, tile, nj, single_tile, loaded, rewalk, i, xi, sub, gbox, greach2, cand_acc,
-                                 inter_acc, sweep_acc, n_over, n_unconv, max_ev);
+                    rewalk_solve(A, I, tile, scratch, rewalk, i, xi, sub, gbox, greach2, cand_acc, inter_acc, sweep_acc,
+                                 max_ev);
             }
             gbase += ng;
         }
     }
-    flush_counters(A, cand_acc, list_acc, inter_acc, sweep_acc, n_over, n_unconv, max_ev, 0, listed_acc);
+    int64_t inter = inter_acc, swept = sweep_acc, listed = list_acc;  // to wavefront totals
+    for (int o = 32; o >= 1; o >>= 1) {
+        inter += __shfl_xor(inter, o, 64);
+        swept += __shfl_xor(swept, o, 64);
+        listed += __shfl_xor(listed, o, 64);
+        max_ev = max(max_ev, __shfl_xor(max_ev, o, 64));
+    }
+    flush_counters(late_args<DensArgs>(), cand_acc, listed, inter, swept, max_ev, 0, listed_acc);
 }
 
 }  // namespace
@@ -956,7 +969,6 @@ int make_sched(sph_ctx* c, int64_t n_items, int waves_per_block, int blocks_per_
     W.persistent = c->prm.schedule == 1 ? 1 : 0;
     W.batch = c->prm.queue_batch > 0 ? c->prm.queue_batch : 4;
     W.n_items = (int)n_items;
-    for (int q = 0; q <= 8; ++q) W.q_begin[q] = (int)xcd_start(n_items, q);
     const int64_t all = (n_items + waves_per_block - 1) / waves_per_block;
     int64_t grid = all;
     if (W.persistent) grid = std::min<int64_t>(all, (int64_t)c->n_cu * blocks_per_cu);
@@ -978,8 +990,9 @@ void density_enqueue(sph_ctx* c, const float* mass, float* h, float* rho, float*
     float4* jf = ghost ? static_cast<float4*>(c->jf.p) : nullptr;
     fill_u32(ctr, 0u, 2 * (int64_t)CT_COUNT, s);  // sums, spread slots, queue heads
     k_dens_prologue<<<blocks_for(n, 256), 256, 0, s>>>(n, static_cast<uint32_t*>(c->perm.p),
-                                                        static_cast<float4*>(c->xrel.p), mass, h, status,
-                                                        fresh ? 1 : 0, jd, hs, st_s, ctr);
+                                                        static_cast<int4*>(c->uni ? c->xfix.p : c->xrel.p), mass, h,
+                                                        status, fresh ? 1 : 0, static_cast<int4*>(c->jd.p), hs, st_s,
+                                                        ctr);
     SPH_HIP(hipGetLastError());
     DensArgs A;
     A.jd = jd;
@@ -994,22 +1007,12 @@ void density_enqueue(sph_ctx* c, const float* mass, float* h, float* rho, float*
     A.f_out = f;
     A.nw_out = nw;
     A.status = status;
-    A.cells = static_cast<int4*>(c->cells_d.p);
-    A.cell_pbox = static_cast<float4*>(c->cell_pbox.p);
-    A.p_rec = static_cast<int2*>(c->p_rec.p);
-    A.p_shift = static_cast<float4*>(c->p_shift.p);
+    A.cell = cell_args(c, static_cast<int4*>(c->uni ? c->cells.p : c->cells_d.p));
     A.ctr = ctr;
     A.target = (float)(3.0 * c->prm.n_ngb / 32.0);
     A.inv_target = (float)(32.0 / (3.0 * c->prm.n_ngb));
     A.tol = (float)c->prm.n_tol;
     A.max_iter = c->prm.max_iter;
-    // a particle with a good guess finds about n_ngb * h_margin^3 candidates
-    // inside its search radius; a lane takes every lpi-th candidate, so give
-    // the lanes room for 70% more than their share
-    const double expect = c->prm.n_ngb * c->prm.h_margin * c->prm.h_margin * c->prm.h_margin;
-    A.nl_est = (float)expect;
-    A.lpi_min = 2;
-    while (A.lpi_min < 16 && A.lpi_min * DSLOTS < 1.7 * expect) A.lpi_min *= 2;
     A.scan_cells = static_cast<int*>(c->scan_cells.p);
     A.vel_in = ghost ? ghost_vel : nullptr;
     A.u_in = ghost ? ghost_u : nullptr;
@@ -1017,39 +1020,43 @@ void density_enqueue(sph_ctx* c, const float* mass, float* h, float* rho, float*
     A.gamma = (float)c->prm.gamma;
     A.drift = static_cast<float*>(c->drift.p);
     A.detail = c->prm.timing == 2 ? 1 : 0;
-    const int grid = make_sched(c, c->n_leaves, WAVES, 12, A.W);
+    const int grid = make_sched(c, c->n_items, WAVES, 16, A.W);
     // re-scan grid: enough wavefronts for a full queue; the surplus exits at once
-    const int scan_grid = (int)std::max<int64_t>(std::min<int64_t>(c->n_leaves, (int64_t)c->n_cu * 8), 1);
+    const int scan_grid = (int)std::max<int64_t>(std::min<int64_t>(c->n_items, (int64_t)c->n_cu * 8), 1);
     if (events) ev_record(c, EV_DENS_K0, s);
-    const bool pers = A.W.persistent != 0;
-    auto launch = [&](auto tcap, auto cullc) {
-        constexpr int T = decltype(tcap)::value;
-        constexpr bool C = decltype(cullc)::value;
-        if (A.detail)
-            pers ? k_density<T, true, true, C><<<grid, BS, 0, s>>>(A)
-                 : k_density<T, false, true, C><<<grid, BS, 0, s>>>(A);
+    // Room of the lists. A good guess finds about n_ngb g^3 candidates inside its
+    // first radius (g the smaller of h_margin and LIST_GROW): a third more on a
+    // grid, where the guesses of a lattice are good, nearly twice that in a tree,
+    // where a particle that needs a second list costs its item a second sweep
+    // (log-normal 2^24). Longer lists cost LDS and registers, so wavefronts.
+    const bool wide = c->prm.h_margin > LIST_WIDE;
+    const double g = wide ? (double)LIST_GROW : c->prm.h_margin;
+    A.grow = wide ? LIST_GROW : 1.0e30f;
+    const double want = (c->uni ? 1.35 : 1.9) * c->prm.n_ngb * g * g * g;
+    auto launch = [&](auto lcap) {
+        constexpr int L = decltype(lcap)::value;
+        if (c->uni)
+            A.detail ? k_density<L, true, true><<<grid, BS, 0, s>>>(A) : k_density<L, true, false><<<grid, BS, 0, s>>>(A);
         else
-            pers ? k_density<T, true, false, C><<<grid, BS, 0, s>>>(A)
-                 : k_density<T, false, false, C><<<grid, BS, 0, s>>>(A);
+            A.detail ? k_density<L, false, true><<<grid, BS, 0, s>>>(A)
+                     : k_density<L, false, false><<<grid, BS, 0, s>>>(A);
     };
-    auto launch_t = [&](auto cullc) {
-        if (c->prm.tile_cap == 512)
-            launch(std::integral_constant<int, 512>{}, cullc);
-        else if (c->prm.tile_cap == 256)
-            launch(std::integral_constant<int, 256>{}, cullc);
-        else
-            launch(std::integral_constant<int, 128>{}, cullc);
-    };
-    // a layout of top cells only (no split) has no cell with more than 27
-    // neighbour cells, so its kernels carry no culling code, and take four
-    // lanes per particle where four hold the expected lists
-    if (c->cells_refined || A.lpi_min > 4)
-        launch_t(std::true_type{});
+    if (want <= 80.0)
+        launch(std::integral_constant<int, 80>{});
+    else if (want <= 96.0)
+        launch(std::integral_constant<int, 96>{});
+    else if (want <= 128.0)
+        launch(std::integral_constant<int, 128>{});
+    else if (want <= 240.0)
+        launch(std::integral_constant<int, 240>{});
     else
-        launch_t(std::false_type{});
+        launch(std::integral_constant<int, 448>{});
     SPH_HIP(hipGetLastError());
     if (events) ev_record(c, EV_DENS_KM, s);
-    k_density_scan<<<scan_grid, BS, 0, s>>>(A);
+    if (c->uni)
+        k_density_scan<true><<<scan_grid, BS, 0, s>>>(A);
+    else
+        k_density_scan<false><<<scan_grid, BS, 0, s>>>(A);
     SPH_HIP(hipGetLastError());
     if (events) ev_record(c, EV_DENS_K1, s);
 }
@@ -1063,7 +1070,7 @@ void density_buffers(sph_ctx* c)
     ensure<float>(c, c->rhos, n);
     ensure<float>(c, c->fs, n);
     ensure<uint8_t>(c, c->st_s, n);
-    ensure<int>(c, c->scan_cells, (size_t)c->n_leaves);
+    ensure<int>(c, c->scan_cells, (size_t)c->n_items);
 }
 
 void density_f32(sph_ctx* c, const float* mass, float* h, float* rho, float* f, float* nw, sph_stats* st,
@@ -1112,6 +1119,7 @@ void density_f32(sph_ctx* c, const float* mass, float* h, float* rho, float* f, 
                 st->tests_density = tot_tests;
                 st->listed_density = tot_listed;
                 st->n_cells = c->n_leaves;
+                finish_build_read(c);
                 st->n_pairs = c->n_pairs;
             }
             if (c->rebuilds > 0) {

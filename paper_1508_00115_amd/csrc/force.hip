@@ -5,7 +5,8 @@
 // The ghost step (after the density, section 3.1's dependency) turns rho, f
 // and u into the per-particle pressure term Phi = f P / rho^2 and sound speed,
 // packed with position, h^2, velocity, mass and 1/h into three float4 per
-// particle: (x, y, z, h^2), (v, m), (rho, Phi, c, 1/h).
+// particle: (x, y, z, h^2), (v, m), (rho, Phi, c, 1/h); x, y, z as the cell
+// layout stores them (see Item in tiles.h).
 // The loop then runs one wavefront per leaf cell exactly like the density
 // loop: the cell's neighbour particles are staged into LDS in chunks and each
 // particle of the cell (several lanes per particle for small cells) gathers
@@ -38,9 +39,11 @@ namespace {
 
 constexpr int BS = 64;     // one wavefront per block (finest LDS allocation)
 constexpr int WAVES = BS / 64;
-constexpr int FCAP = 128;  // candidates per LDS chunk (3 float4 each)
-constexpr int FSLOTS = FCAP / 4;  // a lane (4+ lanes per particle) tests at most every fourth candidate
-static_assert(FCAP % (2 * 4) == 0, "the phase-A stride (two candidates per lane, four lanes) divides a chunk");
+constexpr int FCAP = 128;  // candidates per LDS tile
+constexpr int LCAP = 80;   // entries of a particle's list (64 candidates always fit)
+constexpr int LSEG = LCAP + 4;
+constexpr int NWORDS = (FCAP + 127) / 128;  // hit words per lane
+static_assert(FCAP % 64 == 0 && FCAP <= 256, "whole steps of the filter; byte-sized candidate numbers");
 
 __global__ void k_force_prologue(int64_t n, const uint32_t* __restrict__ perm, const float4* __restrict__ jd,
                                  const float* __restrict__ hs, const float* __restrict__ rhos,
@@ -69,64 +72,19 @@ __global__ void k_force_prologue(int64_t n, const uint32_t* __restrict__ perm, c
 struct ForceArgs {
     const float4* jf;
     float4* jf_w;             // the same array, written by the divergence pass (B in place of 1/h)
-    const int4* cells;     // per schedule slot: first particle, count, first neighbour entry, entries
-    const int2* cell_aux;  // per schedule slot: leaf, box
-    const int2* p_rec;       // per (cell, neighbour cell) record: first particle and count of the neighbour
-    const float4* p_shift;
+    CellArgs cell;         // the items, their frames and candidates
+    const int* cell_item;  // per schedule slot: work item (null: the slot's number)
     const uint32_t* perm;
     float* acc;
     float* dudt;
-    double* cons_part;  // 4 per leaf, may be null
+    double* cons_part;  // 4 per item, may be null
     float* vsig;        // sorted: signal velocity per particle (k_force<true> only)
     float* divv;        // sorted: velocity divergence per particle (k_force<true> only)
     float* bal;         // sorted: Balsara factor per particle (written in the FM_DIVCURL mode)
-    const float* drift; // [0]: bound on the drift since the build (cell boxes widen by it)
     int64_t* ctr;
     WorkSched W;
     float alpha;
 };
-
-// Phase A of one chunk for the lanes of one particle: the lane with index sub
-// in its group tests candidates sub, sub + LPI, ... (slot 0 of the tile: x,
-// y, z, h^2) and appends the chunk index of every candidate inside
-// max(h_i, h_j), except the particle itself, to its byte list (row e of the
-// lists holds entry e of every lane; o is the byte offset of this lane's next
-// entry). The chunk is padded with far positions to its full size
-// (pad_tile), two tile reads are in flight (four, or eight, measured slower:
-// the registers they hold) and the appends are branch-free.
-// A lane (four per particle) tests at most FCAP / 4 candidates of a chunk,
-// so its list of FSLOTS cannot overflow.
-// OWN_H false (the divergence and curl): only the pairs inside h_i.
-template <int LPI, bool OWN_H>
-__device__ __forceinline__ int force_scan(const float4* sj, int len, int sub, float xx, float xy, float xz,
-                                          float h2_i, uint8_t* lists)
-{
-    const int len_pad = (len + 2 * LPI - 1) & ~(2 * LPI - 1);
-    const unsigned o0 = threadIdx.x & 63;
-    unsigned o = o0;
-    for (int k0 = sub; k0 < len_pad; k0 += 2 * LPI) {
-        float4 pj[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) pj[u] = sj[k0 + u * LPI];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const float dx = xx - pj[u].x, dy = xy - pj[u].y, dz = xz - pj[u].z;
-            const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-            const bool in = (r2 < (OWN_H ? fmaxf(h2_i, pj[u].w) : h2_i)) & (r2 > 0.0f);
-            lists[o] = (uint8_t)(k0 + u * LPI);
-            o += in ? 64u : 0u;
-        }
-    }
-    return (int)((o - o0) >> 6);
-}
-
-// Slot 0 of the unused tile entries [len, CAP): a far position with a tiny
-// h^2, so no pair test passes there.
-__device__ __forceinline__ void pad_tile(float4* sj, int len, int cap)
-{
-    for (int t = len + (int)(threadIdx.x & 63); t < cap; t += 64) sj[t] = make_float4(1.0e18f, 1.0e18f, 1.0e18f, 1.0e-12f);
-    wave_sync_lds();
-}
 
 // What a pass of k_force computes: the force; the force with the Balsara
 // switch (4 float4 per particle); the Balsara factors (3 float4 per particle,
@@ -147,191 +105,314 @@ __global__ void k_unsort_f32(int64_t n, const uint32_t* __restrict__ perm, const
 // divergence, rho_i div v_i = -sum_j m_j (v_i - v_j) . grad_i W(r_ij, h_i)
 // (the pairs inside h_i; grad_i W = D_i rhat), from which the next step's
 // smoothing length is predicted (continuity: dh/dt = h div v / 3).
-// ONEBLK: every cell has at most 64 neighbour records (a layout of top cells
-// only has 27), so the multi-block paths of the record cursor drop out.
-template <bool VSIG, int MODE, bool ONEBLK>
+// UNI: a grid layout.
+//
+// An item's candidates are staged FCAP at a time, keeping those within the
+// item's largest h, or their own, of the box around its particles; the next 64
+// are in flight meanwhile. The matrix cores filter the pairs inside max(h_i,
+// h_j): two tables, one with each radius, a pair where either sign is set. The
+// lanes that hold a particle's hit words write the candidates they name to the
+// particle's list in LDS, and the pair loop gives the four lanes of a particle
+// every fourth entry: its trip count follows the item's longest list over
+// four, where lanes that kept their own candidates' hits waited for the longest
+// of 64 short lists.
+template <bool VSIG, int MODE, bool UNI>
 __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_force(ForceArgs A)
 {
     constexpr bool DC = MODE == FM_DIVCURL;
-    constexpr int NF = DC ? 2 : 3;  // float4 staged per candidate (of the 3 per particle)
-    __shared__ float4 tile[NF * FCAP];
-    __shared__ uint8_t lists[FSLOTS * 64];
-    __shared__ uint8_t marks[FCAP];  // record starts of the chunk being fetched
+    __shared__ float4 t0[FCAP];                 // x, y, z, 48 / (pi h^4) (0 in the Balsara mode's stead: h^2)
+    __shared__ float4 t1[FCAP];                 // v, m
+    __shared__ float4 t2[DC ? 1 : FCAP];        // rho, Phi, c, 1/h
+    __shared__ uint2 fa[FCAP];                  // filter input: x, y; z, |x|^2 (half precision)
+    __shared__ uint32_t fb[DC ? 1 : FCAP];      // z, |x|^2 - h^2
+    // the particles' lists (candidate numbers of one tile) share their memory
+    // with the scratch of the walk, which is written again for each tile
+    __shared__ float4 scratch4[(16 * LSEG > WALK_LDS<UNI> ? 16 * LSEG : WALK_LDS<UNI>) / 16];
+    char* scratch = reinterpret_cast<char*>(scratch4);
+    uint8_t* lists = reinterpret_cast<uint8_t*>(scratch4);
     const int lane = threadIdx.x & 63;
-    float4* sj = tile;
-    uint8_t* lst = lists + lane;
+    const int pc = lane & 15, gc = lane >> 4;  // column (particle) and lane group of the filter
+    const int pq = lane >> 2, sub = lane & 3;  // particle and lane of the pair loop
+    const int fin = 4 * (lane & 3) + gc;       // the candidate (of 16) this lane feeds to the filter
     int wstate = 0, a_cur = 0, a_end = 0;
-    int64_t cand_acc = 0, inter_acc = 0;
-    const float K8PI = 8.0f / SPH_PI_F;
+    int64_t cand_acc = 0;  // wave-uniform
+    int inter_acc = 0;     // this lane's pairs
+    const float K6 = 6.0f * 8.0f / SPH_PI_F;  // w'(q) = 6 (U^2 - t^2), U = max(1 - 2 q, 0), t = max(1 - q, 0)
 
     for (;;) {
         if (a_cur >= a_end && !next_items(A.W, A.ctr, WAVES, wstate, a_cur, a_end)) break;
-        const int slot = a_cur++;
-        const int4 ci = A.cells[slot];
-        const int i0 = ci.x, ni = ci.y, pb0 = ci.z, np_all = ONEBLK ? min(ci.w, 64) : ci.w;
-        NbrCursor cu;  // neighbour records 64 at a time
-        cursor_init(cu, A.p_rec, A.p_shift, pb0, np_all);
-        const int nj = np_all <= 64 ? cu.nb.nj : count_candidates(A.p_rec, pb0, np_all);
-        // four lanes per particle on every cell: a lane's byte list (one
-        // chunk's hits) cannot overflow, and the fixed count lets the
-        // compiler specialise every loop (measured faster on every set than
-        // a per-cell choice, even where leaves hold few particles)
-        constexpr int lpi = 4;
-        constexpr int lg = 2;
-        constexpr int per_pass = 64 >> lg;
-        const int g = lane >> lg;
-        const int sub = lane & (lpi - 1);
-        // this cell's share of the box sums: lane 0's totals, kept in scalar
-        // registers across the passes (every lane is active where they change)
-        double cm_cell[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int ib = 0; ib < ni; ib += per_pass) {
-            const int gi = ib + g;
-            const bool valid = gi < ni;
-            const int i = i0 + (valid ? gi : 0);
-            const float4 i0v = A.jf[3 * (int64_t)i + 0];
-            const float4 i1v = A.jf[3 * (int64_t)i + 1];
-            const float4 i2v = A.jf[3 * (int64_t)i + 2];
-            const uint32_t o_i = DC ? 0u : A.perm[i];  // loaded here so the stores wait for nothing
-            const float bal_i = MODE == FM_BALSARA ? i2v.w : 1.0f;
-            const float h2_i = i0v.w;
-            const float hinv_i = MODE == FM_BALSARA ? __builtin_amdgcn_rsqf(h2_i) : i2v.w;
-            // every pass stages its own candidates (with four lanes a cell of
-            // up to 16 particles takes one pass, so a tile kept across passes
-            // would save little, and dropping it frees registers): those within
-            // the pass's largest h, or their own, of the box around its
-            // particles
-            const float reach2 = uniform_f(cull_reach2(sqrtf(wave_max(valid ? h2_i : 0.0f))));
-            const CullBox box = pass_box(i0v.x, i0v.y, i0v.z, valid);
-            const float hinv2_i = hinv_i * hinv_i;
-            const float Ki = K8PI * hinv2_i * hinv2_i;
-            const float rho_i = i2v.x, phi_i = i2v.y, c_i = i2v.z;
-            float ax = 0.f, ay = 0.f, az = 0.f, du = 0.f;
-            float vmax = 0.f;  // (VSIG) largest c_i + c_j - 3 w_ij of this lane's pairs
-            float dvr = 0.f;   // (VSIG) sum_j m_j D_i (v_ij . rhat) = -rho_i div v_i
-            int cnt = 0;
-            ChunkRegs<NF, FCAP> R;
-            int len, kept = 0;  // candidates of this chunk; kept by the box test (all chunks)
-            for (int c0 = 0; c0 < nj; c0 += len) {
-                // stage this chunk's candidates within reach of the pass
-                // (loaded and stored here rather than one chunk ahead: the
-                // registers a fetch in flight would hold cost a wavefront per
-                // SIMD, and the other wavefronts cover the loads)
-                cursor_seek(cu, A.p_rec, A.p_shift, c0);
-                fetch_chunk<NF, FCAP, 3>(R, A.jf, cu.nb, c0 - cu.off0, cursor_chunk(cu, c0, FCAP), marks);
-                len = R.len;
-                const int slen = commit_chunk_culled<NF, FCAP, !DC>(sj, R, box, reach2);
-                pad_tile(sj, slen, FCAP);
-                kept += slen;
-                // phase A: compact the candidates inside max(h_i, h_j) of this chunk
-                int nl = force_scan<lpi, !DC>(sj, slen, sub, i0v.x, i0v.y, i0v.z, h2_i, lists);
-                if (!valid) nl = 0;
-                cnt += nl;
-                // phase B: the pair terms of the compacted neighbours only (not
-                // unrolled: the lanes' list lengths differ, and a second copy of
-                // the body measured 2% slower on every set)
+        const int slot = __builtin_amdgcn_readfirstlane(a_cur);
+        ++a_cur;
+        Item<UNI> it;
+        CandWalk<UNI> w;
+        item_load(it, w, A.cell, slot, 0.0f, 1.0e18f);
+        const int i0 = it.i0, ni = it.ni;
+        // coordinates of a particle's first float4 in the item's frame
+        auto frame = [&](float4 v, float3 sh) {
+            return make_float4(item_coord<UNI>(v.x, it.ox, it.sh, it.sl, sh.x),
+                               item_coord<UNI>(v.y, it.oy, it.sh, it.sl, sh.y),
+                               item_coord<UNI>(v.z, it.oz, it.sh, it.sl, sh.z), v.w);
+        };
+        const float3 none = make_float3(0.f, 0.f, 0.f);
+        // the filter's particle
+        const bool vc = pc < ni;
+        const float4 xc = frame(A.jf[3 * (int64_t)(i0 + min(pc, ni - 1)) + 0], none);
+        const float reach = uniform_f(sqrtf(group_max(vc ? xc.w : 0.0f, 16)));
+        const float reach2 = cull_reach2(reach);
+        const float fs = FILTER_SCALE / (fmaxf(fmaxf(it.hx, it.hy), it.hz) + reach);
+        const float fs2 = fs * fs;
+        f16x4 fcol;
+        f32x4 C1, C2;
+        {
+            const float ux = (xc.x - it.bx) * fs, uy = (xc.y - it.by) * fs, uz = (xc.z - it.bz) * fs;
+            const float n2 = fmaf(ux, ux, fmaf(uy, uy, uz * uz)) * (1.0f - FILTER_EPS) - FILTER_ABS;
+            fcol = filter_column(ux, uy, uz);
+            const float c1 = vc ? fmaf(xc.w * fs2, -(1.0f + FILTER_EPS), n2) : 1.0e9f, c2 = vc ? n2 : 1.0e9f;
+            C1 = {c1, c1, c1, c1};
+            C2 = {c2, c2, c2, c2};
+        }
+        // the pair loop's particle
+        const bool valid = pq < ni;
+        const int i = i0 + (valid ? pq : 0);
+        const float4 i0v = frame(A.jf[3 * (int64_t)i + 0], none);
+        const float4 i1v = A.jf[3 * (int64_t)i + 1];
+        const float4 i2v = A.jf[3 * (int64_t)i + 2];
+        const uint32_t o_i = DC ? 0u : A.perm[i];  // loaded here so the stores wait for nothing
+        const float bal_i = MODE == FM_BALSARA ? i2v.w : 1.0f;
+        const float hinv_i = MODE == FM_BALSARA ? __builtin_amdgcn_rsqf(i0v.w) : i2v.w;
+        const float hinv2_i = hinv_i * hinv_i;
+        const float Ki = K6 * hinv2_i * hinv2_i;
+        const float rho_i = i2v.x, phi_i = i2v.y, c_i = i2v.z;
+        // sums over the pairs (the force: a; s1 = sum m D_i v.rhat, s2 = sum m
+        // visc / 2 (D_i + D_j) v.rhat, du/dt = Phi_i s1 + s2 / 2)
+        float ax = 0.f, ay = 0.f, az = 0.f, s1 = 0.f, s2 = 0.f;
+        float vmax = 0.f;  // (VSIG) largest c_i + c_j - 3 w_ij of this lane's pairs
+        const float visc_k = -0.5f * A.alpha;
+        int kept = 0;      // candidates kept by the box test
+
+        // the next 64 candidates, in flight
+        bool ok = false;
+        int src = 0;
+        float3 sh = make_float3(0.f, 0.f, 0.f);
+        float4 p0 = make_float4(0.f, 0.f, 0.f, 0.f), p1 = p0, p2 = p0;
+        auto fetch = [&]() -> bool {
+            Slots<1> S;
+            if (!walk_next<1>(w, A.cell, scratch, S)) return false;
+            ok = S.ok[0];
+            src = S.src[0];
+            sh = S.sh[0];
+            p0 = A.jf[3 * (int64_t)src + 0];
+            p1 = A.jf[3 * (int64_t)src + 1];
+            if (!DC) p2 = A.jf[3 * (int64_t)src + 2];
+            return true;
+        };
+        walk_table(w, scratch);
+        bool more = fetch();
+        while (more) {
+            // ---- stage up to FCAP candidates ------------------------------------------
+            int nk = 0;
+            do {
+                const float4 xj = frame(p0, sh);
+                const float x = xj.x, y = xj.y, z = xj.z, h2 = xj.w;
+                const float ux = UNI ? x : x - it.bx, uy = UNI ? y : y - it.by, uz = UNI ? z : z - it.bz;
+                const float gx = fmaxf(fabsf(ux) - it.hx, 0.0f), gy = fmaxf(fabsf(uy) - it.hy, 0.0f),
+                            gz = fmaxf(fabsf(uz) - it.hz, 0.0f);
+                const bool keep = ok && fmaf(gx, gx, fmaf(gy, gy, gz * gz)) <
+                                            (DC ? reach2 : fmaxf(reach2, h2 * 1.00002f));
+                const uint64_t m = __ballot(keep);
+                if (keep) {
+                    const int d = nk + lanes_below(m);
+                    float fx = ux * fs, fy = uy * fs, fz = uz * fs;
+                    float n1 = fmaf(fx, fx, fmaf(fy, fy, fz * fz)) * (1.0f - FILTER_EPS);
+                    const float hs2 = h2 * fs2 * (1.0f + FILTER_EPS);
+                    float n2 = n1 - hs2;
+                    if (!DC && fmaxf(n1, hs2) > FILTER_FAR) {  // beyond half precision: propose every pair
+                        fx = fy = fz = 0.0f;
+                        n1 = n2 = -FILTER_FAR;
+                    }
+                    fa[d] = make_uint2(pack_f16(fx, fy), pack_f16(fz, n1));
+                    if constexpr (!DC) {
+                        fb[d] = pack_f16(fz, n2);
+                        // (the third float4 holds 1/h, or B in the Balsara mode)
+                        const float hinv = MODE == FM_BALSARA ? __builtin_amdgcn_rsqf(h2) : p2.w;
+                        const float hinv2 = hinv * hinv;
+                        t0[d] = make_float4(x, y, z, MODE == FM_BALSARA ? h2 : K6 * hinv2 * hinv2);
+                        t2[d] = p2;
+                    } else {
+                        t0[d] = make_float4(x, y, z, h2);
+                    }
+                    t1[d] = p1;
+                }
+                nk += __popcll(m);
+                more = fetch();
+            } while (more && nk + 64 <= FCAP);
+            kept += nk;
+            // unused slots up to a multiple of 64
+            if (nk + lane < ((nk + 63) & ~63)) {
+                fa[nk + lane] = make_uint2(0u, pack_f16(0.0f, FILTER_FAR));
+                if constexpr (!DC) fb[nk + lane] = pack_f16(0.0f, FILTER_FAR);
+            }
+            wave_sync_lds();
+
+            // ---- filter: the lane's hit words --------------------------------------------
+            unsigned hit[NWORDS];
+#pragma unroll
+            for (int k = 0; k < NWORDS; ++k) hit[k] = 0u;
+#pragma unroll
+            for (int q = 0; q < FCAP / 64; ++q) {
+                if (64 * q < nk) {
+                    unsigned m = hit[q >> 1];
+#pragma unroll
+                    for (int b = 4 * q; b < 4 * q + 4; ++b) {
+                        const uint2 a = fa[16 * b + fin];
+                        f32x4 D = __builtin_amdgcn_mfma_f32_4x4x4f16(f16x4_of(a.x, a.y), fcol, C1, 0, 0, 0);
+                        f32x4 E = D;
+                        if constexpr (!DC)
+                            E = __builtin_amdgcn_mfma_f32_4x4x4f16(f16x4_of(a.x, fb[16 * b + fin]), fcol, C2, 0, 0, 0);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            m = __builtin_amdgcn_alignbit(m, __float_as_uint(D[r]) | __float_as_uint(E[r]), 31);
+                    }
+                    hit[q >> 1] = m;
+                }
+            }
+
+            // ---- the words become lists, and the lists pairs: the whole tile at once, or
+            //      (a list would not fit) 64 candidates at a time --------------------------------
+            int n_all = 0, tot = 0;
+#pragma unroll
+            for (int k = 0; k < NWORDS; ++k) n_all += __popc(hit[k]);
+            int pre = column_excl_scan(n_all, tot);
+            const bool whole = !__any(tot > LCAP);
+            for (int part = 0; part < (whole ? 1 : (nk + 63) / 64); ++part) {
+                unsigned now[NWORDS];
+#pragma unroll
+                for (int k = 0; k < NWORDS; ++k) now[k] = whole ? hit[k] : hit_part(hit[k], nk, k, part);
+                if (!whole) {
+                    int n_part = 0;
+#pragma unroll
+                    for (int k = 0; k < NWORDS; ++k) n_part += __popc(now[k]);
+                    pre = column_excl_scan(n_part, tot);
+                }
+                uint8_t* lp = lists + pc * LSEG + pre;
+#pragma unroll
+                for (int k = 0; k < NWORDS; ++k) {
+                    unsigned m = now[k];
+                    const int top = 128 * k + 4 * (word_tests(nk, k) - 1) + gc;
+                    while (m) {
+                        const int bit = __builtin_ctz(m);
+                        m &= m - 1;
+                        *lp++ = (uint8_t)(top - 4 * bit);
+                    }
+                }
+                wave_sync_lds();
+                const int nl = __shfl(tot, pq, 64);
+                const uint8_t* lst = lists + pq * LSEG;
+                // (not unrolled: the lists' lengths differ, and a second copy of
+                // the body measured slower)
 #pragma unroll 1
-                for (int e = 0; e < nl; ++e) {
-                    const int k = lst[e * 64];
-                    const float4 p0 = sj[k];
-                    const float4 p1 = sj[FCAP + k];
-                    const float4 p2 = DC ? p1 : sj[2 * FCAP + k];  // (not staged for the divergence)
-                    const float dx = i0v.x - p0.x, dy = i0v.y - p0.y, dz = i0v.z - p0.z;
-                    const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                for (int e = sub; e < nl; e += 4) {
+                    const int k = lst[e];
+                    const float4 q0 = t0[k], q1 = t1[k];
+                    const float dx = i0v.x - q0.x, dy = i0v.y - q0.y, dz = i0v.z - q0.z;
+                    float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                    // a coincident pair (the particle itself among them) adds nothing: far away
+                    r2 = r2 > 0.0f ? r2 : 1.0e30f;
+                    const float rinv = __builtin_amdgcn_rsqf(r2);
+                    const float r = r2 * rinv;
+                    const float r_2 = 2.0f * r;
+                    // w'(q) of both kernels as truncated powers: t is 0 from q = 1 on, so a
+                    // pair the filter's margin let through adds exactly nothing
+                    const float ti = __builtin_amdgcn_fmed3f(fmaf(-r, hinv_i, 1.0f), 0.0f, 1.0f);
+                    const float ui = __builtin_amdgcn_fmed3f(fmaf(-r_2, hinv_i, 1.0f), 0.0f, 1.0f);
+                    const float Di = Ki * fmaf(ui, ui, -(ti * ti));
+                    const float wx = i1v.x - q1.x, wy = i1v.y - q1.y, wz = i1v.z - q1.z;
                     if constexpr (DC) {
                         // rho_i div v_i = -sum m_j D_i (v_i - v_j) . rhat, rho_i curl v_i =
                         // sum m_j D_i (v_i - v_j) x rhat; D_i is 0 from r = h_i on
-                        const float rinv = __builtin_amdgcn_rsqf(r2);
-                        const float mD = p1.w * Ki * spline_dw_r(r2 * rinv, hinv_i) * rinv;
-                        const float wx = i1v.x - p1.x, wy = i1v.y - p1.y, wz = i1v.z - p1.z;
-                        du = fmaf(mD, fmaf(wx, dx, fmaf(wy, dy, wz * dz)), du);
+                        const float mD = q1.w * Di * rinv;
+                        s1 = fmaf(mD, fmaf(wx, dx, fmaf(wy, dy, wz * dz)), s1);
                         ax = fmaf(mD, wy * dz - wz * dy, ax);
                         ay = fmaf(mD, wz * dx - wx * dz, ay);
                         az = fmaf(mD, wx * dy - wy * dx, az);
                         continue;
                     }
-                    const float hinv_j = MODE == FM_BALSARA ? __builtin_amdgcn_rsqf(p0.w) : p2.w;
-                    const float hinv2_j = hinv_j * hinv_j;
-                    const float rinv = __builtin_amdgcn_rsqf(r2);  // r2 > 0 (phase A), far from denormal
-                    const float r = r2 * rinv;
-                    const float Di = Ki * spline_dw_r(r, hinv_i);
-                    const float Dj = K8PI * hinv2_j * hinv2_j * spline_dw_r(r, hinv_j);
-                    const float vr = ((i1v.x - p1.x) * dx + (i1v.y - p1.y) * dy + (i1v.z - p1.z) * dz) * rinv;
-                    const float wv_ = fminf(vr, 0.0f);
-                    const float vsig_ij = c_i + p2.z - 3.0f * wv_;
-                    float visc = -A.alpha * vsig_ij * wv_ * __builtin_amdgcn_rcpf(rho_i + p2.x);
-                    if constexpr (MODE == FM_BALSARA) visc *= 0.5f * (bal_i + p2.w);
-                    if constexpr (VSIG) {
-                        vmax = fmaxf(vmax, vsig_ij);
-                        dvr = fmaf(p1.w * Di, vr, dvr);
+                    const float4 q2 = t2[DC ? 0 : k];
+                    float hinv_j = q2.w, Kj = q0.w;
+                    if constexpr (MODE == FM_BALSARA) {
+                        hinv_j = __builtin_amdgcn_rsqf(q0.w);
+                        const float hinv2_j = hinv_j * hinv_j;
+                        Kj = K6 * hinv2_j * hinv2_j;
                     }
-                    const float Dbar = 0.5f * (Di + Dj);
-                    const float G = MODE == FM_EQ2 ? fmaf(phi_i + p2.y, Di, visc * Dbar)
-                                                   : fmaf(phi_i, Di, fmaf(p2.y, Dj, visc * Dbar));
-                    const float mGr = p1.w * G * rinv;
+                    const float tj = __builtin_amdgcn_fmed3f(fmaf(-r, hinv_j, 1.0f), 0.0f, 1.0f);
+                    const float uj = __builtin_amdgcn_fmed3f(fmaf(-r_2, hinv_j, 1.0f), 0.0f, 1.0f);
+                    const float Dj = Kj * fmaf(uj, uj, -(tj * tj));
+                    const bool in = ti + tj > 0.0f;
+                    inter_acc += in ? 1 : 0;
+                    const float vr = fmaf(wx, dx, fmaf(wy, dy, wz * dz)) * rinv;
+                    const float wv = fminf(vr, 0.0f);
+                    const float vsig = fmaf(-3.0f, wv, c_i + q2.z);
+                    float v2 = visc_k * (vsig * wv) * __builtin_amdgcn_rcpf(rho_i + q2.x);  // Pi / 2
+                    if constexpr (MODE == FM_BALSARA) v2 *= 0.5f * (bal_i + q2.w);
+                    if constexpr (VSIG) vmax = fmaxf(vmax, in ? vsig : 0.0f);
+                    // G = Phi_i D_i + Phi_j D_j + Pi (D_i + D_j) / 2; Eq. 2: (Phi_i + Phi_j) D_i + Pi (...) / 2
+                    const float Ds = Di + Dj;
+                    const float G = MODE == FM_EQ2 ? fmaf(phi_i + q2.y, Di, v2 * Ds)
+                                                   : fmaf(phi_i + v2, Di, (q2.y + v2) * Dj);
+                    const float mGr = q1.w * G * rinv;
                     ax = fmaf(-mGr, dx, ax);
                     ay = fmaf(-mGr, dy, ay);
                     az = fmaf(-mGr, dz, az);
-                    du = fmaf(p1.w * fmaf(phi_i, Di, 0.5f * visc * Dbar), vr, du);
+                    const float mvr = q1.w * vr;
+                    s1 = fmaf(mvr, Di, s1);
+                    s2 = fmaf(mvr * v2, Ds, s2);
                 }
-                // every lane is done with the tile before the next chunk is staged
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
+                // every lane is done with the lists and the tile
+                wave_sync_lds();
             }
-            ax = group_sum(ax, lpi);
-            ay = group_sum(ay, lpi);
-            az = group_sum(az, lpi);
-            du = group_sum(du, lpi);
-            cnt = group_sum_i(cnt, lpi);
+            if (more) walk_table(w, scratch);  // the lists overwrote it
+        }
+        ax = group_sum(ax, 4);
+        ay = group_sum(ay, 4);
+        az = group_sum(az, 4);
+        s1 = group_sum(s1, 4);
+        if constexpr (DC) {
+            if (valid && sub == 0) {
+                const float ad = fabsf(s1) / rho_i;
+                const float den = ad + sqrtf(fmaf(ax, ax, fmaf(ay, ay, az * az))) / rho_i + 1.0e-4f * c_i * hinv_i;
+                const float B = den > 0.0f ? ad / den : 0.0f;  // no motion and no sound: no viscosity
+                A.bal[i] = B;
+                // B replaces 1/h in the particle's third float4 for the force
+                // pass (the candidates of this pass read only the first two)
+                A.jf_w[3 * (int64_t)i + 2] = make_float4(rho_i, phi_i, c_i, B);
+            }
+            continue;
+        }
+        const float du = fmaf(phi_i, s1, 0.5f * group_sum(s2, 4));
+        if constexpr (VSIG) vmax = group_max(vmax, 4);
+        cand_acc += (int64_t)ni * kept;
+        if (valid) {
+            // the four lanes of a particle store ax, ay, az and du/dt
+            float* dst = sub == 3 ? A.dudt + o_i : A.acc + 3 * (int64_t)o_i + sub;
+            *dst = sub == 0 ? ax : sub == 1 ? ay : sub == 2 ? az : du;
             if constexpr (VSIG) {
-                vmax = group_max(vmax, lpi);
-                dvr = group_sum(dvr, lpi);
-            }
-            const bool leader = valid && sub == 0;
-            if constexpr (DC) {
-                if (leader) {
-                    const float ad = fabsf(du) / rho_i;
-                    const float den = ad + sqrtf(fmaf(ax, ax, fmaf(ay, ay, az * az))) / rho_i +
-                                      1.0e-4f * c_i * hinv_i;
-                    const float B = den > 0.0f ? ad / den : 0.0f;  // no motion and no sound: no viscosity
-                    A.bal[i] = B;
-                    // B replaces 1/h in the particle's third float4 for the force
-                    // pass (the candidates of this pass read only the first two)
-                    A.jf_w[3 * (int64_t)i + 2] = make_float4(rho_i, phi_i, c_i, B);
-                }
-                continue;
-            }
-            cand_acc += (int64_t)wave_count(leader) * kept;
-            double cm[4] = {0.0, 0.0, 0.0, 0.0};
-            if (leader) {
-                A.acc[3 * (int64_t)o_i + 0] = ax;
-                A.acc[3 * (int64_t)o_i + 1] = ay;
-                A.acc[3 * (int64_t)o_i + 2] = az;
-                A.dudt[o_i] = du;
-                if constexpr (VSIG) {
+                if (sub == 0) {
                     A.vsig[i] = fmaxf(vmax, c_i);
-                    A.divv[i] = -dvr / rho_i;
-                }
-                inter_acc += cnt;
-                const double m = i1v.w;
-                cm[0] = m * ax;
-                cm[1] = m * ay;
-                cm[2] = m * az;
-                cm[3] = m * ((double)i1v.x * ax + (double)i1v.y * ay + (double)i1v.z * az + (double)du);
-            }
-            if (A.cons_part) {
-                // only the group leaders (lanes g * lpi) hold terms: the
-                // exchanges at distances below lpi would add zeros
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    for (int o = 32; o >= lpi; o >>= 1) cm[k] += __shfl_xor(cm[k], o, 64);
-                    cm_cell[k] = lane0_d(cm_cell[k] + cm[k]);
+                    A.divv[i] = -s1 / rho_i;
                 }
             }
         }
-        if (!DC && A.cons_part && lane == 0) {
-            const int leaf = A.cell_aux[slot].x;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) A.cons_part[4 * (int64_t)leaf + k] = cm_cell[k];
+        if (A.cons_part) {
+            // lane `sub` of each particle takes component `sub` of the item's
+            // share; then the particles in a fixed order
+            const double m = i1v.w;
+            double cm = sub == 0   ? m * ax
+                        : sub == 1 ? m * ay
+                        : sub == 2 ? m * az
+                                   : m * ((double)i1v.x * ax + (double)i1v.y * ay + (double)i1v.z * az + (double)du);
+            if (!valid) cm = 0.0;
+            for (int o = 32; o >= 4; o >>= 1) cm += __shfl_xor(cm, o, 64);
+            if (lane < 4) A.cons_part[4 * (int64_t)(A.cell_item ? A.cell_item[slot] : slot) + lane] = cm;
         }
     }
     if constexpr (!DC) {
@@ -340,19 +421,19 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
     }
 }
 
-// Per-box sums of the cells' shares: block b adds the shares of its leaves
-// [box_leaf[b], box_leaf[b + 1]) in a fixed order (strided partial sums, then
+// Per-box sums of the items' shares: block b adds the shares of its items
+// [box_item[b], box_item[b + 1]) in a fixed order (strided partial sums, then
 // a tree in LDS), so the result does not depend on scheduling.
 constexpr int CR_BS = 1024;
 
-__global__ void __launch_bounds__(CR_BS) k_cons_reduce(const int* __restrict__ box_leaf,
+__global__ void __launch_bounds__(CR_BS) k_cons_reduce(const int* __restrict__ box_item,
                                                        const double* __restrict__ cons_part, double* __restrict__ cons)
 {
     __shared__ double red[4][CR_BS];
     const int b = blockIdx.x;
     const int t = threadIdx.x;
-    const int l0 = box_leaf[b], l1 = box_leaf[b + 1];
-    // two partial sums per thread (leaves t, t + 2 CR_BS, ... and t + CR_BS,
+    const int l0 = box_item[b], l1 = box_item[b + 1];
+    // two partial sums per thread (items t, t + 2 CR_BS, ... and t + CR_BS,
     // t + 3 CR_BS, ...): two loads in flight, one fixed order
     double v[4] = {0.0, 0.0, 0.0, 0.0}, w[4] = {0.0, 0.0, 0.0, 0.0};
     for (int l = l0 + t; l < l1; l += 2 * CR_BS) {
@@ -414,10 +495,8 @@ void force_enqueue(sph_ctx* c, const float* vel, const float* u, float* acc, flo
     ForceArgs A;
     A.jf = jf;
     A.jf_w = jf;
-    A.cells = static_cast<int4*>(c->cells.p);
-    A.cell_aux = static_cast<int2*>(c->cell_aux.p);
-    A.p_rec = static_cast<int2*>(c->p_rec.p);
-    A.p_shift = static_cast<float4*>(c->p_shift.p);
+    A.cell = cell_args(c, static_cast<int4*>(c->cells.p));
+    A.cell_item = c->uni ? nullptr : static_cast<int*>(c->cell_item.p);
     A.perm = static_cast<uint32_t*>(c->perm.p);
     A.acc = acc;
     A.dudt = dudt;
@@ -426,18 +505,15 @@ void force_enqueue(sph_ctx* c, const float* vel, const float* u, float* acc, flo
     A.vsig = vsig ? static_cast<float*>(c->vsig_s.p) : nullptr;
     A.divv = vsig ? static_cast<float*>(c->divv_s.p) : nullptr;
     A.bal = static_cast<float*>(c->bal_s.p);
-    A.drift = static_cast<float*>(c->drift.p);
     A.ctr = ctr;
-    const int grid = make_sched(c, c->n_leaves, WAVES, 16, A.W);
+    const int grid = make_sched(c, c->n_items, WAVES, 16, A.W);
     A.alpha = c->prm.alpha_visc > 0 ? (float)c->prm.alpha_visc : 0.0f;
     if (events) ev_record(c, EV_FORCE_K0, s);
     const bool bal = c->prm.balsara != 0 && A.alpha > 0.0f;
-    // a layout of top cells only (no split) has at most 27 records per cell
-    const bool one_block = !c->cells_refined;
     auto go = [&](auto vs, auto md) {
         constexpr bool V = decltype(vs)::value;
         constexpr int M = decltype(md)::value;
-        if (one_block)
+        if (c->uni)
             k_force<V, M, true><<<grid, BS, 0, s>>>(A);
         else
             k_force<V, M, false><<<grid, BS, 0, s>>>(A);
@@ -465,7 +541,7 @@ void force_enqueue(sph_ctx* c, const float* vel, const float* u, float* acc, flo
     SPH_HIP(hipGetLastError());
     if (events) ev_record(c, EV_FORCE_K1, s);
     if (cons_d) {
-        k_cons_reduce<<<c->n_boxes, CR_BS, 0, s>>>(static_cast<int*>(c->box_leaf.p), A.cons_part, cons_d);
+        k_cons_reduce<<<c->n_boxes, CR_BS, 0, s>>>(static_cast<int*>(c->box_item.p), A.cons_part, cons_d);
         SPH_HIP(hipGetLastError());
     }
 }
@@ -482,7 +558,7 @@ double* force_buffers(sph_ctx* c, bool cons)
     }
     if (c->prm.balsara) ensure<float>(c, c->bal_s, c->n);
     if (!cons) return nullptr;
-    ensure<double>(c, c->cons_part, (size_t)4 * c->n_leaves);
+    ensure<double>(c, c->cons_part, (size_t)4 * c->n_items);
     return ensure<double>(c, c->cons_d, (size_t)4 * c->n_boxes);
 }
 
@@ -504,6 +580,7 @@ void force_f32(sph_ctx* c, const float* vel, const float* u, float* acc, float* 
             st->interactions_force = hc[CT_FORCE_INTER];
             st->candidates_force = hc[CT_FORCE_CAND];
             st->n_cells = c->n_leaves;
+            finish_build_read(c);
             st->n_pairs = c->n_pairs;
         }
     }

@@ -10,17 +10,15 @@
 // (the remaining 1 - S belongs to a far field of multipoles, not computed
 // here). Coincident pairs add nothing.
 //
-// Work unit: one leaf cell per wavefront, as in the density loop. Its
-// candidates are the particles of the leaves within the cell's own largest
-// search radius (the first part of its neighbour records), which the cutoff
-// may not exceed, so every pair inside r_cut is among them. They are staged
-// through LDS in chunks of GCH, shifted into the cell frame, keeping only
-// those within r_cut of the bounding box of the particles in the pass (the
-// cutoff is usually well inside the search radius the lists were built for);
-// the lanes of each particle split the kept candidates and add up their
-// pairs, then meet in a group sum. It is a gather: each particle sums its own
-// pairs, so there are no atomics and the result has the same bits on every
-// run.
+// Work unit: an item of at most 16 particles per wavefront (tiles.h), as in the
+// density loop. Its candidates are the particles of the cells within its search
+// radii, which the cutoff may not exceed, so every pair inside r_cut is among
+// them. They are staged through LDS, keeping only those within r_cut of the
+// bounding box of the item's particles (the cutoff is usually well inside the
+// search radius); the matrix cores propose the pairs inside r_cut (the filter of
+// tiles.h) and the four lanes of a particle sum every fourth of them. It is a
+// gather: each particle sums its own pairs, so there are no atomics and the
+// result has the same bits on every run.
 #include <cmath>
 
 #include "common.h"
@@ -28,177 +26,197 @@
 
 namespace {
 
-constexpr int GBS = 64;   // one wavefront per block
-constexpr int GCH = 256;  // candidates per staged chunk
+constexpr int GBS = 64;    // one wavefront per block
+constexpr int GCAP = 128;  // candidates per LDS tile
+constexpr int GLCAP = 80;  // entries of a particle's list (64 candidates always fit)
+constexpr int GLSEG = GLCAP + 4;
 
 struct GravArgs {
-    const float4* jg;       // sorted (x, y, z) in the leaf frame, m
+    const float4* jg;       // sorted (x, y, z) as the layout stores them, m
     const uint32_t* perm;   // sorted index -> caller index
-    const int4* cells;      // per schedule slot: first particle, count, first record, density records
-    const int2* p_rec;      // per record: first particle and count of the neighbour leaf
-    const float4* p_shift;  // per record: frame shift of the neighbour leaf
+    CellArgs cell;          // the items, their frames and candidates (within the search radii)
     float* acc;             // caller order, 3 per particle
     int64_t* ctr;
     int n_slots;
-    float G, eps2, rc2, inv_rc2;
+    float G, eps2, rc, rc2, inv_rc2;
+    float delta;            // bound on the drift since the build
 };
 
-// Sorted copies of position (leaf frame) and mass; counts non-positive or
+// Sorted copies of position (bits as the layout stores it) and mass; counts non-positive or
 // non-finite masses.
 __global__ void __launch_bounds__(256) k_grav_prologue(int64_t n, const uint32_t* __restrict__ perm,
-                                                       const float4* __restrict__ xrel,
-                                                       const float* __restrict__ mass, float4* __restrict__ jg,
+                                                       const int4* __restrict__ xs,
+                                                       const float* __restrict__ mass, int4* __restrict__ jg,
                                                        int64_t* __restrict__ ctr)
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     bool bad = false;
     if (p < n) {
         const float m = mass[perm[p]];
-        const float4 x = xrel[p];
-        jg[p] = make_float4(x.x, x.y, x.z, m);
+        const int4 x = xs[p];
+        jg[p] = make_int4(x.x, x.y, x.z, __float_as_int(m));
         bad = !(m > 0.0f) || !isfinite(m);
     }
     const int n_bad = __syncthreads_count(bad);
     if (threadIdx.x == 0 && n_bad) atomicAdd((unsigned long long*)&ctr_slot(ctr)[CT_BAD_INPUT], (unsigned long long)n_bad);
 }
 
-// Store a fetched chunk (x, y, z, m in the cell frame) keeping only the
-// candidates within reach of `box`, packed from slot 0; the slots after them
-// up to GCH get a massless candidate far outside r_cut, so the pair loop may
-// run to a multiple of its stride without a bounds test. Returns how many
-// were kept.
-__device__ __forceinline__ int commit_culled(float4* sj, const ChunkRegs<1, GCH>& R, const CullBox& box,
-                                             float reach2)
+template <bool UNI>
+__global__ void __launch_bounds__(GBS) __attribute__((amdgpu_waves_per_eu(4))) k_gravity(GravArgs A)
 {
+    constexpr int NW = (GCAP + 127) / 128;
+    __shared__ float4 t0[GCAP];  // x, y, z, m
+    __shared__ uint2 fa[GCAP];   // filter input: x, y; z, |x|^2 (half precision)
+    // the lists share their memory with the scratch of the walk
+    __shared__ float4 scratch4[(16 * GLSEG > WALK_LDS<UNI> ? 16 * GLSEG : WALK_LDS<UNI>) / 16];
+    char* scratch = reinterpret_cast<char*>(scratch4);
+    uint8_t* lists = reinterpret_cast<uint8_t*>(scratch4);
     const int lane = threadIdx.x & 63;
-    constexpr int PER = GCH / 64;
-    int n = 0;
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        const int t = lane + 64 * r;
-        float4 a = R.v[r][0];
-        a.x += R.s[r][0];
-        a.y += R.s[r][1];
-        a.z += R.s[r][2];
-        const bool keep = t < R.len && box_dist2(a.x, a.y, a.z, box) < reach2;
-        const uint64_t m = __ballot(keep);
-        if (keep) sj[n + lanes_below(m)] = a;
-        n += __popcll(m);
+    const int pc = lane & 15, gc = lane >> 4;  // column (particle) and lane group of the filter
+    const int pq = lane >> 2, sub = lane & 3;  // particle and lane of the pair loop
+    const int fin = 4 * (lane & 3) + gc;       // the candidate (of 16) this lane feeds to the filter
+    const int slot = xcd_block_index();        // each XCD takes its own run of slots
+    if (slot >= A.n_slots) return;             // whole wavefront
+    Item<UNI> it;
+    CandWalk<UNI> w;
+    item_load(it, w, A.cell, slot, A.delta, A.rc);
+    const int i0 = it.i0, ni = it.ni;
+    auto frame = [&](float4 v, float3 sh) {
+        return make_float4(item_coord<UNI>(v.x, it.ox, it.sh, it.sl, sh.x),
+                           item_coord<UNI>(v.y, it.oy, it.sh, it.sl, sh.y),
+                           item_coord<UNI>(v.z, it.oz, it.sh, it.sl, sh.z), v.w);
+    };
+    const float3 none = make_float3(0.f, 0.f, 0.f);
+    const float reach2 = cull_reach2(A.rc);
+    const float fs = FILTER_SCALE / (fmaxf(fmaxf(it.hx, it.hy), it.hz) + A.rc);
+    f16x4 fcol;
+    f32x4 C;
+    {
+        const float4 xc = frame(A.jg[i0 + min(pc, ni - 1)], none);
+        const float ux = (xc.x - it.bx) * fs, uy = (xc.y - it.by) * fs, uz = (xc.z - it.bz) * fs;
+        const float n2 = fmaf(ux, ux, fmaf(uy, uy, uz * uz)) * (1.0f - FILTER_EPS) - FILTER_ABS;
+        fcol = filter_column(ux, uy, uz);
+        const float c = pc < ni ? fmaf(A.rc2 * (fs * fs), -(1.0f + FILTER_EPS), n2) : 1.0e9f;
+        C = {c, c, c, c};
     }
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        const int t = lane + 64 * r;
-        if (t >= n) sj[t] = make_float4(1.0e18f, 1.0e18f, 1.0e18f, 0.0f);
-    }
-    wave_sync_lds();
-    return n;
-}
-
-// The pairs of one particle with the staged candidates sub, sub + LPI, ...
-// below len (rounded up to a multiple of 4 LPI: the padding adds nothing),
-// four tile reads in flight at once. The pull on i is -m_j S (r^2 + eps^2)^(-3/2)
-// r_ij per pair inside r_cut; a pair outside (or at r = 0) is selected away,
-// so the far padding's overflows never reach the sums. rc2 is the lane's:
-// below zero on a lane without a particle. The pairs inside are counted for
-// the whole wavefront (a ballot of the same test, in scalar registers).
-template <int LPI>
-__device__ __forceinline__ void pair_chunk(const float4* tc, int len, const float4& xi, float rc2, float inv_rc2,
-                                           float eps2, float& ax, float& ay, float& az, int& wcnt)
-{
-    const int len_pad = (len + 4 * LPI - 1) & ~(4 * LPI - 1);
-    for (int k0 = 0; k0 < len_pad; k0 += 4 * LPI, tc += 4 * LPI) {
-        float4 pj[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) pj[u] = tc[u * LPI];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float dx = xi.x - pj[u].x, dy = xi.y - pj[u].y, dz = xi.z - pj[u].z;
-            const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-            const bool in = r2 < rc2 && r2 > 0.0f;
-            const float s = fmaf(-r2, inv_rc2, 1.0f);                 // 1 - x^2
-            const float inv = __builtin_amdgcn_rsqf(r2 + eps2);      // (r^2 + eps^2)^(-1/2)
-            const float f = in ? pj[u].w * (s * s) * (inv * inv * inv) : 0.0f;
-            ax = fmaf(-f, dx, ax);
-            ay = fmaf(-f, dy, ay);
-            az = fmaf(-f, dz, az);
-            wcnt += __popcll(__ballot(in));
-        }
-    }
-}
-
-// ONEBLK: every cell has at most 64 records (a layout of top cells only has
-// 27), so the multi-block paths of the record cursor drop out.
-template <bool ONEBLK>
-__global__ void __launch_bounds__(GBS) k_gravity(GravArgs A)
-{
-    __shared__ float4 tile[GCH];
-    __shared__ uint8_t marks[GCH];  // record starts of the chunk being fetched
-    const int lane = threadIdx.x & 63;
-    const int slot = xcd_block_index();  // each XCD takes its own run of slots
-    if (slot >= A.n_slots) return;       // whole wavefront
-    const int4 ci = A.cells[slot];
-    const int i0 = ci.x, ni = ci.y, pb0 = ci.z, np = ONEBLK ? min(ci.w, 64) : ci.w;
-    NbrCursor cu;
-    cursor_init(cu, A.p_rec, A.p_shift, pb0, np);
-    const int nj = np <= 64 ? cu.nb.nj : count_candidates(A.p_rec, pb0, np);
-    // lanes per particle: the cell's particles spread over the wavefront
-    int lpi = 1;
-    while (lpi < 16 && 2 * lpi * ni <= 64) lpi *= 2;
-    const int per_pass = 64 / lpi;
-    const int g = lane / lpi, sub = lane & (lpi - 1);
-    const float reach2 = cull_reach2(uniform_f(sqrtf(A.rc2)));
-    int pairs = 0;  // wave-uniform
-    int64_t tested = 0;
-    for (int ib = 0; ib < ni; ib += per_pass) {
-        const int gi = ib + g;
-        const bool valid = gi < ni;
-        const int i = i0 + (valid ? gi : 0);
-        const float4 xi = A.jg[i];
-        // only the candidates within r_cut of the pass's bounding box can pair
-        const CullBox box = pass_box(xi.x, xi.y, xi.z, valid);
-        const int n_valid = min(per_pass, ni - ib);
-        const float rc2 = valid ? A.rc2 : -1.0f;
-        float ax = 0.0f, ay = 0.0f, az = 0.0f;
-        ChunkRegs<1, GCH> R;
-        cursor_seek(cu, A.p_rec, A.p_shift, 0);
-        fetch_chunk(R, A.jg, cu.nb, 0, cursor_chunk(cu, 0, GCH), marks);
-        int len;
-        for (int c0 = 0; c0 < nj; c0 += len) {
-            len = R.len;
-            const int kept = commit_culled(tile, R, box, reach2);
-            // the next chunk's loads are in flight while this one is summed
-            const int nx = c0 + len;
-            if (nx < nj) {
-                cursor_seek(cu, A.p_rec, A.p_shift, nx);
-                fetch_chunk(R, A.jg, cu.nb, nx - cu.off0, cursor_chunk(cu, nx, GCH), marks);
+    const bool valid = pq < ni;
+    const int i = i0 + (valid ? pq : 0);
+    const float4 xi = frame(A.jg[i], none);
+    float ax = 0.0f, ay = 0.0f, az = 0.0f;
+    int pairs = 0;  // this lane's
+    int kept = 0;
+    bool ok = false;
+    int src = 0;
+    float3 sh = none;
+    float4 p0 = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto fetch = [&]() -> bool {
+        Slots<1> S;
+            if (!walk_next<1>(w, A.cell, scratch, S)) return false;
+            ok = S.ok[0];
+            src = S.src[0];
+            sh = S.sh[0];
+        p0 = A.jg[src];
+        return true;
+    };
+    walk_table(w, scratch);
+    bool more = fetch();
+    while (more) {
+        // stage the candidates within r_cut of the item's box
+        int nk = 0;
+        do {
+            const float4 q = frame(p0, sh);
+            const float ux = UNI ? q.x : q.x - it.bx, uy = UNI ? q.y : q.y - it.by, uz = UNI ? q.z : q.z - it.bz;
+            const float gx = fmaxf(fabsf(ux) - it.hx, 0.0f), gy = fmaxf(fabsf(uy) - it.hy, 0.0f),
+                        gz = fmaxf(fabsf(uz) - it.hz, 0.0f);
+            const bool keep = ok && fmaf(gx, gx, fmaf(gy, gy, gz * gz)) < reach2;
+            const uint64_t m = __ballot(keep);
+            if (keep) {
+                const int d = nk + lanes_below(m);
+                const float fx = ux * fs, fy = uy * fs, fz = uz * fs;
+                const float n2 = fmaf(fx, fx, fmaf(fy, fy, fz * fz)) * (1.0f - FILTER_EPS);
+                fa[d] = make_uint2(pack_f16(fx, fy), pack_f16(fz, n2));
+                t0[d] = q;
             }
-            tested += (int64_t)n_valid * kept;
-            const float4* tc = tile + sub;
-            if (lpi == 1)
-                pair_chunk<1>(tc, kept, xi, rc2, A.inv_rc2, A.eps2, ax, ay, az, pairs);
-            else if (lpi == 2)
-                pair_chunk<2>(tc, kept, xi, rc2, A.inv_rc2, A.eps2, ax, ay, az, pairs);
-            else if (lpi == 4)
-                pair_chunk<4>(tc, kept, xi, rc2, A.inv_rc2, A.eps2, ax, ay, az, pairs);
-            else if (lpi == 8)
-                pair_chunk<8>(tc, kept, xi, rc2, A.inv_rc2, A.eps2, ax, ay, az, pairs);
-            else
-                pair_chunk<16>(tc, kept, xi, rc2, A.inv_rc2, A.eps2, ax, ay, az, pairs);
-            wave_sync_lds();  // every lane is done with the tile before it is staged again
+            nk += __popcll(m);
+            more = fetch();
+        } while (more && nk + 64 <= GCAP);
+        kept += nk;
+        if (nk + lane < ((nk + 63) & ~63)) fa[nk + lane] = make_uint2(0u, pack_f16(0.0f, FILTER_FAR));
+        wave_sync_lds();
+        unsigned hit[NW];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) hit[k] = 0u;
+#pragma unroll
+        for (int q = 0; q < GCAP / 64; ++q) {
+            if (64 * q < nk) {
+                unsigned m = hit[q >> 1];
+#pragma unroll
+                for (int b = 4 * q; b < 4 * q + 4; ++b) {
+                    const uint2 a = fa[16 * b + fin];
+                    const f32x4 D = __builtin_amdgcn_mfma_f32_4x4x4f16(f16x4_of(a.x, a.y), fcol, C, 0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) m = __builtin_amdgcn_alignbit(m, __float_as_uint(D[r]), 31);
+                }
+                hit[q >> 1] = m;
+            }
         }
-        ax = group_sum(ax, lpi);
-        ay = group_sum(ay, lpi);
-        az = group_sum(az, lpi);
-        if (valid && sub == 0) {
-            const uint32_t o = A.perm[i];
-            A.acc[3 * (int64_t)o + 0] = A.G * ax;
-            A.acc[3 * (int64_t)o + 1] = A.G * ay;
-            A.acc[3 * (int64_t)o + 2] = A.G * az;
+        // the words become lists and the lists pairs: the whole tile at once, or (a
+        // list would not fit) 64 candidates at a time
+        int n_all = 0, tot = 0;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) n_all += __popc(hit[k]);
+        int pre = column_excl_scan(n_all, tot);
+        const bool whole = !__any(tot > GLCAP);
+        for (int part = 0; part < (whole ? 1 : (nk + 63) / 64); ++part) {
+            unsigned now[NW];
+#pragma unroll
+            for (int k = 0; k < NW; ++k) now[k] = whole ? hit[k] : hit_part(hit[k], nk, k, part);
+            if (!whole) {
+                int n_part = 0;
+#pragma unroll
+                for (int k = 0; k < NW; ++k) n_part += __popc(now[k]);
+                pre = column_excl_scan(n_part, tot);
+            }
+            uint8_t* lp = lists + pc * GLSEG + pre;
+#pragma unroll
+            for (int k = 0; k < NW; ++k) {
+                unsigned m = now[k];
+                const int top = 128 * k + 4 * (word_tests(nk, k) - 1) + gc;
+                while (m) {
+                    const int bit = __builtin_ctz(m);
+                    m &= m - 1;
+                    *lp++ = (uint8_t)(top - 4 * bit);
+                }
+            }
+            wave_sync_lds();
+            const int nl = __shfl(tot, pq, 64);
+            const uint8_t* lst = lists + pq * GLSEG;
+            for (int e = sub; e < nl; e += 4) {
+                // the pull on i is -m_j S (r^2 + eps^2)^(-3/2) r_ij per pair inside r_cut
+                const float4 q = t0[lst[e]];
+                const float dx = xi.x - q.x, dy = xi.y - q.y, dz = xi.z - q.z;
+                const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                const bool in = r2 < A.rc2 && r2 > 0.0f;
+                const float s = fmaf(-r2, A.inv_rc2, 1.0f);              // 1 - x^2
+                const float inv = __builtin_amdgcn_rsqf(r2 + A.eps2);    // (r^2 + eps^2)^(-1/2)
+                const float f = in ? q.w * (s * s) * (inv * inv * inv) : 0.0f;
+                ax = fmaf(-f, dx, ax);
+                ay = fmaf(-f, dy, ay);
+                az = fmaf(-f, dz, az);
+                pairs += in ? 1 : 0;
+            }
+            wave_sync_lds();  // every lane is done with the lists and the tile
         }
+        if (more) walk_table(w, scratch);  // the lists overwrote it
     }
+    ax = group_sum(ax, 4);
+    ay = group_sum(ay, 4);
+    az = group_sum(az, 4);
+    if (valid && sub < 3)  // three lanes of a particle store a component each
+        A.acc[3 * (int64_t)A.perm[i] + sub] = A.G * (sub == 0 ? ax : sub == 1 ? ay : az);
     // the gravity call has the counters to itself
-    ctr_add_uniform(A.ctr, CT_FORCE_INTER, pairs);
-    ctr_add_uniform(A.ctr, CT_FORCE_CAND, tested);
+    ctr_wave_add(A.ctr, CT_FORCE_INTER, pairs);
+    ctr_add_uniform(A.ctr, CT_FORCE_CAND, (int64_t)ni * kept);
 }
 
 }  // namespace
@@ -231,27 +249,28 @@ void gravity_p2p(sph_ctx* c, const float* mass, double G, double eps, double r_c
                     std::to_string(c->h_min) + ", less twice the drift since the build)");
     const int64_t n = c->n;
     int64_t* ctr = static_cast<int64_t*>(c->counters.p);
-    float4* jg = ensure<float4>(c, c->jg, n);
+    int4* jg = ensure<int4>(c, c->jg, n);
     fill_u32(ctr, 0u, 2 * (int64_t)CT_COUNT, s);
     k_grav_prologue<<<blocks_for(n, 256), 256, 0, s>>>(n, static_cast<uint32_t*>(c->perm.p),
-                                                       static_cast<float4*>(c->xrel.p), mass, jg, ctr);
+                                                       static_cast<int4*>(c->uni ? c->xfix.p : c->xrel.p), mass,
+                                                       jg, ctr);
     SPH_HIP(hipGetLastError());
     GravArgs A;
-    A.jg = jg;
+    A.jg = static_cast<float4*>(c->jg.p);
     A.perm = static_cast<uint32_t*>(c->perm.p);
-    A.cells = static_cast<int4*>(c->cells_d.p);
-    A.p_rec = static_cast<int2*>(c->p_rec.p);
-    A.p_shift = static_cast<float4*>(c->p_shift.p);
+    A.cell = cell_args(c, static_cast<int4*>(c->uni ? c->cells.p : c->cells_d.p));
     A.acc = acc;
     A.ctr = ctr;
-    A.n_slots = (int)c->n_leaves;
+    A.n_slots = (int)c->n_items;
     A.G = (float)G;
     A.eps2 = (float)(eps * eps);
+    A.delta = delta;
+    A.rc = (float)r_cut;
     A.rc2 = (float)(r_cut * r_cut);
     A.inv_rc2 = (float)(1.0 / (r_cut * r_cut));
     ev_record(c, EV_GRAV_K0, s);
-    const unsigned grid = (unsigned)std::max<int64_t>(c->n_leaves, 1);
-    if (!c->cells_refined)
+    const unsigned grid = (unsigned)std::max<int64_t>(c->n_items, 1);
+    if (c->uni)
         k_gravity<true><<<grid, GBS, 0, s>>>(A);
     else
         k_gravity<false><<<grid, GBS, 0, s>>>(A);

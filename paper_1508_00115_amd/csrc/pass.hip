@@ -102,6 +102,7 @@ void pass_f32(sph_ctx* c, const float* mass, float* h, float* rho, float* f, flo
             st->interactions_force = fi;
             st->candidates_force = fc;
             st->n_cells = c->n_leaves;
+            finish_build_read(c);
             st->n_pairs = c->n_pairs;
         }
         return;
@@ -119,6 +120,7 @@ void pass_f32(sph_ctx* c, const float* mass, float* h, float* rho, float* f, flo
         st->tests_density = hc[CT_DENS_TESTS];
         st->listed_density = hc[CT_DENS_LISTED];
         st->n_cells = c->n_leaves;
+        finish_build_read(c);
         st->n_pairs = c->n_pairs;
     }
     if (c->prm.timing) {

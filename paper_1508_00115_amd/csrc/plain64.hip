@@ -335,6 +335,7 @@ void density_f64(sph_ctx* c, const double* mass, double* h, double* rho, double*
         double* rhos = ensure<double>(c, c->rho64, n);
         double* fs = ensure<double>(c, c->f64, n);
         uint8_t* st_s = ensure<uint8_t>(c, c->st64, n);
+        partner_lists(c, s);
         SPH_HIP(hipMemsetAsync(ctr, 0, CT_COUNT * 8, s));
         k_d64_prologue<<<blocks_for(n, 256), 256, 0, s>>>(n, static_cast<uint32_t*>(c->perm.p), mass, h, status,
                                                           m_s, hs, st_s, ctr);
@@ -395,6 +396,7 @@ void density_f64(sph_ctx* c, const double* mass, double* h, double* rho, double*
                 st->candidates_density = tot_cand;
                 st->candidates_force = 0;
                 st->n_cells = c->n_leaves;
+                finish_build_read(c);
                 st->n_pairs = c->n_pairs;
             }
             SPH_REQUIRE(hc[CT_UNCONV] == 0, SPH_E_NOT_CONVERGED,
@@ -473,6 +475,7 @@ void force_f64(sph_ctx* c, const double* vel, const double* u, double* acc, doub
             st->interactions_force = hc[CT_FORCE_INTER];
             st->candidates_force = hc[CT_FORCE_CAND];
             st->n_cells = c->n_leaves;
+            finish_build_read(c);
             st->n_pairs = c->n_pairs;
         }
     }

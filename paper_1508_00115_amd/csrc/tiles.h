@@ -1,5 +1,6 @@
-// Wavefront-level helpers shared by the hot kernels: the per-XCD work queues
-// and the staging of a cell's neighbour particles into LDS.
+// Wavefront-level helpers shared by the hot kernels: the per-XCD work queues,
+// the work items with their frames and candidates, and the matrix-core filter of
+// the pairs.
 #pragma once
 
 #include "common.h"
@@ -15,12 +16,26 @@
 //   persistent: a grid sized to the machine pops batches of items from eight
 //     per-XCD queues (one atomic per batch) and steals from the other queues
 //     when its own is empty.
+// Queue q covers items [xcd_start(n_items, q), xcd_start(n_items, q + 1)).
 struct WorkSched {
     int persistent;   // 0: hardware dispatch, 1: per-XCD queues
     int batch;        // items per pop (persistent)
     int n_items;
-    int q_begin[9];   // queue q covers items [q_begin[q], q_begin[q+1])
 };
+
+// The kernel's argument block (its only argument, a T), through a pointer the
+// compiler cannot see through: fields read from it are loaded where they are
+// used. Arguments by value all live in scalar registers from the start; the hot
+// loops' wave-uniform values then spill over into vector registers.
+template <class T>
+using KernArgs = const __attribute__((address_space(4))) T*;
+template <class T>
+__device__ __forceinline__ KernArgs<T> late_args()
+{
+    KernArgs<T> p = (KernArgs<T>)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
 
 // Workgroup index with the XCD round-robin undone: blocks that land on the
 // same XCD get consecutive indices.
@@ -48,11 +63,12 @@ __device__ __forceinline__ bool next_items(const WorkSched& W, int64_t* ctr, int
         const int xcd = blockIdx.x & 7;
         while (state < 8) {
             const int q = (xcd + state) & 7;
-            const int size = W.q_begin[q + 1] - W.q_begin[q];
+            const int begin = (int)sph::xcd_start(W.n_items, q);
+            const int size = (int)sph::xcd_start(W.n_items, q + 1) - begin;
             const int64_t k = atomicAdd((unsigned long long*)&ctr[CT_QUEUE + 8 * q], (unsigned long long)W.batch);
             if (k < size) {
-                lo = W.q_begin[q] + (int)k;
-                hi = W.q_begin[q] + (int)min<int64_t>(k + W.batch, size);
+                lo = begin + (int)k;
+                hi = begin + (int)min<int64_t>(k + W.batch, size);
                 break;
             }
             ++state;
@@ -62,33 +78,6 @@ __device__ __forceinline__ bool next_items(const WorkSched& W, int64_t* ctr, int
     a_end = __shfl(hi, 0, 64);
     state = __shfl(state, 0, 64);
     return a >= 0;
-}
-
-// Lanes per particle for a cell of ni particles and nj candidates: the power
-// of two (at least lpi_min) that minimises passes x (candidate tests + list
-// work per particle + fixed work of a pass, per lane), plus the re-staging of
-// every pass when the candidates cannot stay resident in LDS (chunks of
-// `chunk`). Weights are VALU costs in units of one candidate test: list work
-// is given per particle (`list_work`), a pass costs ~25, staging a chunk ~20.
-__device__ __forceinline__ int choose_lpi(int ni, int nj, int lpi_min, float list_work, bool resident, int chunk)
-{
-    const int nchunks = (nj + chunk - 1) / chunk;
-    int best = 16;
-    float best_cost = 3.0e38f;
-#pragma unroll
-    for (int lg = 1; lg <= 4; ++lg) {  // l = 2, 4, 8, 16: every division below is a shift or a constant
-        const int l = 1 << lg;
-        if (l < lpi_min) continue;
-        const int per = 64 >> lg;
-        const float passes = (float)((ni + per - 1) >> (6 - lg));
-        float cost = passes * (((float)nj + list_work) * (1.0f / (float)l) + 25.0f);
-        if (!resident) cost += passes * (float)nchunks * 20.0f;
-        if (cost < best_cost) {
-            best_cost = cost;
-            best = l;
-        }
-    }
-    return best;
 }
 
 __device__ __forceinline__ void wave_sync_lds()
@@ -146,177 +135,11 @@ __device__ __forceinline__ int group_sum_i(int v, int lpi)
     return v;
 }
 
-// Even out the list lengths of the lpi lanes of each particle (aligned groups
-// of lanes; lane l's list is lists[l], lists[l + 64], ...), whose phase B
-// trip count is the longest list in the wavefront: at distance m = 1, 2, ...
-// the lane of each pair with more entries hands the surplus half to its
-// partner, which copies them from the end of the giver's list to the end of
-// its own (the giver only shortens its count, so no lane reads a slot that
-// is being written). After log2(lpi) steps the lists of a particle differ by
-// at most one entry; the set of entries, and so every sum, is unchanged (only
-// the order in which the lanes add them, as with any split of the
-// candidates). No list grows beyond the longest one. Returns the lane's new
-// length; the whole wavefront must be active.
-template <class T>
-__device__ __forceinline__ int balance_lists(T* lists, int nl, int lpi)
-{
-    const int lane = threadIdx.x & 63;
-    for (int m = 1; m < lpi; m <<= 1) {
-        const int nl_p = __shfl_xor(nl, m, 64);
-        const int tot = nl + nl_p;
-        const int mine = (lane & m) ? (tot >> 1) : tot - (tot >> 1);
-        const int take = mine - nl;  // > 0: copy that many from the partner's end
-        const T* src = lists + (lane ^ m) + (nl_p - take) * 64;
-        T* dst = lists + lane + nl * 64;
-        for (int t = 0; t < take; ++t) dst[t * 64] = src[t * 64];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        nl = mine;
-    }
-    return nl;
-}
-
 // Number of lanes for which c holds (a scalar bit count of the ballot).
 __device__ __forceinline__ int wave_count(bool c)
 {
     return __popcll(__ballot(c));
 }
-
-// Number of candidates of a cell: the particles of every cell in its list.
-__device__ __forceinline__ int count_candidates(const int2* __restrict__ p_rec, int pb0, int np_all)
-{
-    const int lane = threadIdx.x & 63;
-    int nj = 0;
-    for (int b0 = 0; b0 < np_all; b0 += 64) {
-        const int q = b0 + lane;
-        int cnt = q < np_all ? p_rec[pb0 + q].y : 0;
-        for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-        nj += cnt;
-    }
-    return nj;
-}
-
-// Neighbour-cell records of a cell with at most 64 neighbour cells, one per
-// lane: first particle, count, exclusive prefix of the counts (the cell's
-// offset in the flattened candidate list) and the shift into the cell frame.
-// A record holds its cell's first particle and count itself (p_rec, written
-// by the build), so the staging is one load away from the cell's record list.
-struct NbrLanes {
-    int bs, bc, off;
-    float sx, sy, sz;
-    int np, nj;
-};
-
-// The records already in registers (lane q: record q, zero beyond np).
-__device__ __forceinline__ NbrLanes nbr_from(int2 rec, float4 sh, int np)
-{
-    const int lane = threadIdx.x & 63;
-    NbrLanes nb;
-    nb.bs = rec.x;
-    nb.bc = rec.y;
-    nb.sx = sh.x;
-    nb.sy = sh.y;
-    nb.sz = sh.z;
-    int inc = nb.bc;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += t;
-    }
-    nb.off = inc - nb.bc;
-    nb.nj = __shfl(inc, 63, 64);
-    nb.np = np;
-    return nb;
-}
-
-__device__ __forceinline__ NbrLanes load_nbr(const int2* __restrict__ p_rec, const float4* __restrict__ p_shift,
-                                             int pb0, int np)
-{
-    const int lane = threadIdx.x & 63;
-    NbrLanes nb;
-    nb.bs = 0;
-    nb.bc = 0;
-    nb.sx = nb.sy = nb.sz = 0.f;
-    if (lane < np) {
-        const int2 rec = p_rec[pb0 + lane];
-        const float4 sh = p_shift[pb0 + lane];
-        nb.bs = rec.x;
-        nb.bc = rec.y;
-        nb.sx = sh.x;
-        nb.sy = sh.y;
-        nb.sz = sh.z;
-    }
-    int inc = nb.bc;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += t;
-    }
-    nb.off = inc - nb.bc;
-    nb.nj = __shfl(inc, 63, 64);
-    nb.np = np;
-    return nb;
-}
-
-// The flattened candidate list of a cell, walked in increasing order: the
-// neighbour-cell records are held 64 at a time (one NbrLanes block), and a
-// chunk never spans two blocks, so any number of neighbour cells is staged
-// with the independent loads of fetch_chunk / stage_fast and every record is
-// read once per sweep. Candidates before the current block: off0.
-struct NbrCursor {
-    NbrLanes nb;
-    int b0, off0;  // first record of the block, candidates before it
-    int pb0, np_all;
-};
-
-__device__ __forceinline__ void cursor_init(NbrCursor& cu, const int2* __restrict__ p_rec,
-                                            const float4* __restrict__ p_shift, int pb0, int np_all)
-{
-    cu.pb0 = pb0;
-    cu.np_all = np_all;
-    cu.b0 = 0;
-    cu.off0 = 0;
-    cu.nb = load_nbr(p_rec, p_shift, pb0, min(np_all, 64));
-}
-
-// The cursor on a cell whose first block of records is already in registers.
-__device__ __forceinline__ void cursor_init_from(NbrCursor& cu, const NbrLanes& nb, int pb0, int np_all)
-{
-    cu.pb0 = pb0;
-    cu.np_all = np_all;
-    cu.b0 = 0;
-    cu.off0 = 0;
-    cu.nb = nb;
-}
-
-// Move the cursor to the block holding candidate c (c at or after the
-// current block's start; back to the first block when c is before it).
-__device__ __forceinline__ void cursor_seek(NbrCursor& cu, const int2* __restrict__ p_rec,
-                                            const float4* __restrict__ p_shift, int c)
-{
-    if (c < cu.off0) cursor_init(cu, p_rec, p_shift, cu.pb0, cu.np_all);
-    while (c >= cu.off0 + cu.nb.nj && cu.b0 + 64 < cu.np_all) {
-        cu.off0 += cu.nb.nj;
-        cu.b0 += 64;
-        cu.nb = load_nbr(p_rec, p_shift, cu.pb0 + cu.b0, min(cu.np_all - cu.b0, 64));
-    }
-}
-
-// Length of the chunk that starts at candidate c (cursor on c's block).
-__device__ __forceinline__ int cursor_chunk(const NbrCursor& cu, int c, int cap)
-{
-    return min(cap, cu.off0 + cu.nb.nj - c);
-}
-
-// A chunk of candidates in flight: the loads of stage_fast split from the LDS
-// stores, so a kernel can fetch chunk c + 1 while it computes chunk c.
-template <int NF, int CAP>
-struct ChunkRegs {
-    float4 v[CAP / 64][NF];
-    float s[CAP / 64][3];
-    int len;
-};
 
 // Lanes of the wavefront below this one whose bit is set in mask.
 __device__ __forceinline__ int lanes_below(uint64_t mask)
@@ -324,107 +147,14 @@ __device__ __forceinline__ int lanes_below(uint64_t mask)
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// Load candidates [c0, c0 + len) of the cursor's block (len <= CAP) into R.
-// The neighbour record (lane of nb) of each slot is found without a search:
-// the record holding c0 is the last one starting at or before it (a ballot
-// over the record lanes), each record starting inside the chunk marks its
-// first slot in mk (CAP bytes of LDS), and a slot's record is that first one
-// plus the marks up to the slot (a ballot of the marks and a lane count).
-// Every record holds at least one particle, so no two records start at the
-// same slot. The loads of the chunk are independent and issue back to back.
-template <int NF, int CAP, int STRIDE = NF>
-__device__ __forceinline__ void fetch_chunk(ChunkRegs<NF, CAP>& R, const float4* __restrict__ jd,
-                                            const NbrLanes& nb, int c0, int len, uint8_t* mk)
-{
-    const int lane = threadIdx.x & 63;
-    constexpr int PER = CAP / 64;
-    R.len = len;
-    const int q0 = __popcll(__ballot(lane < nb.np && nb.off <= c0)) - 1;
-#pragma unroll
-    for (int r = 0; r < PER; ++r) mk[lane + 64 * r] = 0;
-    wave_sync_lds();
-    const int s = nb.off - c0;
-    if (lane < nb.np && s > 0 && s < len) mk[s] = 1;
-    wave_sync_lds();
-    int q = q0;
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        const int t = lane + 64 * r;
-        const bool start = mk[t] != 0;
-        const uint64_t m = __ballot(start);
-        const int qt = t < len ? q + lanes_below(m) + (start ? 1 : 0) : q0;
-        q += __popcll(m);
-        const int kg = c0 + (t < len ? t : 0);
-        const int src = __shfl(nb.bs, qt, 64) + (kg - __shfl(nb.off, qt, 64));
-        R.s[r][0] = __shfl(nb.sx, qt, 64);
-        R.s[r][1] = __shfl(nb.sy, qt, 64);
-        R.s[r][2] = __shfl(nb.sz, qt, 64);
-#pragma unroll
-        for (int f = 0; f < NF; ++f) R.v[r][f] = jd[(int64_t)STRIDE * src + f];
-    }
-}
-
-// True on every lane when a candidate of the fetched chunk has a mass other
-// than m.
-template <int NF, int CAP>
-__device__ __forceinline__ bool chunk_mass_differs(const ChunkRegs<NF, CAP>& R, float m)
-{
-    const int lane = threadIdx.x & 63;
-    bool d = false;
-#pragma unroll
-    for (int r = 0; r < CAP / 64; ++r) d |= (lane + 64 * r < R.len) && (R.v[r][0].w != m);
-    return __any(d);
-}
-
-// Store a fetched one-float4 chunk into the tile (shifted into the cell
-// frame), its unused slots [len, CAP) filled with a position far outside any
-// search radius: a loop over the chunk may then run to a multiple of its
-// stride without a bounds test.
-template <int CAP>
-__device__ __forceinline__ void commit_chunk_padded(float4* sj, const ChunkRegs<1, CAP>& R)
-{
-    const int lane = threadIdx.x & 63;
-    constexpr int PER = CAP / 64;
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        const int t = lane + 64 * r;
-        float4 a = make_float4(1.0e18f, 1.0e18f, 1.0e18f, 0.0f);
-        if (t < R.len) {
-            a = R.v[r][0];
-            a.x += R.s[r][0];
-            a.y += R.s[r][1];
-            a.z += R.s[r][2];
-        }
-        sj[t] = a;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-
 // Culling of staged candidates. A candidate farther from a box than every
 // search radius of the particles inside it (and, for the force, than its own
 // h) pairs with none of them: the 3x3x3 block of cells is a cube, the region
-// within reach of a cell a rounded box about a quarter smaller, and that of
-// a pass's particles smaller still. The force tests its candidates against
-// the box of each pass; the density only on non-uniform cells, against the
-// box of the cell's particles (on a uniform grid the compaction costs more
-// than the tests it saves); the re-scanning kernel against the box of each
-// group of particles. An axis-aligned box in the cell frame: the cell's own
-// box (centre 0, half width hw in every axis, widened by the drift bound) or
-// the bounding box of a set of particles.
+// within reach of a cell a rounded box about a quarter smaller, and that of an
+// item's particles smaller still. An axis-aligned box in the item's frame.
 struct CullBox {
     float cx, cy, cz, hx, hy, hz;
 };
-
-__device__ __forceinline__ CullBox cell_box(float hw)
-{
-    CullBox b;
-    b.cx = b.cy = b.cz = 0.0f;
-    b.hx = b.hy = b.hz = hw;
-    return b;
-}
 
 // A value every active lane holds alike, moved to a scalar register: it then
 // costs no vector register while it stays live across a loop.
@@ -433,22 +163,18 @@ __device__ __forceinline__ float uniform_f(float v)
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
-// Lane 0's double (the first active lane's), in scalar registers.
-__device__ __forceinline__ double lane0_d(double v)
-{
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(b & 0xffffffffull));
-    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(b >> 32));
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
 __device__ __forceinline__ float wave_min(float v)
 {
     for (int o = 32; o >= 1; o >>= 1) v = fminf(v, __shfl_xor(v, o, 64));
     return v;
 }
 
-__device__ __forceinline__ float wave_max(float v);
+// Largest v over the wavefront (every lane active).
+__device__ __forceinline__ float wave_max(float v)
+{
+    for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+    return v;
+}
 
 // Bounding box of the positions of the lanes with `in` set (every lane must
 // take part). The half widths are rounded up by a relative 1e-6 of the
@@ -477,204 +203,375 @@ __device__ __forceinline__ float box_dist2(float x, float y, float z, const Cull
     return fmaf(gx, gx, fmaf(gy, gy, gz * gz));
 }
 
-__device__ __forceinline__ float box_dist2(float x, float y, float z, float hw)
-{
-    const float gx = fmaxf(fabsf(x) - hw, 0.0f), gy = fmaxf(fabsf(y) - hw, 0.0f), gz = fmaxf(fabsf(z) - hw, 0.0f);
-    return fmaf(gx, gx, fmaf(gy, gy, gz * gz));
-}
-
-// Margins of the cell-box test: FP32 positions in the cell frame carry
-// relative errors near 1e-7, so the box grows by 1e-6 of its half width and
-// the radii by 1e-5 (a candidate near the reach is kept, never dropped).
-__device__ __forceinline__ float cull_half_width(float hw) { return hw * 1.000001f; }
+// Margin of the box test: FP32 positions in the item's frame carry relative
+// errors near 1e-7, so the radii grow by 1e-5 (a candidate near the reach is
+// kept, never dropped).
 __device__ __forceinline__ float cull_reach2(float reach) { return (reach * 1.00001f) * (reach * 1.00001f); }
 
-// Store a fetched chunk (NF float4 per candidate, slot 0 = x, y, z, h^2) with
-// the cell-box test: a candidate is kept when the box lies within
-// max(reach, h_j) of it (OWN_H false: within reach). Returns how many were
-// kept (packed from slot 0).
-template <int NF, int CAP, bool OWN_H = true>
-__device__ __forceinline__ int commit_chunk_culled(float4* sj, const ChunkRegs<NF, CAP>& R, const CullBox& box,
-                                                   float reach2)
+// ---- the matrix-core pair filter of the density and force loops ------------------------
+//
+// A work item has at most 16 particles, and its candidates wait in an LDS
+// tile. Which candidate lies within which particle's radius is a table of
+// |x_i|^2 + |x_j|^2 - 2 x_i . x_j, a product of inner size four: the 16 blocks
+// of one v_mfma_f32_4x4x4_16b_f16 hold it for 16 particles x 16 candidates
+// (8 cycles for 256 pairs, where the difference form takes 6 vector
+// operations per pair and lane, 64 cycles). With C = |x_i|^2 - R_i^2 the sign
+// bit of a result is the test, and one v_alignbit per pair gathers the signs of
+// a lane's candidates into a word.
+//
+// Half precision only proposes pairs: the loops recompute every proposed pair
+// from the FP32 differences. Coordinates are taken from the centre of the
+// item's box and scaled so that its half width and reach together make
+// FILTER_SCALE. Rounded toward zero they are off by at most u = 2^-10 of
+// themselves, so 2 x_i . x_j is off by at most (2 u + u^2) (|x_i|^2 + |x_j|^2);
+// the squares are lowered by FILTER_EPS (a little more than that), the radii
+// raised by it and by FILTER_ABS (inputs below the normal range of half
+// precision), so no pair inside its radius is missed. On a cell one search
+// radius wide about 1.5% of the proposed pairs are outside.
+//
+// Lane l is column l % 16 (a particle); of each 16 candidates its results are
+// rows 4 (l / 16) ... + 3 of the table, which the inputs make candidates 4 r +
+// l / 16, r = 0 ... 3: lane group g meets candidates g, g + 4, g + 8, ... of
+// the tile, in order, so neighbours in the candidate list go to different
+// groups (even word counts). Lane l feeds candidate 4 (l % 4) + l / 16.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef __fp16 f16x2_ __attribute__((ext_vector_type(2)));
+
+constexpr float FILTER_SCALE = 32.0f;
+constexpr float FILTER_EPS = 2.1e-3f;   // > 2^-9 + 2^-20
+constexpr float FILTER_ABS = 0.02f;     // scaled units: 2e-5 of the frame's square
+constexpr float FILTER_FAR = 60000.0f;  // |x_j|^2 of an unused slot; also the most a slot may hold
+
+__device__ __forceinline__ uint32_t pack_f16(float a, float b)
+{
+    const f16x2_ v = __builtin_amdgcn_cvt_pkrtz(a, b);
+    uint32_t r;
+    __builtin_memcpy(&r, &v, 4);
+    return r;
+}
+
+__device__ __forceinline__ f16x4 f16x4_of(uint32_t lo, uint32_t hi)
+{
+    const uint2 v = make_uint2(lo, hi);
+    f16x4 r;
+    __builtin_memcpy(&r, &v, 8);
+    return r;
+}
+
+// The filter's particle input (every k of the column): -2 x_i, 1.
+__device__ __forceinline__ f16x4 filter_column(float ax, float ay, float az)
+{
+    return f16x4_of(pack_f16(-2.0f * ax, -2.0f * ay), pack_f16(-2.0f * az, 1.0f));
+}
+
+// Tests of word k (of 32) of a lane's hit words for nk staged candidates: 16
+// or 32 (the tile is padded to a multiple of 64). Test t of the word is bit
+// n - 1 - t and candidate 128 k + 4 t + l / 16.
+__device__ __forceinline__ int word_tests(int nk, int k) { return min(32, (nk - 128 * k + 63) / 64 * 16); }
+
+// The bits of word k that belong to the 64 candidates `part` of the tile.
+__device__ __forceinline__ unsigned hit_part(unsigned word, int nk, int k, int part)
+{
+    if (k != part >> 1) return 0u;
+    return word & (word_tests(nk, k) - 16 * (part & 1) == 32 ? 0xffff0000u : 0x0000ffffu);
+}
+
+// Exclusive prefix sum over the wavefront, with the total on every lane, by
+// DPP (no LDS): sums within rows of 16, then the row totals broadcast on.
+__device__ __forceinline__ int wave_excl_scan(int x, int& total)
+{
+    int v = x;
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false); // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false); // row_bcast:31 into rows 2 and 3
+    total = __builtin_amdgcn_readlane(v, 63);
+    return v - x;
+}
+
+// ---- work items: their particles, frames and candidates ----------------------------------
+//
+// Two layouts. A grid layout (UNI: no top cell split, see the cell build)
+// keeps the particles of every column of top cells in order of z, so an item is
+// 16 consecutive particles of one column whatever cells they are in, and its
+// candidates are at most 18 runs of consecutive particles: the z range within
+// reach of the item's own, in its column and the eight around it, and what
+// wraps around the box. Positions are 32-bit fractions of the box, whose
+// differences are exact and periodic, so there are no frames to shift between.
+// A tree layout's items are runs of one leaf's particles, its candidates the
+// leaf's records (neighbour leaf and frame shift), its positions FP32 offsets
+// from their leaf's centre.
+struct CellArgs {
+    const int4* cells;       // per slot, tree: first particle, count, first record, records. Grid, two per slot:
+                             // first particle, count | G << 8, x | y << 16 of the column, first | last << 16 of
+                             // its fine cells in z; first fine cell of the box, the box's unit of length
+                             // (two floats, high and low part), -
+    const float4* pbox;      // per slot, 2: centre of the box around its particles (grid: 32-bit fractions) and
+                             // largest search radius; half widths, -
+    const int2* p_rec;       // tree: per record, first particle and count of the neighbour
+    const float4* p_shift;   // tree: its frame shift
+    const int* starts;       // grid: first particle of each fine cell
+    int fzb;                 // grid: fine cells in z per top cell, logarithm
+};
+
+inline CellArgs cell_args(sph_ctx* c, const int4* cells)
+{
+    CellArgs g;
+    g.cells = cells;
+    g.pbox = static_cast<float4*>(c->cell_pbox.p);
+    g.p_rec = static_cast<int2*>(c->p_rec.p);
+    g.p_shift = static_cast<float4*>(c->p_shift.p);
+    g.starts = static_cast<int*>(c->starts.p);
+    g.fzb = c->fzb;
+    return g;
+}
+
+template <bool UNI>
+struct Item {
+    int i0, ni;              // particles
+    int ox, oy, oz;          // grid: the frame's origin, the box centre
+    float sh, sl;            // grid: unit of length
+    float bx, by, bz;        // box centre in the frame (grid: 0)
+    float hx, hy, hz, H;     // half widths; largest search radius
+};
+
+// x of a particle in the item's frame from its stored coordinate.
+template <bool UNI>
+__device__ __forceinline__ float item_coord(float v, int o, float sh, float sl, float shift)
+{
+    if constexpr (UNI) {
+        const float d = (float)(int)((unsigned)__float_as_int(v) - (unsigned)o);
+        return fmaf(d, sh, d * sl);
+    } else {
+        return v + shift;
+    }
+}
+
+// The candidates of an item, walked in order: its records (tree) or runs
+// (grid), 64 at a time in the lanes, 64 candidates per step. The lanes' records
+// also wait in an LDS table (first particle minus offset, and the shift), where
+// each candidate slot reads its own; the record of a slot is found from marks
+// at the first slots of the records, made for 256 slots at a time.
+template <bool UNI>
+struct CandWalk {
+    int pb0, np;            // tree: first record, records
+    int b0;                 // tree: first record of the block in the lanes
+    int nj;                 // candidates of the block
+    int c;                  // next candidate of the block
+    int q;                  // record holding the last slot before the marks' next 64
+    int cnt, off;           // this lane's record: candidates, and those of the block before it
+    int first;              // its first particle
+    float sx, sy, sz;       // tree: its shift
+    // tree: the item's box and its reach, for the records (a leaf of which no
+    // particle can be within reach is left out), widened by the drift
+    float bx, by, bz, hx, hy, hz, reach;
+};
+
+constexpr int WALK_MARKS = 256;
+template <bool UNI>
+constexpr int WALK_LDS = 64 * (UNI ? 4 : 16) + WALK_MARKS;  // table and marks
+
+__device__ __forceinline__ void walk_load(CandWalk<false>& w, const CellArgs& G)
 {
     const int lane = threadIdx.x & 63;
-    constexpr int PER = CAP / 64;
-    int n = 0;
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        const int t = lane + 64 * r;
-        float4 a = R.v[r][0];
-        a.x += R.s[r][0];
-        a.y += R.s[r][1];
-        a.z += R.s[r][2];
-        const bool keep = t < R.len && box_dist2(a.x, a.y, a.z, box) < (OWN_H ? fmaxf(reach2, a.w * 1.00002f) : reach2);
-        const uint64_t m = __ballot(keep);
-        if (keep) {
-            const int d = n + lanes_below(m);
-            sj[d] = a;
-#pragma unroll
-            for (int f = 1; f < NF; ++f) sj[f * CAP + d] = R.v[r][f];
-        }
-        n += __popcll(m);
+    int2 rec = make_int2(0, 0);
+    float4 sh = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (w.b0 + lane < w.np) {
+        rec = G.p_rec[w.pb0 + w.b0 + lane];
+        sh = G.p_shift[w.pb0 + w.b0 + lane];
+        const float gx = fmaxf(fabsf(sh.x - w.bx) - w.hx - sh.w, 0.0f),
+                    gy = fmaxf(fabsf(sh.y - w.by) - w.hy - sh.w, 0.0f),
+                    gz = fmaxf(fabsf(sh.z - w.bz) - w.hz - sh.w, 0.0f);
+        if (!(fmaf(gx, gx, fmaf(gy, gy, gz * gz)) < w.reach * w.reach)) rec.y = 0;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    return n;
+    w.cnt = rec.y;
+    w.first = rec.x;
+    w.off = wave_excl_scan(rec.y, w.nj);
+    w.sx = sh.x;
+    w.sy = sh.y;
+    w.sz = sh.z;
+    w.c = 0;
 }
 
-// Store a fetched one-float4 chunk (x, y, z, m; shifted into the cell frame)
-// keeping only the candidates within reach of the cell's box (box_dist2 <
-// reach2), packed from slot 0, and fill the rest of the CAP slots with a far
-// position, so a loop may run to a multiple of its stride without a bounds
-// test. Returns how many were kept. A candidate farther from the box than
-// every search radius of the cell pairs with none of its particles.
-template <int CAP>
-__device__ __forceinline__ int commit_chunk_culled_padded(float4* sj, const ChunkRegs<1, CAP>& R, const CullBox& box,
-                                                          float reach2)
+// Order of the nine columns: centre and corners, then edges, so a chunk of the
+// list samples the whole neighbourhood (even lists).
+__constant__ signed char COL9[9][2] = {{0, 0}, {-1, -1}, {1, 1}, {-1, 0}, {0, 1}, {1, -1}, {-1, 1}, {1, 0}, {0, -1}};
+
+template <bool UNI>
+__device__ __forceinline__ void item_load(Item<UNI>& it, CandWalk<UNI>& w, const CellArgs& G, int slot,
+                                          float delta, float reach)
+{
+    const float4 b0 = G.pbox[2 * (int64_t)slot], b1 = G.pbox[2 * (int64_t)slot + 1];
+    it.hx = uniform_f(b1.x);
+    it.hy = uniform_f(b1.y);
+    it.hz = uniform_f(b1.z);
+    it.H = uniform_f(b0.w);
+    if constexpr (UNI) {
+        const int4 c0 = G.cells[2 * (int64_t)slot], c1 = G.cells[2 * (int64_t)slot + 1];
+        it.i0 = __builtin_amdgcn_readfirstlane(c0.x);
+        it.ni = __builtin_amdgcn_readfirstlane(c0.y & 0xff);
+        it.ox = __builtin_amdgcn_readfirstlane(__float_as_int(b0.x));
+        it.oy = __builtin_amdgcn_readfirstlane(__float_as_int(b0.y));
+        it.oz = __builtin_amdgcn_readfirstlane(__float_as_int(b0.z));
+        it.sh = uniform_f(__int_as_float(c1.y));
+        it.sl = uniform_f(__int_as_float(c1.z));
+        it.bx = it.by = it.bz = 0.0f;
+        // lane q < 9: the run of column q inside the box; q + 9: what wraps around it
+        const int lane = threadIdx.x & 63;
+        const int g = c0.y >> 8, gz = g << G.fzb, reach = 1 << G.fzb;
+        const bool wrap = lane >= 9;
+        const int q = lane < 9 ? lane : lane < 18 ? lane - 9 : 0;
+        int x = (c0.z & 0xffff) + COL9[q][0], y = (c0.z >> 16) + COL9[q][1];
+        x += x < 0 ? g : x >= g ? -g : 0;
+        y += y < 0 ? g : y >= g ? -g : 0;
+        const int lo = (c0.w & 0xffff) - reach, hi = (c0.w >> 16) + reach;
+        int a, b;  // fine cells [a, b)
+        if (!wrap) {
+            a = max(lo, 0);
+            b = min(hi + 1, gz);
+        } else {
+            a = lo < 0 ? lo + gz : 0;
+            b = lo < 0 ? gz : max(hi + 1 - gz, 0);
+        }
+        w.cnt = 0;
+        w.first = 0;
+        if (lane < 18 && a < b) {
+            const int64_t col = (int64_t)c1.x + (int64_t)(x * g + y) * gz;
+            w.first = G.starts[col + a];
+            w.cnt = G.starts[col + b] - w.first;
+        }
+        w.off = wave_excl_scan(w.cnt, w.nj);
+        w.c = 0;
+        w.np = 18;
+        w.b0 = 0;
+    } else {
+        const int4 c0 = G.cells[slot];
+        it.i0 = __builtin_amdgcn_readfirstlane(c0.x);
+        it.ni = __builtin_amdgcn_readfirstlane(c0.y);
+        it.ox = it.oy = it.oz = 0;
+        it.sh = it.sl = 0.0f;
+        it.bx = uniform_f(b0.x);
+        it.by = uniform_f(b0.y);
+        it.bz = uniform_f(b0.z);
+        w.pb0 = __builtin_amdgcn_readfirstlane(c0.z);
+        w.np = __builtin_amdgcn_readfirstlane(c0.w);
+        w.b0 = 0;
+        const float d = 1.0e-5f * it.H + delta;
+        w.bx = it.bx;
+        w.by = it.by;
+        w.bz = it.bz;
+        w.hx = it.hx + d;
+        w.hy = it.hy + d;
+        w.hz = it.hz + d;
+        w.reach = reach > 0.0f ? reach : it.H;
+        walk_load(w, G);
+    }
+}
+
+// The block's table and the marks of the 256 slots from w.c - w.c % 256 on, into
+// LDS (again after anything else used it). Records with no candidate are left
+// out of both.
+template <bool UNI>
+__device__ __forceinline__ void walk_table(CandWalk<UNI>& w, char* lds)
 {
     const int lane = threadIdx.x & 63;
-    constexpr int PER = CAP / 64;
-    int n = 0;
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        const int t = lane + 64 * r;
-        float4 a = R.v[r][0];
-        a.x += R.s[r][0];
-        a.y += R.s[r][1];
-        a.z += R.s[r][2];
-        const bool keep = t < R.len && box_dist2(a.x, a.y, a.z, box) < reach2;
-        const uint64_t m = __ballot(keep);
-        if (keep) sj[n + lanes_below(m)] = a;
-        n += __popcll(m);
+    uint8_t* mk = reinterpret_cast<uint8_t*>(lds + 64 * (UNI ? 4 : 16));
+    const bool rec = w.cnt > 0;
+    const int row = lanes_below(__ballot(rec));
+    wave_sync_lds();
+    reinterpret_cast<uint32_t*>(mk)[lane] = 0;
+    if (rec) {
+        if constexpr (UNI)
+            reinterpret_cast<int*>(lds)[row] = w.first - w.off;
+        else
+            reinterpret_cast<float4*>(lds)[row] = make_float4(w.sx, w.sy, w.sz, __int_as_float(w.first - w.off));
     }
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        const int t = lane + 64 * r;
-        if (t >= n) sj[t] = make_float4(1.0e18f, 1.0e18f, 1.0e18f, 0.0f);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    return n;
+    wave_sync_lds();
+    const int s = w.off - (w.c & ~(WALK_MARKS - 1));
+    if (rec && s >= 0 && s < WALK_MARKS) mk[s] = 1;
+    w.q = __popcll(__ballot(rec && w.off < w.c)) - 1;
+    wave_sync_lds();
 }
 
-// Largest v over the wavefront (every lane active).
-__device__ __forceinline__ float wave_max(float v)
+// Back to the first candidate.
+template <bool UNI>
+__device__ __forceinline__ void walk_start(CandWalk<UNI>& w, const CellArgs& G, char* lds)
 {
-    for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+    if constexpr (!UNI) {
+        if (w.b0 != 0) {
+            w.b0 = 0;
+            walk_load(w, G);
+        }
+    }
+    w.c = 0;
+    walk_table(w, lds);
 }
 
-// Stage candidates [c0, c0 + len) (len <= CAP) into the tile: every lane finds
-// the neighbour cell of each of its candidates by a binary search over the
-// lane-held prefix offsets, so all global loads of the chunk are independent
-// and issue back to back.
-template <int NF, int CAP>
-__device__ __forceinline__ void stage_fast(float4* sj, const float4* __restrict__ jd, const NbrLanes& nb, int c0,
-                                           int len)
+// The next 64 U candidates (U 1, 2 or 4), U slots per lane: false when none is
+// left. ok: there is one; src: its particle (a valid index in any case); sh: its
+// shift into the item's frame (tree).
+template <int U>
+struct Slots {
+    bool ok[U];
+    int src[U];
+    float3 sh[U];
+};
+
+template <int U, bool UNI>
+__device__ __forceinline__ bool walk_next(CandWalk<UNI>& w, const CellArgs& G, char* lds, Slots<U>& S)
+{
+    static_assert(WALK_MARKS % (64 * U) == 0, "a step stays inside one set of marks");
+    const int lane = threadIdx.x & 63;
+    if (w.c >= w.nj) {
+        if constexpr (UNI) {
+            return false;
+        } else {
+            do {
+                if (w.b0 + 64 >= w.np) return false;
+                w.b0 += 64;
+                walk_load(w, G);
+            } while (w.nj == 0);
+            walk_table(w, lds);
+        }
+    } else if ((w.c & (WALK_MARKS - 1)) == 0 && w.c > 0) {
+        walk_table(w, lds);
+    }
+    const uint8_t* mk = reinterpret_cast<const uint8_t*>(lds + 64 * (UNI ? 4 : 16)) + (w.c & (WALK_MARKS - 1));
+    bool start[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) start[u] = mk[64 * u + lane] != 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint64_t m = __ballot(start[u]);
+        const int row = w.q + lanes_below(m) + (start[u] ? 1 : 0);
+        w.q += __popcll(m);
+        const int c = w.c + 64 * u + lane;
+        S.ok[u] = c < w.nj;
+        const int t = min(c, w.nj - 1);
+        if constexpr (UNI) {
+            S.src[u] = reinterpret_cast<const int*>(lds)[row] + t;
+            S.sh[u] = make_float3(0.f, 0.f, 0.f);
+        } else {
+            const float4 r = reinterpret_cast<const float4*>(lds)[row];
+            S.src[u] = __float_as_int(r.w) + t;
+            S.sh[u] = make_float3(r.x, r.y, r.z);
+        }
+    }
+    w.c += 64 * U;
+    return true;
+}
+
+// The sum over the four lanes of a column (lanes l, l ^ 16, l ^ 32, l ^ 48) and
+// the share of the lower groups, for counts.
+__device__ __forceinline__ int column_excl_scan(int n, int& total)
 {
     const int lane = threadIdx.x & 63;
-    constexpr int PER = CAP / 64;
-    int src[PER];
-    float s3[PER][3];
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        const int t = lane + 64 * r;
-        const int kg = c0 + (t < len ? t : 0);
-        int q = 0;
-#pragma unroll
-        for (int step = 32; step >= 1; step >>= 1) {
-            const int cand = q + step;
-            const int v = __shfl(nb.off, cand < nb.np ? cand : nb.np - 1, 64);
-            if (cand < nb.np && v <= kg) q = cand;
-        }
-        src[r] = __shfl(nb.bs, q, 64) + (kg - __shfl(nb.off, q, 64));
-        s3[r][0] = __shfl(nb.sx, q, 64);
-        s3[r][1] = __shfl(nb.sy, q, 64);
-        s3[r][2] = __shfl(nb.sz, q, 64);
-    }
-    float4 v[PER][NF];
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        if (lane + 64 * r < len) {
-#pragma unroll
-            for (int f = 0; f < NF; ++f) v[r][f] = jd[(int64_t)NF * src[r] + f];
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        const int t = lane + 64 * r;
-        if (t < len) {
-            float4 a = v[r][0];
-            a.x += s3[r][0];
-            a.y += s3[r][1];
-            a.z += s3[r][2];
-            sj[t] = a;
-#pragma unroll
-            for (int f = 1; f < NF; ++f) sj[f * CAP + t] = v[r][f];
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const int n1 = __shfl_xor(n, 16, 64);
+    const int p = n + n1;
+    const int p2 = __shfl_xor(p, 32, 64);
+    total = p + p2;
+    return ((lane & 16) ? n1 : 0) + ((lane & 32) ? p2 : 0);
 }
-
-// stage_fast keeping only the candidates within reach of `box` (distance to
-// it below sqrt(reach2)), packed from slot 0 in candidate order; returns how
-// many it kept.
-template <int NF, int CAP>
-__device__ __forceinline__ int stage_fast_culled(float4* sj, const float4* __restrict__ jd, const NbrLanes& nb,
-                                                 int c0, int len, const CullBox& box, float reach2)
-{
-    const int lane = threadIdx.x & 63;
-    constexpr int PER = CAP / 64;
-    int src[PER];
-    float s3[PER][3];
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        const int t = lane + 64 * r;
-        const int kg = c0 + (t < len ? t : 0);
-        int q = 0;
-#pragma unroll
-        for (int step = 32; step >= 1; step >>= 1) {
-            const int cand = q + step;
-            const int v = __shfl(nb.off, cand < nb.np ? cand : nb.np - 1, 64);
-            if (cand < nb.np && v <= kg) q = cand;
-        }
-        src[r] = __shfl(nb.bs, q, 64) + (kg - __shfl(nb.off, q, 64));
-        s3[r][0] = __shfl(nb.sx, q, 64);
-        s3[r][1] = __shfl(nb.sy, q, 64);
-        s3[r][2] = __shfl(nb.sz, q, 64);
-    }
-    float4 v[PER][NF];
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        if (lane + 64 * r < len) {
-#pragma unroll
-            for (int f = 0; f < NF; ++f) v[r][f] = jd[(int64_t)NF * src[r] + f];
-        }
-    }
-    int n = 0;
-#pragma unroll
-    for (int r = 0; r < PER; ++r) {
-        float4 a = v[r][0];
-        a.x += s3[r][0];
-        a.y += s3[r][1];
-        a.z += s3[r][2];
-        const bool keep = lane + 64 * r < len && box_dist2(a.x, a.y, a.z, box) < reach2;
-        const uint64_t m = __ballot(keep);
-        if (keep) {
-            const int d = n + lanes_below(m);
-            sj[d] = a;
-#pragma unroll
-            for (int f = 1; f < NF; ++f) sj[f * CAP + d] = v[r][f];
-        }
-        n += __popcll(m);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    return n;
-}
-
