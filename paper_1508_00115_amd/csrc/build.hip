@@ -17,6 +17,7 @@
 // kernels per tree level, and a stack-based walk per (leaf, surrounding top
 // cell). The host only reads back counts to size buffers.
 #include "common.h"
+#include "tiles.h"
 
 #include <algorithm>
 #include <cmath>
@@ -548,53 +549,6 @@ __global__ void k_box_item(int n_boxes, int64_t n, int64_t nl, const int64_t* __
     box_item[b] = (int)it_start[p < n ? leaf_of[p] : nl];
 }
 
-// Particles of each leaf of 2 to 64 particles in decreasing order of search
-// radius (ties by input index), one wavefront per leaf, a bitonic network
-// over the 64 lanes; a leaf whose radii are all equal is left as it is. The hot kernels take a leaf's particles a pass at a
-// time and cull the staged candidates to the pass's largest radius, which
-// this order makes as small as it can be for every pass but the first.
-// Only the order inside each leaf changes: leaves, nodes and lists stay.
-__global__ void __launch_bounds__(256) k_leaf_sort_h(int64_t nl, const int* __restrict__ lf_start,
-                                                     const int* __restrict__ lf_count, uint32_t* __restrict__ perm,
-                                                     float* __restrict__ Hs)
-{
-    const int64_t leaf = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63;
-    if (leaf >= nl) return;  // whole wavefronts
-    const int n = lf_count[leaf];
-    if (n < 2 || n > 64) return;
-    const int p0 = lf_start[leaf];
-    // key: H descending, then index ascending; empty lanes last
-    float k = lane < n ? Hs[p0 + lane] : -INFINITY;
-    // a leaf whose radii are all equal keeps its order (every pass has the
-    // same reach), without the network
-    float lo = lane < n ? k : INFINITY, hi = k;
-    for (int o = 32; o >= 1; o >>= 1) {
-        lo = fminf(lo, __shfl_xor(lo, o, 64));
-        hi = fmaxf(hi, __shfl_xor(hi, o, 64));
-    }
-    if (lo == hi) return;  // whole wavefront
-    uint32_t v = lane < n ? perm[p0 + lane] : 0xffffffffu;
-    for (int size = 2; size <= 64; size <<= 1) {
-        for (int stride = size >> 1; stride >= 1; stride >>= 1) {
-            const float ko = __shfl_xor(k, stride, 64);
-            const uint32_t vo = (uint32_t)__shfl_xor((int)v, stride, 64);
-            const bool before = (ko > k) || (ko == k && vo < v);  // the partner sorts first
-            const bool lower = (lane & stride) == 0;              // this lane keeps the first of the pair
-            const bool desc_block = (lane & size) == 0;           // blocks alternate in bitonic order
-            const bool take = (lower == desc_block) ? before : !before;
-            if (take) {
-                k = ko;
-                v = vo;
-            }
-        }
-    }
-    if (lane < n) {
-        Hs[p0 + lane] = k;
-        perm[p0 + lane] = v;
-    }
-}
-
 __global__ void k_leaf_fix(int64_t nl, const int* __restrict__ lf_node, const int* __restrict__ nd_count,
                            const unsigned* __restrict__ nd_hmax, int* __restrict__ nd_leaf,
                            int* __restrict__ lf_count, float* __restrict__ lf_hmax)
@@ -644,6 +598,7 @@ struct RecordOut {
     int2* p_rec;
     const int* lf_start;
     const int* lf_count;
+    const uint32_t* it_start;  // null: no items
 };
 
 // Depth-first walk below top cell T (seen through the periodic image shift S)
@@ -692,7 +647,7 @@ __device__ __forceinline__ void walk_top(int T, const double S[3], int code, con
                 ro.p_leaf[o] = lf;
                 ro.p_rec[o] = make_int2(ro.lf_start[lf], cnt);
                 ro.p_shift[o] = make_float4((float)(cX[0] + S[0] - cA[0]), (float)(cX[1] + S[1] - cA[1]),
-                                            (float)(cX[2] + S[2] - cA[2]), (float)(0.5 * wX));
+                                            (float)(cX[2] + S[2] - cA[2]), __int_as_float(ro.it_start ? (int)ro.it_start[lf] : 0));
                 ro.p_code[o] = code;
             }
             nd += dens ? 1u : 0u;
@@ -761,14 +716,9 @@ __device__ __forceinline__ void block_counters(const int64_t (&v)[NV], int64_t (
 // ITEM_N, one wavefront each. A wavefront takes ITEM_N particles at a time
 // (four lanes per particle), so a leaf of more would be a serial loop: as
 // separate items its runs go to several wavefronts (a box of 16^3 particles
-// has 125 leaves of 27 to 64 particles for 1024 SIMDs). The nt items of a leaf of ni particles hold
-// ni / nt each, the first ni % nt one more: (offset, count) of item t.
+// has 125 leaves of 27 to 64 particles for 1024 SIMDs). item_range (tiles.h)
+// says which particles an item holds.
 constexpr int ITEM_N = 16;
-__device__ __forceinline__ int2 item_range(int ni, int nt, int t)
-{
-    const int q = ni / nt, r = ni % nt;
-    return make_int2(t * q + min(t, r), q + (t < r ? 1 : 0));
-}
 
 __global__ void k_item_count(int64_t nl, const int* __restrict__ lf_count, uint32_t* __restrict__ it_cnt)
 {
@@ -901,13 +851,14 @@ __global__ void k_sched_fill(int64_t n_items, const uint32_t* __restrict__ by_co
 }
 
 // Bounding box of each item's particles at their current offsets (sixteen
-// lanes per schedule slot), for the culling of staged candidates: centre and
-// the item's largest search radius, then the half widths, rounded up by a
+// lanes per schedule slot), for the culling of candidates, by slot and by item:
+// centre and the item's largest search radius, then the half widths, rounded up by a
 // relative 1e-6 of the coordinates so that the FP32 centre and widths still
 // contain every particle.
 __global__ void __launch_bounds__(256) k_cell_pbox(int64_t n_items, const int4* __restrict__ cells,
+                                                   const int* __restrict__ cell_item,
                                                    const float4* __restrict__ xrel, const float* __restrict__ Hs,
-                                                   float4* __restrict__ pbox)
+                                                   float4* __restrict__ pbox, float4* __restrict__ ibox)
 {
     // every lane takes part in the shuffles, a group past the last item with no data
     const int64_t slot = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
@@ -933,10 +884,15 @@ __global__ void __launch_bounds__(256) k_cell_pbox(int64_t n_items, const int4* 
         H = fmaxf(H, __shfl_xor(H, o, 64));
     }
     if (live && sub == 0) {
-        pbox[2 * slot] = make_float4(0.5f * (lx + hx), 0.5f * (ly + hy), 0.5f * (lz + hz), H);
-        pbox[2 * slot + 1] = make_float4(0.5f * (hx - lx) * 1.000001f + 1.0e-6f * fmaxf(fabsf(lx), fabsf(hx)),
-                                         0.5f * (hy - ly) * 1.000001f + 1.0e-6f * fmaxf(fabsf(ly), fabsf(hy)),
-                                         0.5f * (hz - lz) * 1.000001f + 1.0e-6f * fmaxf(fabsf(lz), fabsf(hz)), 0.0f);
+        const float4 c = make_float4(0.5f * (lx + hx), 0.5f * (ly + hy), 0.5f * (lz + hz), H);
+        const float4 h = make_float4(0.5f * (hx - lx) * 1.000001f + 1.0e-6f * fmaxf(fabsf(lx), fabsf(hx)),
+                                     0.5f * (hy - ly) * 1.000001f + 1.0e-6f * fmaxf(fabsf(ly), fabsf(hy)),
+                                     0.5f * (hz - lz) * 1.000001f + 1.0e-6f * fmaxf(fabsf(lz), fabsf(hz)), 0.0f);
+        const int64_t it = cell_item[slot];
+        pbox[2 * slot] = c;
+        pbox[2 * slot + 1] = h;
+        ibox[2 * it] = c;
+        ibox[2 * it + 1] = h;
     }
 }
 
@@ -1061,7 +1017,8 @@ static void fill_lists(sph_ctx* c, const uint32_t* it_start, int64_t n_items, in
         static_cast<int*>(c->top.p), static_cast<int64_t*>(c->box_top_base.p), static_cast<int*>(c->box_G.p),
         static_cast<double*>(c->box_len.p), static_cast<uint32_t*>(c->p_cnt.p), static_cast<uint32_t*>(c->p_cntd.p),
         static_cast<uint32_t*>(c->p_start.p),
-        RecordOut{p_leaf, p_shift, p_code, p_rec, static_cast<int*>(c->lf_start.p), static_cast<int*>(c->lf_count.p)},
+        RecordOut{p_leaf, p_shift, p_code, p_rec, static_cast<int*>(c->lf_start.p), static_cast<int*>(c->lf_count.p),
+                  it_start},
         it_start, n_items, it_leaf, sk, sv, xcd_local, static_cast<int64_t*>(c->counters.p));
     SPH_HIP(hipGetLastError());
     c->lists_built = true;
@@ -1333,10 +1290,6 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
                                                  static_cast<unsigned*>(c->nd_hmax.p),
                                                  static_cast<int*>(c->nd_leaf.p), lf_count, lf_hmax);
     SPH_HIP(hipGetLastError());
-    if (!c->uni) {  // (a grid's items follow z)
-        k_leaf_sort_h<<<(unsigned)blocks_for(nl * 64, 256), 256, 0, s>>>(nl, lf_start, lf_count, perm, Hs);
-        SPH_HIP(hipGetLastError());
-    }
 
     // ---- partner lists: their number, and in a tree layout the lists and the items ------------
     uint32_t* p_cnt = ensure<uint32_t>(c, c->p_cnt, nl + 1);
@@ -1344,7 +1297,7 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     const TreeView tv = tree_view(c);
     k_partners<<<(unsigned)blocks_for(nl * 32, PBS), PBS, 0, s>>>(
         nl, 0, lf_node, tv, static_cast<int*>(c->nd_box.p), top, box_top_base, box_G, box_len, p_cnt, p_cntd, nullptr,
-        RecordOut{nullptr, nullptr, nullptr, nullptr, lf_start, lf_count}, nullptr, 0, nullptr, nullptr, nullptr, 0,
+        RecordOut{nullptr, nullptr, nullptr, nullptr, lf_start, lf_count, nullptr}, nullptr, 0, nullptr, nullptr, nullptr, 0,
         ctr);
     SPH_HIP(hipGetLastError());
     c->lists_built = false;
@@ -1485,9 +1438,9 @@ void cell_boxes(sph_ctx* c, hipStream_t s)
                                                            static_cast<int4*>(c->xfix.p),
                                                            static_cast<float*>(c->Hs.p), pbox);
     else
-        k_cell_pbox<<<blocks_for(16 * ni, 256), 256, 0, s>>>(ni, static_cast<int4*>(c->cells.p),
-                                                            static_cast<float4*>(c->xrel.p),
-                                                            static_cast<float*>(c->Hs.p), pbox);
+        k_cell_pbox<<<blocks_for(16 * ni, 256), 256, 0, s>>>(
+            ni, static_cast<int4*>(c->cells.p), static_cast<int*>(c->cell_item.p), static_cast<float4*>(c->xrel.p),
+            static_cast<float*>(c->Hs.p), pbox, ensure<float4>(c, c->item_box, 2 * ni));
     SPH_HIP(hipGetLastError());
 }
 

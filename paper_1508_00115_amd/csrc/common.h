@@ -190,7 +190,7 @@ struct sph_ctx {
                              // within its largest search radius (all the density needs)
     sph::Buf p_leaf;         // int
     sph::Buf p_rec;          // int2 per record: first particle and count of the neighbour leaf
-    sph::Buf p_shift;        // float4 (dx, dy, dz, 0): leaf-centre frame offset
+    sph::Buf p_shift;        // float4 (dx, dy, dz, bits): leaf-centre frame offset, first item of the leaf
     sph::Buf p_code;         // int: periodic image code (3 x 2 bits)
     // work items of the hot kernels: runs of at most 16 particles of one leaf
     // (tree), or of one column of top cells (grid)
@@ -205,6 +205,7 @@ struct sph_ctx {
     sph::Buf cell_item;      // int per slot: item
     sph::Buf cell_pbox;      // float4 x 2 per slot: box of the item's particles at their current offsets
                              // (centre, largest search radius; half widths, 0)
+    sph::Buf item_box;       // tree: float4 x 2 per item, as cell_pbox
     sph::Buf cells_d;        // int4 per slot as `cells`, with the density's record count (a prefix)
     sph::Buf sched_key, sched_key_alt, sched_val, sched_val_alt;  // cost sort
     sph::Buf scan_tmp;       // scan workspace

@@ -312,7 +312,7 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
         ++a_cur;
         Item<UNI> it;
         CandWalk<UNI> w;
-        item_load(it, w, A.cell, slot, 0.5f * two_delta, 0.0f);
+        item_load(it, w, A.cell, slot, scratch);
         const int i0 = it.i0, ni = it.ni;
         // this lane's column
         const int ic = i0 + min(pc, ni - 1);
@@ -395,12 +395,12 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                 Slots<U> S;
                 float4 p0[U];
                 auto fetch = [&]() -> bool {
-                    if (!walk_next<U>(w, A.cell, scratch, S)) return false;
+                    if (!walk_next<U>(w, A.cell, it, scratch, S)) return false;
 #pragma unroll
                     for (int u = 0; u < U; ++u) p0[u] = A.jd[S.src[u]];
                     return true;
                 };
-                walk_start(w, A.cell, scratch);
+                walk_start(w, A.cell, it, scratch, reach, false);
                 bool more = fetch();
                 for (;;) {
                     // ---- stage, while the tile has room ------------------------------------------------
@@ -424,8 +424,12 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                             m[u] = __ballot(keep);
                             n += __popcll(m[u]);
                         }
-                        full = nk + n > DCAP;
-                        if (!full) {
+                        // A grid keeps every candidate, so its tile is one step; a tree about a
+                        // third of them, so a step that does not fit is taken again after the tile
+                        // (never one that does not fit an empty tile: boxes 1757 -> 1725 us; in a
+                        // tree whole steps alone fill the tile less: clustered 764 -> 777 us).
+                        full = UNI || nk + n > DCAP;
+                        if (UNI || !full) {
 #pragma unroll
                             for (int u = 0; u < U; ++u) {
                                 differs |= S.ok[u] && p0[u].w != m0;
@@ -736,10 +740,10 @@ __device__ __forceinline__ int rescan_stage(const DensArgs& A, RescanItem<UNI>& 
                                             bool first, bool& more, const CullBox& box, float reach2)
 {
     int nk = 0;
-    if (first) walk_start(I.w, A.cell, scratch);
+    if (first) walk_start(I.w, A.cell, I.it, scratch, I.it.H, false);
     do {
         Slots<1> S;
-        more = walk_next<1>(I.w, A.cell, scratch, S);
+        more = walk_next<1>(I.w, A.cell, I.it, scratch, S);
         if (!more) break;
         float4 a = A.jd[S.src[0]];
         a.x = item_coord<UNI>(a.x, I.it.ox, I.it.sh, I.it.sl, S.sh[0].x);
@@ -851,7 +855,7 @@ __global__ void __launch_bounds__(BS) k_density_scan(DensArgs A)
         const int kc = k / split, part = k - kc * split;
         const int slot = A.scan_cells[kc];
         RescanItem<UNI> I;
-        item_load(I.it, I.w, A.cell, slot, 0.5f * two_delta, 0.0f);
+        item_load(I.it, I.w, A.cell, slot, scratch);
         const int i0 = I.it.i0, ni = I.it.ni;
         int gbase = 0;  // groups in the cell's earlier blocks
         for (int b0 = 0; b0 < ni; b0 += 64) {

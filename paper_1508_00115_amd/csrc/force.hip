@@ -41,7 +41,7 @@ constexpr int BS = 64;     // one wavefront per block (finest LDS allocation)
 constexpr int WAVES = BS / 64;
 constexpr int FCAP = 128;  // candidates per LDS tile
 constexpr int LCAP = 80;   // entries of a particle's list (64 candidates always fit)
-constexpr int LSEG = LCAP + 4;
+constexpr int LSEG = LCAP;
 constexpr int NWORDS = (FCAP + 127) / 128;  // hit words per lane
 static_assert(FCAP % 64 == 0 && FCAP <= 256, "whole steps of the filter; byte-sized candidate numbers");
 
@@ -125,11 +125,9 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
     __shared__ float4 t2[DC ? 1 : FCAP];        // rho, Phi, c, 1/h
     __shared__ uint2 fa[FCAP];                  // filter input: x, y; z, |x|^2 (half precision)
     __shared__ uint32_t fb[DC ? 1 : FCAP];      // z, |x|^2 - h^2
-    // the particles' lists (candidate numbers of one tile) share their memory
-    // with the scratch of the walk, which is written again for each tile
-    __shared__ float4 scratch4[(16 * LSEG > WALK_LDS<UNI> ? 16 * LSEG : WALK_LDS<UNI>) / 16];
+    __shared__ uint8_t lists[16 * LSEG];  // of the particles: candidate numbers of one tile
+    __shared__ float4 scratch4[WALK_LDS<UNI> / 16];
     char* scratch = reinterpret_cast<char*>(scratch4);
-    uint8_t* lists = reinterpret_cast<uint8_t*>(scratch4);
     const int lane = threadIdx.x & 63;
     const int pc = lane & 15, gc = lane >> 4;  // column (particle) and lane group of the filter
     const int pq = lane >> 2, sub = lane & 3;  // particle and lane of the pair loop
@@ -145,7 +143,7 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
         ++a_cur;
         Item<UNI> it;
         CandWalk<UNI> w;
-        item_load(it, w, A.cell, slot, 0.0f, 1.0e18f);
+        item_load(it, w, A.cell, slot, scratch);
         const int i0 = it.i0, ni = it.ni;
         // coordinates of a particle's first float4 in the item's frame
         auto frame = [&](float4 v, float3 sh) {
@@ -197,7 +195,7 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
         float4 p0 = make_float4(0.f, 0.f, 0.f, 0.f), p1 = p0, p2 = p0;
         auto fetch = [&]() -> bool {
             Slots<1> S;
-            if (!walk_next<1>(w, A.cell, scratch, S)) return false;
+            if (!walk_next<1>(w, A.cell, it, scratch, S)) return false;
             ok = S.ok[0];
             src = S.src[0];
             sh = S.sh[0];
@@ -206,7 +204,7 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
             if (!DC) p2 = A.jf[3 * (int64_t)src + 2];
             return true;
         };
-        walk_table(w, scratch);
+        walk_start(w, A.cell, it, scratch, reach, !DC);
         bool more = fetch();
         while (more) {
             // ---- stage up to FCAP candidates ------------------------------------------
@@ -370,8 +368,7 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                 // every lane is done with the lists and the tile
                 wave_sync_lds();
             }
-            if (more) walk_table(w, scratch);  // the lists overwrote it
-        }
+            }
         ax = group_sum(ax, 4);
         ay = group_sum(ay, 4);
         az = group_sum(az, 4);

@@ -29,7 +29,7 @@ namespace {
 constexpr int GBS = 64;    // one wavefront per block
 constexpr int GCAP = 128;  // candidates per LDS tile
 constexpr int GLCAP = 80;  // entries of a particle's list (64 candidates always fit)
-constexpr int GLSEG = GLCAP + 4;
+constexpr int GLSEG = GLCAP;
 
 struct GravArgs {
     const float4* jg;       // sorted (x, y, z) as the layout stores them, m
@@ -39,7 +39,6 @@ struct GravArgs {
     int64_t* ctr;
     int n_slots;
     float G, eps2, rc, rc2, inv_rc2;
-    float delta;            // bound on the drift since the build
 };
 
 // Sorted copies of position (bits as the layout stores it) and mass; counts non-positive or
@@ -67,10 +66,9 @@ __global__ void __launch_bounds__(GBS) __attribute__((amdgpu_waves_per_eu(4))) k
     constexpr int NW = (GCAP + 127) / 128;
     __shared__ float4 t0[GCAP];  // x, y, z, m
     __shared__ uint2 fa[GCAP];   // filter input: x, y; z, |x|^2 (half precision)
-    // the lists share their memory with the scratch of the walk
-    __shared__ float4 scratch4[(16 * GLSEG > WALK_LDS<UNI> ? 16 * GLSEG : WALK_LDS<UNI>) / 16];
+    __shared__ uint8_t lists[16 * GLSEG];  // of the particles: candidate numbers of one tile
+    __shared__ float4 scratch4[WALK_LDS<UNI> / 16];
     char* scratch = reinterpret_cast<char*>(scratch4);
-    uint8_t* lists = reinterpret_cast<uint8_t*>(scratch4);
     const int lane = threadIdx.x & 63;
     const int pc = lane & 15, gc = lane >> 4;  // column (particle) and lane group of the filter
     const int pq = lane >> 2, sub = lane & 3;  // particle and lane of the pair loop
@@ -79,7 +77,7 @@ __global__ void __launch_bounds__(GBS) __attribute__((amdgpu_waves_per_eu(4))) k
     if (slot >= A.n_slots) return;             // whole wavefront
     Item<UNI> it;
     CandWalk<UNI> w;
-    item_load(it, w, A.cell, slot, A.delta, A.rc);
+    item_load(it, w, A.cell, slot, scratch);
     const int i0 = it.i0, ni = it.ni;
     auto frame = [&](float4 v, float3 sh) {
         return make_float4(item_coord<UNI>(v.x, it.ox, it.sh, it.sl, sh.x),
@@ -111,14 +109,14 @@ __global__ void __launch_bounds__(GBS) __attribute__((amdgpu_waves_per_eu(4))) k
     float4 p0 = make_float4(0.f, 0.f, 0.f, 0.f);
     auto fetch = [&]() -> bool {
         Slots<1> S;
-            if (!walk_next<1>(w, A.cell, scratch, S)) return false;
+            if (!walk_next<1>(w, A.cell, it, scratch, S)) return false;
             ok = S.ok[0];
             src = S.src[0];
             sh = S.sh[0];
         p0 = A.jg[src];
         return true;
     };
-    walk_table(w, scratch);
+    walk_start(w, A.cell, it, scratch, A.rc, false);
     bool more = fetch();
     while (more) {
         // stage the candidates within r_cut of the item's box
@@ -207,7 +205,6 @@ __global__ void __launch_bounds__(GBS) __attribute__((amdgpu_waves_per_eu(4))) k
             }
             wave_sync_lds();  // every lane is done with the lists and the tile
         }
-        if (more) walk_table(w, scratch);  // the lists overwrote it
     }
     ax = group_sum(ax, 4);
     ay = group_sum(ay, 4);
@@ -264,7 +261,6 @@ void gravity_p2p(sph_ctx* c, const float* mass, double G, double eps, double r_c
     A.n_slots = (int)c->n_items;
     A.G = (float)G;
     A.eps2 = (float)(eps * eps);
-    A.delta = delta;
     A.rc = (float)r_cut;
     A.rc2 = (float)(r_cut * r_cut);
     A.inv_rc2 = (float)(1.0 / (r_cut * r_cut));

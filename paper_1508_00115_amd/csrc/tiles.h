@@ -311,8 +311,9 @@ struct CellArgs {
                              // (two floats, high and low part), -
     const float4* pbox;      // per slot, 2: centre of the box around its particles (grid: 32-bit fractions) and
                              // largest search radius; half widths, -
-    const int2* p_rec;       // tree: per record, first particle and count of the neighbour
-    const float4* p_shift;   // tree: its frame shift
+    const int2* p_rec;       // tree: per record, first particle and count of the neighbour leaf
+    const float4* p_shift;   // tree: its frame shift, first item (bits)
+    const float4* ibox;      // tree: pbox by item rather than by slot
     const int* starts;       // grid: first particle of each fine cell
     int fzb;                 // grid: fine cells in z per top cell, logarithm
 };
@@ -324,6 +325,7 @@ inline CellArgs cell_args(sph_ctx* c, const int4* cells)
     g.pbox = static_cast<float4*>(c->cell_pbox.p);
     g.p_rec = static_cast<int2*>(c->p_rec.p);
     g.p_shift = static_cast<float4*>(c->p_shift.p);
+    g.ibox = static_cast<float4*>(c->item_box.p);
     g.starts = static_cast<int*>(c->starts.p);
     g.fzb = c->fzb;
     return g;
@@ -350,50 +352,120 @@ __device__ __forceinline__ float item_coord(float v, int o, float sh, float sl, 
     }
 }
 
-// The candidates of an item, walked in order: its records (tree) or runs
-// (grid), 64 at a time in the lanes, 64 candidates per step. The lanes' records
-// also wait in an LDS table (first particle minus offset, and the shift), where
-// each candidate slot reads its own; the record of a slot is found from marks
-// at the first slots of the records, made for 256 slots at a time.
+// The candidates of an item, walked in order, 64 U per step: its runs (grid), or
+// its records' leaves (tree). Of a neighbour leaf only the items whose boxes are
+// within reach of this item's box are walked, from the first of them to the
+// last: a leaf within reach of a leaf has many particles that are not (force
+// loop, where the reach may be the neighbour's: 726 -> 607 us on the clustered
+// 2^20 set, 9.9 -> 8.3 ms on the log-normal 2^24 set). The
+// runs left, up to 64 at a time, are rows of an LDS table (first particle minus
+// offset, and the shift), where each candidate slot reads its own; the row of a
+// slot is found from marks at the first slots of the rows, made for 256 slots at
+// a time.
 template <bool UNI>
 struct CandWalk {
     int pb0, np;            // tree: first record, records
-    int b0;                 // tree: first record of the block in the lanes
-    int nj;                 // candidates of the block
-    int c;                  // next candidate of the block
-    int q;                  // record holding the last slot before the marks' next 64
-    int cnt, off;           // this lane's record: candidates, and those of the block before it
-    int first;              // its first particle
-    float sx, sy, sz;       // tree: its shift
-    // tree: the item's box and its reach, for the records (a leaf of which no
-    // particle can be within reach is left out), widened by the drift
-    float bx, by, bz, hx, hy, hz, reach;
+    int b0;                 // tree: first record not in the table yet
+    int nj;                 // candidates of the table
+    int c;                  // next of them
+    int q;                  // row holding the last slot before the marks' next 64
+    int off;                // candidates before row `lane` (no such row: out of range)
+    float reach;            // tree: an item is in reach within this, or (own) its own largest radius
+    bool own;
 };
+
+// (offset, count) of item t of the nt = ceil(ni / 16) items of a leaf of ni
+// particles: even runs, none over 16.
+__device__ __forceinline__ int2 item_range(int ni, int nt, int t)
+{
+    const int a = ni * t / nt;
+    return make_int2(a, ni * (t + 1) / nt - a);
+}
 
 constexpr int WALK_MARKS = 256;
 template <bool UNI>
 constexpr int WALK_LDS = 64 * (UNI ? 4 : 16) + WALK_MARKS;  // table and marks
 
-__device__ __forceinline__ void walk_load(CandWalk<false>& w, const CellArgs& G)
+constexpr int WALK_NO_ROW = 0x40000000;
+
+// The marks of the 256 slots from w.c (a multiple of 256) on.
+template <bool UNI>
+__device__ __forceinline__ void walk_marks(CandWalk<UNI>& w, char* lds)
 {
     const int lane = threadIdx.x & 63;
-    int2 rec = make_int2(0, 0);
-    float4 sh = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (w.b0 + lane < w.np) {
-        rec = G.p_rec[w.pb0 + w.b0 + lane];
-        sh = G.p_shift[w.pb0 + w.b0 + lane];
-        const float gx = fmaxf(fabsf(sh.x - w.bx) - w.hx - sh.w, 0.0f),
-                    gy = fmaxf(fabsf(sh.y - w.by) - w.hy - sh.w, 0.0f),
-                    gz = fmaxf(fabsf(sh.z - w.bz) - w.hz - sh.w, 0.0f);
-        if (!(fmaf(gx, gx, fmaf(gy, gy, gz * gz)) < w.reach * w.reach)) rec.y = 0;
-    }
-    w.cnt = rec.y;
-    w.first = rec.x;
-    w.off = wave_excl_scan(rec.y, w.nj);
-    w.sx = sh.x;
-    w.sy = sh.y;
-    w.sz = sh.z;
+    uint8_t* mk = reinterpret_cast<uint8_t*>(lds + 64 * (UNI ? 4 : 16));
+    wave_sync_lds();
+    reinterpret_cast<uint32_t*>(mk)[lane] = 0;
+    wave_sync_lds();
+    const int s = w.off - w.c;
+    if (s >= 0 && s < WALK_MARKS) mk[s] = 1;
+    w.q = __popcll(__ballot(w.off < w.c)) - 1;
+    wave_sync_lds();
+}
+
+// The table of the next records (tree), as many blocks of 64 as fit in its rows.
+__device__ __forceinline__ void walk_fill(CandWalk<false>& w, const CellArgs& G, const Item<false>& it, char* lds)
+{
+    const int lane = threadIdx.x & 63;
+    int* offs = reinterpret_cast<int*>(lds + 64 * 16);  // (in the place of the marks)
+    int rows = 0;
+    wave_sync_lds();
+    w.nj = 0;
+    do {
+        const int r = w.b0 + lane;
+        int cnt = 0, first = 0;
+        float4 sh = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (r < w.np) {
+            const int2 rec = G.p_rec[w.pb0 + r];
+            sh = G.p_shift[w.pb0 + r];
+            const int nt = (rec.y + 15) >> 4;
+            first = rec.x;
+            cnt = rec.y;
+            if (nt <= 4) {
+                const float4* b = G.ibox + 2 * (int64_t)__float_as_int(sh.w);
+                int lo = 4, hi = 0;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int k = 2 * min(t, nt - 1);
+                    const float4 c = b[k], h = b[k + 1];
+                    const float gx = fmaxf(fabsf(sh.x + c.x - it.bx) - (it.hx + h.x), 0.0f),
+                                gy = fmaxf(fabsf(sh.y + c.y - it.by) - (it.hy + h.y), 0.0f),
+                                gz = fmaxf(fabsf(sh.z + c.z - it.bz) - (it.hz + h.z), 0.0f);
+                    const float R = w.own ? fmaxf(w.reach, c.w) : w.reach;
+                    if (fmaf(gx, gx, fmaf(gy, gy, gz * gz)) < cull_reach2(R)) {
+                        lo = min(lo, t);
+                        hi = t + 1;
+                    }
+                }
+                hi = min(hi, nt);
+                // (the division of item_range; exact for a product below 2^15)
+                auto part = [&](int k) {
+                    const int x = rec.y * k;
+                    return nt == 1 ? x : nt == 2 ? x >> 1 : nt == 3 ? (x * 21846) >> 16 : x >> 2;
+                };
+                const int a = lo < hi ? part(lo) : 0;
+                first += a;
+                cnt = lo < hi ? part(hi) - a : 0;
+            }
+        }
+        const uint64_t m = __ballot(cnt > 0);
+        const int k = __popcll(m);
+        if (rows + k > 64) break;
+        int n;
+        const int off = w.nj + wave_excl_scan(cnt, n);
+        if (cnt > 0) {
+            const int row = rows + lanes_below(m);
+            reinterpret_cast<float4*>(lds)[row] = make_float4(sh.x, sh.y, sh.z, __int_as_float(first - off));
+            offs[row] = off;
+        }
+        rows += k;
+        w.nj += n;
+        w.b0 += 64;
+    } while (w.b0 < w.np);
+    wave_sync_lds();
+    w.off = lane < rows ? offs[lane] : WALK_NO_ROW;
     w.c = 0;
+    walk_marks(w, lds);
 }
 
 // Order of the nine columns: centre and corners, then edges, so a chunk of the
@@ -401,8 +473,7 @@ __device__ __forceinline__ void walk_load(CandWalk<false>& w, const CellArgs& G)
 __constant__ signed char COL9[9][2] = {{0, 0}, {-1, -1}, {1, 1}, {-1, 0}, {0, 1}, {1, -1}, {-1, 1}, {1, 0}, {0, -1}};
 
 template <bool UNI>
-__device__ __forceinline__ void item_load(Item<UNI>& it, CandWalk<UNI>& w, const CellArgs& G, int slot,
-                                          float delta, float reach)
+__device__ __forceinline__ void item_load(Item<UNI>& it, CandWalk<UNI>& w, const CellArgs& G, int slot, char* lds)
 {
     const float4 b0 = G.pbox[2 * (int64_t)slot], b1 = G.pbox[2 * (int64_t)slot + 1];
     it.hx = uniform_f(b1.x);
@@ -436,17 +507,23 @@ __device__ __forceinline__ void item_load(Item<UNI>& it, CandWalk<UNI>& w, const
             a = lo < 0 ? lo + gz : 0;
             b = lo < 0 ? gz : max(hi + 1 - gz, 0);
         }
-        w.cnt = 0;
-        w.first = 0;
+        int cnt = 0, first = 0;
         if (lane < 18 && a < b) {
             const int64_t col = (int64_t)c1.x + (int64_t)(x * g + y) * gz;
-            w.first = G.starts[col + a];
-            w.cnt = G.starts[col + b] - w.first;
+            first = G.starts[col + a];
+            cnt = G.starts[col + b] - first;
         }
-        w.off = wave_excl_scan(w.cnt, w.nj);
-        w.c = 0;
-        w.np = 18;
-        w.b0 = 0;
+        // rows in the order of the lanes; runs with no particle are left out
+        const uint64_t m = __ballot(cnt > 0);
+        const int off = wave_excl_scan(cnt, w.nj), row = lanes_below(m), rows = __popcll(m);
+        int* offs = reinterpret_cast<int*>(lds + 64 * 4);  // (in the place of the marks)
+        wave_sync_lds();
+        if (cnt > 0) {
+            reinterpret_cast<int*>(lds)[row] = first - off;
+            offs[row] = off;
+        }
+        wave_sync_lds();
+        w.off = lane < rows ? offs[lane] : WALK_NO_ROW;
     } else {
         const int4 c0 = G.cells[slot];
         it.i0 = __builtin_amdgcn_readfirstlane(c0.x);
@@ -459,55 +536,24 @@ __device__ __forceinline__ void item_load(Item<UNI>& it, CandWalk<UNI>& w, const
         w.pb0 = __builtin_amdgcn_readfirstlane(c0.z);
         w.np = __builtin_amdgcn_readfirstlane(c0.w);
         w.b0 = 0;
-        const float d = 1.0e-5f * it.H + delta;
-        w.bx = it.bx;
-        w.by = it.by;
-        w.bz = it.bz;
-        w.hx = it.hx + d;
-        w.hy = it.hy + d;
-        w.hz = it.hz + d;
-        w.reach = reach > 0.0f ? reach : it.H;
-        walk_load(w, G);
     }
 }
 
-// The block's table and the marks of the 256 slots from w.c - w.c % 256 on, into
-// LDS (again after anything else used it). Records with no candidate are left
-// out of both.
+// To the first candidate, of those within reach of the item's box (tree; own:
+// or of their own largest search radius).
 template <bool UNI>
-__device__ __forceinline__ void walk_table(CandWalk<UNI>& w, char* lds)
-{
-    const int lane = threadIdx.x & 63;
-    uint8_t* mk = reinterpret_cast<uint8_t*>(lds + 64 * (UNI ? 4 : 16));
-    const bool rec = w.cnt > 0;
-    const int row = lanes_below(__ballot(rec));
-    wave_sync_lds();
-    reinterpret_cast<uint32_t*>(mk)[lane] = 0;
-    if (rec) {
-        if constexpr (UNI)
-            reinterpret_cast<int*>(lds)[row] = w.first - w.off;
-        else
-            reinterpret_cast<float4*>(lds)[row] = make_float4(w.sx, w.sy, w.sz, __int_as_float(w.first - w.off));
-    }
-    wave_sync_lds();
-    const int s = w.off - (w.c & ~(WALK_MARKS - 1));
-    if (rec && s >= 0 && s < WALK_MARKS) mk[s] = 1;
-    w.q = __popcll(__ballot(rec && w.off < w.c)) - 1;
-    wave_sync_lds();
-}
-
-// Back to the first candidate.
-template <bool UNI>
-__device__ __forceinline__ void walk_start(CandWalk<UNI>& w, const CellArgs& G, char* lds)
+__device__ __forceinline__ void walk_start(CandWalk<UNI>& w, const CellArgs& G, const Item<UNI>& it, char* lds,
+                                           float reach, bool own)
 {
     if constexpr (!UNI) {
-        if (w.b0 != 0) {
-            w.b0 = 0;
-            walk_load(w, G);
-        }
+        w.b0 = 0;
+        w.reach = reach;
+        w.own = own;
+        walk_fill(w, G, it, lds);
+    } else {
+        w.c = 0;
+        walk_marks(w, lds);
     }
-    w.c = 0;
-    walk_table(w, lds);
 }
 
 // The next 64 U candidates (U 1, 2 or 4), U slots per lane: false when none is
@@ -521,7 +567,8 @@ struct Slots {
 };
 
 template <int U, bool UNI>
-__device__ __forceinline__ bool walk_next(CandWalk<UNI>& w, const CellArgs& G, char* lds, Slots<U>& S)
+__device__ __forceinline__ bool walk_next(CandWalk<UNI>& w, const CellArgs& G, const Item<UNI>& it, char* lds,
+                                          Slots<U>& S)
 {
     static_assert(WALK_MARKS % (64 * U) == 0, "a step stays inside one set of marks");
     const int lane = threadIdx.x & 63;
@@ -530,14 +577,12 @@ __device__ __forceinline__ bool walk_next(CandWalk<UNI>& w, const CellArgs& G, c
             return false;
         } else {
             do {
-                if (w.b0 + 64 >= w.np) return false;
-                w.b0 += 64;
-                walk_load(w, G);
+                if (w.b0 >= w.np) return false;
+                walk_fill(w, G, it, lds);
             } while (w.nj == 0);
-            walk_table(w, lds);
         }
     } else if ((w.c & (WALK_MARKS - 1)) == 0 && w.c > 0) {
-        walk_table(w, lds);
+        walk_marks(w, lds);
     }
     const uint8_t* mk = reinterpret_cast<const uint8_t*>(lds + 64 * (UNI ? 4 : 16)) + (w.c & (WALK_MARKS - 1));
     bool start[U];
