@@ -491,7 +491,7 @@ __global__ void k_lvl_assign(int64_t n, const int* __restrict__ nid, const int* 
 __global__ void k_lvl_children(int64_t Mprev, int64_t base_prev, const int* __restrict__ nd_leaf,
                                const int* __restrict__ nd_start, const int* __restrict__ nd_count,
                                const int* __restrict__ nid, int* __restrict__ nd_child0,
-                               int* __restrict__ nd_child1, int* __restrict__ nd_parent)
+                               int* __restrict__ nd_child1)
 {
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= Mprev) return;
@@ -501,7 +501,6 @@ __global__ void k_lvl_children(int64_t Mprev, int64_t base_prev, const int* __re
     const int c0 = nid[s], c1 = nid[s + nd_count[id] - 1];
     nd_child0[id] = c0;
     nd_child1[id] = c1;
-    for (int c = c0; c <= c1; ++c) nd_parent[c] = (int)id;
 }
 
 __global__ void k_top_table(int64_t bound, const uint32_t* __restrict__ dM, const int* __restrict__ nd_box,
@@ -561,13 +560,13 @@ __global__ void k_leaf_fix(int64_t nl, const int* __restrict__ lf_node, const in
     lf_hmax[L] = __uint_as_float(nd_hmax[id]);
 }
 
-__device__ __forceinline__ void node_geom(int id, const int* nd_coord, const int* nd_level, double wtop,
-                                          double c[3], double& w)
+// Centre and width of a node with integer coordinates (x, y, z) and level w.
+__device__ __forceinline__ void node_box(int4 n, double wtop, double c[3], double& w)
 {
-    const int l = nd_level[id];
-    w = wtop / (double)(1u << l);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) c[a] = ((double)nd_coord[3 * id + a] + 0.5) * w;
+    w = ldexp(wtop, -n.w);
+    c[0] = ((double)n.x + 0.5) * w;
+    c[1] = ((double)n.y + 0.5) * w;
+    c[2] = ((double)n.z + 0.5) * w;
 }
 
 // The 27 top cells around a leaf's own, in the order its partner list visits
@@ -580,16 +579,27 @@ __constant__ signed char NB27[27][3] = {
     {-1, -1, 0}, {-1, 0, -1}, {-1, 1, 1}, {0, -1, -1}, {0, 0, 1}, {0, 1, 0}, {1, -1, 1}, {1, 0, 0}, {1, 1, -1},
     {-1, -1, 1}, {-1, 0, 0}, {-1, 1, -1}, {0, -1, 0}, {0, 0, -1}, {0, 1, 1}, {1, -1, -1}, {1, 0, 1}, {1, 1, 0}};
 
+// The tree as the walks below read it, two words of 16 bytes per node: integer
+// centre and level; largest search radius (bits), leaf or -1 - first child,
+// particles of a leaf or number of children (their ids are consecutive), -.
 struct TreeView {
-    const int* nd_coord;
-    const int* nd_level;
-    const unsigned* nd_hmax;
-    const int* nd_leaf;
-    const int* nd_child0;
-    const int* nd_child1;
-    const int* nd_parent;
+    const int4* nodes;
     int n_nodes;
 };
+
+__global__ void k_tree_pack(int64_t n_nodes, const int* __restrict__ nd_coord, const int* __restrict__ nd_level,
+                            const unsigned* __restrict__ nd_hmax, const int* __restrict__ nd_leaf,
+                            const int* __restrict__ nd_child0, const int* __restrict__ nd_child1,
+                            const int* __restrict__ lf_count,
+                            int4* __restrict__ nodes)
+{
+    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= n_nodes) return;
+    const int lf = nd_leaf[id];
+    nodes[2 * id] = make_int4(nd_coord[3 * id], nd_coord[3 * id + 1], nd_coord[3 * id + 2], nd_level[id]);
+    nodes[2 * id + 1] = make_int4((int)nd_hmax[id], lf >= 0 ? lf : -1 - nd_child0[id],
+                                  lf >= 0 ? lf_count[lf] : nd_child1[id] - nd_child0[id] + 1, 0);
+}
 
 struct RecordOut {
     int* p_leaf;
@@ -600,64 +610,6 @@ struct RecordOut {
     const int* lf_count;
     const uint32_t* it_start;  // null: no items
 };
-
-// Depth-first walk below top cell T (seen through the periodic image shift S)
-// for the leaves of partner lists of leaf a (centre cA, width wA, largest
-// search radius HA): every leaf whose box lies within max(HA, its own largest
-// radius) of a's box. nd counts those within HA, nf the others. FILL writes
-// them from od and of on; nj adds up their particles. The walk needs no
-// stack: a split node's children have consecutive ids, so after a node the
-// walk goes to its next sibling, or climbs to the first ancestor below T that
-// has one. Children come in increasing id order. A tree that would take more
-// steps than it has nodes is reported (CT_BAD_INPUT) and the walk ends.
-template <bool FILL>
-__device__ __forceinline__ void walk_top(int T, const double S[3], int code, const double cA[3], double wA,
-                                         double wtop, float HA, const TreeView& tv, const RecordOut& ro,
-                                         uint32_t od, uint32_t of, uint32_t& nd, uint32_t& nf, int& nj,
-                                         int64_t* __restrict__ ctr)
-{
-    const double eps = 1e-9 * wtop;
-    int X = T;
-    for (int steps = 0;; ++steps) {
-        if (steps > tv.n_nodes) {
-            atomicAdd((unsigned long long*)&ctr[CT_BAD_INPUT], 1ull);
-            return;
-        }
-        double cX[3], wX;
-        node_geom(X, tv.nd_coord, tv.nd_level, wtop, cX, wX);
-        double d2 = 0.0;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            double g = fabs(cX[k] + S[k] - cA[k]) - 0.5 * (wA + wX) - eps;
-            g = g > 0.0 ? g : 0.0;
-            d2 += g * g;
-        }
-        const double R = (double)fmaxf(HA, __uint_as_float(tv.nd_hmax[X]));
-        if (d2 < R * R) {
-            const int lf = tv.nd_leaf[X];
-            if (lf < 0) {  // split: its first child next
-                X = tv.nd_child0[X];
-                continue;
-            }
-            const bool dens = d2 < (double)HA * (double)HA;
-            const int cnt = ro.lf_count[lf];
-            nj += cnt;
-            if (FILL) {
-                const uint32_t o = dens ? od + nd : of + nf;
-                ro.p_leaf[o] = lf;
-                ro.p_rec[o] = make_int2(ro.lf_start[lf], cnt);
-                ro.p_shift[o] = make_float4((float)(cX[0] + S[0] - cA[0]), (float)(cX[1] + S[1] - cA[1]),
-                                            (float)(cX[2] + S[2] - cA[2]), __int_as_float(ro.it_start ? (int)ro.it_start[lf] : 0));
-                ro.p_code[o] = code;
-            }
-            nd += dens ? 1u : 0u;
-            nf += dens ? 0u : 1u;
-        }
-        while (X != T && X == tv.nd_child1[tv.nd_parent[X]]) X = tv.nd_parent[X];
-        if (X == T) return;
-        ++X;
-    }
-}
 
 // Sums over the 32 lanes of a half-wavefront.
 __device__ __forceinline__ uint32_t half_sum(uint32_t v)
@@ -727,21 +679,32 @@ __global__ void k_item_count(int64_t nl, const int* __restrict__ lf_count, uint3
 }
 
 // The cell-pair tasks (section 3.1: the neighbouring cells of each leaf, found
-// with a tree), one half-wavefront per leaf and one lane per surrounding top
-// cell. fill == 0 counts each leaf's records (all into p_cnt, the density's
-// into p_cntd). fill == 1 writes the list at p_start[a], in two parts: first
-// the leaves within Hmax_a of a's box (p_cntd[a] of them), then those that
-// reach a only with their own radius. The density of a's particles (a gather
-// over j inside h_i <= Hmax_a) needs only the first part; the force (pairs
-// inside max(h_i, h_j)) takes both. Within each part the records follow the
-// NB27 order of their top cells, depth-first below each, so each lane writes
-// from the sum of the counts of the lanes before it (it walks its subtree
-// twice: to count, then to write). The count also adds up the build's shape
-// counters (CT_B_*). The fill also writes (it_start != null) the leaf of each of
-// its work items and the item's schedule key (sk != null), its cost particles
-// x candidates as 12 bits of its float (exponent and four bits of mantissa)
-// in decreasing order, prefixed with the XCD whose Morton range holds the
-// item when xcd_local.
+// with a tree), one half-wavefront per leaf a: every leaf whose box lies within
+// max(HA, its own largest radius) of a's box, HA the largest radius in a. fill ==
+// 0 counts each leaf's records (all into p_cnt, the density's into p_cntd). fill
+// == 1 writes the list at p_start[a], in two parts: first the leaves within HA
+// (p_cntd[a] of them), then those that reach a only with their own radius. The
+// density of a's particles (a gather over j inside h_i <= HA) needs only the
+// first part; the force (pairs inside max(h_i, h_j)) takes both. The count also
+// adds up the build's shape counters (CT_B_*). The fill also writes (it_start !=
+// null) the leaf of each of its work items and the item's schedule key (sk !=
+// null), its cost particles x candidates as 12 bits of its float (exponent and
+// four bits of mantissa) in decreasing order, prefixed with the XCD whose Morton
+// range holds the item when xcd_local.
+//
+// The nodes still to be tested, at first the 27 surrounding top cells, wait on a
+// stack in LDS, and every step tests its uppermost 32 at once: a walk visits
+// hundreds of nodes where the set is clustered, most of them below two or three
+// of the top cells, so a lane per top cell left the rest idle behind the longest
+// walk and took a memory latency per node (clustered 2^20: 1.10 ms a call, 0.23
+// here; log-normal 2^24: 11 ms and 1.7; 0.73 with the packed nodes alone). The
+// order is fixed, so the lists have the same records in the same order in every
+// build. A step takes fewer nodes where their children could overrun
+// PSTACK; single nodes add at most seven per level after that.
+constexpr int PSTACK = 256;
+constexpr int MAX_LEVELS = 10;
+constexpr int PSTACK_ALL = PSTACK + 7 * MAX_LEVELS + 2;
+
 __global__ void __launch_bounds__(PBS) k_partners(int64_t nl, int fill, const int* __restrict__ lf_node,
                                                   TreeView tv, const int* __restrict__ nd_box,
                                                   const int* __restrict__ top,
@@ -753,59 +716,131 @@ __global__ void __launch_bounds__(PBS) k_partners(int64_t nl, int fill, const in
                                                   int* __restrict__ it_leaf, uint64_t* __restrict__ sk,
                                                   uint32_t* __restrict__ sv, int xcd_local, int64_t* __restrict__ ctr)
 {
-    const int q = threadIdx.x & 31;
+    const int q = threadIdx.x & 31, half = threadIdx.x >> 5, upper = threadIdx.x & 32;
     const int64_t a = ((int64_t)blockIdx.x * PBS + threadIdx.x) >> 5;
     const bool leaf_ok = a < nl;
-    uint32_t nd = 0, nf = 0;
-    int T = -1, code = 0;
-    double S[3] = {0.0, 0.0, 0.0}, cA[3] = {0.0, 0.0, 0.0}, wA = 0.0, wtop = 1.0;
+    __shared__ int st_node[PBS / 32][PSTACK_ALL];
+    __shared__ uint8_t st_code[PBS / 32][PSTACK_ALL];
+    __shared__ int64_t red[5][PBS / 64];
+    int* const sn = st_node[half];
+    uint8_t* const sc = st_code[half];
+    auto half_ballot = [&](bool v) { return (uint32_t)(__ballot(v) >> upper); };
+    const uint32_t below = (1u << q) - 1u;
+    double cA[3] = {0.0, 0.0, 0.0}, wA = 0.0, wtop = 1.0, L = 0.0;
     float HA = 0.0f;
-    if (leaf_ok && q < 27) {
+    int T = -1, code = 0;
+    if (leaf_ok) {
         const int A = lf_node[a];
         const int b = nd_box[A];
         const int G = box_G[b];
-        const double L = box_len[b];
+        L = box_len[b];
         wtop = L / G;
-        node_geom(A, tv.nd_coord, tv.nd_level, wtop, cA, wA);
-        HA = __uint_as_float(tv.nd_hmax[A]);
-        const int lA = tv.nd_level[A];
-        int t[3], s[3];
+        const int4 nA = tv.nodes[2 * (int64_t)A];
+        node_box(nA, wtop, cA, wA);
+        HA = __int_as_float(tv.nodes[2 * (int64_t)A + 1].x);
+        if (q < 27) {
+            const int tA[3] = {nA.x, nA.y, nA.z};
+            int t[3], s[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            t[k] = (tv.nd_coord[3 * A + k] >> lA) + NB27[q][k];
-            s[k] = 0;
-            if (t[k] < 0) { t[k] += G; s[k] = -1; }
-            else if (t[k] >= G) { t[k] -= G; s[k] = 1; }
-            S[k] = s[k] * L;
+            for (int k = 0; k < 3; ++k) {
+                t[k] = (tA[k] >> nA.w) + NB27[q][k];
+                s[k] = 0;
+                if (t[k] < 0) { t[k] += G; s[k] = -1; }
+                else if (t[k] >= G) { t[k] -= G; s[k] = 1; }
+            }
+            T = top[box_top_base[b] + ((int64_t)t[0] * G + t[1]) * G + t[2]];
+            code = image_code(s[0], s[1], s[2]);
         }
-        T = top[box_top_base[b] + ((int64_t)t[0] * G + t[1]) * G + t[2]];
-        code = image_code(s[0], s[1], s[2]);
     }
-    int nj = 0;
-    if (T >= 0) walk_top<false>(T, S, code, cA, wA, wtop, HA, tv, ro, 0u, 0u, nd, nf, nj, ctr);
-    __shared__ int64_t red[5][PBS / 64];
+    const double eps = 1e-9 * wtop, HA2 = (double)HA * (double)HA;
+    int size = 0;  // of the half's stack
+    {
+        const uint32_t m = half_ballot(T >= 0);
+        if (T >= 0) {
+            const int d = __popc(m & below);
+            sn[d] = T;
+            sc[d] = (uint8_t)code;
+        }
+        size = __popc(m);
+    }
+    uint32_t nd = 0, nf = 0;  // records so far
+    int nj = 0;               // particles of this lane's
+    const uint32_t od = fill && leaf_ok ? p_start[a] : 0u, of = fill && leaf_ok ? od + p_cntd[a] : 0u;
+    for (int64_t steps = 0; __any(size > 0); ++steps) {
+        if (steps > 27 * (int64_t)tv.n_nodes) {  // (whole wavefront) more than any tree has
+            if ((threadIdx.x & 63) == 0) atomicAdd((unsigned long long*)&ctr[CT_BAD_INPUT], 1ull);
+            break;
+        }
+        wave_sync_lds();
+        const int m = min(min(32, size), max(1, (PSTACK - size) / 7));
+        size -= m;
+        bool dens = false, far = false;
+        int kids = 0, child = 0, lf = 0, cnt = 0, img = 0;
+        float4 sh = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (q < m) {
+            const int64_t X = sn[size + q];
+            img = sc[size + q];
+            const int4 na = tv.nodes[2 * X], nb = tv.nodes[2 * X + 1];
+            double cX[3], wX;
+            node_box(na, wtop, cX, wX);
+            const double S[3] = {image_shift(img, 0, L), image_shift(img, 1, L), image_shift(img, 2, L)};
+            double d2 = 0.0;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                double g = fabs(cX[k] + S[k] - cA[k]) - 0.5 * (wA + wX) - eps;
+                g = g > 0.0 ? g : 0.0;
+                d2 += g * g;
+            }
+            const double R = (double)fmaxf(HA, __int_as_float(nb.x));
+            if (d2 < R * R) {
+                if (nb.y < 0) {
+                    child = -1 - nb.y;
+                    kids = nb.z;
+                } else {
+                    lf = nb.y;
+                    cnt = nb.z;
+                    nj += cnt;
+                    dens = d2 < HA2;
+                    far = !dens;
+                    sh = make_float4((float)(cX[0] + S[0] - cA[0]), (float)(cX[1] + S[1] - cA[1]),
+                                     (float)(cX[2] + S[2] - cA[2]), 0.0f);
+                }
+            }
+        }
+        const uint32_t md = half_ballot(dens), mf = half_ballot(far);
+        if (fill && (dens || far)) {
+            const uint32_t o = dens ? od + nd + __popc(md & below) : of + nf + __popc(mf & below);
+            sh.w = __int_as_float(ro.it_start ? (int)ro.it_start[lf] : 0);
+            ro.p_leaf[o] = lf;
+            ro.p_rec[o] = make_int2(ro.lf_start[lf], cnt);
+            ro.p_shift[o] = sh;
+            ro.p_code[o] = img;
+        }
+        nd += __popc(md);
+        nf += __popc(mf);
+        // the children, on the stack
+        const uint32_t at = half_excl_scan((uint32_t)kids);
+        wave_sync_lds();  // every lane has read its node
+        for (int k = 0; k < kids; ++k) {
+            sn[size + at + k] = child + k;
+            sc[size + at + k] = (uint8_t)img;
+        }
+        size += __shfl((int)at + kids, 31, 32);
+    }
     if (!fill) {
-        const uint32_t td = half_sum(nd), tf = half_sum(nf);
         const int tj = (int)half_sum((uint32_t)nj);
         const bool lead = leaf_ok && q == 0;
         if (lead) {
-            p_cnt[a] = td + tf;
-            p_cntd[a] = td;
+            p_cnt[a] = nd + nf;
+            p_cntd[a] = nd;
         }
         // the build's shape: the candidate pairs and the records of all leaves
         // (in 64 bits: the list offsets are a 32-bit scan), then the maxima
         const int ni = leaf_ok ? ro.lf_count[a] : 0;
-        const int64_t r[5] = {lead ? (int64_t)ni * tj : 0, lead ? (int64_t)(td + tf) : 0, lead ? ni : 0,
-                              lead ? (int64_t)(td + tf) : 0, lead ? tj : 0};
+        const int64_t r[5] = {lead ? (int64_t)ni * tj : 0, lead ? (int64_t)(nd + nf) : 0, lead ? ni : 0,
+                              lead ? (int64_t)(nd + nf) : 0, lead ? tj : 0};
         block_counters<5>(r, red, ctr, CT_B_CAND_PAIRS, 2);
         return;
-    }
-    const uint32_t sd = half_excl_scan(nd), sf = half_excl_scan(nf);
-    if (T >= 0) {
-        const uint32_t base = p_start[a];
-        uint32_t cd = 0, cf = 0;
-        int again = 0;
-        walk_top<true>(T, S, code, cA, wA, wtop, HA, tv, ro, base + sd, base + p_cntd[a] + sf, cd, cf, again, ctr);
     }
     if (!it_start) return;
     nj = (int)half_sum((uint32_t)nj);
@@ -910,7 +945,8 @@ __global__ void k_sorted_fill(int64_t n, const uint32_t* __restrict__ perm, cons
     const int id = lf_node[leaf_of[p]];
     const int b = nd_box[id];
     double c[3], w;
-    node_geom(id, nd_coord, nd_level, box_len[b] / box_G[b], c, w);
+    node_box(make_int4(nd_coord[3 * id], nd_coord[3 * id + 1], nd_coord[3 * id + 2], nd_level[id]),
+             box_len[b] / box_G[b], c, w);
     const double L = box_len[b];
     double d[3];
 #pragma unroll
@@ -973,10 +1009,7 @@ namespace sph {
 
 static TreeView tree_view(sph_ctx* c)
 {
-    return TreeView{static_cast<int*>(c->nd_coord.p),  static_cast<int*>(c->nd_level.p),
-                    static_cast<unsigned*>(c->nd_hmax.p), static_cast<int*>(c->nd_leaf.p),
-                    static_cast<int*>(c->nd_child0.p), static_cast<int*>(c->nd_child1.p),
-                    static_cast<int*>(c->nd_parent.p), (int)c->n_nodes};
+    return TreeView{static_cast<int4*>(c->nd_pack.p), (int)c->n_nodes};
 }
 
 // Offsets of the leaves' partner lists from their counts (p_cnt); sets n_pairs
@@ -1097,7 +1130,7 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     }
     c->bits_box = nb > 1 ? ceil_log2((uint64_t)nb) : 0;
     c->bits_top = std::max(1, ceil_log2(maxG3));
-    c->levels = std::min(10, (63 - c->bits_box - c->bits_top) / 3);
+    c->levels = std::min(MAX_LEVELS, (63 - c->bits_box - c->bits_top) / 3);
     SPH_REQUIRE(c->levels >= 1, SPH_E_ARG, "too many boxes or top cells for the key layout");
     int* box_G = ensure<int>(c, c->box_G, nb);
     int64_t* box_top_base = ensure<int64_t>(c, c->box_top_base, nb + 1);
@@ -1192,7 +1225,6 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
             grow_keep<int>(c, c->nd_wide, cap, node_base, s);
             grow_keep<int>(c, c->nd_child0, cap, node_base, s);
             grow_keep<int>(c, c->nd_child1, cap, node_base, s);
-            grow_keep<int>(c, c->nd_parent, cap, node_base, s);
             grow_keep<int>(c, c->nd_leaf, cap, node_base, s);
             grow_keep<int>(c, c->nd_box, cap, node_base, s);
             grow_keep<int>(c, c->nd_level, cap, node_base, s);
@@ -1205,7 +1237,6 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
         int* nd_wide = static_cast<int*>(c->nd_wide.p);
         int* nd_child0 = static_cast<int*>(c->nd_child0.p);
         int* nd_child1 = static_cast<int*>(c->nd_child1.p);
-        int* nd_parent = static_cast<int*>(c->nd_parent.p);
         int* nd_leaf = static_cast<int*>(c->nd_leaf.p);
         int* nd_box = static_cast<int*>(c->nd_box.p);
         int* nd_level = static_cast<int*>(c->nd_level.p);
@@ -1222,8 +1253,7 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
             SPH_HIP(hipGetLastError());
         } else {
             k_lvl_children<<<blocks_for(prev_M, BS), BS, 0, s>>>(prev_M, prev_base, nd_leaf, nd_start,
-                                                                 nd_count, nid, nd_child0, nd_child1,
-                                                                 nd_parent);
+                                                                 nd_count, nid, nd_child0, nd_child1);
             SPH_HIP(hipGetLastError());
         }
         uint32_t* nflag = ensure<uint32_t>(c, c->nflag, bound + 1);
@@ -1294,6 +1324,12 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     // ---- partner lists: their number, and in a tree layout the lists and the items ------------
     uint32_t* p_cnt = ensure<uint32_t>(c, c->p_cnt, nl + 1);
     uint32_t* p_cntd = ensure<uint32_t>(c, c->p_cntd, nl + 1);
+    k_tree_pack<<<blocks_for(c->n_nodes, BS), BS, 0, s>>>(
+        c->n_nodes, static_cast<int*>(c->nd_coord.p), static_cast<int*>(c->nd_level.p),
+        static_cast<unsigned*>(c->nd_hmax.p), static_cast<int*>(c->nd_leaf.p), static_cast<int*>(c->nd_child0.p),
+        static_cast<int*>(c->nd_child1.p), lf_count,
+        ensure<int4>(c, c->nd_pack, 2 * c->n_nodes));
+    SPH_HIP(hipGetLastError());
     const TreeView tv = tree_view(c);
     k_partners<<<(unsigned)blocks_for(nl * 32, PBS), PBS, 0, s>>>(
         nl, 0, lf_node, tv, static_cast<int*>(c->nd_box.p), top, box_top_base, box_G, box_len, p_cnt, p_cntd, nullptr,

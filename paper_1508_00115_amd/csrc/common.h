@@ -175,7 +175,7 @@ struct sph_ctx {
     sph::Buf nid;            // int per particle: node at the current level
     // nodes (all levels, level-major)
     sph::Buf build_out;
-    sph::Buf nd_start, nd_count, nd_hmax, nd_wide, nd_child0, nd_child1, nd_parent, nd_leaf, nd_box, nd_level,
+    sph::Buf nd_start, nd_count, nd_hmax, nd_wide, nd_child0, nd_child1, nd_leaf, nd_box, nd_level,
         nd_coord;
     int64_t node_cap = 0;
     sph::Buf nflag, nscan;   // per-node temporaries of one level
@@ -205,6 +205,7 @@ struct sph_ctx {
     sph::Buf cell_item;      // int per slot: item
     sph::Buf cell_pbox;      // float4 x 2 per slot: box of the item's particles at their current offsets
                              // (centre, largest search radius; half widths, 0)
+    sph::Buf nd_pack;        // int4 x 2 per node: the tree as the partner walks read it
     sph::Buf item_box;       // tree: float4 x 2 per item, as cell_pbox
     sph::Buf cells_d;        // int4 per slot as `cells`, with the density's record count (a prefix)
     sph::Buf sched_key, sched_key_alt, sched_val, sched_val_alt;  // cost sort
