@@ -486,8 +486,7 @@ __global__ void k_lvl_assign(int64_t n, const int* __restrict__ nid, const int* 
 
 // Children of the split nodes of the previous level: the level-l nodes holding
 // the first and last particle of each split parent (level-l nodes are
-// numbered in particle order, so a parent's children are the ids between),
-// and each child's parent.
+// numbered in particle order, so a parent's children are the ids between).
 __global__ void k_lvl_children(int64_t Mprev, int64_t base_prev, const int* __restrict__ nd_leaf,
                                const int* __restrict__ nd_start, const int* __restrict__ nd_count,
                                const int* __restrict__ nid, int* __restrict__ nd_child0,

@@ -1032,11 +1032,14 @@ void density_enqueue(sph_ctx* c, const float* mass, float* h, float* rho, float*
     // first radius (g the smaller of h_margin and LIST_GROW): a third more on a
     // grid, where the guesses of a lattice are good, nearly twice that in a tree,
     // where a particle that needs a second list costs its item a second sweep
-    // (log-normal 2^24). Longer lists cost LDS and registers, so wavefronts.
+    // (log-normal 2^24: 96 entries, 27 of 1000 particles, 11.9 ms; 128, 3 of 1000,
+    // 11.5 ms). Longer lists cost LDS and registers, so wavefronts: the clustered
+    // 2^20 set with 48 neighbours and the default margin, which just fits 128,
+    // takes 936 us with 128 entries and 1291 us with 240.
     const bool wide = c->prm.h_margin > LIST_WIDE;
     const double g = wide ? (double)LIST_GROW : c->prm.h_margin;
     A.grow = wide ? LIST_GROW : 1.0e30f;
-    const double want = (c->uni ? 1.35 : 1.9) * c->prm.n_ngb * g * g * g;
+    const double want = (c->uni ? 1.35 : 1.85) * c->prm.n_ngb * g * g * g;
     auto launch = [&](auto lcap) {
         constexpr int L = decltype(lcap)::value;
         if (c->uni)
