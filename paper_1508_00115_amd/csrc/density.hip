@@ -560,7 +560,7 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                 solved = mine && Tq <= room;
                 many = Tq > LIST_MOST;
                 const int len = solved ? Tq : 0;
-                const int nj4 = (__builtin_amdgcn_readfirstlane((int)wave_max((float)len)) + 4 * lpp - 1) >> (lg + 2);
+                const int nj4 = (wave_max_u(len) + 4 * lpp - 1) >> (lg + 2);
                 float* lq = list + (round == 0 ? SEG : 4 * SEG) * (lane >> lg);
                 for (int e = len + sub; e < 4 * lpp * nj4; e += lpp) lq[e] = FAR2;
                 wave_sync_lds();
@@ -579,11 +579,11 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                 //      t^2) with t = max(1 - q, 0), u = max(1/2 - q, 0): the cubic spline as truncated
                 //      powers, no branch and no select ------------------------------------------------
                 bool run = solved;
+                int inside_h = 0, swept = 0;
                 while (__any(run)) {
                     const float hinv = __builtin_amdgcn_rcpf(s.h);
-                    const uint64_t live = __ballot(run);
                     float At = 0.f, Au = 0.f, Bt = 0.f, Bu = 0.f;
-                    int cnt = 0;  // wave-uniform
+                    int cnt = 0;  // this lane's entries inside h
                     auto entry = [&](float r) {
                         const float q = r * hinv;
                         const float t = __builtin_amdgcn_fmed3f(fmaf(-r, hinv, 1.0f), 0.0f, 1.0f);
@@ -593,7 +593,7 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                         Au = fmaf(u2, u, Au);
                         Bt = fmaf(q, t2, Bt);
                         Bu = fmaf(q, u2, Bu);
-                        cnt += __popcll(__ballot(t > 0.0f) & live);  // r < h
+                        cnt += t > 0.0f ? 1 : 0;  // r < h
                     };
 #pragma unroll
                     for (int j = 0; j < NR; ++j) {
@@ -604,10 +604,11 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                             entry(r4[j].w);
                         }
                     }
-                    sweep_acc += cnt;
                     const float S0 = group_sum(fmaf(2.0f, At, -8.0f * Au), lpp);
                     const float S1 = group_sum(fmaf(24.0f, Bu, -6.0f * Bt), lpp);
                     if (run) {
+                        inside_h = cnt;
+                        swept += cnt;
                         fS0 = S0;
                         fS1 = S1;
                         hsolve_step(s, S0, S1, A.inv_target, A.tol, A.max_iter);
@@ -615,12 +616,17 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                     }
                 }
                 {
-                    // evaluations: their most, and the entries they read
+                    // evaluations: their most, the entries they read and those inside h, and the
+                    // interactions at the final h, which is the last one evaluated (less the
+                    // particle itself)
                     while (__any(solved && s.nev > max_ev)) ++max_ev;
-                    int v = solved && sub == 0 ? s.nev * len : 0;
-#pragma unroll
-                    for (int o = 32; o >= 4; o >>= 1) v += __shfl_xor(v, o, 64);
-                    list_acc += __builtin_amdgcn_readfirstlane(v);
+                    int a, b, d;
+                    wave_excl_scan(solved && sub == 0 ? s.nev * len : 0, a);
+                    wave_excl_scan(swept, b);
+                    wave_excl_scan(solved && s.state == ST_DONE ? inside_h - (sub == 0 ? 1 : 0) : 0, d);
+                    list_acc += a;
+                    sweep_acc += b;
+                    inter_acc += d;
                 }
                 // a root beyond a list that stopped short of H: once more, out to H
                 const bool beyond = solved && s.state == ST_OVERFLOW && cut;
@@ -629,28 +635,6 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                 const unsigned bm = (unsigned)__ballot(inb && beyond_c) & 0xffffu;
                 wide |= bm;
                 todo &= ~(batch & ~bm & (round == 0 ? ~over : ~0u));
-                {
-                    // interactions at the final h (less the particle itself)
-                    const uint64_t live = __ballot(solved && s.state == ST_DONE);
-                    if (live) {
-                        const float hinv = __builtin_amdgcn_rcpf(s.h);
-                        int cnt = 0;
-                        auto entry = [&](float r) {
-                            const float t = __builtin_amdgcn_fmed3f(fmaf(-r, hinv, 1.0f), 0.0f, 1.0f);
-                            cnt += __popcll(__ballot(t > 0.0f) & live);
-                        };
-#pragma unroll
-                        for (int j = 0; j < NR; ++j) {
-                            if (j < nj4) {
-                                entry(r4[j].x);
-                                entry(r4[j].y);
-                                entry(r4[j].z);
-                                entry(r4[j].w);
-                            }
-                        }
-                        inter_acc += cnt - (__popcll(live) >> lg);
-                    }
-                }
                 if (!mixed || !__any(solved)) break;
             }
             if (mixed) n_scan += wave_count(solved && sub == 0 && !many);  // walked again

@@ -292,6 +292,18 @@ __device__ __forceinline__ int wave_excl_scan(int x, int& total)
     return v - x;
 }
 
+// Largest v >= 0 over the wavefront, in the same steps.
+__device__ __forceinline__ int wave_max_u(int v)
+{
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
 // ---- work items: their particles, frames and candidates ----------------------------------
 //
 // Two layouts. A grid layout (UNI: no top cell split, see the cell build)
@@ -610,13 +622,14 @@ __device__ __forceinline__ bool walk_next(CandWalk<UNI>& w, const CellArgs& G, c
 }
 
 // The sum over the four lanes of a column (lanes l, l ^ 16, l ^ 32, l ^ 48) and
-// the share of the lower groups, for counts.
+// the share of the lower groups, for counts. Row and half swaps give both
+// partners' values in two registers each, with no trip through LDS.
 __device__ __forceinline__ int column_excl_scan(int n, int& total)
 {
     const int lane = threadIdx.x & 63;
-    const int n1 = __shfl_xor(n, 16, 64);
-    const int p = n + n1;
-    const int p2 = __shfl_xor(p, 32, 64);
-    total = p + p2;
-    return ((lane & 16) ? n1 : 0) + ((lane & 32) ? p2 : 0);
+    const auto r = __builtin_amdgcn_permlane16_swap(n, n, false, false);  // rows (0, 0, 2, 2), (1, 1, 3, 3)
+    const int p = (int)(r[0] + r[1]);
+    const auto h = __builtin_amdgcn_permlane32_swap(p, p, false, false);  // lower half, upper half
+    total = (int)(h[0] + h[1]);
+    return ((lane & 16) ? (int)r[0] : 0) + ((lane & 32) ? (int)h[0] : 0);
 }
