@@ -337,12 +337,6 @@ __global__ void k_sorted_H(int64_t n, const uint32_t* __restrict__ perm, const f
     if (leaf_tmp) leaf_tmp[p] = -1;
 }
 
-__global__ void k_fill_int(int64_t n, int* __restrict__ a, int v)
-{
-    int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < n) a[p] = v;
-}
-
 __global__ void k_lvl_head(int64_t n, const uint64_t* __restrict__ keys, const int* __restrict__ leaf_tmp,
                            int shift, uint32_t* __restrict__ head)
 {
@@ -430,10 +424,13 @@ __global__ void k_lvl_nodes(int64_t n, const uint64_t* __restrict__ keys, const 
 // The per-level kernels below run over a bound on the level's node count
 // that the host knows (the launch), and take the count itself (*dM) from the
 // device: slots k in [*dM, bound) hold no node.
+// The sums of a level's nodes; at the first level also the table of top cells.
 __global__ void k_lvl_clear(int64_t node_base, int64_t bound, int* __restrict__ nd_count,
-                            unsigned* __restrict__ nd_hmax, int* __restrict__ nd_wide)
+                            unsigned* __restrict__ nd_hmax, int* __restrict__ nd_wide, int64_t n_top,
+                            int* __restrict__ top)
 {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < n_top) top[k] = -1;
     if (k >= bound) return;
     nd_count[node_base + k] = 0;
     nd_hmax[node_base + k] = 0u;
@@ -557,6 +554,29 @@ __global__ void k_leaf_fix(int64_t nl, const int* __restrict__ lf_node, const in
     nd_leaf[id] = (int)L;
     lf_count[L] = nd_count[id];
     lf_hmax[L] = __uint_as_float(nd_hmax[id]);
+}
+
+// The leaves where no top cell splits: they are the level-0 nodes, whose order is
+// the particles' already (nid: the node of each particle), so one kernel stands
+// for the renumbering, its scan and the packing of the tree (seven launches; a
+// leapfrog step with a rebuild at 48^3 particles 261 -> 249 us).
+__global__ void k_leaf_top(int64_t n, int64_t nl, const int* __restrict__ nid, const int* __restrict__ nd_start,
+                           const int* __restrict__ nd_count, const unsigned* __restrict__ nd_hmax,
+                           const int* __restrict__ nd_coord, int* __restrict__ leaf_of, int* __restrict__ lf_start,
+                           int* __restrict__ lf_node, int* __restrict__ lf_count, float* __restrict__ lf_hmax,
+                           int4* __restrict__ nodes)
+{
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p < n) leaf_of[p] = nid[p];
+    if (p >= nl) return;
+    const int cnt = nd_count[p];
+    const unsigned h = nd_hmax[p];
+    lf_start[p] = nd_start[p];
+    lf_node[p] = (int)p;
+    lf_count[p] = cnt;
+    lf_hmax[p] = __uint_as_float(h);
+    nodes[2 * p] = make_int4(nd_coord[3 * p], nd_coord[3 * p + 1], nd_coord[3 * p + 2], 0);
+    nodes[2 * p + 1] = make_int4((int)h, (int)p, cnt, 0);
 }
 
 // Centre and width of a node with integer coordinates (x, y, z) and level w.
@@ -976,9 +996,12 @@ __global__ void __launch_bounds__(BS) k_min_H(int64_t n, const float* __restrict
     }
 }
 
+// Bound, step maximum, smallest search radius (before its minimum), non-finite flag.
+__global__ void k_drift_init(unsigned* drift) { drift[threadIdx.x] = threadIdx.x == 2 ? 0x7f800000u : 0u; }
+
 // The build's shape counters folded over their spread slots, and the
-// smallest search radius, into out (BUILD_OUT_WORDS words): a buffer no other
-// kernel writes, so its copy to the host can wait for the next synchronisation.
+// smallest search radius, into out (BUILD_OUT_WORDS words of pinned host memory,
+// read after the next synchronisation).
 __global__ void k_build_out(const int64_t* __restrict__ ctr, const unsigned* __restrict__ hmin,
                             int64_t* __restrict__ out)
 {
@@ -1199,8 +1222,6 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     uint32_t* d_M = reinterpret_cast<uint32_t*>(&ctr[CT_TOTAL]);
     uint32_t* d_K = d_M + 1;
     int* top = ensure<int>(c, c->top, (size_t)c->n_top);
-    k_fill_int<<<blocks_for(c->n_top, BS), BS, 0, s>>>(c->n_top, top, -1);
-    SPH_HIP(hipGetLastError());
 
     int64_t node_base = 0, leaf_base = 0, prev_base = 0, prev_M = 0;
     int64_t bound = std::min<int64_t>(n, c->n_top);
@@ -1241,7 +1262,9 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
         int* nd_level = static_cast<int*>(c->nd_level.p);
         int* nd_coord = static_cast<int*>(c->nd_coord.p);
         const unsigned gb = (unsigned)blocks_for(bound, BS);
-        k_lvl_clear<<<gb, BS, 0, s>>>(node_base, bound, nd_count, nd_hmax, nd_wide);
+        const int64_t n_clear = level == 0 ? c->n_top : 0;
+        k_lvl_clear<<<(unsigned)blocks_for(std::max(bound, n_clear), BS), BS, 0, s>>>(node_base, bound, nd_count, nd_hmax,
+                                                                                      nd_wide, n_clear, top);
         SPH_HIP(hipGetLastError());
         k_lvl_nodes<<<blocks_for(n, BS), BS, 0, s>>>(n, keys, leaf_tmp, head, excl, Hs, level, kl, node_base,
                                                      nid, nd_start, nd_count, nd_hmax, nd_wide, nd_box, nd_level,
@@ -1300,35 +1323,43 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     c->n_nodes = node_base;
 
     // ---- leaves in Morton (particle) order ---------------------------------------------------
-    k_leaf_head<<<blocks_for(n, BS), BS, 0, s>>>(n, leaf_tmp, head);
-    SPH_HIP(hipGetLastError());
-    scan_exclusive(c, head, excl, n, nullptr, s);
     const int64_t nl = leaf_base;  // the leaves of all levels, one per run of leaf_tmp
     c->n_leaves = nl;
     int* leaf_of = ensure<int>(c, c->leaf_of, n);
-    // lo2node lives in lf_start's buffer; move it aside before lf_start is written
-    int* lo2 = ensure<int>(c, c->nid, std::max<int64_t>(n, nl));
-    SPH_HIP(hipMemcpyAsync(lo2, lo2node, (size_t)nl * 4, hipMemcpyDeviceToDevice, s));
-    int* lf_start = ensure<int>(c, c->lf_start, nl + 1);
     int* lf_node = ensure<int>(c, c->lf_node, nl);
     int* lf_count = ensure<int>(c, c->lf_count, nl);
     float* lf_hmax = ensure<float>(c, c->lf_hmax, nl);
-    k_leaf_fill<<<blocks_for(n, BS), BS, 0, s>>>(n, head, excl, leaf_tmp, lo2, leaf_of, lf_start, lf_node);
-    SPH_HIP(hipGetLastError());
-    k_leaf_fix<<<blocks_for(nl, BS), BS, 0, s>>>(nl, lf_node, static_cast<int*>(c->nd_count.p),
-                                                 static_cast<unsigned*>(c->nd_hmax.p),
-                                                 static_cast<int*>(c->nd_leaf.p), lf_count, lf_hmax);
-    SPH_HIP(hipGetLastError());
+    int4* nodes = ensure<int4>(c, c->nd_pack, 2 * c->n_nodes);
+    int* lf_start = static_cast<int*>(c->lf_start.p);  // (lo2node's buffer: n + 1)
+    if (c->n_nodes == nl) {
+        k_leaf_top<<<blocks_for(n, BS), BS, 0, s>>>(
+            n, nl, nid, static_cast<int*>(c->nd_start.p), static_cast<int*>(c->nd_count.p),
+            static_cast<unsigned*>(c->nd_hmax.p), static_cast<int*>(c->nd_coord.p), leaf_of, lf_start, lf_node, lf_count,
+            lf_hmax, nodes);
+        SPH_HIP(hipGetLastError());
+    } else {
+        k_leaf_head<<<blocks_for(n, BS), BS, 0, s>>>(n, leaf_tmp, head);
+        SPH_HIP(hipGetLastError());
+        scan_exclusive(c, head, excl, n, nullptr, s);
+        // lo2node lives in lf_start's buffer; move it aside before lf_start is written
+        int* lo2 = ensure<int>(c, c->nid, std::max<int64_t>(n, nl));
+        SPH_HIP(hipMemcpyAsync(lo2, lo2node, (size_t)nl * 4, hipMemcpyDeviceToDevice, s));
+        k_leaf_fill<<<blocks_for(n, BS), BS, 0, s>>>(n, head, excl, leaf_tmp, lo2, leaf_of, lf_start, lf_node);
+        SPH_HIP(hipGetLastError());
+        k_leaf_fix<<<blocks_for(nl, BS), BS, 0, s>>>(nl, lf_node, static_cast<int*>(c->nd_count.p),
+                                                     static_cast<unsigned*>(c->nd_hmax.p),
+                                                     static_cast<int*>(c->nd_leaf.p), lf_count, lf_hmax);
+        SPH_HIP(hipGetLastError());
+        k_tree_pack<<<blocks_for(c->n_nodes, BS), BS, 0, s>>>(
+            c->n_nodes, static_cast<int*>(c->nd_coord.p), static_cast<int*>(c->nd_level.p),
+            static_cast<unsigned*>(c->nd_hmax.p), static_cast<int*>(c->nd_leaf.p), static_cast<int*>(c->nd_child0.p),
+            static_cast<int*>(c->nd_child1.p), lf_count, nodes);
+        SPH_HIP(hipGetLastError());
+    }
 
     // ---- partner lists: their number, and in a tree layout the lists and the items ------------
     uint32_t* p_cnt = ensure<uint32_t>(c, c->p_cnt, nl + 1);
     uint32_t* p_cntd = ensure<uint32_t>(c, c->p_cntd, nl + 1);
-    k_tree_pack<<<blocks_for(c->n_nodes, BS), BS, 0, s>>>(
-        c->n_nodes, static_cast<int*>(c->nd_coord.p), static_cast<int*>(c->nd_level.p),
-        static_cast<unsigned*>(c->nd_hmax.p), static_cast<int*>(c->nd_leaf.p), static_cast<int*>(c->nd_child0.p),
-        static_cast<int*>(c->nd_child1.p), lf_count,
-        ensure<int4>(c, c->nd_pack, 2 * c->n_nodes));
-    SPH_HIP(hipGetLastError());
     const TreeView tv = tree_view(c);
     k_partners<<<(unsigned)blocks_for(nl * 32, PBS), PBS, 0, s>>>(
         nl, 0, lf_node, tv, static_cast<int*>(c->nd_box.p), top, box_top_base, box_G, box_len, p_cnt, p_cntd, nullptr,
@@ -1376,17 +1407,15 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     // no drift since this build; the smallest search radius bounds how far
     // the particles may drift before the cells are rebuilt
     unsigned* drift = ensure<unsigned>(c, c->drift, 4);
-    fill_u32(drift, 0u, 4, s);               // bound, step maximum, (minimum below), non-finite flag
-    fill_u32(drift + 2, 0x7f800000u, 1, s);  // +inf before the minimum
+    k_drift_init<<<1, 4, 0, s>>>(drift);
+    SPH_HIP(hipGetLastError());
     k_min_H<<<(unsigned)std::max<int64_t>(1, std::min<int64_t>(blocks_for(n, BS), 256)), BS, 0, s>>>(n, Hs,
                                                                                                  drift + 2);
     SPH_HIP(hipGetLastError());
     // the shape counters and the smallest radius come back behind an event;
     // the next synchronisation (or finish_build_read) picks them up
-    int64_t* bo = ensure<int64_t>(c, c->build_out, BUILD_OUT_WORDS);
-    k_build_out<<<1, 64, 0, s>>>(ctr, drift + 2, bo);
+    k_build_out<<<1, 64, 0, s>>>(ctr, drift + 2, c->h_build);
     SPH_HIP(hipGetLastError());
-    SPH_HIP(hipMemcpyAsync(c->h_build, bo, BUILD_OUT_WORDS * sizeof(int64_t), hipMemcpyDeviceToHost, s));
     SPH_HIP(hipEventRecord(c->ev_build, s));
     c->build_read_pending = true;
     c->binfo.n_cells = nl;

@@ -174,7 +174,6 @@ struct sph_ctx {
     sph::Buf head, scan1;    // uint32 per particle
     sph::Buf nid;            // int per particle: node at the current level
     // nodes (all levels, level-major)
-    sph::Buf build_out;
     sph::Buf nd_start, nd_count, nd_hmax, nd_wide, nd_child0, nd_child1, nd_leaf, nd_box, nd_level,
         nd_coord;
     int64_t node_cap = 0;
@@ -232,8 +231,8 @@ struct sph_ctx {
     sph::Buf cons64_d;       // double, CONS_SLOTS x 4 per box (plain FP64 form)
     int64_t* h_counters = nullptr;  // pinned host mirror of counters
     // the build's shape counters and smallest search radius come back without
-    // a wait of their own: folded on the device into build_out, copied into
-    // this pinned buffer behind ev_build, read by finish_build_read
+    // a wait of their own: folded by a kernel into this pinned buffer behind
+    // ev_build, read by finish_build_read
     int64_t* h_build = nullptr;
     hipEvent_t ev_build = nullptr;
     bool build_read_pending = false;
