@@ -131,6 +131,7 @@ void sph_destroy(sph_ctx* c)
     if (c->h_build) hipHostFree(c->h_build);
     if (c->ev_build) hipEventDestroy(c->ev_build);
     if (c->h_cons) hipHostFree(c->h_cons);
+    if (c->h_boxes) hipHostFree(c->h_boxes);
     if (c->pass_exec) hipGraphExecDestroy(c->pass_exec);
     if (c->cap_stream) hipStreamDestroy(c->cap_stream);
     delete c;

@@ -996,6 +996,58 @@ __global__ void __launch_bounds__(BS) k_min_H(int64_t n, const float* __restrict
     }
 }
 
+// The tables of boxes between host and device, by kernels on pinned memory: a
+// copy of a few words costs 5 to 10 us each, and a build had eight of them.
+struct BoxTables {
+    int64_t* first;     // n_boxes + 1
+    double* len;        // n_boxes
+    int64_t* top_base;  // n_boxes + 1
+    int64_t* bad;       // 1
+    unsigned* hmax;     // n_boxes
+    int* G;             // n_boxes
+    int* col_base;      // n_boxes + 1
+    uint32_t* level;    // LEVEL_WORDS: a level's counts and the grid's (CT_TOTAL, CT_GRID)
+};
+constexpr int LEVEL_WORDS = 6;
+static_assert(CT_GRID == CT_TOTAL + 2, "the level's counts and the grid's are read together");
+
+// At the start of a build: the boxes (len null: as they are), and zero maxima and
+// counters.
+__global__ void k_build_begin(int nb, BoxTables h, int64_t* __restrict__ box_first, double* __restrict__ box_len,
+                              unsigned* __restrict__ box_hmax, int64_t* __restrict__ ctr)
+{
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (box_len) {
+        if (k <= nb) box_first[k] = h.first[k];
+        if (k < nb) box_len[k] = h.len[k];
+    }
+    if (k < nb) box_hmax[k] = 0u;
+    if (k < CT_COUNT) ctr[k] = 0;
+}
+
+__global__ void k_hmax_out(int nb, const unsigned* __restrict__ box_hmax, const int64_t* __restrict__ ctr, BoxTables h)
+{
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < nb) h.hmax[k] = box_hmax[k];
+    if (k == 0) *h.bad = ctr[CT_BAD_INPUT];
+}
+
+__global__ void k_box_tables(int nb, BoxTables h, int* __restrict__ box_G, int64_t* __restrict__ top_base,
+                             int* __restrict__ col_base)
+{
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < nb) box_G[k] = h.G[k];
+    if (k <= nb) {
+        top_base[k] = h.top_base[k];
+        col_base[k] = h.col_base[k];
+    }
+}
+
+__global__ void k_level_out(const uint32_t* __restrict__ d, BoxTables h)
+{
+    if (threadIdx.x < LEVEL_WORDS) h.level[threadIdx.x] = d[threadIdx.x];
+}
+
 // Bound, step maximum, smallest search radius (before its minimum), non-finite flag.
 __global__ void k_drift_init(unsigned* drift) { drift[threadIdx.x] = threadIdx.x == 2 ? 0x7f800000u : 0u; }
 
@@ -1028,6 +1080,41 @@ int ceil_log2(uint64_t v)
 }  // namespace
 
 namespace sph {
+
+// The pinned tables, for the context's number of boxes. Nothing of an earlier build
+// still reads what the next one writes here: k_build_begin's part is read before the
+// wait for k_hmax_out, k_box_tables' before the wait for the first level's counts
+// or, if the build ended early, before the next wait for k_hmax_out.
+static BoxTables box_tables(sph_ctx* c)
+{
+    const size_t nb = (size_t)c->n_boxes;
+    if (c->h_boxes_cap < nb) {
+        if (c->h_boxes) SPH_HIP(hipHostFree(c->h_boxes));
+        c->h_boxes = nullptr;
+        c->h_boxes_cap = 0;
+        SPH_HIP(hipHostMalloc((void**)&c->h_boxes, (nb + 1) * 36 + LEVEL_WORDS * 4, hipHostMallocDefault));
+        c->h_boxes_cap = nb;
+    }
+    const size_t m = c->h_boxes_cap + 1;
+    BoxTables t;
+    t.first = reinterpret_cast<int64_t*>(c->h_boxes);
+    t.top_base = t.first + m;
+    t.len = reinterpret_cast<double*>(t.top_base + m);  // the last word of each: spare, or `bad`
+    t.bad = reinterpret_cast<int64_t*>(t.len + m - 1);
+    t.hmax = reinterpret_cast<unsigned*>(t.len + m);
+    t.G = reinterpret_cast<int*>(t.hmax + m);
+    t.col_base = t.G + m;
+    t.level = reinterpret_cast<uint32_t*>(t.col_base + m);
+    return t;
+}
+
+static void build_begin(sph_ctx* c, const BoxTables& bt, int64_t* box_first, double* box_len, unsigned* box_hmax,
+                        int64_t* ctr, hipStream_t s)
+{
+    k_build_begin<<<blocks_for(std::max<int64_t>(c->n_boxes + 1, CT_COUNT), BS), BS, 0, s>>>(
+        c->n_boxes, bt, box_first, box_len, box_hmax, ctr);
+    SPH_HIP(hipGetLastError());
+}
 
 static TreeView tree_view(sph_ctx* c)
 {
@@ -1112,19 +1199,18 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
 
     // ---- largest search radius per box (k_wrap / k_box_hmax ran) -> top grid --------
     unsigned* box_hmax = static_cast<unsigned*>(c->box_hmax.p);
-    std::vector<unsigned> hm(nb);
-    int64_t bad = 0;
-    SPH_HIP(hipMemcpyAsync(hm.data(), box_hmax, (size_t)nb * 4, hipMemcpyDeviceToHost, s));
-    SPH_HIP(hipMemcpyAsync(&bad, &ctr[CT_BAD_INPUT], 8, hipMemcpyDeviceToHost, s));
+    const BoxTables bt = box_tables(c);
+    k_hmax_out<<<blocks_for(nb, BS), BS, 0, s>>>(nb, box_hmax, ctr, bt);
+    SPH_HIP(hipGetLastError());
     SPH_HIP(hipStreamSynchronize(s));
-    SPH_REQUIRE(bad == 0, SPH_E_ARG, "non-finite position or non-positive/non-finite h_guess");
+    SPH_REQUIRE(*bt.bad == 0, SPH_E_ARG, "non-finite position or non-positive/non-finite h_guess");
     c->h_box_G.assign(nb, 0);
     c->h_box_top_base.assign(nb + 1, 0);
     uint64_t maxG3 = 1;
     for (int b = 0; b < nb; ++b) {
         const int64_t cnt = c->h_box_first[b + 1] - c->h_box_first[b];
         float H;
-        std::memcpy(&H, &hm[b], 4);
+        std::memcpy(&H, &bt.hmax[b], 4);
         const double L = c->h_box_len[b];
         int G = 3;
         if (cnt > 0) {
@@ -1144,10 +1230,13 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     // columns of top cells of each box, for a grid layout, which needs at least
     // four cells per side (the frame of an item reaches a cell and a half from
     // its centre) and a table of fine cells in proportion to the particles
-    std::vector<int> col_base_h(nb + 1, 0);
     bool grid_ok = true;
+    bt.col_base[0] = 0;
+    bt.top_base[0] = 0;
     for (int b = 0; b < nb; ++b) {
-        col_base_h[b + 1] = col_base_h[b] + c->h_box_G[b] * c->h_box_G[b];
+        bt.col_base[b + 1] = bt.col_base[b] + c->h_box_G[b] * c->h_box_G[b];
+        bt.top_base[b + 1] = c->h_box_top_base[b + 1];
+        bt.G[b] = c->h_box_G[b];
         if (c->h_box_first[b + 1] > c->h_box_first[b] && c->h_box_G[b] < 4) grid_ok = false;
     }
     c->bits_box = nb > 1 ? ceil_log2((uint64_t)nb) : 0;
@@ -1156,9 +1245,9 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     SPH_REQUIRE(c->levels >= 1, SPH_E_ARG, "too many boxes or top cells for the key layout");
     int* box_G = ensure<int>(c, c->box_G, nb);
     int64_t* box_top_base = ensure<int64_t>(c, c->box_top_base, nb + 1);
-    SPH_HIP(hipMemcpyAsync(box_G, c->h_box_G.data(), (size_t)nb * 4, hipMemcpyHostToDevice, s));
-    SPH_HIP(hipMemcpyAsync(box_top_base, c->h_box_top_base.data(), (size_t)(nb + 1) * 8,
-                           hipMemcpyHostToDevice, s));
+    int* col_base = ensure<int>(c, c->col_base, nb + 1);
+    k_box_tables<<<blocks_for(nb + 1, BS), BS, 0, s>>>(nb, bt, box_G, box_top_base, col_base);
+    SPH_HIP(hipGetLastError());
 
     // ---- keys and sort -------------------------------------------------------------------
     // Sorted by box, top cell and fine cell in z first (as many fine cells, up to
@@ -1171,7 +1260,7 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     }
     const int64_t n_fine = c->n_top << c->fzb;
     grid_ok = grid_ok && n_fine <= 16 * n + 4096 && n_fine < (int64_t)1 << 30;
-    const int n_cols = col_base_h[nb];
+    const int n_cols = bt.col_base[nb];
     KeyLayout kl{c->bits_top, c->levels, c->fzb};
     uint64_t* keys = ensure<uint64_t>(c, c->keys, n);
     uint64_t* keys_alt = ensure<uint64_t>(c, c->keys_alt, n);
@@ -1187,8 +1276,6 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     // ---- the items of a grid layout (used if no top cell splits) --------------------------------
     uint32_t* d_grid = reinterpret_cast<uint32_t*>(&ctr[CT_GRID]);
     if (grid_ok) {
-        int* col_base = ensure<int>(c, c->col_base, nb + 1);
-        SPH_HIP(hipMemcpyAsync(col_base, col_base_h.data(), (size_t)(nb + 1) * 4, hipMemcpyHostToDevice, s));
         int* starts = ensure<int>(c, c->starts, (size_t)n_fine + 1);
         uint32_t* it_start = ensure<uint32_t>(c, c->it_start, (size_t)n_cols + 1);
         int* box_item = ensure<int>(c, c->box_item, nb + 1);
@@ -1288,10 +1375,10 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
         SPH_HIP(hipGetLastError());
         k_lvl_assign<<<blocks_for(n, BS), BS, 0, s>>>(n, nid, nd_leaf, leaf_tmp);
         SPH_HIP(hipGetLastError());
-        uint32_t mk[6] = {0u, 0u, 0u, 0u, 0u, 0u};  // d_M, d_K, -, -, d_grid
-        static_assert(CT_GRID == CT_TOTAL + 2, "the level's counts and the grid's travel in one copy");
-        SPH_HIP(hipMemcpyAsync(mk, d_M, sizeof(mk), hipMemcpyDeviceToHost, s));
+        k_level_out<<<1, 64, 0, s>>>(d_M, bt);
+        SPH_HIP(hipGetLastError());
         SPH_HIP(hipStreamSynchronize(s));
+        const uint32_t* mk = bt.level;  // d_M, d_K, -, -, d_grid
         const int64_t M = mk[0], K = mk[1];
         if (level == 0) {
             c->uni = grid_ok && K == M && mk[5] == 0u;
@@ -1457,15 +1544,15 @@ void build_cells(sph_ctx* c, int32_t n_boxes, const int64_t* box_first, const do
     c->h_box_len.assign(box_len, box_len + n_boxes);
     int64_t* bf = ensure<int64_t>(c, c->box_first, n_boxes + 1);
     double* bl = ensure<double>(c, c->box_len, n_boxes);
-    SPH_HIP(hipMemcpyAsync(bf, box_first, (size_t)(n_boxes + 1) * 8, hipMemcpyHostToDevice, s));
-    SPH_HIP(hipMemcpyAsync(bl, box_len, (size_t)n_boxes * 8, hipMemcpyHostToDevice, s));
     ensure<int64_t>(c, c->counters, CT_COUNT);
     double* pw = ensure<double>(c, c->pos_w, 3 * n);
     float* hg = ensure<float>(c, c->hguess, n);
     unsigned* box_hmax = ensure<unsigned>(c, c->box_hmax, n_boxes);
     int64_t* ctr = static_cast<int64_t*>(c->counters.p);
-    SPH_HIP(hipMemsetAsync(box_hmax, 0, (size_t)n_boxes * 4, s));
-    SPH_HIP(hipMemsetAsync(ctr, 0, CT_COUNT * 8, s));
+    const BoxTables bt = box_tables(c);
+    std::copy(box_first, box_first + n_boxes + 1, bt.first);
+    std::copy(box_len, box_len + n_boxes, bt.len);
+    build_begin(c, bt, bf, bl, box_hmax, ctr, s);
     k_wrap<<<blocks_for(n, WBS), WBS, 0, s>>>(n, pos, bf, n_boxes, bl, h_guess, pw, hg, box_hmax,
                                             (float)c->prm.h_margin, ctr);
     SPH_HIP(hipGetLastError());
@@ -1516,8 +1603,7 @@ void rebuild_cells(sph_ctx* c, const float* h_caller, hipStream_t s)
     int64_t* ctr = static_cast<int64_t*>(c->counters.p);
     if (h_caller && h_caller != hg)  // null: the guesses of the last build
         SPH_HIP(hipMemcpyAsync(hg, h_caller, (size_t)c->n * 4, hipMemcpyDeviceToDevice, s));
-    SPH_HIP(hipMemsetAsync(box_hmax, 0, (size_t)c->n_boxes * 4, s));
-    SPH_HIP(hipMemsetAsync(ctr, 0, CT_COUNT * 8, s));
+    build_begin(c, box_tables(c), nullptr, nullptr, box_hmax, ctr, s);
     k_box_hmax<<<blocks_for(c->n, WBS), WBS, 0, s>>>(c->n, static_cast<int64_t*>(c->box_first.p), c->n_boxes, hg,
                                                    box_hmax, (float)c->prm.h_margin, ctr);
     SPH_HIP(hipGetLastError());

@@ -236,6 +236,8 @@ struct sph_ctx {
     int64_t* h_build = nullptr;
     hipEvent_t ev_build = nullptr;
     bool build_read_pending = false;
+    char* h_boxes = nullptr;        // pinned tables of the boxes (build.hip), h_boxes_cap of them
+    size_t h_boxes_cap = 0;
     double* h_cons = nullptr;       // pinned host landing buffer of the conservation sums
     size_t h_cons_cap = 0;          // doubles it holds
 
