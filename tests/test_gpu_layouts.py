@@ -1,0 +1,90 @@
+"""The two layouts of the work items and the edges of the rules that choose
+between them and between the list lengths, against the FP64 oracle.
+
+A grid layout takes boxes of at least four top cells per side none of which
+splits, and whose items of 16 particles span few enough cells; everything else
+is a tree. The density lists have room for 80 to 448 entries by the number of
+neighbours and the margin; a particle whose list is too short, or whose root
+lies beyond it, is taken again with more room. Tolerances: parity.TOL32, which
+holds for every FP32 result whatever the cells.
+"""
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from parity import TOL32, assert_within, errors
+
+pytestmark = pytest.mark.gpu
+
+
+def _lattice(side, seed):
+    return workloads.lattice_box(side, [1508, 950, seed], jitter=0.3, u=1.0, vel_sigma=0.2)
+
+
+def _clustered():
+    return workloads.clustered(n_uniform=3000, n_spheres=3, per_sphere=900)
+
+
+def _boxes():
+    """Boxes of other lengths, one empty, one too small for a grid's sides."""
+    parts, first, lens = [], [0], []
+    for k, (side, L) in enumerate([(12, 2.5), (0, 1.0), (13, 0.3), (17, 40.0)]):
+        lens.append(L)
+        if side:
+            d = _lattice(side, 20 + k)
+            d["pos"] = d["pos"] * L
+            d["h0"] = (d["h0"] * L).astype(np.float32)
+            parts.append(d)
+        first.append(first[-1] + (side**3 if side else 0))
+    out = {k: np.concatenate([p[k] for p in parts], axis=0) for k in ("pos", "vel", "mass", "u", "h0")}
+    out["box_first"] = np.asarray(first, dtype=np.int64)
+    out["box_len"] = np.asarray(lens, dtype=np.float64)
+    return out
+
+
+# set, neighbours, factor on the guesses, masses from U(0.5, 1.5)
+CASES = {
+    "three_cells": (lambda: _lattice(11, 1), 48, 1.0, False),      # tree: G = 3
+    "four_cells": (lambda: _lattice(12, 2), 48, 1.0, False),       # the smallest grid
+    "items_too_long": (lambda: _lattice(8, 3), 16, 1.0, False),    # 16 particles span a column of four cells
+    "few_neighbours": (lambda: _lattice(17, 4), 16, 1.0, False),
+    "lists_128": (lambda: _lattice(15, 5), 60, 1.0, False),
+    "lists_240": (lambda: _lattice(18, 6), 100, 1.0, False),
+    "lists_448": (lambda: _lattice(21, 7), 200, 1.0, False),
+    "guess_low": (lambda: _lattice(15, 8), 48, 0.85, False),       # every root beyond the first list
+    "guess_high": (lambda: _lattice(20, 9), 48, 1.3, False),       # lists that do not fit
+    "masses": (lambda: _lattice(15, 10), 40, 1.0, True),
+    "boxes": (_boxes, 48, 1.0, False),
+    "tree_few": (_clustered, 24, 1.0, False),
+    "tree_34": (_clustered, 34, 1.0, False),
+    "tree_low": (_clustered, 48, 0.85, False),
+    "tree_high": (_clustered, 40, 1.3, False),
+    "tree_masses": (_clustered, 48, 1.0, True),
+    "tree_240": (_clustered, 80, 1.0, False),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_layouts_match_oracle(gpu_lib, name):
+    make, n_ngb, guess, mixed = CASES[name]
+    d = make()
+    n = d["pos"].shape[0]
+    d["h0"] = (d["h0"] * guess * (n_ngb / 48.0) ** (1.0 / 3.0)).astype(np.float32)
+    if mixed:
+        d["mass"] = (d["mass"] * np.random.default_rng([1508, 951]).uniform(0.5, 1.5, n)).astype(np.float32)
+    print("case", name, "N", n, flush=True)
+    ctx = gpu_lib.Context(0, n_ngb=float(n_ngb))
+    try:
+        g = gpu_lib.run_workload(ctx, d)
+    finally:
+        ctx.close()
+    r = oracle.run(d, n_ngb=float(n_ngb))
+    e = errors(g, r)
+    print(name, e, g["stats_density"], flush=True)
+    assert_within(e, TOL32, name)
+    # counts: equal up to pairs within FP32 rounding of r = h
+    n_d, n_f = int(r["nngb"].sum()), int(r["npair"].sum())
+    assert abs(g["stats_density"]["interactions_density"] - n_d) <= 1e-5 * n_d + 2
+    assert abs(g["stats_force"]["interactions_force"] - n_f) <= 1e-5 * n_f + 2
