@@ -14,8 +14,8 @@
 // tree as the end of section 3.1 describes -- with the periodic image of each.
 //
 // All of it runs on the GPU: integer keys, a radix sort, one pass of small
-// kernels per tree level, and a stack-based walk per (leaf, surrounding top
-// cell). The host only reads back counts to size buffers.
+// kernels per tree level, and one walk per leaf over a stack of nodes in LDS. The
+// host only reads back counts to size buffers.
 #include "common.h"
 #include "tiles.h"
 
@@ -180,7 +180,9 @@ __global__ void k_keys(int64_t n, const double* __restrict__ pos_w, const int64_
 // Particles sorted by box, column of top cells (x, y), z in fine cells. Work
 // items take them 16 at a time along each column, whatever cells they are in:
 // cells of a grid one search radius wide hold 8 to 27 particles, and items of
-// single cells left a third of the lanes without a particle.
+// single cells left a third of the lanes without a particle (a pass over 256
+// boxes: 4.97 ms with one wavefront per cell, 5.12 ms with cells in items of at
+// most 16, 3.47 ms along columns; gravity 1.20, 1.36 and 0.72 ms).
 
 // First particle of every fine cell (starts[n_fine] = n): the thread of a
 // particle that begins a cell also fills the empty cells before it.
@@ -1229,7 +1231,11 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     c->n_top = c->h_box_top_base[nb];
     // columns of top cells of each box, for a grid layout, which needs at least
     // four cells per side (the frame of an item reaches a cell and a half from
-    // its centre) and a table of fine cells in proportion to the particles
+    // its centre, and with three the cells on both sides are the same ones) and a
+    // table of fine cells in proportion to the particles. Where a top cell splits
+    // the radii differ so much that the columns would hold many candidates for
+    // nothing: with the top cells kept whole a pass over 32768 clustered particles
+    // takes 607 us, split (the tree) 558; a log-normal set of 64000 268 and 190
     bool grid_ok = true;
     bt.col_base[0] = 0;
     bt.top_base[0] = 0;

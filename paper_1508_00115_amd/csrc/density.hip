@@ -30,6 +30,16 @@
 // and masses, or by re-testing every candidate, 16 lanes per particle. A
 // particle whose root lies beyond its search radius H is flagged; the host
 // rebuilds the cells around a larger guess and solves it again.
+//
+// What bounds it: the issue of vector instructions, about 145 per particle on a
+// grid, where one leaves every 4.0 cycles of a SIMD (they cost 2.6 to 4.4 by kind)
+// with four wavefronts there; a wavefront's cycles go 14% to staging, 30% to the
+// filter and the lists, 21% to Newton and a third to the item's start and end. In a
+// tree (265 per particle, three wavefronts, by LDS) one leaves every 6: the walk of the candidates
+// takes 38%. Measured, here / with one wavefront per cell and no matrix cores:
+// 256 boxes 1.65 / 2.60 ms, clustered 2^20 0.75 / 0.98 ms, log-normal 2^24 11.5 /
+// 11.8 ms (the last two with the re-scans the older form left). Tiles of 256, 192 and
+// 128 candidates: 2.09, 1.91 and 1.72 ms on the boxes (occupancy), 64: 1.95.
 #include "common.h"
 #include "tiles.h"
 

@@ -7,15 +7,22 @@
 // packed with position, h^2, velocity, mass and 1/h into three float4 per
 // particle: (x, y, z, h^2), (v, m), (rho, Phi, c, 1/h); x, y, z as the cell
 // layout stores them (see Item in tiles.h).
-// The loop then runs one wavefront per leaf cell exactly like the density
-// loop: the cell's neighbour particles are staged into LDS in chunks and each
-// particle of the cell (several lanes per particle for small cells) gathers
-// the terms of every pair inside max(h_i, h_j). The gather form evaluates each
-// pair from both sides, so no two waves write the same particle and the result
-// does not depend on scheduling. Per-box momentum and energy rates are summed
-// in FP64: each wave stores its cell's share (plain stores, no atomics) and a
-// second kernel adds the shares of each box's cells in a fixed order, so the
-// sums are also reproducible.
+// The loop then runs one wavefront per item of at most 16 particles like the
+// density loop: the candidates are staged into an LDS tile, the matrix cores
+// propose the pairs inside max(h_i, h_j) (two tables, one per radius), and the
+// four lanes of a particle gather the terms of every fourth pair of its list.
+// The gather form evaluates each pair from both sides, so no two waves write the
+// same particle and the result does not depend on scheduling. Per-box momentum
+// and energy rates are summed in FP64: each wave stores its item's share (plain
+// stores, no atomics) and a second kernel adds the shares of each box's items in a
+// fixed order, so the sums are also reproducible.
+//
+// What bounds it: the issue of vector instructions (one per 3.6 cycles of a SIMD on
+// a grid, 4.4 in a tree), most of them in the pair loop, whose lists' lengths
+// differ between particles. Measured, here / with one wavefront per cell and
+// every candidate tested on the vector units: 256 boxes 1.57 / 2.25 ms, clustered
+// 2^20 0.60 / 0.83 ms, log-normal 2^24 8.3 / 10.7 ms. Tiles of 192 candidates
+// instead of 128: 1.91 against 1.64 ms on the boxes (LDS holds fewer wavefronts).
 //
 // With the Balsara switch (not in the paper; the Gadget-2 form) the same loop
 // first runs in a gather mode that sums the velocity divergence and curl of
@@ -41,7 +48,7 @@ constexpr int BS = 64;     // one wavefront per block (finest LDS allocation)
 constexpr int WAVES = BS / 64;
 constexpr int FCAP = 128;  // candidates per LDS tile
 constexpr int LCAP = 80;   // entries of a particle's list (64 candidates always fit)
-constexpr int LSEG = LCAP;
+constexpr int LSEG = LCAP;  // (20 words: the lists of 16 particles start in different banks)
 constexpr int NWORDS = (FCAP + 127) / 128;  // hit words per lane
 static_assert(FCAP % 64 == 0 && FCAP <= 256, "whole steps of the filter; byte-sized candidate numbers");
 

