@@ -98,7 +98,7 @@ typedef struct {
                              density loop's list-building tests and listed
                              candidates (sph_stats.tests_density,
                              listed_density), in a kernel instance that takes
-                             a few percent longer */
+                             about half as long again (a walk of its own) */
     int32_t schedule;     /* how cells reach wavefronts: 0 = hardware dispatch,
                              one cell per wavefront, XCD-contiguous blocks;
                              1 = persistent wavefronts popping per-XCD queues */

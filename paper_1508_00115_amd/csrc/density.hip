@@ -336,6 +336,29 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
         unsigned todo = (unsigned)__ballot(lane < ni && A.st_s[ic] == ST_ACTIVE);
         unsigned wide = 0u, scan = 0u;
         int n_flag = 0;
+        if constexpr (DETAIL) {
+            // the candidates inside H (the lists need not reach it): a walk of its own
+            const float Hp = (todo >> pc) & 1u ? Hc : 0.0f, H2 = Hp * Hp;
+            int inside = 0, all;
+            Slots<1> S;
+            walk_start(w, A.cell, it, scratch, uniform_f(group_max(Hp, 16)), false);
+            while (walk_next<1>(w, A.cell, it, scratch, S)) {
+                const float4 v = A.jd[S.src[0]];
+                wave_sync_lds();
+                t0[lane] = S.ok[0] ? make_float4(item_coord<UNI>(v.x, it.ox, it.sh, it.sl, S.sh[0].x),
+                                                 item_coord<UNI>(v.y, it.oy, it.sh, it.sl, S.sh[0].y),
+                                                 item_coord<UNI>(v.z, it.oz, it.sh, it.sl, S.sh[0].z), 0.0f)
+                                   : make_float4(1.0e15f, 0.0f, 0.0f, 0.0f);
+                wave_sync_lds();
+                for (int k = 0; k < 16; ++k) {
+                    const float4 q = t0[4 * k + gc];
+                    const float dx = xc - q.x, dy = yc - q.y, dz = zc - q.z;
+                    inside += fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < H2 ? 1 : 0;
+                }
+            }
+            wave_excl_scan(inside, all);
+            listed_acc += all;
+        }
 
         for (int round = 0; todo; ++round) {
             // ---- this round's particles, and which one this lane works for -------------------
@@ -399,7 +422,6 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                     C = {c, c, c, c};
                 }
                 int T = 0, kept = 0, nk = 0;  // entries of this column's particle; candidates kept; in the tile
-                int inside = 0;               // (DETAIL) lane p: candidates of particle p inside its H
                 bool differs = false;
                 float cM0t = 0.f, cM0u = 0.f, cM1t = 0.f, cM1u = 0.f;
                 Slots<U> S;
@@ -443,16 +465,6 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
 #pragma unroll
                             for (int u = 0; u < U; ++u) {
                                 differs |= S.ok[u] && p0[u].w != m0;
-                                if constexpr (DETAIL) {
-                                    for (int p = 0; p < (round == 0 && !acc ? ni : 0); ++p) {
-                                        const float Hp = __shfl(inb ? Hc : 0.0f, p, 64);
-                                        const float dx = x[u] - __shfl(xc, p, 64), dy = y[u] - __shfl(yc, p, 64),
-                                                    dz = z[u] - __shfl(zc, p, 64);
-                                        const int k =
-                                            wave_count(S.ok[u] && fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < Hp * Hp);
-                                        inside += lane == p ? k : 0;
-                                    }
-                                }
                                 if ((m[u] >> lane) & 1u) {
                                     const int d = nk + lanes_below(m[u]);
                                     const float fx = (x[u] - it.bx) * fs, fy = (y[u] - it.by) * fs,
@@ -559,13 +571,6 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                 const unsigned over = (unsigned)__ballot(inb && T > room) & 0xffffu;
                 if (round > 0) scan |= over;  // (no room here either)
                 if (round == 0) n_scan += wave_count(lane < 16 && inb && T > LIST_MOST);  // walked again
-                if constexpr (DETAIL) {
-                    if (round == 0) {
-                        int v = lane < 16 && inb ? inside : 0;
-                        for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-                        listed_acc += __builtin_amdgcn_readfirstlane(v);
-                    }
-                }
                 const int Tq = __shfl(T, pq & 15, 64);
                 solved = mine && Tq <= room;
                 many = Tq > LIST_MOST;

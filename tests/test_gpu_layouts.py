@@ -88,3 +88,28 @@ def test_layouts_match_oracle(gpu_lib, name):
     n_d, n_f = int(r["nngb"].sum()), int(r["npair"].sum())
     assert abs(g["stats_density"]["interactions_density"] - n_d) <= 1e-5 * n_d + 2
     assert abs(g["stats_force"]["interactions_force"] - n_f) <= 1e-5 * n_f + 2
+
+
+@pytest.mark.parametrize("name", ["four_cells", "tree_few"])
+@pytest.mark.parametrize("margin", [1.05, 1.26])
+def test_listed_counts(gpu_lib, name, margin):
+    """timing = 2 counts every particle inside each search radius, also where
+    the lists stop short of it (wide margins) or the walk leaves out what the
+    lists cannot reach (trees)."""
+    import torch
+    from scipy.spatial import cKDTree
+    d = CASES[name][0]()
+    ctx = gpu_lib.Context(0, timing=2, h_margin=margin)
+    try:
+        # guesses at the roots, so that nothing is rebuilt
+        h0 = torch.from_numpy(oracle.run(d)["h"].astype(np.float32)).cuda()
+        ctx.build_cells(torch.from_numpy(d["pos"]).cuda(), h0, d["box_first"], d["box_len"])
+        st = ctx.density(torch.from_numpy(d["mass"]).cuda(), h0.clone())["stats"]
+    finally:
+        ctx.close()
+    H = (np.float32(margin) * h0.cpu().numpy()).astype(np.float64)
+    tree = cKDTree(np.mod(d["pos"], 1.0), boxsize=1.0)
+    lo, hi = (int(tree.query_ball_point(np.mod(d["pos"], 1.0), H * s, return_length=True).sum())
+              for s in (1.0 - 1e-5, 1.0 + 1e-5))
+    print(name, margin, st, lo, hi, flush=True)
+    assert st["rebuilds"] == 0 and lo <= st["listed_density"] <= hi
