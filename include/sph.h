@@ -99,14 +99,17 @@ typedef struct {
                              candidates (sph_stats.tests_density,
                              listed_density), in a kernel instance that takes
                              about half as long again (a walk of its own) */
-    int32_t schedule;     /* how cells reach wavefronts: 0 = hardware dispatch,
-                             one cell per wavefront, XCD-contiguous blocks;
-                             1 = persistent wavefronts popping per-XCD queues */
-    int32_t queue_batch;  /* cells per queue pop when schedule = 1 (4) */
+    int32_t schedule;     /* how work items (up to 16 particles) reach wavefronts:
+                             0 = hardware dispatch, one item per wavefront,
+                             XCD-contiguous blocks; 1 = persistent wavefronts
+                             popping per-XCD queues */
+    int32_t queue_batch;  /* items per queue pop when schedule = 1 (4) */
     int32_t tile_cap;     /* accepted (128, 256 or 512; 128) and without effect: the
                              density kernel stages every item's candidates
                              through one tile size */
-    int32_t cell_order;   /* order cells reach wavefronts: 0 = by decreasing cost,
+    int32_t cell_order;   /* order items reach wavefronts (where a top cell splits;
+                             otherwise along the columns of cells in any case):
+                             0 = by decreasing cost,
                              dealt out to the 8 XCDs (balance; default);
                              1 = Morton order, a contiguous range per XCD
                              (neighbouring cells share an XCD's L2);

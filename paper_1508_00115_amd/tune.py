@@ -10,9 +10,10 @@ legal cell layout):
     cell_ratio   smallest cell width below the top grid, in search radii
     leaf_target  cells holding more particles than this are split
     schedule     hardware dispatch or persistent per-XCD queues
-    tile_cap     candidates the density kernel keeps resident in LDS
-    cell_order   cells by decreasing cost (balance), in Morton order (L2 reuse), or
-                 Morton ranges per XCD each ordered by cost
+    tile_cap     accepted and without effect
+    cell_order   work items by decreasing cost (balance), in Morton order (L2
+                 reuse), or Morton ranges per XCD each ordered by cost; without
+                 effect where no top cell splits (columns of cells, in order)
 
 Each setting is timed on the caller's particles as whole density + force
 passes (sph_pass, after a warm-up, HIP events around the calls); the fastest
