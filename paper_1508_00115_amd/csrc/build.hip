@@ -285,8 +285,12 @@ __global__ void k_fix_fill(int64_t n, const uint32_t* __restrict__ perm, const d
     xfix[p] = make_int4(v[0], v[1], v[2], 0);
 }
 
-// As k_cell_pbox for a grid layout: the box's centre in 32-bit fractions.
-__global__ void __launch_bounds__(256) k_fix_pbox(int64_t n_items, const int4* __restrict__ cells,
+// As k_cell_pbox for a grid layout: the box's centre in 32-bit fractions. The
+// particles are measured from the middle of the item's cells, which no particle is
+// half the box away from (an item spans at most G - 2 of G cells): differences from
+// one of the particles would wrap in an item longer than half the box, and the frame
+// around the wrapped box would tear its pairs apart.
+__global__ void __launch_bounds__(256) k_fix_pbox(int64_t n_items, const int4* __restrict__ cells, int fzb,
                                                   const int4* __restrict__ xfix, const float* __restrict__ Hs,
                                                   float4* __restrict__ pbox)
 {
@@ -295,16 +299,22 @@ __global__ void __launch_bounds__(256) k_fix_pbox(int64_t n_items, const int4* _
     const bool live = it < n_items;
     const int4 c0 = live ? cells[2 * it] : make_int4(0, 0, 0, 0);
     const int ni = c0.y & 0xff;
-    const int4 x0 = live ? xfix[c0.x] : make_int4(0, 0, 0, 0);
-    int lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
-    float H = 0.0f;
-    if (sub < ni) {
-        const int4 x = xfix[c0.x + sub];
-        lo[0] = hi[0] = (int)((unsigned)x.x - (unsigned)x0.x);
-        lo[1] = hi[1] = (int)((unsigned)x.y - (unsigned)x0.y);
-        lo[2] = hi[2] = (int)((unsigned)x.z - (unsigned)x0.z);
-        H = Hs[c0.x + sub];
+    unsigned x0[3] = {0u, 0u, 0u};
+    if (live) {
+        const unsigned G = (unsigned)(c0.y >> 8);
+        const unsigned x2 = 2u * (unsigned)(c0.z & 0xffff) + 1u, y2 = 2u * (unsigned)(c0.z >> 16) + 1u,
+                       z2 = (unsigned)(c0.w & 0xffff) + (unsigned)(c0.w >> 16) + 1u;  // twice the middle
+        x0[0] = (unsigned)(((uint64_t)x2 << 31) / G);
+        x0[1] = (unsigned)(((uint64_t)y2 << 31) / G);
+        x0[2] = (unsigned)(((uint64_t)z2 << 31) / (G << fzb));
     }
+    // (lanes past the item's particles repeat its first)
+    const int4 x = live ? xfix[c0.x + (sub < ni ? sub : 0)] : make_int4(0, 0, 0, 0);
+    int lo[3], hi[3];
+    lo[0] = hi[0] = (int)((unsigned)x.x - x0[0]);
+    lo[1] = hi[1] = (int)((unsigned)x.y - x0[1]);
+    lo[2] = hi[2] = (int)((unsigned)x.z - x0[2]);
+    float H = live && sub < ni ? Hs[c0.x + sub] : 0.0f;
     for (int o = 8; o >= 1; o >>= 1) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -321,8 +331,7 @@ __global__ void __launch_bounds__(256) k_fix_pbox(int64_t n_items, const int4* _
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const long long mid = ((long long)lo[a] + (long long)hi[a]) >> 1;
-            const unsigned base = (unsigned)(a == 0 ? x0.x : a == 1 ? x0.y : x0.z);
-            o[a] = base + (unsigned)mid;
+            o[a] = x0[a] + (unsigned)mid;
             h[a] = (float)((double)((long long)hi[a] - mid) * u) * 1.00001f;
         }
         pbox[2 * it] = make_float4(__int_as_float((int)o[0]), __int_as_float((int)o[1]), __int_as_float((int)o[2]), H);
@@ -1591,7 +1600,7 @@ void cell_boxes(sph_ctx* c, hipStream_t s)
     float4* pbox = ensure<float4>(c, c->cell_pbox, 2 * ni);
     if (ni == 0) return;
     if (c->uni)
-        k_fix_pbox<<<blocks_for(16 * ni, 256), 256, 0, s>>>(ni, static_cast<int4*>(c->cells.p),
+        k_fix_pbox<<<blocks_for(16 * ni, 256), 256, 0, s>>>(ni, static_cast<int4*>(c->cells.p), c->fzb,
                                                            static_cast<int4*>(c->xfix.p),
                                                            static_cast<float*>(c->Hs.p), pbox);
     else

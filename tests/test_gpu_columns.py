@@ -1,0 +1,112 @@
+"""Grid layouts with few particles along a column, against the FP64 oracle.
+
+A grid layout cuts every column of top cells into items of at most 16
+consecutive particles. Where the columns are sparse (few neighbours asked for, or
+a body in an otherwise empty box) 16 of them lie over much of the box, which the
+frames of the items have to cover without tearing a pair apart. Tolerances:
+parity.TOL32, and those of the near-field gravity tests.
+"""
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from oracle import gravity as og
+from parity import TOL32, assert_within, errors
+from test_gpu_gravity import TOL, _window_free
+
+pytestmark = pytest.mark.gpu
+
+
+def _body(n, inside, seed):
+    """Points of an n^3 jittered lattice in the unit box for which inside(x) holds
+    (x in lattice spacings), the rest of the box empty."""
+    rng = np.random.default_rng([1508, 960, seed])
+    x = np.stack(np.meshgrid(*[np.arange(n) + 0.5] * 3, indexing="ij"), axis=-1).reshape(-1, 3)
+    p = (x + rng.uniform(-0.2, 0.2, x.shape))[inside(x)]
+    m = p.shape[0]
+    return {"pos": np.mod(p / n, 1.0), "vel": rng.normal(0.0, 0.2, (m, 3)).astype(np.float32),
+            "mass": np.full(m, 1.0 / n**3, np.float32), "u": np.ones(m, np.float32),
+            "h0": np.full(m, np.cbrt(3.0 * 48.0 / (4.0 * np.pi)) / n, np.float32),
+            "box_first": np.array([0, m], np.int64), "box_len": np.array([1.0])}
+
+
+def _cylinder(n, radius):
+    return _body(n, lambda x: ((x[:, :2] - n / 2) ** 2).sum(1) < radius * radius, n)
+
+
+# set, neighbours, h_margin
+SETS = {
+    "lattice_16": (lambda: workloads.lattice_box(16, [1508, 960, 0], jitter=0.2, vel_sigma=0.2), 12.0, 1.1),
+    "lattice_13": (lambda: workloads.lattice_box(13, [1508, 960, 2], jitter=0.3, vel_sigma=0.2), 12.0, 1.05),
+    "cylinder_24": (lambda: _cylinder(24, 7), 48.0, 1.26),
+    "slab_14": (lambda: _body(14, lambda x: x[:, 0] < 4, 3), 48.0, 1.05),
+}
+
+
+def _set(name):
+    """The set with its smoothing lengths for guesses (so no cells are rebuilt),
+    and the oracle's results."""
+    make, n_ngb, margin = SETS[name]
+    d = make()
+    d["h0"] = (d["h0"] * np.cbrt(n_ngb / 48.0)).astype(np.float32)
+    r = oracle.run(d, n_ngb=n_ngb)
+    d["h0"] = r["h"].astype(np.float32)
+    return d, r, n_ngb, margin
+
+
+def _columns(d, margin):
+    """(G, the particles of each column of top cells in order of z), by the rule
+    of the cell build for one box of side 1."""
+    H = float((np.float32(margin) * d["h0"]).max())
+    G = int(np.floor(1.0 / H))
+    xy = np.minimum(np.floor(d["pos"][:, :2] * G).astype(int), G - 1)
+    col = xy[:, 0] * G + xy[:, 1]
+    order = np.lexsort((d["pos"][:, 2], col))
+    return G, np.split(order, np.flatnonzero(np.diff(col[order])) + 1)
+
+
+def _longest_run(d, margin):
+    """Largest extent in z of 16 consecutive particles of a column (in runs from its first)."""
+    _, cols = _columns(d, margin)
+    z = d["pos"][:, 2]
+    return max(z[c[min(i + 15, len(c) - 1)]] - z[c[i]] for c in cols for i in range(0, len(c), 16))
+
+
+@pytest.mark.parametrize("name", ["lattice_16", "lattice_13", "cylinder_24"])
+def test_runs_longer_than_half_the_box(gpu_lib, name):
+    """Density, force and gravity where 16 particles of a column lie over more
+    than half the box, and again after a drift that keeps the cells."""
+    import torch
+    d, r, n_ngb, margin = _set(name)
+    assert _longest_run(d, margin) > 0.5
+    print("columns", name, "N", len(d["h0"]), "G", _columns(d, margin)[0], "run", _longest_run(d, margin), flush=True)
+    rc = 0.95 * float(d["h0"].min())
+    t = {k: torch.from_numpy(d[k]).cuda() for k in ("pos", "vel", "mass", "u", "h0")}
+    # a drift of a third of the margin's budget: delta is sqrt(3) times the largest component
+    budget = (1.0 - 1.0 / margin) * margin * float(d["h0"].min())
+    dt = 0.5 * budget / 3.0 / np.sqrt(3.0) / float(np.abs(d["vel"]).max())
+    ctx = gpu_lib.Context(0, n_ngb=n_ngb, h_margin=margin)
+    try:
+        ctx.build_cells(t["pos"], t["h0"], d["box_first"], d["box_len"])
+        for step in range(2):
+            if step:
+                ctx.drift(dt, t["vel"], t["pos"])
+                d = dict(d, pos=t["pos"].cpu().numpy())
+                r = oracle.run(d, n_ngb=n_ngb)
+            acc = ctx.gravity_p2p(t["mass"], 1.0, 0.0, rc)[0].double().cpu().numpy()
+            nw = torch.empty_like(t["h0"])
+            g = ctx.density(t["mass"], t["h0"].clone(), nw=nw)
+            assert g["stats"]["rebuilds"] == 0 and ctx.timings()["builds"] == 1
+            g.update(ctx.force(t["vel"], t["u"]))
+            out = {k: g[k].double().cpu().numpy() for k in ("h", "rho", "f", "nw", "acc", "dudt")}
+            e = errors(out, r)
+            o = og.p2p(d["pos"], d["mass"], 1.0, 0.0, rc)
+            W = _window_free(d["pos"], d["mass"], 1.0, 0.0, rc)
+            eg = float(np.max(np.linalg.norm(acc - o["acc"], axis=1) / np.where(W > 0, W, 1.0)))
+            print(name, "step", step, e, "gravity", eg, flush=True)
+            assert_within(e, TOL32, name)
+            assert eg <= TOL
+    finally:
+        ctx.close()
