@@ -215,57 +215,114 @@ __device__ __forceinline__ int box_of_col(const int* col_base, int n_boxes, int 
     return lo;
 }
 
-__global__ void k_col_count(int n_cols, int n_boxes, const int* __restrict__ col_base, const int* __restrict__ box_G,
-                            const int64_t* __restrict__ box_top_base, int fzb, const int* __restrict__ starts,
-                            uint32_t* __restrict__ it_cnt)
+// A column of top cells (one wavefront): its box, place and particles, and the
+// fine cell in z of a particle.
+struct Column {
+    int b, G, gz, x, y, p0, p1;
+    int64_t base, f;         // first fine cell of the box, of the column
+    const uint64_t* keys;
+    uint64_t mask;
+    __device__ __forceinline__ int z(int p) const { return (int)((keys[p] & mask) - (uint64_t)(f - base)); }
+};
+
+__device__ __forceinline__ Column column_of(int r, int n_boxes, const int* col_base, const int* box_G,
+                                            const int64_t* box_top_base, KeyLayout kl, const int* starts,
+                                            const uint64_t* keys)
 {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n_cols) return;
-    const int b = box_of_col(col_base, n_boxes, r);
-    const int gz = box_G[b] << fzb;
-    const int64_t f = (box_top_base[b] << fzb) + (int64_t)(r - col_base[b]) * gz;
-    it_cnt[r] = (uint32_t)((starts[f + gz] - starts[f] + 15) / 16);
+    Column c;
+    c.b = box_of_col(col_base, n_boxes, r);
+    c.G = box_G[c.b];
+    c.gz = c.G << kl.low;
+    const int xy = r - col_base[c.b];
+    c.x = xy / c.G;
+    c.y = xy % c.G;
+    c.base = box_top_base[c.b] << kl.low;
+    c.f = c.base + (int64_t)xy * c.gz;
+    c.p0 = starts[c.f];
+    c.p1 = starts[c.f + c.gz];
+    c.keys = keys;
+    c.mask = (1ull << (kl.bits_top + kl.low)) - 1;
+    return c;
+}
+
+// A column's items are its particles 16 at a time; 16 that lie over more than
+// ITEM_CELLS top cells (a sparse column) are cut into items that do not. FP32
+// coordinates from an item's centre hold separations as well as offsets from the
+// cells' centres do up to there and worse beyond (rms error of a separation over
+// that of cell-centred offsets, 16 cells a side, along z and over the three axes:
+// 0.95 and 0.95 at one cell, 1.11 and 1.01 at two, 1.50 and 1.16 at three, 2.64 and
+// 1.71 at six). No cell is then the candidate of an item twice, with four cells per
+// side or more. Whole columns in pieces of two cells instead: sedov 64^3 192 -> 200
+// us a pass, for 2% of the runs are too long there, and a piece holds 19 particles.
+constexpr int ITEM_CELLS = 2;
+
+// Calls f(first, end) for the items of the particles [i0, i1) of a column, i1 - i0
+// <= 16, and returns their number.
+template <class F>
+__device__ __forceinline__ int column_run(const Column& c, int fzb, int i0, int i1, F f)
+{
+    if (i0 >= i1) return 0;
+    int n = 0, first = i0, z0 = c.z(i0);
+    if (c.z(i1 - 1) - z0 >= ITEM_CELLS << fzb) {
+        for (int i = i0 + 1; i < i1; ++i) {
+            const int z = c.z(i);
+            if (z - z0 < ITEM_CELLS << fzb) continue;
+            f(n++, first, i);
+            first = i;
+            z0 = z;
+        }
+    }
+    f(n++, first, i1);
+    return n;
+}
+
+__global__ void __launch_bounds__(256) k_col_count(int n_cols, int n_boxes, const int* __restrict__ col_base,
+                                                   const int* __restrict__ box_G,
+                                                   const int64_t* __restrict__ box_top_base, KeyLayout kl,
+                                                   const int* __restrict__ starts, const uint64_t* __restrict__ keys,
+                                                   uint32_t* __restrict__ it_cnt)
+{
+    const int r = (int)(((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
+    const int lane = threadIdx.x & 63;
+    if (r >= n_cols) return;  // whole wavefronts
+    const Column c = column_of(r, n_boxes, col_base, box_G, box_top_base, kl, starts, keys);
+    int n = 0;
+    for (int i0 = c.p0 + 16 * lane; i0 < c.p1; i0 += 16 * 64)
+        n += column_run(c, kl.low, i0, min(i0 + 16, c.p1), [](int, int, int) {});
+    for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o, 64);
+    if (lane == 0) it_cnt[r] = (uint32_t)n;
 }
 
 // The items of each column (one wavefront per column) and the first item of
-// each box. An item that spans so many cells that some cell would be its
-// candidate twice (a sparse column of a small grid) sets grid[1]: the build then
-// uses the tree layout. grid[0]: the number of items.
+// each box.
 __global__ void __launch_bounds__(256) k_col_items(int n_cols, int n_boxes, const int* __restrict__ col_base,
                                                    const int* __restrict__ box_G, const double* __restrict__ box_len,
                                                    const int64_t* __restrict__ box_top_base, KeyLayout kl,
                                                    const int* __restrict__ starts, const uint64_t* __restrict__ keys,
                                                    const uint32_t* __restrict__ it_start, int4* __restrict__ cells,
-                                                   int* __restrict__ box_item, uint32_t* __restrict__ grid)
+                                                   int* __restrict__ box_item)
 {
     const int r = (int)(((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
     const int lane = threadIdx.x & 63;
     if (r >= n_cols) return;  // whole wavefronts
-    const int fzb = kl.low;
-    const int b = box_of_col(col_base, n_boxes, r);
-    const int G = box_G[b], gz = G << fzb, xy = r - col_base[b];
-    const int x = xy / G, y = xy % G;
-    const int64_t base = box_top_base[b] << fzb;
-    const int64_t f = base + (int64_t)xy * gz;
-    const int p0 = starts[f], p1 = starts[f + gz];
-    const double unit = box_len[b] / 4294967296.0;
+    const Column c = column_of(r, n_boxes, col_base, box_G, box_top_base, kl, starts, keys);
+    const double unit = box_len[c.b] / 4294967296.0;
     const float sh = (float)unit, sl = (float)(unit - (double)sh);
-    const uint64_t mask = (1ull << (kl.bits_top + kl.low)) - 1;
+    const unsigned step = (unsigned)(4294967296.0 / c.G);
+    int64_t it = it_start[r];
     if (lane == 0) {
-        if (xy == 0) box_item[b] = (int)it_start[r];
-        if (r == n_cols - 1) {
-            box_item[n_boxes] = (int)it_start[n_cols];
-            grid[0] = it_start[n_cols];
-        }
+        if (c.x == 0 && c.y == 0) box_item[c.b] = (int)it;
+        if (r == n_cols - 1) box_item[n_boxes] = (int)it_start[n_cols];
     }
-    for (int t = lane; t < (p1 - p0 + 15) / 16; t += 64) {
-        const int i0 = p0 + 16 * t, ni = min(16, p1 - i0);
-        const int z0 = (int)((keys[i0] & mask) - (uint64_t)(f - base));
-        const int z1 = (int)((keys[i0 + ni - 1] & mask) - (uint64_t)(f - base));
-        if ((z1 >> fzb) - (z0 >> fzb) + 3 > G) atomicOr(&grid[1], 1u);
-        const int64_t it = it_start[r] + t;
-        cells[2 * it] = make_int4(i0, ni | (G << 8), x | (y << 16), z0 | (z1 << 16));
-        cells[2 * it + 1] = make_int4((int)base, __float_as_int(sh), __float_as_int(sl), 0);
+    for (int i = c.p0; i < c.p1; i += 16 * 64) {
+        const int i0 = i + 16 * lane, i1 = min(i0 + 16, c.p1);
+        int all;
+        const int64_t k = it + wave_excl_scan(column_run(c, kl.low, i0, i1, [](int, int, int) {}), all);
+        column_run(c, kl.low, i0, i1, [&](int q, int a, int b) {
+            cells[2 * (k + q)] = make_int4(a, (b - a) | (c.G << 8), c.x | (c.y << 16), c.z(a) | (c.z(b - 1) << 16));
+            cells[2 * (k + q) + 1] = make_int4((int)c.base, __float_as_int(sh), __float_as_int(sl), (int)step);
+        });
+        it += all;
     }
 }
 
@@ -287,9 +344,9 @@ __global__ void k_fix_fill(int64_t n, const uint32_t* __restrict__ perm, const d
 
 // As k_cell_pbox for a grid layout: the box's centre in 32-bit fractions. The
 // particles are measured from the middle of the item's cells, which no particle is
-// half the box away from (an item spans at most G - 2 of G cells): differences from
-// one of the particles would wrap in an item longer than half the box, and the frame
-// around the wrapped box would tear its pairs apart.
+// half the box away from: differences from one of the particles would wrap in an item
+// longer than half the box, and the frame around the wrapped box would tear its pairs
+// apart.
 __global__ void __launch_bounds__(256) k_fix_pbox(int64_t n_items, const int4* __restrict__ cells, int fzb,
                                                   const int4* __restrict__ xfix, const float* __restrict__ Hs,
                                                   float4* __restrict__ pbox)
@@ -301,12 +358,11 @@ __global__ void __launch_bounds__(256) k_fix_pbox(int64_t n_items, const int4* _
     const int ni = c0.y & 0xff;
     unsigned x0[3] = {0u, 0u, 0u};
     if (live) {
-        const unsigned G = (unsigned)(c0.y >> 8);
-        const unsigned x2 = 2u * (unsigned)(c0.z & 0xffff) + 1u, y2 = 2u * (unsigned)(c0.z >> 16) + 1u,
-                       z2 = (unsigned)(c0.w & 0xffff) + (unsigned)(c0.w >> 16) + 1u;  // twice the middle
-        x0[0] = (unsigned)(((uint64_t)x2 << 31) / G);
-        x0[1] = (unsigned)(((uint64_t)y2 << 31) / G);
-        x0[2] = (unsigned)(((uint64_t)z2 << 31) / (G << fzb));
+        const unsigned step = (unsigned)cells[2 * it + 1].w, fstep = step >> fzb;  // width of a cell, of a fine one
+        const unsigned z0 = (unsigned)(c0.w & 0xffff), z1 = (unsigned)(c0.w >> 16) + 1u;
+        x0[0] = (unsigned)(c0.z & 0xffff) * step + (step >> 1);
+        x0[1] = (unsigned)(c0.z >> 16) * step + (step >> 1);
+        x0[2] = z0 * fstep + (((z1 - z0) * fstep) >> 1);
     }
     // (lanes past the item's particles repeat its first)
     const int4 x = live ? xfix[c0.x + (sub < ni ? sub : 0)] : make_int4(0, 0, 0, 0);
@@ -1017,10 +1073,9 @@ struct BoxTables {
     unsigned* hmax;     // n_boxes
     int* G;             // n_boxes
     int* col_base;      // n_boxes + 1
-    uint32_t* level;    // LEVEL_WORDS: a level's counts and the grid's (CT_TOTAL, CT_GRID)
+    uint32_t* level;    // LEVEL_WORDS: a level's nodes and leaves (CT_TOTAL), the grid's items
 };
-constexpr int LEVEL_WORDS = 6;
-static_assert(CT_GRID == CT_TOTAL + 2, "the level's counts and the grid's are read together");
+constexpr int LEVEL_WORDS = 3;
 
 // At the start of a build: the boxes (len null: as they are), and zero maxima and
 // counters.
@@ -1054,9 +1109,11 @@ __global__ void k_box_tables(int nb, BoxTables h, int* __restrict__ box_G, int64
     }
 }
 
-__global__ void k_level_out(const uint32_t* __restrict__ d, BoxTables h)
+// n_items: of a grid layout (null: none made)
+__global__ void k_level_out(const uint32_t* __restrict__ d, const uint32_t* __restrict__ n_items, BoxTables h)
 {
-    if (threadIdx.x < LEVEL_WORDS) h.level[threadIdx.x] = d[threadIdx.x];
+    if (threadIdx.x < 2) h.level[threadIdx.x] = d[threadIdx.x];
+    if (threadIdx.x == 2) h.level[2] = n_items ? *n_items : 0u;
 }
 
 // Bound, step maximum, smallest search radius (before its minimum), non-finite flag.
@@ -1288,23 +1345,18 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     SPH_HIP(hipGetLastError());
     radix_sort(c, keys, perm, keys_alt, perm_alt, n, c->bits_box + c->bits_top + c->fzb, s);
 
-    // ---- the items of a grid layout (used if no top cell splits) --------------------------------
-    uint32_t* d_grid = reinterpret_cast<uint32_t*>(&ctr[CT_GRID]);
+    // ---- the number of items of a grid layout (made if no top cell splits) -----------------------
+    int* starts = nullptr;
+    uint32_t* col_start = nullptr;
     if (grid_ok) {
-        int* starts = ensure<int>(c, c->starts, (size_t)n_fine + 1);
-        uint32_t* it_start = ensure<uint32_t>(c, c->it_start, (size_t)n_cols + 1);
-        int* box_item = ensure<int>(c, c->box_item, nb + 1);
-        int4* cells = ensure<int4>(c, c->cells, 2 * (size_t)(n / 16 + n_cols));
+        starts = ensure<int>(c, c->starts, (size_t)n_fine + 1);
+        col_start = ensure<uint32_t>(c, c->it_start, (size_t)n_cols + 1);
         k_fine_starts<<<blocks_for(n, BS), BS, 0, s>>>(n, keys, kl, box_top_base, n_fine, starts);
         SPH_HIP(hipGetLastError());
-        k_col_count<<<blocks_for(n_cols, BS), BS, 0, s>>>(n_cols, nb, col_base, box_G, box_top_base, c->fzb, starts,
-                                                         it_start);
+        k_col_count<<<blocks_for((int64_t)n_cols * 64, 256), 256, 0, s>>>(n_cols, nb, col_base, box_G, box_top_base, kl,
+                                                                          starts, keys, col_start);
         SPH_HIP(hipGetLastError());
-        scan_exclusive(c, it_start, it_start, n_cols, it_start + n_cols, s);
-        k_col_items<<<blocks_for((int64_t)n_cols * 64, 256), 256, 0, s>>>(n_cols, nb, col_base, box_G, box_len,
-                                                                          box_top_base, kl, starts, keys, it_start,
-                                                                          cells, box_item, d_grid);
-        SPH_HIP(hipGetLastError());
+        scan_exclusive(c, col_start, col_start, n_cols, col_start + n_cols, s);
     }
 
     float* Hs = ensure<float>(c, c->Hs, n);
@@ -1390,14 +1442,21 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
         SPH_HIP(hipGetLastError());
         k_lvl_assign<<<blocks_for(n, BS), BS, 0, s>>>(n, nid, nd_leaf, leaf_tmp);
         SPH_HIP(hipGetLastError());
-        k_level_out<<<1, 64, 0, s>>>(d_M, bt);
+        k_level_out<<<1, 64, 0, s>>>(d_M, level == 0 && grid_ok ? col_start + n_cols : nullptr, bt);
         SPH_HIP(hipGetLastError());
         SPH_HIP(hipStreamSynchronize(s));
-        const uint32_t* mk = bt.level;  // d_M, d_K, -, -, d_grid
-        const int64_t M = mk[0], K = mk[1];
+        const int64_t M = bt.level[0], K = bt.level[1];
         if (level == 0) {
-            c->uni = grid_ok && K == M && mk[5] == 0u;
-            if (c->uni) c->n_items = mk[4];
+            c->uni = grid_ok && K == M;
+            if (c->uni) {
+                c->n_items = bt.level[2];
+                int* box_item = ensure<int>(c, c->box_item, nb + 1);
+                int4* cells = ensure<int4>(c, c->cells, 2 * (size_t)c->n_items);
+                k_col_items<<<blocks_for((int64_t)n_cols * 64, 256), 256, 0, s>>>(n_cols, nb, col_base, box_G, box_len,
+                                                                                  box_top_base, kl, starts, keys,
+                                                                                  col_start, cells, box_item);
+                SPH_HIP(hipGetLastError());
+            }
         }
         // every particle not yet in a leaf heads or joins a node of this level,
         // so the bound (its parents' children) holds them; a larger count is a bug

@@ -77,7 +77,6 @@ enum {
     CT_SCAN_POP = 18,    // next queued cell to take
     CT_TOTAL = 19,       // scratch for device-computed totals read by the host (two uint32)
     CT_DT_MIN = 20,      // sph_timestep: smallest h / v_sig (float bits in the low word)
-    CT_GRID = 21,        // build: work items of a grid layout, and nonzero if it cannot be used (two uint32)
     CT_QUEUE = 32,       // 8 work-queue heads (one per XCD), one 64-byte line each: CT_QUEUE + 8 q
     CT_SPREAD = 96,      // CT_SPREAD_SLOTS copies of the sums, CT_SUMS entries each
     CT_SPREAD_SLOTS = 64,
@@ -163,7 +162,7 @@ struct sph_ctx {
     sph::Buf drift;
     float h_min = 0.0f;           // smallest Hs of the last build (host copy; see finish_build_read)
     // The layout of the last build (Item in tiles.h). Grid: no top cell was
-    // split and no item meets a cell twice; tree otherwise. A grid build leaves
+    // split; tree otherwise. A grid build leaves
     // the leaves' partner lists to the calls that walk them (partner_lists).
     bool uni = false;
     int fzb = 0;                  // grid: fine cells in z per top cell, logarithm

@@ -321,7 +321,7 @@ struct CellArgs {
     const int4* cells;       // per slot, tree: first particle, count, first record, records. Grid, two per slot:
                              // first particle, count | G << 8, x | y << 16 of the column, first | last << 16 of
                              // its fine cells in z; first fine cell of the box, the box's unit of length
-                             // (two floats, high and low part), -
+                             // (two floats, high and low part), width of a cell in 32-bit fractions
     const float4* pbox;      // per slot, 2: centre of the box around its particles (grid: 32-bit fractions) and
                              // largest search radius; half widths, -
     const int2* p_rec;       // tree: per record, first particle and count of the neighbour leaf

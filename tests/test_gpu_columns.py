@@ -110,3 +110,36 @@ def test_runs_longer_than_half_the_box(gpu_lib, name):
             assert eg <= TOL
     finally:
         ctx.close()
+
+
+def test_separations_in_sparse_columns(gpu_lib):
+    """The pull between the two particles of close pairs, in columns of 16 cells of
+    width w with 40 particles each, is as exact as offsets from cell centres make
+    it: an item spans at most two cells, so coordinates of at most w from its centre
+    are rounded twice (32-bit fraction to FP32, times the unit), each by at most
+    2^-25 w (w a power of two), and the separation along z is off by at most 2^-23 w,
+    along x and y by half of that. The pull m / r^2 is then off by 2 |dr| / r of
+    itself (1e-4 of that bound for the FP32 arithmetic of the pull)."""
+    import torch
+    G, margin = 16, 1.26
+    w = 1.0 / G
+    rng = np.random.default_rng([1508, 961])
+    n, r = 20 * G * G, 2e-4 * w
+    a = rng.uniform(0.0, 1.0, (n, 3))
+    e = rng.normal(0.0, 1.0, (n, 3))
+    pos = np.mod(np.concatenate([a, a + r * e / np.linalg.norm(e, axis=1)[:, None]]), 1.0)
+    d = {"pos": pos, "h0": np.full(2 * n, 0.06249 / margin, np.float32)}
+    assert _columns(d, margin)[0] == G and 8 * w < _longest_run(d, margin) < 13 * w
+    mass = np.full(2 * n, 1.0, np.float32)
+    rc = 0.9 * float(d["h0"][0])
+    print("close pairs", n, "run", _longest_run(d, margin) / w, flush=True)
+    ctx = gpu_lib.Context(0, h_margin=margin)
+    try:
+        ctx.build_cells(torch.from_numpy(pos).cuda(), torch.from_numpy(d["h0"]).cuda())
+        acc = ctx.gravity_p2p(torch.from_numpy(mass).cuda(), 1.0, 0.0, rc)[0].double().cpu().numpy()
+    finally:
+        ctx.close()
+    o = og.p2p(pos, mass, 1.0, 0.0, rc)["acc"]
+    off = np.linalg.norm(acc - o, axis=1) / np.linalg.norm(o, axis=1) * r
+    print("separations off by", off.max() / 2 / w, "w, rms", np.sqrt((off**2).mean()) / 2 / w, flush=True)
+    assert off.max() <= 2.0 * np.sqrt(1.5) * 2.0**-23 * w * 1.0001
