@@ -184,6 +184,20 @@ __global__ void k_keys(int64_t n, const double* __restrict__ pos_w, const int64_
 // boxes: 4.97 ms with one wavefront per cell, 5.12 ms with cells in items of at
 // most 16, 3.47 ms along columns; gravity 1.20, 1.36 and 0.72 ms).
 
+// Positions are 32-bit fractions of the box, or, from 16 cells a side, of one of its
+// 2^k equal pieces, k so that a piece is 8 to 15 cells wide. What a frame holds lies
+// within 3.5 cells of its centre (two of an item, one on either side, and the
+// drift), so that differences wrap around a piece as they would around the box, and
+// the fraction stays below 2^-28 of a cell's width: fractions of the whole box would
+// be coarser than FP32 offsets from the cells' centres from about 128 cells a side
+// on (2^-24 of the width at 256).
+__host__ __device__ inline int piece_bits(int G)
+{
+    int k = 0;
+    while (G >> (k + 1) >= 8) ++k;
+    return k;
+}
+
 // First particle of every fine cell (starts[n_fine] = n): the thread of a
 // particle that begins a cell also fills the empty cells before it.
 __global__ void k_fine_starts(int64_t n, const uint64_t* __restrict__ keys, KeyLayout kl,
@@ -306,9 +320,10 @@ __global__ void __launch_bounds__(256) k_col_items(int n_cols, int n_boxes, cons
     const int lane = threadIdx.x & 63;
     if (r >= n_cols) return;  // whole wavefronts
     const Column c = column_of(r, n_boxes, col_base, box_G, box_top_base, kl, starts, keys);
-    const double unit = box_len[c.b] / 4294967296.0;
+    const double pieces = 4294967296.0 * (double)(1 << piece_bits(c.G));
+    const double unit = box_len[c.b] / pieces;
     const float sh = (float)unit, sl = (float)(unit - (double)sh);
-    const unsigned step = (unsigned)(4294967296.0 / c.G);
+    const unsigned step = (unsigned)(pieces / c.G);
     int64_t it = it_start[r];
     if (lane == 0) {
         if (c.x == 0 && c.y == 0) box_item[c.b] = (int)it;
@@ -326,16 +341,17 @@ __global__ void __launch_bounds__(256) k_col_items(int n_cols, int n_boxes, cons
     }
 }
 
-// Positions as 32-bit fractions of the box, sorted: differences are exact and
+// Positions as 32-bit fractions (piece_bits), sorted: differences are exact and
 // wrap around the box by themselves.
 __global__ void k_fix_fill(int64_t n, const uint32_t* __restrict__ perm, const double* __restrict__ pos_w,
                            const int64_t* __restrict__ box_first, int n_boxes, const double* __restrict__ box_len,
-                           int4* __restrict__ xfix)
+                           const int* __restrict__ box_G, int4* __restrict__ xfix)
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
     const int64_t o = perm[p];
-    const double s = 4294967296.0 / box_len[box_of(box_first, n_boxes, o)];
+    const int b = box_of(box_first, n_boxes, o);
+    const double s = 4294967296.0 * (double)(1 << piece_bits(box_G[b])) / box_len[b];
     int v[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) v[a] = (int)(unsigned)(unsigned long long)llrint(pos_w[3 * o + a] * s);
@@ -1644,7 +1660,8 @@ void refresh_offsets(sph_ctx* c, hipStream_t s)
         k_fix_fill<<<blocks_for(c->n, BS), BS, 0, s>>>(c->n, static_cast<uint32_t*>(c->perm.p),
                                                       static_cast<double*>(c->pos_w.p),
                                                       static_cast<int64_t*>(c->box_first.p), c->n_boxes,
-                                                      static_cast<double*>(c->box_len.p), xfix);
+                                                      static_cast<double*>(c->box_len.p),
+                                                      static_cast<int*>(c->box_G.p), xfix);
         SPH_HIP(hipGetLastError());
     } else {
         sorted_fill(c, s);

@@ -197,7 +197,7 @@ struct sph_ctx {
     sph::Buf box_item;       // int, n_boxes + 1: first item of each box
     sph::Buf starts;         // grid: int, first particle of each fine cell
     sph::Buf col_base;       // grid: int, n_boxes + 1: first column of each box
-    sph::Buf xfix;           // grid: int4 (x, y, z, 0), positions as 32-bit fractions of the box, sorted
+    sph::Buf xfix;           // grid: int4 (x, y, z, 0), positions as 32-bit fractions (piece_bits in build.hip), sorted
     // their schedule (one slot per item, see xcd_start)
     sph::Buf cells;          // int4 per slot (grid: two) as CellArgs (tiles.h) describes
     sph::Buf cell_item;      // int per slot: item

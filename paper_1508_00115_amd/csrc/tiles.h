@@ -312,7 +312,8 @@ __device__ __forceinline__ int wave_max_u(int v)
 // 16 consecutive particles of one column whatever cells they are in, and its
 // candidates are at most 18 runs of consecutive particles: the z range within
 // reach of the item's own, in its column and the eight around it, and what
-// wraps around the box. Positions are 32-bit fractions of the box, whose
+// wraps around the box. Positions are 32-bit fractions of the box or of an equal
+// piece of it (piece_bits in the cell build), whose
 // differences are exact and periodic, so there are no frames to shift between.
 // A tree layout's items are runs of one leaf's particles, its candidates the
 // leaf's records (neighbour leaf and frame shift), its positions FP32 offsets

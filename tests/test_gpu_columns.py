@@ -143,3 +143,47 @@ def test_separations_in_sparse_columns(gpu_lib):
     off = np.linalg.norm(acc - o, axis=1) / np.linalg.norm(o, axis=1) * r
     print("separations off by", off.max() / 2 / w, "w, rms", np.sqrt((off**2).mean()) / 2 / w, flush=True)
     assert off.max() <= 2.0 * np.sqrt(1.5) * 2.0**-23 * w * 1.0001
+
+
+def test_separations_on_a_fine_grid(gpu_lib):
+    """The pull between the two particles of close pairs on 256 cells a side (2^22
+    particles, 16 pairs in a clump 2e-3 of a cell wide in two cells of every column,
+    at any place of the cell), from which the error of each separation follows: the
+    pull r / r^3 changes by (e - 3 (e . r) r / r^2) / r^3 for an error e. Offsets from
+    cell centres are rounded by at most 2^-26 of the width w in half of the cell, 2^-27
+    in a quarter and so on, 0.4365 x 2^-26 w rms, so separations are off by 1.069 x
+    2^-26 w rms (six of those); 5% for the sample's own spread."""
+    import torch
+    G, margin = 256, 1.26
+    w = 1.0 / G
+    rng = np.random.default_rng([1508, 962])
+    xy = np.repeat(np.stack(np.meshgrid(np.arange(G), np.arange(G), indexing="ij"), axis=-1).reshape(-1, 2), 2, axis=0)
+    z = np.tile([60, 190], G * G)
+    centre = (np.concatenate([xy, z[:, None]], axis=1) + rng.uniform(0.01, 0.99, (2 * G * G, 3))) * w
+    a = centre[:, None] + rng.uniform(-1e-3, 1e-3, (2 * G * G, 16, 3)) * w
+    e = rng.normal(0.0, 1.0, a.shape)
+    pos = np.concatenate([a, a + 1e-5 * w * e / np.linalg.norm(e, axis=2)[..., None]], axis=1).reshape(-1, 3)
+    n = pos.shape[0]
+    h0 = np.full(n, 0.9999 * w / margin, np.float32)
+    print("clumps", 2 * G * G, "particles", n, flush=True)
+    ctx = gpu_lib.Context(0, h_margin=margin)
+    try:
+        ctx.build_cells(torch.from_numpy(pos).cuda(), torch.from_numpy(h0).cuda())
+        assert ctx.build_info()["n_cells"] >= 2 * G * G
+        acc = ctx.gravity_p2p(torch.ones(n, device="cuda"), 1.0, 0.0, 0.01 * w)[0].double().cpu().numpy()
+    finally:
+        ctx.close()
+    off = []
+    for k in rng.choice(2 * G * G, 400, replace=False):
+        p = pos[32 * k:32 * k + 32]
+        d = p[None] - p[:, None]
+        r = np.linalg.norm(d, axis=2) + 1e9 * np.eye(32)
+        pull = np.where(r < 0.01 * w, (1.0 - (r / (0.01 * w)) ** 2) ** 2, 0.0)[..., None] * d / r[..., None] ** 3
+        da = acc[32 * k:32 * k + 32] - pull.sum(1)
+        to = d[np.arange(32), np.arange(32) ^ 16]  # to the other particle of the pair
+        r = np.linalg.norm(to, axis=1)[:, None]
+        along = (da * to).sum(1)[:, None] * to / r**2
+        off.append((da - 1.5 * along) * r**3)
+    rms = float(np.sqrt((np.concatenate(off) ** 2).sum(1).mean()))
+    print("separations off by", rms / w, "w rms", flush=True)
+    assert rms <= 1.05 * 1.069 * 2.0**-26 * w
