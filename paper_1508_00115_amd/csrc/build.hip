@@ -770,8 +770,8 @@ __device__ __forceinline__ void block_counters(const int64_t (&v)[NV], int64_t (
 // ITEM_N, one wavefront each. A wavefront takes ITEM_N particles at a time
 // (four lanes per particle), so a leaf of more would be a serial loop: as
 // separate items its runs go to several wavefronts (a box of 16^3 particles
-// has 125 leaves of 27 to 64 particles for 1024 SIMDs). item_range (tiles.h)
-// says which particles an item holds.
+// has 125 leaves of 27 to 64 particles for 1024 SIMDs). item_range.h says which
+// particles an item holds.
 constexpr int ITEM_N = 16;
 
 __global__ void k_item_count(int64_t nl, const int* __restrict__ lf_count, uint32_t* __restrict__ it_cnt)
@@ -954,7 +954,7 @@ __global__ void __launch_bounds__(PBS) k_partners(int64_t nl, int fill, const in
             const int it = t0 + t;
             it_leaf[it] = (int)a;
             if (!sk) continue;
-            const float cost = (float)item_range(ni, nt, t).y * (float)nj;
+            const float cost = (float)(item_first(ni, nt, t + 1) - item_first(ni, nt, t)) * (float)nj;
             uint64_t x = 0;
             if (xcd_local)
                 while (x < 7 && it >= sph::xcd_start(n_items, (int)x + 1)) ++x;
@@ -981,9 +981,9 @@ __global__ void k_sched_fill(int64_t n_items, const uint32_t* __restrict__ by_co
     const int64_t slot = by_cost && deal ? sph::xcd_start(n_items, (int)(r & 7)) + (r >> 3) : r;
     const int a = it_leaf[it];
     const int t0 = (int)it_start[a], nt = (int)it_start[a + 1] - t0;
-    const int2 rg = item_range(lf_count[a], nt, it - t0);
-    cells[slot] = make_int4(lf_start[a] + rg.x, rg.y, (int)p_start[a], (int)(p_start[a + 1] - p_start[a]));
-    cells_d[slot] = make_int4(lf_start[a] + rg.x, rg.y, (int)p_start[a], (int)p_cntd[a]);
+    const int i0 = item_first(lf_count[a], nt, it - t0), ni = item_first(lf_count[a], nt, it - t0 + 1) - i0;
+    cells[slot] = make_int4(lf_start[a] + i0, ni, (int)p_start[a], (int)(p_start[a + 1] - p_start[a]));
+    cells_d[slot] = make_int4(lf_start[a] + i0, ni, (int)p_start[a], (int)p_cntd[a]);
     cell_item[slot] = it;
 }
 

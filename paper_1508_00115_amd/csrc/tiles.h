@@ -4,6 +4,7 @@
 #pragma once
 
 #include "common.h"
+#include "item_range.h"
 
 // Work sources of the hot kernels. Items are schedule slots: either work items
 // ranked by decreasing cost (particles x candidates) and dealt out to the 8
@@ -388,14 +389,6 @@ struct CandWalk {
     bool own;
 };
 
-// (offset, count) of item t of the nt = ceil(ni / 16) items of a leaf of ni
-// particles: even runs, none over 16.
-__device__ __forceinline__ int2 item_range(int ni, int nt, int t)
-{
-    const int a = ni * t / nt;
-    return make_int2(a, ni * (t + 1) / nt - a);
-}
-
 constexpr int WALK_MARKS = 256;
 template <bool UNI>
 constexpr int WALK_LDS = 64 * (UNI ? 4 : 16) + WALK_MARKS;  // table and marks
@@ -452,14 +445,9 @@ __device__ __forceinline__ void walk_fill(CandWalk<false>& w, const CellArgs& G,
                     }
                 }
                 hi = min(hi, nt);
-                // (the division of item_range; exact for a product below 2^15)
-                auto part = [&](int k) {
-                    const int x = rec.y * k;
-                    return nt == 1 ? x : nt == 2 ? x >> 1 : nt == 3 ? (x * 21846) >> 16 : x >> 2;
-                };
-                const int a = lo < hi ? part(lo) : 0;
+                const int a = lo < hi ? item_first_small(rec.y, nt, lo) : 0;
                 first += a;
-                cnt = lo < hi ? part(hi) - a : 0;
+                cnt = lo < hi ? item_first_small(rec.y, nt, hi) - a : 0;
             }
         }
         const uint64_t m = __ballot(cnt > 0);

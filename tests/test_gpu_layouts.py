@@ -113,3 +113,28 @@ def test_listed_counts(gpu_lib, name, margin):
               for s in (1.0 - 1e-5, 1.0 + 1e-5))
     print(name, margin, st, lo, hi, flush=True)
     assert st["rebuilds"] == 0 and lo <= st["listed_density"] <= hi
+
+
+def test_leaf_of_many_particles(gpu_lib):
+    """A leaf whose particles times items pass 2^31 (guesses far too wide for a
+    clump of 200,000 keep it whole): gravity of a sample against the oracle,
+    tolerance as in the gravity tests."""
+    import torch
+    from oracle import gravity as og
+    from test_gpu_gravity import TOL, _window_free
+    n, rc = 200_000, 0.01
+    rng = np.random.default_rng([1508, 952])
+    pos = rng.uniform(0.02, 0.12, (n, 3))
+    print("leaf of", n, flush=True)
+    ctx = gpu_lib.Context(0)
+    try:
+        ctx.build_cells(torch.from_numpy(pos).cuda(), torch.full((n,), 0.25, device="cuda"))
+        assert ctx.build_info()["max_cell_particles"] == n
+        acc = ctx.gravity_p2p(torch.ones(n, device="cuda"), 1.0, 1e-3, rc)[0].double().cpu().numpy()
+    finally:
+        ctx.close()
+    rows = np.sort(rng.choice(n, 40, replace=False))
+    o = og.p2p_rows(pos, np.ones(n), 1.0, 1e-3, rc, rows)["acc"]
+    err = np.linalg.norm(acc[rows] - o, axis=1) / _window_free(pos, np.ones(n), 1.0, 1e-3, rc, rows=rows)
+    print("errors", err.max(), flush=True)
+    assert err.max() <= TOL
