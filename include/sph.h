@@ -185,8 +185,12 @@ typedef struct {
     int64_t sweep_interactions_density; /* pairs inside the trial h, summed over
                                            every Newton evaluation */
     int64_t rescanned_density;  /* particles whose candidates the solve walked more
-                                   than once (unequal masses, or a neighbour
-                                   list far too long for its slots) */
+                                   than once: with unequal masses among them, a
+                                   neighbour list too long for its slots, or a
+                                   root beyond a list that stopped short of the
+                                   search radius (each once per pass over the
+                                   cells, so again after a rebuild if it is
+                                   solved again) */
     int64_t tests_density;      /* FP32 loops: (i, j) candidate pairs tested against
                                    i's search radius outside the Newton lists (the
                                    list-building scans, and the rare re-walks of a

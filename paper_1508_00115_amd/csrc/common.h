@@ -45,8 +45,8 @@ struct Buf {
 }  // namespace sph
 
 // Per-particle state of one FP32 density solve: flags in the caller's order.
-// ST_SCAN: the particle's neighbour list did not fit its LDS slots (or masses
-// differ); it is solved by the re-scanning kernel instead.
+// ST_SCAN: the particle's neighbour list did not even fit the slots of a second
+// round; it is solved by the re-scanning kernel instead.
 enum : uint8_t { ST_ACTIVE = 0, ST_DONE = 1, ST_OVERFLOW = 2, ST_UNCONVERGED = 3, ST_SCAN = 4 };
 
 // Device counters (int64 entries) written by the kernels.
@@ -63,7 +63,7 @@ enum {
     CT_UNCONV = 6,       // particles that hit max_iter
     CT_BAD_INPUT = 7,    // non-finite or non-positive inputs seen by a kernel
     CT_DENS_SWEEP_INTER = 8,  // pairs inside the trial h, summed over every evaluation
-    CT_NEED_SCAN = 9,    // particles left to the re-scanning density kernel
+    CT_NEED_SCAN = 9,    // particles whose candidates the density walked more than once
     CT_B_CAND_PAIRS = 10,  // build: sum over leaves of particles x candidates
     CT_B_PAIRS64 = 11,     // build: (cell, neighbour cell) records, counted in 64 bits
     CT_B_MAX_NI = 12,      // build: largest leaf (max)

@@ -55,7 +55,6 @@ constexpr int DCAP = 128;      // candidates per LDS tile (list kernel)
 constexpr int SCAP = 512;      // candidates per LDS tile (re-scanning kernel)
 constexpr float LIST_GROW = 1.12f;  // first list radius over the starting h, where the margin is wide
 constexpr double LIST_WIDE = 1.2;   // h_margin from which lists start at LIST_GROW
-constexpr int LIST_MOST = 240;      // candidates inside it from which a particle counts as re-scanned
 
 struct DensArgs {
     const float4* jd;        // sorted (x, y, z) as the layout stores them, m
@@ -335,6 +334,7 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
         // masks over the item's particles: unsolved; those to be listed out to H; left to the re-scan
         unsigned todo = (unsigned)__ballot(lane < ni && A.st_s[ic] == ST_ACTIVE);
         unsigned wide = 0u, scan = 0u;
+        unsigned again = 0u;  // those whose candidates are walked more than once (rescanned_density)
         int n_flag = 0;
         if constexpr (DETAIL) {
             // the candidates inside H (the lists need not reach it): a walk of its own
@@ -394,7 +394,7 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                 s.Hi = s.hi = R;
             }
             const bool cut = s.Hi < H;  // the list may miss the root
-            bool solved = false, many = false;
+            bool solved = false;
             bool mixed = false;         // wave-uniform: masses differ
             float fS0 = 0.f, fS1 = 0.f, M0 = 0.f, M1 = 0.f;
             for (int acc = 0;; acc = 1) {
@@ -570,10 +570,8 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                 // ---- the lists that fit, in registers: entries 4 (j lpp + sub) ... + 3 -----------------
                 const unsigned over = (unsigned)__ballot(inb && T > room) & 0xffffu;
                 if (round > 0) scan |= over;  // (no room here either)
-                if (round == 0) n_scan += wave_count(lane < 16 && inb && T > LIST_MOST);  // walked again
                 const int Tq = __shfl(T, pq & 15, 64);
                 solved = mine && Tq <= room;
-                many = Tq > LIST_MOST;
                 const int len = solved ? Tq : 0;
                 const int nj4 = (wave_max_u(len) + 4 * lpp - 1) >> (lg + 2);
                 float* lq = list + (round == 0 ? SEG : 4 * SEG) * (lane >> lg);
@@ -649,10 +647,11 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                 const bool beyond_c = __shfl(beyond ? 1 : 0, lane_c, 64) != 0;
                 const unsigned bm = (unsigned)__ballot(inb && beyond_c) & 0xffffu;
                 wide |= bm;
+                again |= over | bm;
                 todo &= ~(batch & ~bm & (round == 0 ? ~over : ~0u));
                 if (!mixed || !__any(solved)) break;
             }
-            if (mixed) n_scan += wave_count(solved && sub == 0 && !many);  // walked again
+            if (mixed) again |= batch;
             if (solved && sub == 0) {
                 if (!mixed) {
                     M0 = m0 * fS0;
@@ -662,6 +661,7 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                 write_result(K, iq, K->perm[iq], s, fS0, M0, M1);
             }
         }
+        n_scan += __popc(again);
         if ((scan >> lane) & 1u && lane < 16) {
             late_args<DensArgs>()->st_s[i0 + lane] = ST_SCAN;
             n_flag = 1;
