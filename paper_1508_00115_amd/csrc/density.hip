@@ -831,7 +831,6 @@ __global__ void __launch_bounds__(BS) k_density_scan(DensArgs A)
     const float two_delta = 2.0f * A.drift[0];
     int64_t cand_acc = 0;  // wave-uniform
     int list_acc = 0, inter_acc = 0, sweep_acc = 0;
-    int64_t listed_acc = 0;  // wave-uniform
     int max_ev = 0;
     const int n_queued = (int)A.ctr[CT_SCAN_CELLS];  // final: written by the list kernel
     // A short queue leaves most wavefronts idle while a few take long cells
@@ -904,11 +903,6 @@ __global__ void __launch_bounds__(BS) k_density_scan(DensArgs A)
                 cand_acc += (int64_t)wave_count(valid && sub == 0) * kept_tot;
                 const int nl = (int)((o - o_lane) >> 8);
                 const bool fits = group_sum_i(nl > RSLOTS ? 1 : 0, RLPI) == 0;
-                if (A.detail) {
-                    int v = valid && fits ? nl : 0;
-                    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-                    listed_acc += __builtin_amdgcn_readfirstlane(v);
-                }
 
                 // ---- phase B: Newton's method over the lists ---------------------
                 const bool listed = valid && fits;
@@ -957,7 +951,7 @@ __global__ void __launch_bounds__(BS) k_density_scan(DensArgs A)
         listed += __shfl_xor(listed, o, 64);
         max_ev = max(max_ev, __shfl_xor(max_ev, o, 64));
     }
-    flush_counters(late_args<DensArgs>(), cand_acc, listed, inter, swept, max_ev, 0, listed_acc);
+    flush_counters(late_args<DensArgs>(), cand_acc, listed, inter, swept, max_ev, 0, 0);
 }
 
 }  // namespace

@@ -75,3 +75,49 @@ def test_counts_particles_walked_again(gpu_lib, name):
         assert g["stats"]["rebuilds"] == 0
         assert lo <= g["stats"]["rescanned_density"] <= hi, g["stats"]
         assert_within(errors(g, r), TOL32, name)
+
+
+# lattice side, factor on the guesses of a few particles, h_margin, leaf_target, slots of the
+# second walk, most neighbours inside the search radius (512: the re-scanning kernel's own lists)
+SCANNED = {
+    "grid_lists": (20, 1.95, 1.05, 4096, 320, 512),
+    "grid_no_lists": (24, 2.3, 1.05, 4096, 320, 1000),
+    "tree": (24, 2.2, 1.26, 64, 512, 1200),
+}
+
+
+def _scanned(name):
+    n, wide, margin, leaf_target, room, most = SCANNED[name]
+    d, r = _lattice(n, 2, wide, radius=0.08)
+    first, all_ = _listed(d, 1.12 if margin > 1.2 else margin), _listed(d, margin)
+    left = int((first > room).sum())
+    # a handful of particles: a queue far shorter than the kernel's wavefronts
+    assert 4 <= left < 64 and first[first > room].min() > room + 4 and room < all_.max() <= most
+    return d, r, left, int(all_.sum()), {"h_margin": margin, "leaf_target": leaf_target}
+
+
+@pytest.mark.parametrize("name", list(SCANNED))
+def test_particles_left_to_the_rescanning_kernel(gpu_lib, name):
+    """Particles with more neighbours than a second walk has slots for, in both
+    layouts, through density and force and through the pass, whose ghost step runs
+    in the re-scanning kernel for them."""
+    d, r, left, _, params = _scanned(name)
+    print("left to the re-scan", name, left, flush=True)
+    for g in _run(gpu_lib, d, **params):
+        e = errors(g, r)
+        print(name, e, g["stats"], flush=True)
+        assert g["stats"]["rebuilds"] == 0 and g["stats"]["rescanned_density"] >= left
+        assert_within(e, TOL32, name)
+        n_d = int(r["nngb"].sum())
+        assert abs(g["stats"]["interactions_density"] - n_d) <= 1e-5 * n_d + 2
+
+
+@pytest.mark.parametrize("name", list(SCANNED))
+def test_listed_counts_with_a_rescan(gpu_lib, name):
+    """timing = 2 counts every neighbour inside the search radii once, also those
+    of particles that the re-scanning kernel lists."""
+    d, _, left, listed, params = _scanned(name)
+    near = [int(_listed(d, params["h_margin"], s).sum()) for s in (1.0 - 1e-5, 1.0 + 1e-5)]
+    for g in _run(gpu_lib, d, timing=2, **params):
+        print("listed", name, left, g["stats"]["listed_density"], near, flush=True)
+        assert near[0] <= g["stats"]["listed_density"] <= near[1]
