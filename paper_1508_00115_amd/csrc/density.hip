@@ -88,6 +88,7 @@ struct DensArgs {
     float gamma;
     const float* drift;      // [0]: bound on the drift since the build (search Hs - 2 drift)
     float grow;              // first list radius over the starting h
+    int scan_lists;          // the re-scanning kernel's lists hold more than a second round of the list kernel
     int detail;              // count the list-building tests and the listed candidates
                              // (sph_params.timing = 2; the list kernel's DETAIL instance)
 };
@@ -672,18 +673,19 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
 }
 
 // ---- the re-scanning kernel: particles flagged ST_SCAN -------------------------------
-// Persistent wavefronts take the queued cells one at a time (or, when the
-// queue is short, a share of a cell's groups: see `split`); a wavefront with
-// no queued cell left exits at once, so the launch costs little when nothing
-// was queued. The flagged particles of a cell are compacted and taken four at
-// a time, RLPI = 16 lanes each. Phase A walks the cell's candidates once and
+// Persistent wavefronts take the queued items one at a time (or, when the
+// queue is short, a share of an item's groups: see `split`); a wavefront with
+// no queued item left exits at once, so the launch costs little when nothing
+// was queued. The flagged particles of an item are compacted and taken four at
+// a time, RLPI = 16 lanes each. Phase A walks the item's candidates once and
 // appends the distance and the mass of every hit inside the search radius to
-// the lane's lists (room for RLPI * RSLOTS hits per particle, four times what
-// the list kernel gives its widest groups); phase B runs Newton's method over
-// the lists with mass-weighted sums. A particle with still more hits re-tests every candidate at each evaluation
-// (rewalk_solve).
+// the lane's lists (room for RLPI * RSLOTS hits per particle); phase B runs
+// Newton's method over the lists with mass-weighted sums. A particle with still more
+// hits re-tests every candidate at each evaluation (rewalk_solve); where the list
+// kernel's second round has as much room, that is all of them, and nothing is listed.
 constexpr int RLPI = 16;
 constexpr int RSLOTS = 32;
+constexpr int GP = 64 / RLPI;  // particles per group
 
 // One evaluation over a lane's list (r and m at stride 64) at 1/h = hinv:
 // S0 = sum w, S1 = sum q w', M0 = sum m w, M1 = sum m q w', and the entries
@@ -818,7 +820,7 @@ __global__ void __launch_bounds__(BS) k_density_scan(DensArgs A)
     __shared__ float4 tile[SCAP];
     __shared__ float lr_all[(RSLOTS + 1) * 64];
     __shared__ float lm_all[(RSLOTS + 1) * 64];
-    __shared__ int pidx[64];
+    __shared__ int pidx[16];
     __shared__ float4 scratch4[WALK_LDS<UNI> / 16];
     char* scratch = reinterpret_cast<char*>(scratch4);
     const int lane = threadIdx.x & 63;
@@ -833,15 +835,14 @@ __global__ void __launch_bounds__(BS) k_density_scan(DensArgs A)
     int list_acc = 0, inter_acc = 0, sweep_acc = 0;
     int max_ev = 0;
     const int n_queued = (int)A.ctr[CT_SCAN_CELLS];  // final: written by the list kernel
-    // A short queue leaves most wavefronts idle while a few take long cells
-    // (a blast's hot centre: thousands of candidates, groups taken one after
-    // another). Each queued cell then becomes `split` items, and item `part`
-    // takes the cell's groups of flagged particles whose number is part
-    // modulo split. A group's arithmetic does not depend on which wavefront
-    // runs it, so the results keep their bits.
+    // A short queue leaves most wavefronts idle while a few take items with
+    // thousands of candidates, groups taken one after another. Each queued item
+    // then goes to `split` wavefronts (an item has at most four groups). A group's
+    // arithmetic does not depend on which wavefront runs it, so the results keep
+    // their bits.
     const int n_waves = (int)gridDim.x * WAVES;
     int split = 1;
-    while (split < 16 && (int64_t)n_queued * split * 2 <= n_waves) split *= 2;
+    while (split < 16 / GP && (int64_t)n_queued * split * 2 <= n_waves) split *= 2;
     const int n_items = n_queued * split;
     if ((int)blockIdx.x * WAVES + (int)(threadIdx.x >> 6) >= n_items) return;
 
@@ -855,93 +856,86 @@ __global__ void __launch_bounds__(BS) k_density_scan(DensArgs A)
         RescanItem<UNI> I;
         item_load(I.it, I.w, A.cell, slot, scratch);
         const int i0 = I.it.i0, ni = I.it.ni;
-        int gbase = 0;  // groups in the cell's earlier blocks
-        for (int b0 = 0; b0 < ni; b0 += 64) {
-            // the flagged particles of these 64, compacted into pidx
-            const bool flag = b0 + lane < ni && A.st_s[i0 + b0 + lane] == ST_SCAN;
-            const uint64_t fm = __ballot(flag);
-            const int nflag = __popcll(fm);
-            wave_sync_lds();  // the previous block's reads of pidx are done
-            if (flag) pidx[lanes_below(fm)] = b0 + lane;
-            wave_sync_lds();
-            constexpr int GP = 64 / RLPI;  // particles per group
-            const int ng = (nflag + GP - 1) / GP;
-            // this item's groups q of the block: gbase + q = part (mod split)
-            for (int q = (part - gbase) & (split - 1); q < ng; q += split) {
-                const int p0 = q * GP;
-                const bool valid = p0 + g < nflag;
-                const int i = i0 + pidx[valid ? p0 + g : p0];
-                float4 xi = A.jd[i];
-                xi.x = item_coord<UNI>(xi.x, I.it.ox, I.it.sh, I.it.sl, 0.0f);
-                xi.y = item_coord<UNI>(xi.y, I.it.oy, I.it.sh, I.it.sl, 0.0f);
-                xi.z = item_coord<UNI>(xi.z, I.it.oz, I.it.sh, I.it.sl, 0.0f);
-                HSolve s = hsolve_init(A.hs[i], A.Hs[i] - two_delta, !valid, ST_ACTIVE);
+        // the item's flagged particles, compacted into pidx
+        const bool flag = lane < ni && A.st_s[i0 + lane] == ST_SCAN;
+        const uint64_t fm = __ballot(flag);
+        const int nflag = __popcll(fm);
+        wave_sync_lds();  // the previous item's reads of pidx are done
+        if (flag) pidx[lanes_below(fm)] = lane;
+        wave_sync_lds();
+        // this wavefront's groups of them: those whose number is part modulo split
+        for (int p0 = GP * part; p0 < nflag; p0 += GP * split) {
+            const bool valid = p0 + g < nflag;
+            const int i = i0 + pidx[valid ? p0 + g : p0];
+            float4 xi = A.jd[i];
+            xi.x = item_coord<UNI>(xi.x, I.it.ox, I.it.sh, I.it.sl, 0.0f);
+            xi.y = item_coord<UNI>(xi.y, I.it.oy, I.it.sh, I.it.sl, 0.0f);
+            xi.z = item_coord<UNI>(xi.z, I.it.oz, I.it.sh, I.it.sl, 0.0f);
+            HSolve s = hsolve_init(A.hs[i], A.Hs[i] - two_delta, !valid, ST_ACTIVE);
 
-                // ---- phase A: every candidate once, hits inside H listed ----------
-                const float H2 = valid ? s.Hi * s.Hi : -1.0f;
-                // the staged candidates any particle of this group can pair with:
-                // within its largest search radius of the box around the group
-                const CullBox gbox = pass_box(xi.x, xi.y, xi.z, valid);
-                const float greach2 = uniform_f(cull_reach2(wave_max(valid ? s.Hi : 0.0f)));
-                unsigned o = o_lane;
-                int kept_tot = 0;
-                bool more = true;
-                for (bool head = true; more; head = false) {
-                    const int kept = rescan_stage(A, I, tile, scratch, head, more, gbox, greach2);
-                    kept_tot += kept;
-                    for (int kk = sub; kk < kept; kk += RLPI) {
-                        const float4 pj = tile[kk];
-                        const float dx = xi.x - pj.x, dy = xi.y - pj.y, dz = xi.z - pj.z;
-                        const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                        const unsigned oo = min(o, o_cap);
-                        *reinterpret_cast<float*>(br + oo) = r2;
-                        *reinterpret_cast<float*>(bm + oo) = pj.w;
-                        o += r2 < H2 ? 256u : 0u;
-                    }
-                    wave_sync_lds();
+            // ---- phase A: every candidate once, hits inside H listed ----------
+            const float H2 = valid ? s.Hi * s.Hi : -1.0f;
+            // the staged candidates any particle of this group can pair with:
+            // within its largest search radius of the box around the group
+            const CullBox gbox = pass_box(xi.x, xi.y, xi.z, valid);
+            const float greach2 = uniform_f(cull_reach2(wave_max(valid ? s.Hi : 0.0f)));
+            unsigned o = o_lane;
+            int kept_tot = 0;
+            bool more = A.scan_lists != 0;
+            for (bool head = true; more; head = false) {
+                const int kept = rescan_stage(A, I, tile, scratch, head, more, gbox, greach2);
+                kept_tot += kept;
+                for (int kk = sub; kk < kept; kk += RLPI) {
+                    const float4 pj = tile[kk];
+                    const float dx = xi.x - pj.x, dy = xi.y - pj.y, dz = xi.z - pj.z;
+                    const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                    const unsigned oo = min(o, o_cap);
+                    *reinterpret_cast<float*>(br + oo) = r2;
+                    *reinterpret_cast<float*>(bm + oo) = pj.w;
+                    o += r2 < H2 ? 256u : 0u;
                 }
-                cand_acc += (int64_t)wave_count(valid && sub == 0) * kept_tot;
-                const int nl = (int)((o - o_lane) >> 8);
-                const bool fits = group_sum_i(nl > RSLOTS ? 1 : 0, RLPI) == 0;
-
-                // ---- phase B: Newton's method over the lists ---------------------
-                const bool listed = valid && fits;
-                if (!listed) s.done = true;
-                const int len_l = listed ? nl : 0;
-                for (int e = 0; e < len_l; ++e) lr[e * 64] = __builtin_amdgcn_sqrtf(lr[e * 64]);
-                float fS0 = 0.f, fM0 = 0.f, fM1 = 0.f;
-                int fcnt = 0;
-                while (__any(!s.done)) {
-                    const float hinv = __builtin_amdgcn_rcpf(s.h);
-                    const int len_e = s.done ? 0 : len_l;
-                    const ListSums L = list_sums(lr, lm, len_e, hinv);
-                    list_acc += len_e;
-                    const float S0 = group_sum(L.S0, RLPI);
-                    const float S1 = group_sum(L.S1, RLPI);
-                    const float M0 = group_sum(L.M0, RLPI);
-                    const float M1 = group_sum(L.M1, RLPI);
-                    const int cnt = group_sum_i(L.cnt, RLPI);
-                    if (s.done) continue;
-                    if (sub == 0) sweep_acc += cnt;
-                    fS0 = S0;
-                    fM0 = M0;
-                    fM1 = M1;
-                    fcnt = cnt;
-                    hsolve_step(s, S0, S1, A.inv_target, A.tol, A.max_iter);
-                }
-                if (listed && sub == 0) {
-                    if (s.state == ST_DONE) inter_acc += fcnt - 1;
-                    max_ev = max(max_ev, s.nev);
-                    write_result<false>(late_args<DensArgs>(), i, A.perm[i], s, fS0, fM0, fM1);
-                }
-
-                // ---- lists too short: re-test every candidate per evaluation -------
-                const bool rewalk = valid && !fits;
-                if (__any(rewalk))
-                    rewalk_solve(A, I, tile, scratch, rewalk, i, xi, sub, gbox, greach2, cand_acc, inter_acc, sweep_acc,
-                                 max_ev);
+                wave_sync_lds();
             }
-            gbase += ng;
+            cand_acc += (int64_t)wave_count(valid && sub == 0) * kept_tot;
+            const int nl = (int)((o - o_lane) >> 8);
+            const bool fits = A.scan_lists && group_sum_i(nl > RSLOTS ? 1 : 0, RLPI) == 0;
+
+            // ---- phase B: Newton's method over the lists ---------------------
+            const bool listed = valid && fits;
+            if (!listed) s.done = true;
+            const int len_l = listed ? nl : 0;
+            for (int e = 0; e < len_l; ++e) lr[e * 64] = __builtin_amdgcn_sqrtf(lr[e * 64]);
+            float fS0 = 0.f, fM0 = 0.f, fM1 = 0.f;
+            int fcnt = 0;
+            while (__any(!s.done)) {
+                const float hinv = __builtin_amdgcn_rcpf(s.h);
+                const int len_e = s.done ? 0 : len_l;
+                const ListSums L = list_sums(lr, lm, len_e, hinv);
+                list_acc += len_e;
+                const float S0 = group_sum(L.S0, RLPI);
+                const float S1 = group_sum(L.S1, RLPI);
+                const float M0 = group_sum(L.M0, RLPI);
+                const float M1 = group_sum(L.M1, RLPI);
+                const int cnt = group_sum_i(L.cnt, RLPI);
+                if (s.done) continue;
+                if (sub == 0) sweep_acc += cnt;
+                fS0 = S0;
+                fM0 = M0;
+                fM1 = M1;
+                fcnt = cnt;
+                hsolve_step(s, S0, S1, A.inv_target, A.tol, A.max_iter);
+            }
+            if (listed && sub == 0) {
+                if (s.state == ST_DONE) inter_acc += fcnt - 1;
+                max_ev = max(max_ev, s.nev);
+                write_result<false>(late_args<DensArgs>(), i, A.perm[i], s, fS0, fM0, fM1);
+            }
+
+            // ---- lists too short: re-test every candidate per evaluation -------
+            const bool rewalk = valid && !fits;
+            if (__any(rewalk))
+                rewalk_solve(A, I, tile, scratch, rewalk, i, xi, sub, gbox, greach2, cand_acc, inter_acc, sweep_acc,
+                             max_ev);
         }
     }
     int64_t inter = inter_acc, swept = sweep_acc, listed = list_acc;  // to wavefront totals
@@ -1035,6 +1029,7 @@ void density_enqueue(sph_ctx* c, const float* mass, float* h, float* rho, float*
     const double want = (c->uni ? 1.35 : 1.85) * c->prm.n_ngb * g * g * g;
     auto launch = [&](auto lcap) {
         constexpr int L = decltype(lcap)::value;
+        A.scan_lists = 4 * L < RLPI * RSLOTS ? 1 : 0;
         if (c->uni)
             A.detail ? k_density<L, true, true><<<grid, BS, 0, s>>>(A) : k_density<L, true, false><<<grid, BS, 0, s>>>(A);
         else
