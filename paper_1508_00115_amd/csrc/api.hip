@@ -122,8 +122,7 @@ void sph_destroy(sph_ctx* c)
                        &c->lf_node, &c->lf_hmax, &c->lf_tmp, &c->p_start, &c->p_cnt, &c->p_leaf, &c->p_shift,
                        &c->p_code, &c->scan_tmp, &c->sort_hist, &c->jd, &c->hs, &c->rhos, &c->fs, &c->status,
                        &c->st_s, &c->jf, &c->vsig_s, &c->bal_s, &c->drift, &c->p_rec, &c->counters, &c->cons_d, &c->cons_part, &c->cons64_d, &c->h64, &c->rho64, &c->f64, &c->st64,
-                       &c->m64s, &c->jf64, &c->hf_tmp, &c->scan_cells, &c->cells, &c->cell_item, &c->it_start, &c->it_leaf, &c->box_item, &c->starts, &c->col_base, &c->xfix, &c->cell_pbox, &c->item_box, &c->cells_d, &c->p_cntd, &c->divv_s,
-                       &c->sched_key, &c->sched_key_alt, &c->sched_val, &c->sched_val_alt, &c->jg};
+                       &c->m64s, &c->jf64, &c->hf_tmp, &c->scan_cells, &c->cells, &c->cell_item, &c->it_start, &c->box_item, &c->starts, &c->col_base, &c->xfix, &c->cell_pbox, &c->item_box, &c->cells_d, &c->p_cntd, &c->divv_s, &c->jg};
     for (sph::Buf* b : all) sph::free_buf(c, *b);
     for (auto& e : c->ev)
         if (e) hipEventDestroy(e);

@@ -726,7 +726,7 @@ __global__ void k_tree_pack(int64_t n_nodes, const int* __restrict__ nd_coord, c
 struct RecordOut {
     int* p_leaf;
     float4* p_shift;
-    int* p_code;
+    uint8_t* p_code;
     int2* p_rec;
     const int* lf_start;
     const int* lf_count;
@@ -936,7 +936,7 @@ __global__ void __launch_bounds__(PBS) k_partners(int64_t nl, int fill, const in
             ro.p_leaf[o] = lf;
             ro.p_rec[o] = make_int2(ro.lf_start[lf], cnt);
             ro.p_shift[o] = sh;
-            ro.p_code[o] = img;
+            ro.p_code[o] = (uint8_t)img;
         }
         nd += __popc(md);
         nf += __popc(mf);
@@ -1053,7 +1053,8 @@ __global__ void __launch_bounds__(256) k_cell_pbox(int64_t n_items, const int4* 
     }
 }
 
-// Sorted FP64 positions and FP32 offsets from the centre of each particle's leaf.
+// Sorted FP32 offsets from the centre of each particle's leaf, or (xrel null) FP64
+// positions.
 __global__ void k_sorted_fill(int64_t n, const uint32_t* __restrict__ perm, const double* __restrict__ pos_w,
                               const int* __restrict__ leaf_of, const int* __restrict__ lf_node,
                               const int* __restrict__ nd_coord, const int* __restrict__ nd_level,
@@ -1077,10 +1078,10 @@ __global__ void k_sorted_fill(int64_t n, const uint32_t* __restrict__ perm, cons
         // a drift across the box boundary, the one on the leaf's side
         const double x = pos_w[3 * (int64_t)o + a];
         const double img = L * rint((x - c[a]) / L);
-        pos_s[3 * p + a] = x - img;
+        if (!xrel) pos_s[3 * p + a] = x - img;
         d[a] = (x - c[a]) - img;
     }
-    xrel[p] = make_float4((float)d[0], (float)d[1], (float)d[2], 0.0f);
+    if (xrel) xrel[p] = make_float4((float)d[0], (float)d[1], (float)d[2], 0.0f);
 }
 
 // Smallest search radius (float bits; non-negative floats order like their bits).
@@ -1256,7 +1257,7 @@ static void fill_lists(sph_ctx* c, const uint32_t* it_start, int64_t n_items, in
     const int64_t nl = c->n_leaves, np = c->n_pairs;
     int* p_leaf = ensure<int>(c, c->p_leaf, np);
     float4* p_shift = ensure<float4>(c, c->p_shift, np);
-    int* p_code = ensure<int>(c, c->p_code, np);
+    uint8_t* p_code = ensure<uint8_t>(c, c->p_code, np);
     int2* p_rec = ensure<int2>(c, c->p_rec, np);
     k_partners<<<(unsigned)blocks_for(nl * 32, PBS), PBS, 0, s>>>(
         nl, 1, static_cast<int*>(c->lf_node.p), tree_view(c), static_cast<int*>(c->nd_box.p),
@@ -1270,11 +1271,9 @@ static void fill_lists(sph_ctx* c, const uint32_t* it_start, int64_t n_items, in
     c->lists_built = true;
 }
 
-static void sorted_fill(sph_ctx* c, hipStream_t s)
+static void sorted_fill(sph_ctx* c, double* pos_s, float4* xrel, hipStream_t s)
 {
     const int64_t n = c->n;
-    double* pos_s = ensure<double>(c, c->pos_s, 3 * n);
-    float4* xrel = ensure<float4>(c, c->xrel, n);
     k_sorted_fill<<<blocks_for(n, BS), BS, 0, s>>>(
         n, static_cast<uint32_t*>(c->perm.p), static_cast<double*>(c->pos_w.p), static_cast<int*>(c->leaf_of.p),
         static_cast<int*>(c->lf_node.p), static_cast<int*>(c->nd_coord.p), static_cast<int*>(c->nd_level.p),
@@ -1284,17 +1283,18 @@ static void sorted_fill(sph_ctx* c, hipStream_t s)
 
 void partner_lists(sph_ctx* c, hipStream_t s)
 {
-    if (!c->uni) return;  // the build made them, and every drift the positions
-    finish_build_read(c);
     if (!c->lists_built) {
+        finish_build_read(c);
         list_offsets(c, true, s);
         fill_lists(c, nullptr, 0, nullptr, nullptr, nullptr, 0, s);
     }
-    sorted_fill(c, s);
+    if (!c->pos_built) sorted_fill(c, ensure<double>(c, c->pos_s, 3 * c->n), nullptr, s);
+    c->pos_built = true;
 }
 
 // Everything after the positions are wrapped: keys, sort, tree, leaves, lists.
-static void build_from_wrapped(sph_ctx* c, hipStream_t s)
+// allow_grid: take the grid layout where it serves.
+static void build_layout(sph_ctx* c, bool allow_grid, hipStream_t s)
 {
     const int64_t n = c->n;
     const int nb = c->n_boxes;
@@ -1338,7 +1338,7 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     // the radii differ so much that the columns would hold many candidates for
     // nothing: with the top cells kept whole a pass over 32768 clustered particles
     // takes 607 us, split (the tree) 558; a log-normal set of 64000 268 and 190
-    bool grid_ok = true;
+    bool grid_ok = allow_grid;
     bt.col_base[0] = 0;
     bt.top_base[0] = 0;
     for (int b = 0; b < nb; ++b) {
@@ -1581,15 +1581,12 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
         // ranges each ordered by decreasing cost
         const int order = c->prm.cell_order;
         const bool by_cost = order != 1;
-        int* it_leaf = ensure<int>(c, c->it_leaf, ni);
-        uint64_t* sk = by_cost ? ensure<uint64_t>(c, c->sched_key, ni) : nullptr;
-        uint32_t* sv = by_cost ? ensure<uint32_t>(c, c->sched_val, ni) : nullptr;
+        // (in what the particles' keys and scans leave free: no more items than particles)
+        int* it_leaf = reinterpret_cast<int*>(excl);
+        uint64_t* sk = by_cost ? keys : nullptr;
+        uint32_t* sv = by_cost ? perm_alt : nullptr;
         fill_lists(c, it_start, ni, it_leaf, sk, sv, order == 2 ? 1 : 0, s);
-        if (by_cost) {
-            uint64_t* ska = ensure<uint64_t>(c, c->sched_key_alt, ni);
-            uint32_t* sva = ensure<uint32_t>(c, c->sched_val_alt, ni);
-            radix_sort(c, sk, sv, ska, sva, ni, order == 2 ? 15 : 12, s);
-        }
+        if (by_cost) radix_sort(c, sk, sv, keys_alt, head, ni, order == 2 ? 15 : 12, s);
         int4* cells = ensure<int4>(c, c->cells, ni);
         int* cell_item = ensure<int>(c, c->cell_item, ni);
         int4* cells_d = ensure<int4>(c, c->cells_d, ni);
@@ -1625,6 +1622,22 @@ static void build_from_wrapped(sph_ctx* c, hipStream_t s)
     ++c->layout_serial;  // cell arrays and grid sizes changed
     c->density_done = false;
     c->density64_done = false;
+}
+
+// The build. Where memory runs out with a grid's tables (held for this build or
+// kept from an earlier one) those are given back and the cells made as a tree, so that
+// what the tree alone has room for is accepted.
+static void build_from_wrapped(sph_ctx* c, hipStream_t s)
+{
+    try {
+        build_layout(c, true, s);
+    } catch (const Error& e) {
+        if (e.code != SPH_E_NOMEM || !c->starts.p) throw;
+        SPH_HIP(hipDeviceSynchronize());
+        for (Buf* b : {&c->starts, &c->xfix, &c->it_start, &c->cells, &c->cell_pbox}) free_buf(c, *b);
+        fill_u32(c->counters.p, 0u, 2 * (int64_t)CT_COUNT, s);
+        build_layout(c, false, s);
+    }
 }
 
 void finish_build_read(sph_ctx* c)
@@ -1670,11 +1683,12 @@ void build_cells(sph_ctx* c, int32_t n_boxes, const int64_t* box_first, const do
     build_from_wrapped(c, s);
 }
 
-// The sorted positions (32-bit fractions, or offsets from the leaf centres and
-// FP64 positions) and the items' boxes from the current positions, keeping the
-// cells: at a build and after a drift.
+// The sorted positions (32-bit fractions, or offsets from the leaf centres) and
+// the items' boxes from the current positions, keeping the cells: at a build and
+// after a drift.
 void refresh_offsets(sph_ctx* c, hipStream_t s)
 {
+    c->pos_built = false;
     if (c->uni) {
         int4* xfix = ensure<int4>(c, c->xfix, c->n);
         k_fix_fill<<<blocks_for(c->n, BS), BS, 0, s>>>(c->n, static_cast<uint32_t*>(c->perm.p),
@@ -1684,7 +1698,7 @@ void refresh_offsets(sph_ctx* c, hipStream_t s)
                                                       static_cast<int*>(c->box_G.p), xfix);
         SPH_HIP(hipGetLastError());
     } else {
-        sorted_fill(c, s);
+        sorted_fill(c, nullptr, ensure<float4>(c, c->xrel, c->n), s);
     }
     cell_boxes(c, s);
 }

@@ -151,7 +151,7 @@ struct sph_ctx {
     sph::Buf pos_w;          // double3 AoS, wrapped, caller order
     sph::Buf hguess;         // float, caller order (copy of h_guess)
     sph::Buf keys, keys_alt, perm, perm_alt;  // sort
-    sph::Buf pos_s;          // double3 AoS, sorted
+    sph::Buf pos_s;          // double3 AoS, sorted (the plain FP64 form alone reads them)
     sph::Buf xrel;           // float4 (x, y, z, 0) offsets from the leaf centre, sorted
     sph::Buf Hs;             // float search radius h_margin * h_guess, sorted
     // Drift since the last build (the cells are kept across drifts), 4 words:
@@ -167,6 +167,7 @@ struct sph_ctx {
     bool uni = false;
     int fzb = 0;                  // grid: fine cells in z per top cell, logarithm
     bool lists_built = false;     // p_start, p_leaf, p_code ... hold the current cells' lists
+    bool pos_built = false;       // pos_s holds the current positions
     bool drift_pending = false;   // a drift since the last check of delta
     sph::Buf leaf_of;        // int, sorted particle -> leaf
     sph::Buf unassigned;     // int flags per particle during the level loop
@@ -189,11 +190,10 @@ struct sph_ctx {
     sph::Buf p_leaf;         // int
     sph::Buf p_rec;          // int2 per record: first particle and count of the neighbour leaf
     sph::Buf p_shift;        // float4 (dx, dy, dz, bits): leaf-centre frame offset, first item of the leaf
-    sph::Buf p_code;         // int: periodic image code (3 x 2 bits)
+    sph::Buf p_code;         // uint8: periodic image code (3 x 2 bits)
     // work items of the hot kernels: runs of at most 16 particles of one leaf
     // (tree), or of one column of top cells (grid)
     sph::Buf it_start;       // uint32: first item of each leaf or column, and their number
-    sph::Buf it_leaf;        // int per item: its leaf (tree)
     sph::Buf box_item;       // int, n_boxes + 1: first item of each box
     sph::Buf starts;         // grid: int, first particle of each fine cell
     sph::Buf col_base;       // grid: int, n_boxes + 1: first column of each box
@@ -206,7 +206,6 @@ struct sph_ctx {
     sph::Buf nd_pack;        // int4 x 2 per node: the tree as the partner walks read it
     sph::Buf item_box;       // tree: float4 x 2 per item, as cell_pbox
     sph::Buf cells_d;        // int4 per slot as `cells`, with the density's record count (a prefix)
-    sph::Buf sched_key, sched_key_alt, sched_val, sched_val_alt;  // cost sort
     sph::Buf scan_tmp;       // scan workspace
     sph::Buf sort_hist;      // radix-sort histograms
 
@@ -483,8 +482,9 @@ double timestep_noalloc(sph_ctx* c, double courant, hipStream_t s);
 void scratch_setup(int device);
 // Offsets from the leaf centres from the current positions (build.hip).
 void refresh_offsets(sph_ctx* c, hipStream_t s);
-// The leaves' partner lists and sorted FP64 positions of the current cells,
-// where the build left them out (a grid layout; the plain FP64 form walks them).
+// The leaves' partner lists and the sorted FP64 positions of the current cells,
+// which the plain FP64 form walks, where they are not there yet (a build leaves the
+// positions out, and in a grid layout the lists).
 void partner_lists(sph_ctx* c, hipStream_t s);
 // Bounding boxes of the items' particles at their current offsets (cell_pbox).
 void cell_boxes(sph_ctx* c, hipStream_t s);

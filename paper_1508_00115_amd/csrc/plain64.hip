@@ -31,7 +31,7 @@ struct D64Args {
     const uint32_t* p_start;
     const uint32_t* p_cntd;   // per leaf: its records within its largest search radius (a prefix)
     const int* p_leaf;
-    const int* p_code;
+    const uint8_t* p_code;
     const uint32_t* perm;
     double* h_out;
     double* rho_out;
@@ -208,7 +208,7 @@ struct F64Args {
     const double* box_len;
     const uint32_t* p_start;
     const int* p_leaf;
-    const int* p_code;
+    const uint8_t* p_code;
     const uint32_t* perm;
     double* acc;
     double* dudt;
@@ -358,7 +358,7 @@ void density_f64(sph_ctx* c, const double* mass, double* h, double* rho, double*
         A.p_start = static_cast<uint32_t*>(c->p_start.p);
         A.p_cntd = static_cast<uint32_t*>(c->p_cntd.p);
         A.p_leaf = static_cast<int*>(c->p_leaf.p);
-        A.p_code = static_cast<int*>(c->p_code.p);
+        A.p_code = static_cast<uint8_t*>(c->p_code.p);
         A.perm = static_cast<uint32_t*>(c->perm.p);
         A.h_out = h;
         A.rho_out = rho;
@@ -456,7 +456,7 @@ void force_f64(sph_ctx* c, const double* vel, const double* u, double* acc, doub
     A.box_len = static_cast<double*>(c->box_len.p);
     A.p_start = static_cast<uint32_t*>(c->p_start.p);
     A.p_leaf = static_cast<int*>(c->p_leaf.p);
-    A.p_code = static_cast<int*>(c->p_code.p);
+    A.p_code = static_cast<uint8_t*>(c->p_code.p);
     A.perm = static_cast<uint32_t*>(c->perm.p);
     A.acc = acc;
     A.dudt = dudt;
