@@ -49,7 +49,8 @@
  *     calls synchronise `stream` once.
  *   - Errors: every call returns an sph_status. On error the outputs are
  *     unspecified and sph_last_error() describes the cause. A context stays
- *     usable after any error except SPH_E_HIP.
+ *     usable after any error except SPH_E_HIP; after a build or rebuild that
+ *     ran out of memory it has no cells (SPH_E_STATE until sph_build_cells).
  *   - A context is not thread-safe; use one context per stream.
  */
 #ifndef SPH_MI355X_H

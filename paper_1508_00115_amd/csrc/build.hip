@@ -1331,6 +1331,8 @@ static void build_layout(sph_ctx* c, bool allow_grid, hipStream_t s)
         maxG3 = std::max<uint64_t>(maxG3, (uint64_t)G * G * G);
     }
     c->n_top = c->h_box_top_base[nb];
+    // from here on the last cells are taken apart: none to compute on until these are whole
+    c->built = false;
     // columns of top cells of each box, for a grid layout, which needs at least
     // four cells per side (the frame of an item reaches a cell and a half from
     // its centre, and with three the cells on both sides are the same ones) and a

@@ -70,3 +70,47 @@ def test_a_tree_fits_without_the_grids_tables(gpu_lib):
         finally:
             ctx.close()
     assert np.array_equal(acc[0], acc[1]) and np.array_equal(acc[0], acc[2])
+
+
+def test_a_rebuild_without_room_leaves_no_cells(gpu_lib):
+    """Limits that have room for the first cells but not for those of a rebuild (the
+    guesses are much too small, and the lists of the wider cells longer): every call
+    on the half-made cells is refused, and the context takes new ones."""
+    import torch
+    d = workloads.clustered(n_uniform=20000, n_spheres=4, per_sphere=2000)
+    t = {k: torch.from_numpy(d[k]).cuda() for k in ("pos", "vel", "mass", "u", "h0")}
+    n = t["h0"].numel()
+    low = (0.7 * t["h0"]).contiguous()
+    small = workloads.lattice_box(10, [1508, 983], jitter=0.1)
+    refused = 0
+    for limit in np.geomspace(5e6, 30e6, 80).astype(int).tolist():
+        ctx = gpu_lib.Context(0, workspace_limit=limit)
+        try:
+            ctx.build_cells(t["pos"], low)
+            try:
+                ctx.density(t["mass"], low.clone())
+                continue
+            except gpu_lib.SphError as e:
+                assert e.code == gpu_lib.SPH_E_NOMEM
+            calls = (lambda: ctx.density(t["mass"], low.clone()), lambda: ctx.force(t["vel"], t["u"]),
+                     lambda: ctx.pass_(t["mass"], low.clone(), t["vel"], t["u"]),
+                     lambda: ctx.drift(1e-9, t["vel"], t["pos"]), lambda: ctx.gravity_p2p(t["mass"], 1.0, 0.0, 1e-4),
+                     lambda: ctx.density_f64(t["mass"].double(), low.double()))
+            codes = []
+            for call in calls:
+                try:
+                    call()
+                    codes.append(0)
+                except gpu_lib.SphError as e:
+                    codes.append(e.code)
+            if codes[0] == gpu_lib.SPH_E_STATE:  # the cells are gone (not only a buffer of the density)
+                refused += 1
+                assert set(codes) == {gpu_lib.SPH_E_STATE}, codes
+            ctx.build_cells(torch.from_numpy(small["pos"]).cuda(), torch.from_numpy(small["h0"]).cuda())
+            ctx.density(torch.from_numpy(small["mass"]).cuda(), torch.from_numpy(small["h0"]).cuda())
+        except gpu_lib.SphError as e:
+            assert e.code == gpu_lib.SPH_E_NOMEM  # no room for the first cells
+        finally:
+            ctx.close()
+    print("rebuilds refused:", refused, "N", n, flush=True)
+    assert refused > 0
