@@ -431,10 +431,14 @@ __global__ void __launch_bounds__(256) k_fix_pbox(int64_t n_items, const int4* _
     }
 }
 
+// Sorted search radii; also no drift yet (sph_ctx::drift: bound, step maximum,
+// smallest search radius before its minimum, non-finite flag).
 __global__ void k_sorted_H(int64_t n, const uint32_t* __restrict__ perm, const float* __restrict__ hg,
-                           float margin, float* __restrict__ Hs, int* __restrict__ leaf_tmp)
+                           float margin, float* __restrict__ Hs, int* __restrict__ leaf_tmp,
+                           unsigned* __restrict__ drift)
 {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p < 4) drift[p] = p == 2 ? 0x7f800000u : 0u;
     if (p >= n) return;
     Hs[p] = margin * hg[perm[p]];
     if (leaf_tmp) leaf_tmp[p] = -1;
@@ -1153,9 +1157,6 @@ __global__ void k_level_out(const uint32_t* __restrict__ d, const uint32_t* __re
     if (threadIdx.x == 2) h.level[2] = n_items ? *n_items : 0u;
 }
 
-// Bound, step maximum, smallest search radius (before its minimum), non-finite flag.
-__global__ void k_drift_init(unsigned* drift) { drift[threadIdx.x] = threadIdx.x == 2 ? 0x7f800000u : 0u; }
-
 // The build's shape counters folded over their spread slots, and the
 // smallest search radius, into out (BUILD_OUT_WORDS words of pinned host memory,
 // read after the next synchronisation).
@@ -1399,8 +1400,9 @@ static void build_layout(sph_ctx* c, bool allow_grid, hipStream_t s)
 
     float* Hs = ensure<float>(c, c->Hs, n);
     int* leaf_tmp = ensure<int>(c, c->lf_tmp, n);
+    unsigned* drift = ensure<unsigned>(c, c->drift, 4);
     k_sorted_H<<<blocks_for(n, BS), BS, 0, s>>>(n, perm, static_cast<float*>(c->hguess.p), margin, Hs,
-                                                leaf_tmp);
+                                                leaf_tmp, drift);
     SPH_HIP(hipGetLastError());
 
     // ---- tree, level by level ---------------------------------------------------------------
@@ -1510,7 +1512,7 @@ static void build_layout(sph_ctx* c, bool allow_grid, hipStream_t s)
             SPH_HIP(hipGetLastError());
             radix_sort(c, keys, perm, keys_alt, perm_alt, n, c->bits_box + c->bits_top + 3 * c->levels, s);
             k_sorted_H<<<blocks_for(n, BS), BS, 0, s>>>(n, perm, static_cast<float*>(c->hguess.p), margin, Hs,
-                                                        nullptr);
+                                                        nullptr, drift);
             SPH_HIP(hipGetLastError());
         }
         prev_base = node_base;
@@ -1600,11 +1602,8 @@ static void build_layout(sph_ctx* c, bool allow_grid, hipStream_t s)
 
     // ---- sorted particle streams ------------------------------------------------------------------
     refresh_offsets(c, s);
-    // no drift since this build; the smallest search radius bounds how far
-    // the particles may drift before the cells are rebuilt
-    unsigned* drift = ensure<unsigned>(c, c->drift, 4);
-    k_drift_init<<<1, 4, 0, s>>>(drift);
-    SPH_HIP(hipGetLastError());
+    // the smallest search radius bounds how far the particles may drift before
+    // the cells are rebuilt
     k_min_H<<<(unsigned)std::max<int64_t>(1, std::min<int64_t>(blocks_for(n, BS), 256)), BS, 0, s>>>(n, Hs,
                                                                                                  drift + 2);
     SPH_HIP(hipGetLastError());
