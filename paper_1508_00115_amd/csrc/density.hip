@@ -292,8 +292,10 @@ __device__ __forceinline__ void enqueue_scan(KernArgs<DensArgs> A, int slot, int
 //
 // Rounds: the first takes all of the item's particles, four lanes each; those
 // whose list did not fit, or whose root lies beyond it, are taken up to four at
-// a time after that, 16 lanes and four times the room each.
-template <int LCAP, bool UNI, bool DETAIL>
+// a time after that, 16 lanes and four times the room each. HALF: eight particles
+// at first, eight lanes and twice the room each, then the others: for more
+// neighbours than 16 lists of LDS and registers hold with two wavefronts on a SIMD.
+template <int LCAP, bool HALF, bool UNI, bool DETAIL>
 __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_density(DensArgs A)
 {
     static_assert(LCAP % 16 == 0, "a lane reads its list four entries at a time");
@@ -361,21 +363,26 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
             listed_acc += all;
         }
 
+        unsigned big = 0u;  // (HALF) those to be taken with the most room
         for (int round = 0; todo; ++round) {
             // ---- this round's particles, and which one this lane works for -------------------
-            const int lpp = round == 0 ? 4 : 16, lg = round == 0 ? 2 : 4;
+            const bool first = HALF ? (todo & ~big) != 0u : round == 0;
+            const int lg = first ? (HALF ? 3 : 2) : 4, lpp = 1 << lg;
             const int sub = lane & (lpp - 1);
-            unsigned batch = todo;
+            const unsigned pool = HALF && first ? todo & ~big : todo;
+            unsigned batch = pool;
             int pq = lane >> lg;
-            if (round > 0) {
-                unsigned rest = todo;
+            if (HALF || !first) {
+                unsigned rest = pool;
                 int pk = 0;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    pk = pq == k && rest ? __builtin_ctz(rest) : pk;
-                    rest &= rest - 1;
+                for (int k = 0; k < (HALF ? 8 : 4); ++k) {
+                    if (k < 64 >> lg) {
+                        pk = pq == k && rest ? __builtin_ctz(rest) : pk;
+                        rest &= rest - 1;
+                    }
                 }
-                batch = todo & ~rest;
+                batch = pool & ~rest;
                 const bool any = pq < __popc(batch);
                 pq = any ? pk : 31;
             }
@@ -383,10 +390,11 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
             const int iq = i0 + (mine ? pq : 0);
             // column pc: its list segment, and the first lane of its particle
             const bool inb = (batch >> pc) & 1u;
-            const int rank = round == 0 ? pc : __popc(batch & ((1u << pc) - 1u));
+            const int rank = HALF || !first ? __popc(batch & ((1u << pc) - 1u)) : pc;
             const int lane_c = (rank << lg) & 63;
-            const int seg = round == 0 ? SEG * pc : 4 * SEG * rank;
-            const int room = round == 0 ? LCAP : 4 * LCAP;
+            const int parts = lpp >> 2;  // a list's segments
+            const int seg = parts * SEG * rank;
+            const int room = parts * LCAP;
             const float h_start = A.hs[iq], H = A.Hs[iq] - two_delta;
             HSolve s = hsolve_init(h_start, H, !mine, ST_ACTIVE);
             {
@@ -570,12 +578,12 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
 
                 // ---- the lists that fit, in registers: entries 4 (j lpp + sub) ... + 3 -----------------
                 const unsigned over = (unsigned)__ballot(inb && T > room) & 0xffffu;
-                if (round > 0) scan |= over;  // (no room here either)
+                if (!first) scan |= over;  // (no room here either)
                 const int Tq = __shfl(T, pq & 15, 64);
                 solved = mine && Tq <= room;
                 const int len = solved ? Tq : 0;
                 const int nj4 = (wave_max_u(len) + 4 * lpp - 1) >> (lg + 2);
-                float* lq = list + (round == 0 ? SEG : 4 * SEG) * (lane >> lg);
+                float* lq = list + parts * SEG * (lane >> lg);
                 for (int e = len + sub; e < 4 * lpp * nj4; e += lpp) lq[e] = FAR2;
                 wave_sync_lds();
                 float4 r4[NR];
@@ -649,7 +657,8 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                 const unsigned bm = (unsigned)__ballot(inb && beyond_c) & 0xffffu;
                 wide |= bm;
                 again |= over | bm;
-                todo &= ~(batch & ~bm & (round == 0 ? ~over : ~0u));
+                big |= over | bm;
+                todo &= ~(batch & ~bm & (first ? ~over : ~0u));
                 if (!mixed || !__any(solved)) break;
             }
             if (mixed) again |= batch;
@@ -1015,37 +1024,54 @@ void density_enqueue(sph_ctx* c, const float* mass, float* h, float* rho, float*
     // re-scan grid: enough wavefronts for a full queue; the surplus exits at once
     const int scan_grid = (int)std::max<int64_t>(std::min<int64_t>(c->n_items, (int64_t)c->n_cu * 8), 1);
     if (events) ev_record(c, EV_DENS_K0, s);
-    // Room of the lists. A good guess finds about n_ngb g^3 candidates inside its
+    // Room of the lists. A good guess finds about x = n_ngb g^3 candidates inside its
     // first radius (g the smaller of h_margin and LIST_GROW): a third more on a
     // grid, where the guesses of a lattice are good, nearly twice that in a tree,
     // where a particle that needs a second list costs its item a second sweep
     // (log-normal 2^24: 96 entries, 27 of 1000 particles, 11.9 ms; 128, 3 of 1000,
     // 11.5 ms). Longer lists cost LDS and registers, so wavefronts: the clustered
     // 2^20 set with 48 neighbours and the default margin, which just fits 128,
-    // takes 936 us with 128 entries and 1291 us with 240.
+    // takes 936 us with 128 entries and 1291 us with 240. 240 serve to x = 235 on a
+    // grid and 200 in a tree, 320 to x = 300: with 448 for all, the lattices in a tree
+    // were slower than with a list per cell (64^3, 140 neighbours, margin 1.26: 0.58 ms
+    // so, 0.88 with 448, 0.43 with 240; 100^3, 200 and 1.05: 1.79, 2.62, and 1.63 with
+    // 320), and clustered sets slower than with 320 (2^20, 200 and 1.05: 5.5 and 4.7
+    // ms). 240 by halves are better on those (4.4 ms) and worse on the lattices (2.1
+    // ms). Beyond, half the item at a time: 64^3 with 300 neighbours and
+    // 1.05, 240 by halves 0.84 ms, 448 1.14; 100^3 with 400 and 1.26, x = 562, 320 by
+    // halves 5.6 ms, 448 17.8.
     const bool wide = c->prm.h_margin > LIST_WIDE;
     const double g = wide ? (double)LIST_GROW : c->prm.h_margin;
     A.grow = wide ? LIST_GROW : 1.0e30f;
-    const double want = (c->uni ? 1.35 : 1.85) * c->prm.n_ngb * g * g * g;
-    auto launch = [&](auto lcap) {
+    const double x = c->prm.n_ngb * g * g * g;
+    const double want = (c->uni ? 1.35 : 1.85) * x;
+    auto launch = [&](auto lcap, auto half) {
         constexpr int L = decltype(lcap)::value;
+        constexpr bool H = decltype(half)::value;
         A.scan_lists = 4 * L < RLPI * RSLOTS ? 1 : 0;
         if (c->uni)
-            A.detail ? k_density<L, true, true><<<grid, BS, 0, s>>>(A) : k_density<L, true, false><<<grid, BS, 0, s>>>(A);
+            A.detail ? k_density<L, H, true, true><<<grid, BS, 0, s>>>(A)
+                     : k_density<L, H, true, false><<<grid, BS, 0, s>>>(A);
         else
-            A.detail ? k_density<L, false, true><<<grid, BS, 0, s>>>(A)
-                     : k_density<L, false, false><<<grid, BS, 0, s>>>(A);
+            A.detail ? k_density<L, H, false, true><<<grid, BS, 0, s>>>(A)
+                     : k_density<L, H, false, false><<<grid, BS, 0, s>>>(A);
     };
+    using Whole = std::false_type;
+    using Half = std::true_type;
     if (want <= 80.0)
-        launch(std::integral_constant<int, 80>{});
+        launch(std::integral_constant<int, 80>{}, Whole{});
     else if (want <= 96.0)
-        launch(std::integral_constant<int, 96>{});
+        launch(std::integral_constant<int, 96>{}, Whole{});
     else if (want <= 128.0)
-        launch(std::integral_constant<int, 128>{});
-    else if (want <= 240.0)
-        launch(std::integral_constant<int, 240>{});
+        launch(std::integral_constant<int, 128>{}, Whole{});
+    else if (x <= (c->uni ? 235.0 : 200.0))
+        launch(std::integral_constant<int, 240>{}, Whole{});
+    else if (x <= 300.0)
+        launch(std::integral_constant<int, 320>{}, Whole{});
+    else if (x <= 470.0)
+        launch(std::integral_constant<int, 240>{}, Half{});
     else
-        launch(std::integral_constant<int, 448>{});
+        launch(std::integral_constant<int, 320>{}, Half{});
     SPH_HIP(hipGetLastError());
     if (events) ev_record(c, EV_DENS_KM, s);
     if (c->uni)

@@ -121,3 +121,27 @@ def test_listed_counts_with_a_rescan(gpu_lib, name):
     for g in _run(gpu_lib, d, timing=2, **params):
         print("listed", name, left, g["stats"]["listed_density"], near, flush=True)
         assert near[0] <= g["stats"]["listed_density"] <= near[1]
+
+
+@pytest.mark.parametrize("layout", ["grid", "tree"])
+@pytest.mark.parametrize("n,n_ngb,margin", [(19, 200.0, 1.26), (21, 300.0, 1.05), (24, 400.0, 1.26)])
+@pytest.mark.parametrize("guess", [1.0, 0.86, 1.2, "masses"])
+def test_many_neighbours(gpu_lib, layout, n, n_ngb, margin, guess):
+    """Many neighbours: lists of 320 entries to 300 expected neighbours, then half an
+    item at a time (to 470 twice 240 entries, above twice 320), with good guesses, roots beyond the first list or the cells, lists that do not fit, and
+    masses from U(0.5, 1.5)."""
+    d = workloads.lattice_box(n, [1508, 971], jitter=0.2, u=1.0, vel_sigma=0.2)
+    if guess == "masses":
+        d["mass"] = (d["mass"] * np.random.default_rng([1508, 972]).uniform(0.5, 1.5, n**3)).astype(np.float32)
+        guess = 1.0
+    d["h0"] = (d["h0"] * guess * np.cbrt(n_ngb / 48.0)).astype(np.float32)
+    if margin * float(d["h0"].max()) * 3.0 > 1.0:
+        pytest.skip("guesses above a third of the box")
+    print("many", layout, n, n_ngb, margin, guess, "G", int(1.0 / (margin * float(d["h0"].max()))), flush=True)
+    r = oracle.run(d, n_ngb=n_ngb)
+    for g in _run(gpu_lib, d, n_ngb=n_ngb, h_margin=margin, leaf_target=100000 if layout == "grid" else 64):
+        e = errors(g, r)
+        assert_within(e, TOL32, "many")
+        n_d = int(r["nngb"].sum())
+        assert abs(g["stats"]["interactions_density"] - n_d) <= 1e-5 * n_d + 2
+    print(e, g["stats"], flush=True)
