@@ -88,6 +88,7 @@ struct DensArgs {
     float gamma;
     const float* drift;      // [0]: bound on the drift since the build (search Hs - 2 drift)
     float grow;              // first list radius over the starting h
+    int list_room;           // (HALF) room of a list at which an item is taken whole
     int scan_lists;          // the re-scanning kernel's lists hold more than a second round of the list kernel
     int detail;              // count the list-building tests and the listed candidates
                              // (sph_params.timing = 2; the list kernel's DETAIL instance)
@@ -292,15 +293,17 @@ __device__ __forceinline__ void enqueue_scan(KernArgs<DensArgs> A, int slot, int
 //
 // Rounds: the first takes all of the item's particles, four lanes each; those
 // whose list did not fit, or whose root lies beyond it, are taken up to four at
-// a time after that, 16 lanes and four times the room each. HALF: eight particles
-// at first, eight lanes and twice the room each, then the others: for more
-// neighbours than 16 lists of LDS and registers hold with two wavefronts on a SIMD.
+// a time after that, 16 lanes and four times the room each. HALF, for more neighbours
+// than 16 lists hold with two wavefronts on a SIMD: the item's particles still at
+// once where they are so few that each has room for list_room entries, else eight at a
+// time, eight lanes and twice the room each.
 template <int LCAP, bool HALF, bool UNI, bool DETAIL>
 __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_density(DensArgs A)
 {
     static_assert(LCAP % 16 == 0, "a lane reads its list four entries at a time");
     constexpr int SEG = LCAP + 4;    // (skewed against bank conflicts)
-    constexpr int NR = LCAP / 16;
+    constexpr int TOT = 16 * SEG;    // LDS entries of the lists
+    constexpr int NR = HALF && LCAP < 300 ? 28 : LCAP / 16;  // float4 of a lane's entries
     constexpr int NW = (DCAP + 127) / 128;
     constexpr int U = 2;             // candidates per lane and step
     constexpr float FAR2 = 1.0e30f;  // r^2 of an empty entry
@@ -367,16 +370,17 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
         for (int round = 0; todo; ++round) {
             // ---- this round's particles, and which one this lane works for -------------------
             const bool first = HALF ? (todo & ~big) != 0u : round == 0;
-            const int lg = first ? (HALF ? 3 : 2) : 4, lpp = 1 << lg;
-            const int sub = lane & (lpp - 1);
             const unsigned pool = HALF && first ? todo & ~big : todo;
+            const bool whole = HALF && first && A.list_room <= 16 * NR && __popc(pool) * (A.list_room + 4) <= TOT;
+            const int lg = first ? (HALF && !whole ? 3 : 2) : 4, lpp = 1 << lg;
+            const int sub = lane & (lpp - 1);
             unsigned batch = pool;
             int pq = lane >> lg;
             if (HALF || !first) {
                 unsigned rest = pool;
                 int pk = 0;
 #pragma unroll
-                for (int k = 0; k < (HALF ? 8 : 4); ++k) {
+                for (int k = 0; k < (HALF ? 16 : 4); ++k) {
                     if (k < 64 >> lg) {
                         pk = pq == k && rest ? __builtin_ctz(rest) : pk;
                         rest &= rest - 1;
@@ -392,9 +396,10 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
             const bool inb = (batch >> pc) & 1u;
             const int rank = HALF || !first ? __popc(batch & ((1u << pc) - 1u)) : pc;
             const int lane_c = (rank << lg) & 63;
-            const int parts = lpp >> 2;  // a list's segments
-            const int seg = parts * SEG * rank;
-            const int room = parts * LCAP;
+            // (a list's stride and room)
+            const int stride = whole ? min(16 * NR, (TOT / __popc(pool) - 4) & ~15) + 4 : (lpp >> 2) * SEG;
+            const int seg = stride * rank;
+            const int room = whole ? stride - 4 : (lpp >> 2) * LCAP;
             const float h_start = A.hs[iq], H = A.Hs[iq] - two_delta;
             HSolve s = hsolve_init(h_start, H, !mine, ST_ACTIVE);
             {
@@ -583,8 +588,9 @@ __global__ void __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) k_
                 solved = mine && Tq <= room;
                 const int len = solved ? Tq : 0;
                 const int nj4 = (wave_max_u(len) + 4 * lpp - 1) >> (lg + 2);
-                float* lq = list + parts * SEG * (lane >> lg);
-                for (int e = len + sub; e < 4 * lpp * nj4; e += lpp) lq[e] = FAR2;
+                // (lane groups without a particle have no list: they read the first and write none)
+                float* lq = list + (mine ? stride * (lane >> lg) : 0);
+                for (int e = len + sub; mine && e < 4 * lpp * nj4; e += lpp) lq[e] = FAR2;
                 wave_sync_lds();
                 float4 r4[NR];
 #pragma unroll
@@ -1032,14 +1038,14 @@ void density_enqueue(sph_ctx* c, const float* mass, float* h, float* rho, float*
     // 11.5 ms). Longer lists cost LDS and registers, so wavefronts: the clustered
     // 2^20 set with 48 neighbours and the default margin, which just fits 128,
     // takes 936 us with 128 entries and 1291 us with 240. 240 serve to x = 235 on a
-    // grid and 200 in a tree, 320 to x = 300: with 448 for all, the lattices in a tree
-    // were slower than with a list per cell (64^3, 140 neighbours, margin 1.26: 0.58 ms
-    // so, 0.88 with 448, 0.43 with 240; 100^3, 200 and 1.05: 1.79, 2.62, and 1.63 with
-    // 320), and clustered sets slower than with 320 (2^20, 200 and 1.05: 5.5 and 4.7
-    // ms). 240 by halves are better on those (4.4 ms) and worse on the lattices (2.1
-    // ms). Beyond, half the item at a time: 64^3 with 300 neighbours and
-    // 1.05, 240 by halves 0.84 ms, 448 1.14; 100^3 with 400 and 1.26, x = 562, 320 by
-    // halves 5.6 ms, 448 17.8.
+    // grid and 200 in a tree. Beyond, longer lists for all of an item leave one
+    // wavefront on a SIMD (448 entries; one and a half with 320): half an item at a time,
+    // or a small one (a tree's leaf of nine) whole, with the same LDS, is better (ms: a
+    // list per cell of old / 448 / 320 / so): 64^3, 170 neighbours, margin 1.26: 0.74 /
+    // 0.90 / 0.59 / 0.49; 100^3, 250 and 1.05: 1.94 / 4.5 / 2.85 / 2.29; 100^3, 300 and
+    // 1.05: 2.37 / 4.2 / - / 3.1; clustered 2^20, 200 and 1.26: 55 / 9.6 / 9.8 / 7.6;
+    // log-normal 2^21, 200 and 1.05: 6.9 / 8.9 / 7.3 / 6.1. Above x = 470 the halves'
+    // lists have room for 640: 100^3, 400 and 1.26, x = 562: 24.7 / 17.8 / 10.9 / 5.6.
     const bool wide = c->prm.h_margin > LIST_WIDE;
     const double g = wide ? (double)LIST_GROW : c->prm.h_margin;
     A.grow = wide ? LIST_GROW : 1.0e30f;
@@ -1056,6 +1062,7 @@ void density_enqueue(sph_ctx* c, const float* mass, float* h, float* rho, float*
             A.detail ? k_density<L, H, false, true><<<grid, BS, 0, s>>>(A)
                      : k_density<L, H, false, false><<<grid, BS, 0, s>>>(A);
     };
+    A.list_room = (int)std::min(1.08 * x + 23.0, 1.0e6) & ~15;
     using Whole = std::false_type;
     using Half = std::true_type;
     if (want <= 80.0)
@@ -1066,8 +1073,6 @@ void density_enqueue(sph_ctx* c, const float* mass, float* h, float* rho, float*
         launch(std::integral_constant<int, 128>{}, Whole{});
     else if (x <= (c->uni ? 235.0 : 200.0))
         launch(std::integral_constant<int, 240>{}, Whole{});
-    else if (x <= 300.0)
-        launch(std::integral_constant<int, 320>{}, Whole{});
     else if (x <= 470.0)
         launch(std::integral_constant<int, 240>{}, Half{});
     else

@@ -127,8 +127,9 @@ def test_listed_counts_with_a_rescan(gpu_lib, name):
 @pytest.mark.parametrize("n,n_ngb,margin", [(19, 200.0, 1.26), (21, 300.0, 1.05), (24, 400.0, 1.26)])
 @pytest.mark.parametrize("guess", [1.0, 0.86, 1.2, "masses"])
 def test_many_neighbours(gpu_lib, layout, n, n_ngb, margin, guess):
-    """Many neighbours: lists of 320 entries to 300 expected neighbours, then half an
-    item at a time (to 470 twice 240 entries, above twice 320), with good guesses, roots beyond the first list or the cells, lists that do not fit, and
+    """More neighbours than the lists of a whole item hold: half of it at a time (to
+    470 expected neighbours twice 240 entries, above twice 320; items small enough
+    whole, with lists as long as their number allows), with good guesses, roots beyond the first list or the cells, lists that do not fit, and
     masses from U(0.5, 1.5)."""
     d = workloads.lattice_box(n, [1508, 971], jitter=0.2, u=1.0, vel_sigma=0.2)
     if guess == "masses":
