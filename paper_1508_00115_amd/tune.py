@@ -10,7 +10,6 @@ legal cell layout):
     cell_ratio   smallest cell width below the top grid, in search radii
     leaf_target  cells holding more particles than this are split
     schedule     hardware dispatch or persistent per-XCD queues
-    tile_cap     accepted and without effect
     cell_order   work items by decreasing cost (balance), in Morton order (L2
                  reuse), or Morton ranges per XCD each ordered by cost; without
                  effect where no top cell splits (columns of cells, in order)
@@ -36,12 +35,11 @@ import os
 import numpy as np
 
 DEFAULT_GRID = [
-    {"h_margin": m, "cell_ratio": cr, "leaf_target": lt, "schedule": s, "tile_cap": tc, "cell_order": co}
+    {"h_margin": m, "cell_ratio": cr, "leaf_target": lt, "schedule": s, "cell_order": co}
     for m in (1.05, 1.1, 1.18, 1.26)
     for cr in (1.0, 0.5)
     for lt in (64, 32)
     for s in (0, 1)
-    for tc in (128, 512)
     for co in (0, 1, 2)
 ]
 
