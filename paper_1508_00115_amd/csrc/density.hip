@@ -189,9 +189,11 @@ __device__ __forceinline__ void hsolve_step(HSolve& s, float S0, float S1, float
     }
     const float slope = -S1 * __builtin_amdgcn_rcpf(S0);  // d ln S0 / d ln h
     float hn = slope > 0.05f ? s.h * __expf(-__logf(ratio) * __builtin_amdgcn_rcpf(slope)) : 2.0f * s.h;
+    // a step to Hi is always evaluated there: however short, the root may lie beyond
+    const bool edge = hn >= s.hi && !s.hi_known;
     if (hn >= s.hi) hn = s.hi_known ? 0.5f * (s.h + s.hi) : s.Hi;
     if (hn <= s.lo) hn = 0.5f * (s.lo + s.h);
-    if (fabsf(hn - s.h) <= 2.5e-7f * s.h) {
+    if (!edge && fabsf(hn - s.h) <= 2.5e-7f * s.h) {
         s.done = true;  // the next step is below FP32 resolution of h: h is the root
         s.state = ST_DONE;
         return;

@@ -146,3 +146,40 @@ def test_many_neighbours(gpu_lib, layout, n, n_ngb, margin, guess):
         n_d = int(r["nngb"].sum())
         assert abs(g["stats"]["interactions_density"] - n_d) <= 1e-5 * n_d + 2
     print(e, g["stats"], flush=True)
+
+
+@pytest.mark.parametrize("margin,first", [(1.26, 1.12), (1.1, 1.1)])
+def test_steps_that_end_just_inside_the_first_radius(gpu_lib, margin, first):
+    """Guesses from which the first Newton step ends a relative 1.2e-7 inside the
+    first radius with the root well beyond it: the next step, to the radius, is below
+    FP32 resolution, but the root is not there. (With a margin of 1.1 the radius is
+    the search radius, and the cells are rebuilt.)"""
+    d = workloads.lattice_box(15, [1508, 973], jitter=0.35, u=1.0, vel_sigma=0.2)
+    r = oracle.run(d)
+    n = len(r["h"])
+    p = np.mod(d["pos"], 1.0)
+    near, _ = cKDTree(p, boxsize=1.0).query(p, k=160)
+
+    def step(h):
+        """h after one Newton step on ln S0 against ln h, over h."""
+        q = near / h[:, None]
+        t, u = np.maximum(1.0 - q, 0.0), np.maximum(0.5 - q, 0.0)
+        S0 = (2.0 * t**3 - 8.0 * u**3).sum(1)
+        slope = -(q * (24.0 * u**2 - 6.0 * t**2)).sum(1) / S0
+        return np.exp(-np.log(S0 / 4.5) / slope)
+
+    goal = first * (1.0 - 1.2e-7)
+    lo, hi = r["h"] / first * 0.97, r["h"] / first * 1.03
+    found = (step(lo) > goal) & (step(hi) < goal)  # the step shrinks as the guess grows
+    for _ in range(60):
+        mid = 0.5 * (lo + hi)
+        up = step(mid) > goal
+        lo, hi = np.where(up, mid, lo), np.where(up, hi, mid)
+    short = found & (r["h"] > first * hi * (1.0 + 1e-4))
+    assert short.sum() > 100
+    d["h0"] = np.where(short, hi, r["h"]).astype(np.float32)
+    print("steps to the edge", int(short.sum()), "of", n, flush=True)
+    for g in _run(gpu_lib, d, h_margin=margin):
+        e = errors(g, r)
+        print(e, g["stats"], flush=True)
+        assert_within(e, TOL32, "edge")
