@@ -236,7 +236,8 @@ sph_status sph_build_cells(sph_ctx* ctx, int32_t n_boxes, const int64_t* box_fir
 /*
  * Density loop (section 2, Eq. 1) with the smoothing length of every particle
  * solved for n_ngb weighted neighbours (section 2), FP32 arithmetic on FP32
- * cell-relative offsets of the FP64 positions.
+ * offsets of the FP64 positions from the centre of their cell, or of the
+ * group of at most 16 particles (and two cells) they are worked on with.
  *   mass        device, n floats (> 0)
  *   h           device, n floats: in, starting h (usually the h_guess given
  *               to sph_build_cells); out, converged h

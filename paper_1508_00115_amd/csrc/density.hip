@@ -37,9 +37,10 @@
 // filter and the lists, 21% to Newton and a third to the item's start and end. In a
 // tree (265 per particle, three wavefronts, by LDS) one leaves every 6: the walk of the candidates
 // takes 38%. Measured, here / with one wavefront per cell and no matrix cores:
-// 256 boxes 1.65 / 2.60 ms, clustered 2^20 0.75 / 0.98 ms, log-normal 2^24 11.5 /
-// 11.8 ms (the last two with the re-scans the older form left). Tiles of 256, 192 and
-// 128 candidates: 2.09, 1.91 and 1.72 ms on the boxes (occupancy), 64: 1.95.
+// 256 boxes of 20^3 to 40^3 particles, 6.9 million in all, 1.64 / 2.60 ms, clustered
+// 2^20 0.75 / 1.01 ms, log-normal 2^24 11.3 / 11.8 ms (the last two with the re-scans,
+// which the older form left more of); bench.py's 7.2 million in 256 boxes 1.77 ms. Tiles of 256, 192 and
+// 128 candidates: 2.09, 1.91 and 1.72 ms on the 6.9 million (occupancy), 64: 1.95.
 #include "common.h"
 #include "tiles.h"
 

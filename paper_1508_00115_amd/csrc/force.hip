@@ -20,8 +20,9 @@
 // What bounds it: the issue of vector instructions (one per 3.6 cycles of a SIMD on
 // a grid, 4.4 in a tree), most of them in the pair loop, whose lists' lengths
 // differ between particles. Measured, here / with one wavefront per cell and
-// every candidate tested on the vector units: 256 boxes 1.57 / 2.25 ms, clustered
-// 2^20 0.60 / 0.83 ms, log-normal 2^24 8.3 / 10.7 ms. Tiles of 192 candidates
+// every candidate tested on the vector units: 256 boxes of 20^3 to 40^3 particles,
+// 6.9 million in all, 1.57 / 2.25 ms, clustered 2^20 0.62 / 0.85 ms, log-normal 2^24
+// 8.2 / 10.8 ms; bench.py's 7.2 million in 256 boxes 1.73 ms. Tiles of 192 candidates
 // instead of 128: 1.91 against 1.64 ms on the boxes (LDS holds fewer wavefronts).
 //
 // With the Balsara switch (not in the paper; the Gadget-2 form) the same loop
