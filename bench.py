@@ -144,9 +144,9 @@ def cpu_gravity(d: dict, order, min_seconds: float = 3.0) -> dict:
 
 
 KERNEL_SOURCES = {
-    "k_density": ["density.hip", "tiles.h", "common.h"],
-    "k_force": ["force.hip", "tiles.h", "common.h"],
-    "k_gravity": ["gravity.hip", "tiles.h", "common.h"],
+    "k_density": ["density.hip", "tiles.h", "item_range.h", "common.h"],
+    "k_force": ["force.hip", "tiles.h", "item_range.h", "common.h"],
+    "k_gravity": ["gravity.hip", "tiles.h", "item_range.h", "common.h"],
 }
 
 
