@@ -43,7 +43,6 @@ SETS = {
     "lattice_16": (lambda: workloads.lattice_box(16, [1508, 960, 0], jitter=0.2, vel_sigma=0.2), 12.0, 1.1),
     "lattice_13": (lambda: workloads.lattice_box(13, [1508, 960, 2], jitter=0.3, vel_sigma=0.2), 12.0, 1.05),
     "cylinder_24": (lambda: _cylinder(24, 7), 48.0, 1.26),
-    "slab_14": (lambda: _body(14, lambda x: x[:, 0] < 4, 3), 48.0, 1.05),
 }
 
 
@@ -76,7 +75,7 @@ def _longest_run(d, margin):
     return max(z[c[min(i + 15, len(c) - 1)]] - z[c[i]] for c in cols for i in range(0, len(c), 16))
 
 
-@pytest.mark.parametrize("name", ["lattice_16", "lattice_13", "cylinder_24"])
+@pytest.mark.parametrize("name", list(SETS))
 def test_runs_longer_than_half_the_box(gpu_lib, name):
     """Density, force and gravity where 16 particles of a column lie over more
     than half the box, and again after a drift that keeps the cells."""
